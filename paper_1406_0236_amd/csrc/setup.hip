@@ -385,21 +385,197 @@ __global__ void add_half_identity_kernel(double2 *A, int M, int NG) {
     A[((int64_t)m * NG + i) * NG + i].x += 0.5;
 }
 
-// Gauss-Jordan inverse with partial pivoting (ties -> lowest row), one block
-// per matrix; the matrices of every shape (all modes) in one launch.
+// Inverses of all matrices (every shape, every mode) by in-place Gauss-Jordan
+// elimination with partial pivoting (largest entry of the column among the rows
+// not yet used as pivots; ties -> lowest row).  Rows are never moved: pivot row
+// r_j belongs to column j, and the end result B gives A^{-1}[j][r_c] =
+// B[r_j][c] (gj_finish_kernel).
+//
+// Blocked by GJB = 16 columns so that the work runs over the whole chip
+// instead of one workgroup per matrix.  In the columns K of a block the
+// elimination leaves T = A[:, K] (A[R, K])^{-1} with the pivot rows R holding
+// the inverse itself and the others its negated product; all other columns
+// then need A <- A (pivot rows zeroed) + T A_old[R, :], one product with an
+// inner dimension of 16:
+//   gj_panel_kernel  - one workgroup per matrix, one row per thread held in
+//                      registers; bound by its 16 serial steps (two barriers each);
+//   gj_update_kernel - a 16 x 16 tile per wavefront on the FP64 matrix cores,
+//                      read from one copy of the matrix and written to the other
+//                      (the pivot rows are read by every tile).
+// 41 matrices of 200 x 200 (MI355X): 26 launches, 0.60 ms (13 x 30 us + 13 x 16
+// us); one workgroup per matrix over global memory took 19.97 ms.
 struct GJItem {
     const double2 *A;   // NG x NG, row-major
-    double2 *work;      // NG x 2 NG
+    double2 *b0, *b1;   // two copies of NG x NG the blocks alternate between
+    double2 *T;         // NG x GJB
+    int32_t *prow;      // [NG] pivot row of each column
+    int32_t *col;       // [NG] column of each row, -1 while it is no pivot
     double2 *S;         // NG x NG, row-major: A^{-1}
-    int NG, pad;
+    int32_t NG, pad;
 };
+constexpr int GJB = 16;
+constexpr int GJ_ROWS = 1024;   // one thread per row: larger matrices take gauss_jordan_kernel
+
+typedef double gj_f64x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ const double2 *gj_src(const GJItem &it, int step) {
+    return step == 0 ? it.A : (step & 1) ? it.b0 : it.b1;
+}
+
+template <int BS>
+__global__ __launch_bounds__(BS) void gj_panel_kernel(const GJItem *__restrict__ items, int step) {
+    const GJItem it = items[blockIdx.x];
+    const int NG = it.NG, k0 = step * GJB;
+    if (k0 >= NG) return;
+    const int nb = min(GJB, NG - k0);
+    const int r = threadIdx.x, lane = r & 63, wave = r >> 6;
+    constexpr int NW = BS / 64;
+    __shared__ double s_max[2][NW];
+    __shared__ int s_row[2][NW];
+    __shared__ double2 s_piv[2][GJB];
+    const bool live = r < NG;
+    const double2 *src = gj_src(it, step) + (int64_t)r * NG + k0;
+    double ar[GJB], ai[GJB];
+#pragma unroll
+    for (int j = 0; j < GJB; ++j) {
+        double2 v = make_double2(0.0, 0.0);
+        if (live && j < nb) v = src[j];
+        ar[j] = v.x;
+        ai[j] = v.y;
+    }
+    int mycol = !live ? 0 : step == 0 ? -1 : it.col[r];
+#pragma unroll
+    for (int c = 0; c < GJB; ++c) {
+        if (c >= nb) break;
+        double mag = -1.0;
+        if (mycol < 0) {
+            mag = ar[c] * ar[c] + ai[c] * ai[c];
+            if (!(mag >= 0.0)) mag = 0.0;   // NaN: the result is NaN whatever the pivot
+        }
+        double wm = mag;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) wm = fmax(wm, __shfl_xor(wm, o, 64));
+        const int first = __ffsll((unsigned long long)__ballot(mag == wm)) - 1;
+        if (lane == 0) {
+            s_max[c & 1][wave] = wm;
+            s_row[c & 1][wave] = wave * 64 + first;
+        }
+        __syncthreads();
+        double best = s_max[c & 1][0];
+        int pr = s_row[c & 1][0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w)
+            if (s_max[c & 1][w] > best) {
+                best = s_max[c & 1][w];
+                pr = s_row[c & 1][w];
+            }
+        if (r == pr) {
+            const double den = ar[c] * ar[c] + ai[c] * ai[c];
+            const double pr_ = ar[c] / den, pi_ = -ai[c] / den;
+            ar[c] = 1.0;
+            ai[c] = 0.0;
+#pragma unroll
+            for (int j = 0; j < GJB; ++j) {
+                const double x = ar[j] * pr_ - ai[j] * pi_, y = ar[j] * pi_ + ai[j] * pr_;
+                ar[j] = x;
+                ai[j] = y;
+                s_piv[c & 1][j] = make_double2(x, y);
+            }
+            mycol = k0 + c;
+            it.prow[k0 + c] = r;
+        }
+        __syncthreads();
+        if (r != pr) {
+            const double fr = ar[c], fi = ai[c];
+            ar[c] = 0.0;
+            ai[c] = 0.0;
+#pragma unroll
+            for (int j = 0; j < GJB; ++j) {
+                const double2 u = s_piv[c & 1][j];
+                ar[j] = fma(-fr, u.x, fma(fi, u.y, ar[j]));
+                ai[j] = fma(-fr, u.y, fma(-fi, u.x, ai[j]));
+            }
+        }
+    }
+    if (!live) return;
+    it.col[r] = mycol;
+#pragma unroll
+    for (int j = 0; j < GJB; ++j) it.T[(int64_t)r * GJB + j] = make_double2(ar[j], ai[j]);
+}
+
+__global__ __launch_bounds__(256) void gj_update_kernel(const GJItem *__restrict__ items, int step) {
+    const GJItem it = items[blockIdx.z];
+    const int NG = it.NG, k0 = step * GJB;
+    if (k0 >= NG) return;
+    const int nb = min(GJB, NG - k0);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
+    const int r0 = blockIdx.y * 32 + (wave >> 1) * 16, c0 = blockIdx.x * 32 + (wave & 1) * 16;
+    if (r0 >= NG || c0 >= NG) return;
+    const double2 *src = gj_src(it, step);
+    double2 *dst = (step & 1) ? it.b1 : it.b0;
+    const int col = c0 + (lane & 15);
+    if (c0 == k0) {   // the block's own columns
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = r0 + q + 4 * v;
+            if (row < NG && col < NG) dst[(int64_t)row * NG + col] = it.T[(int64_t)row * GJB + (lane & 15)];
+        }
+        return;
+    }
+    gj_f64x4 accr, acci;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int row = r0 + q + 4 * v;
+        double2 x = make_double2(0.0, 0.0);
+        if (row < NG && col < NG) {
+            const int pc = it.col[row];
+            if (pc < k0) x = src[(int64_t)row * NG + col];   // not a pivot row of this block
+        }
+        accr[v] = x.x;
+        acci[v] = x.y;
+    }
+    const int arow = r0 + (lane & 15);
+#pragma unroll
+    for (int k = 0; k < GJB; k += 4) {
+        double2 a = make_double2(0.0, 0.0), b = a;
+        if (k + q < nb) {
+            if (arow < NG) a = it.T[(int64_t)arow * GJB + k + q];
+            if (col < NG) b = src[(int64_t)it.prow[k0 + k + q] * NG + col];
+        }
+        accr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, accr, 0, 0, 0);
+        acci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, acci, 0, 0, 0);
+        accr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, accr, 0, 0, 0);
+        acci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.x, acci, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int row = r0 + q + 4 * v;
+        if (row < NG && col < NG) dst[(int64_t)row * NG + col] = make_double2(accr[v], acci[v]);
+    }
+}
+
+// S[j][r_c] = B[r_j][c]
+__global__ __launch_bounds__(256) void gj_finish_kernel(const GJItem *__restrict__ items) {
+    const GJItem it = items[blockIdx.y];
+    const int NG = it.NG;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= (int64_t)NG * NG) return;
+    const int j = (int)(t / NG), c = (int)(t % NG);
+    const double2 *B = gj_src(it, (NG + GJB - 1) / GJB);
+    it.S[(int64_t)j * NG + it.prow[c]] = B[(int64_t)it.prow[j] * NG + c];
+}
+
+// Gauss-Jordan inverse with partial pivoting (ties -> lowest row), one block
+// per matrix, in global memory: matrices of more than GJ_ROWS rows, which one
+// workgroup of the blocked elimination cannot hold at a row per thread.  The
+// work array (NG x 2 NG) is b0 followed by b1.
 template <int BS>
 __global__ __launch_bounds__(BS) void gauss_jordan_kernel(const GJItem *__restrict__ items) {
     const GJItem it = items[blockIdx.x];
     const int NG = it.NG;
     const int W = 2 * NG;
     const double2 *a = it.A;
-    double2 *g = it.work;
+    double2 *g = it.b0;
     double2 *s = it.S;
     __shared__ double rmax[BS];
     __shared__ int ridx[BS];
@@ -718,24 +894,30 @@ void precompute_shape(Ctx &c, Shape &s) {
         c.dfree(ptr);
 }
 
-// S_m = A~_m^{-1} for every shape and mode: one Gauss-Jordan launch over all
-// the matrices (per shape only M + 1 workgroups would run), in groups whose
-// work arrays (NG x 2 NG per matrix) stay within 4 GiB
+// S_m = A~_m^{-1} for every shape and mode, in groups of shapes whose work
+// arrays (about NG x 2 NG per matrix) stay within 4 GiB.  Per group one launch
+// sequence over all its matrices: two launches per 16 columns, or one launch of
+// gauss_jordan_kernel where a matrix has more rows than a workgroup has threads.
 void invert_shapes(Ctx &c) {
     constexpr size_t WORK_CAP = (size_t)4 << 30;
+    auto per = [](const Shape &s) {   // work bytes per matrix
+        return ((size_t)2 * s.NG * s.NG + (size_t)GJB * s.NG) * sizeof(double2) + (size_t)2 * s.NG * sizeof(int32_t);
+    };
     size_t k = 0;
     while (k < c.shapes.size()) {
-        size_t k1 = k, bytes = 0;
+        size_t k1 = k, bytes = 0, nmat = 0;
         int maxNG = 0;
+        const bool blocked = c.shapes[k].NG <= GJ_ROWS;
         while (k1 < c.shapes.size()) {
             const Shape &s = c.shapes[k1];
-            const size_t b = (size_t)(s.M + 1) * s.NG * 2 * s.NG * sizeof(double2);
-            if (k1 > k && bytes + b > WORK_CAP) break;
+            const size_t b = (size_t)(s.M + 1) * per(s);
+            if (k1 > k && (bytes + b > WORK_CAP || (s.NG <= GJ_ROWS) != blocked || nmat + s.M + 1 > 65535)) break;
             bytes += b;
+            nmat += s.M + 1;
             maxNG = std::max(maxNG, s.NG);
             ++k1;
         }
-        double2 *work = (double2 *)c.dalloc(bytes);
+        char *work = (char *)c.dalloc(bytes);
         std::vector<GJItem> items;
         size_t off = 0;
         for (size_t q = k; q < k1; ++q) {
@@ -744,16 +926,46 @@ void invert_shapes(Ctx &c) {
             double2 *S = (double2 *)c.dalloc((size_t)(s.M + 1) * nn * sizeof(double2));
             s.S64 = (double *)S;
             for (int m = 0; m <= s.M; ++m) {
-                items.push_back(GJItem{(const double2 *)s.A64 + m * nn, work + off, S + m * nn, s.NG, 0});
-                off += (size_t)2 * nn;
+                GJItem g{};
+                g.A = (const double2 *)s.A64 + m * nn;
+                g.b0 = (double2 *)(work + off);
+                g.b1 = g.b0 + nn;
+                g.T = g.b1 + nn;
+                g.S = S + m * nn;
+                g.NG = s.NG;
+                off += ((size_t)2 * nn + (size_t)GJB * s.NG) * sizeof(double2);
+                items.push_back(g);
             }
         }
+        for (auto &g : items) {
+            g.prow = (int32_t *)(work + off);
+            g.col = g.prow + g.NG;
+            off += (size_t)2 * g.NG * sizeof(int32_t);
+        }
         GJItem *d_items = (GJItem *)c.dalloc(items.size() * sizeof(GJItem));
-        AXS_HIP(hipMemcpy(d_items, items.data(), items.size() * sizeof(GJItem), hipMemcpyHostToDevice));
-        hipLaunchKernelGGL(gauss_jordan_kernel<256>, dim3((unsigned)items.size()), dim3(256),
-                           maxNG * sizeof(double2), c.stream, d_items);
+        AXS_HIP(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(GJItem), hipMemcpyHostToDevice, c.stream));
+        const unsigned n = (unsigned)items.size();
+        if (blocked) {
+            const unsigned t32 = (unsigned)ceil_div(maxNG, 32);
+            const int steps = (int)ceil_div(maxNG, GJB);
+            for (int st = 0; st < steps; ++st) {
+                if (maxNG <= 64)
+                    hipLaunchKernelGGL(gj_panel_kernel<64>, dim3(n), dim3(64), 0, c.stream, d_items, st);
+                else if (maxNG <= 256)
+                    hipLaunchKernelGGL(gj_panel_kernel<256>, dim3(n), dim3(256), 0, c.stream, d_items, st);
+                else if (maxNG <= 512)
+                    hipLaunchKernelGGL(gj_panel_kernel<512>, dim3(n), dim3(512), 0, c.stream, d_items, st);
+                else
+                    hipLaunchKernelGGL(gj_panel_kernel<GJ_ROWS>, dim3(n), dim3(GJ_ROWS), 0, c.stream, d_items, st);
+                hipLaunchKernelGGL(gj_update_kernel, dim3(t32, t32, n), dim3(256), 0, c.stream, d_items, st);
+            }
+            hipLaunchKernelGGL(gj_finish_kernel, dim3((unsigned)ceil_div((int64_t)maxNG * maxNG, 256), n), dim3(256), 0,
+                               c.stream, d_items);
+        } else {
+            hipLaunchKernelGGL(gauss_jordan_kernel<256>, dim3(n), dim3(256), maxNG * sizeof(double2), c.stream, d_items);
+        }
         AXS_HIP(hipGetLastError());
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        AXS_HIP(hipStreamSynchronize(c.stream));   // items is pageable host memory; the work array is released
         c.dfree(d_items);
         c.dfree(work);
         k = k1;
