@@ -13,7 +13,7 @@ namespace axs {
 
 void gauss_legendre_public(int n, std::vector<double> &x, std::vector<double> &w);
 void split_planar(Ctx &c, Shape &s, const double *src, double *r64, double *i64, float *r32, float *i32);
-void build_ring_tables(Ctx &c);
+void build_node_tables(Ctx &c);
 void interbody_shape(Ctx &c, int prec, int nrhs, int out[4]);
 
 void *Ctx::dalloc(size_t bytes) {
@@ -230,7 +230,7 @@ void finish_precompute(Ctx &c) {
         c.max_NG = std::max(c.max_NG, s.NG);
     }
     c.gemm = (GemmBatch *)c.dalloc(gb.size() * sizeof(GemmBatch));
-    AXS_HIP(hipMemcpy(c.gemm, gb.data(), gb.size() * sizeof(GemmBatch), hipMemcpyHostToDevice));
+    AXS_HIP(hipMemcpyAsync(c.gemm, gb.data(), gb.size() * sizeof(GemmBatch), hipMemcpyHostToDevice, c.stream));
     c.ngemm = (int)gb.size();
     // twiddles per distinct N_F
     std::map<int, int64_t> twoff;
@@ -248,8 +248,8 @@ void finish_precompute(Ctx &c) {
     c.tw64 = (double *)c.dalloc(tw.size() * sizeof(double));
     c.tw32 = (float *)c.dalloc(tw.size() * sizeof(float));
     std::vector<float> tw32(tw.begin(), tw.end());
-    AXS_HIP(hipMemcpy(c.tw64, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(c.tw32, tw32.data(), tw32.size() * sizeof(float), hipMemcpyHostToDevice));
+    AXS_HIP(hipMemcpyAsync(c.tw64, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
+    AXS_HIP(hipMemcpyAsync(c.tw32, tw32.data(), tw32.size() * sizeof(float), hipMemcpyHostToDevice, c.stream));
     // body descriptors
     c.body_dev_host.clear();
     for (auto &b : c.bodies) {
@@ -267,42 +267,9 @@ void finish_precompute(Ctx &c) {
         c.body_dev_host.push_back(d);
     }
     c.body_dev = (BodyDev *)c.dalloc(c.body_dev_host.size() * sizeof(BodyDev));
-    AXS_HIP(hipMemcpy(c.body_dev, c.body_dev_host.data(), c.body_dev_host.size() * sizeof(BodyDev),
-                      hipMemcpyHostToDevice));
-    // global node arrays, FP64 (7 x N) and FP32 (6 x N)
-    const int64_t N = c.N;
-    std::vector<double> g(7 * N);
-    for (auto &b : c.bodies) {
-        const Shape &s = c.shapes[b.shape];
-        for (int i = 0; i < s.NG; ++i) {
-            const double sp = std::hypot(s.dr[i], s.dz[i]);
-            const double nr = -s.dz[i] / sp, nz = s.dr[i] / sp;
-            const double w = (2.0 * M_PI / s.NF) * s.r[i] * sp * s.gw[i];
-            for (int l = 0; l < s.NF; ++l) {
-                const double th = 2.0 * M_PI * l / s.NF;
-                const double ct = std::cos(th), st = std::sin(th);
-                const double loc[3] = {s.r[i] * ct, s.r[i] * st, s.z[i]};
-                const double nl[3] = {nr * ct, nr * st, nz};
-                const int64_t j = b.offset + (int64_t)i * s.NF + l;
-                for (int a = 0; a < 3; ++a) {
-                    double xv = b.centre[a], nv = 0;
-                    for (int q = 0; q < 3; ++q) {
-                        xv += b.rot[3 * a + q] * loc[q];
-                        nv += b.rot[3 * a + q] * nl[q];
-                    }
-                    g[a * N + j] = xv;
-                    g[(3 + a) * N + j] = nv;
-                }
-                g[6 * N + j] = w;
-            }
-        }
-    }
-    std::vector<float> g32(g.begin(), g.begin() + 6 * N);
-    c.g64 = (double *)c.dalloc(7 * N * sizeof(double));
-    c.g32 = (float *)c.dalloc(6 * N * sizeof(float));
-    AXS_HIP(hipMemcpy(c.g64, g.data(), 7 * N * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(c.g32, g32.data(), 6 * N * sizeof(float), hipMemcpyHostToDevice));
-    build_ring_tables(c);
+    AXS_HIP(hipMemcpyAsync(c.body_dev, c.body_dev_host.data(), c.body_dev_host.size() * sizeof(BodyDev),
+                           hipMemcpyHostToDevice, c.stream));
+    build_node_tables(c);
     AXS_HIP(hipStreamSynchronize(c.stream));
     c.precomputed = true;
 }

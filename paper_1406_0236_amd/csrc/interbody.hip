@@ -1270,162 +1270,239 @@ static std::vector<IBWork> build_work(Ctx &c, int tile, int splits, Units units)
     return build_work_table(wb, U, tile, splits);
 }
 
-// ring tables, body frames and per-node azimuth cos/sin (built once)
-void build_ring_tables(Ctx &c) {
+// ---------------------------------------------------------------------------
+// Node arrays, ring tables and MFMA source operands, built once per context on
+// the device from each shape's contour (a few hundred numbers) and each body's
+// pose: 24 values per node, which the host formed with its own sines and
+// cosines and copied over pageable memory in 36 ms for 437,400 nodes; the two
+// kernels below write them at HBM rate (about 0.1 ms).
+// ---------------------------------------------------------------------------
+struct TableBody {
+    int64_t off;          // first node
+    int64_t entry;        // first mirror-pair entry
+    int32_t NG, NF, ring, contour;   // first ring; offset of the shape's contour record
+};
+struct NodeOut {
+    double *g64;          // [7][N]
+    float *g32;           // [6][N]
+    double *cs64;         // [2][N]
+    float *cs32;
+    double *mf64;         // [8][N] as [2 N] 4-vectors, or null at zero frequency
+    float *mf32;
+};
+
+// contour: [5][nc]: r, z, n_r, n_z, area weight of one azimuthal node
+__global__ __launch_bounds__(256) void node_tables_kernel(const TableBody *__restrict__ tb,
+                                                          const double *__restrict__ contour, int nc,
+                                                          const double *__restrict__ frame, int64_t N, int bi,
+                                                          double k2pi, NodeOut o) {
+    bi += blockIdx.y;
+    const TableBody b = tb[bi];
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= b.NG * b.NF) return;
+    const int i = t / b.NF, l = t - i * b.NF;
+    const double *f = frame + FRAME * bi;
+    // azimuths l and N_F - l are exact mirror images (same cosine, opposite sine)
+    const bool mir = 2 * l > b.NF;
+    double ct, st;
+    sincospi(2.0 * (mir ? b.NF - l : l) / b.NF, &st, &ct);
+    if (mir) st = -st;
+    const double *cn = contour + b.contour + i;
+    const double r = cn[0], z = cn[nc], nr = cn[2 * (int64_t)nc], nz = cn[3 * (int64_t)nc];
+    const double y[3] = {r * ct, r * st, z}, n[3] = {nr * ct, nr * st, nz};
+    const int64_t j = b.off + t;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double *R = f + 3 + 3 * a;
+        const double xv = fma(R[0], y[0], fma(R[1], y[1], fma(R[2], y[2], f[a])));
+        const double nv = fma(R[0], n[0], fma(R[1], n[1], R[2] * n[2]));
+        o.g64[a * N + j] = xv;
+        o.g64[(3 + a) * N + j] = nv;
+        o.g32[a * N + j] = (float)xv;
+        o.g32[(3 + a) * N + j] = (float)nv;
+    }
+    o.g64[6 * N + j] = cn[4 * (int64_t)nc];
+    o.cs64[j] = ct;
+    o.cs64[N + j] = st;
+    o.cs32[j] = (float)ct;
+    o.cs32[N + j] = (float)st;
+    if (o.mf64) {
+        // MFMA source operands in the body's frame, scaled so that the products
+        // give R'^2 and nd' of the ring order directly
+        const double s2 = k2pi * k2pi, c1 = s2 * k2pi;
+        const double v[8] = {-2.0 * s2 * y[0],
+                             -2.0 * s2 * y[1],
+                             -2.0 * s2 * y[2],
+                             s2 * (r * r + z * z),
+                             c1 * n[0],
+                             c1 * n[1],
+                             c1 * n[2],
+                             -c1 * (nr * r + nz * z)};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            o.mf64[4 * j + k] = v[k];
+            o.mf64[4 * (N + j) + k] = v[4 + k];
+            o.mf32[4 * j + k] = (float)v[k];
+            o.mf32[4 * (N + j) + k] = (float)v[4 + k];
+        }
+    }
+}
+
+// per ring: ids [0, nr) node offset, N_F, body, first entry (eoff[nr] by the
+// last ring); geometry r, z, n_r, n_z, -n_r / (2 r); its mirror-pair entries
+// e = 0 .. N_F/2: azimuth e and N_F - e
+__global__ __launch_bounds__(64) void ring_tables_kernel(const TableBody *__restrict__ tb,
+                                                         const double *__restrict__ contour, int nc, int bi, int nr_,
+                                                         int32_t *__restrict__ ri, double *__restrict__ g64,
+                                                         float *__restrict__ g32, int2 *__restrict__ pair) {
+    bi += blockIdx.y;
+    const int i = blockIdx.x;
+    const TableBody b = tb[bi];
+    if (i >= b.NG) return;
+    const int id = b.ring + i, ne = b.NF / 2 + 1;
+    const int32_t off = (int32_t)(b.off + (int64_t)i * b.NF);
+    const int64_t e0 = b.entry + (int64_t)i * ne;
+    for (int e = threadIdx.x; e < ne; e += 64)
+        pair[e0 + e] = make_int2(off + e, (e == 0 || 2 * e == b.NF) ? -1 : off + b.NF - e);
+    if (threadIdx.x) return;
+    ri[id] = off;
+    ri[nr_ + id] = b.NF;
+    ri[2 * nr_ + id] = bi;
+    ri[3 * nr_ + id] = (int32_t)e0;
+    if (id == nr_ - 1) ri[3 * nr_ + nr_] = (int32_t)(e0 + ne);
+    const double *cn = contour + b.contour + i;
+    const double r = cn[0], nrv = cn[2 * (int64_t)nc];
+    const double v[5] = {r, cn[nc], nrv, cn[3 * (int64_t)nc], r > 0 ? -0.5 * nrv / r : 0.0};
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        g64[(int64_t)k * nr_ + id] = v[k];
+        g32[(int64_t)k * nr_ + id] = (float)v[k];
+    }
+}
+
+// node arrays, ring tables, body frames, per-node azimuth cos/sin, MFMA operands
+void build_node_tables(Ctx &c) {
     const int64_t N = c.N;
-    std::vector<int32_t> ri;
-    std::vector<double> rg, fr, csv(2 * N);
+    AXS_REQUIRE(N < (int64_t)INT32_MAX, AXS_EINVAL, "node count beyond 32-bit ring tables");
+    // contour records of the distinct shapes
+    int nc = 0;
+    std::vector<int> coff;
+    for (auto &s : c.shapes) {
+        coff.push_back(nc);
+        nc += s.NG;
+    }
+    std::vector<double> cont(5 * (size_t)nc), fr;
+    for (size_t k = 0; k < c.shapes.size(); ++k) {
+        const Shape &s = c.shapes[k];
+        for (int i = 0; i < s.NG; ++i) {
+            const double sp = std::hypot(s.dr[i], s.dz[i]);
+            const int o = coff[k] + i;
+            cont[o] = s.r[i];
+            cont[nc + o] = s.z[i];
+            cont[2 * (size_t)nc + o] = -s.dz[i] / sp;
+            cont[3 * (size_t)nc + o] = s.dr[i] / sp;
+            cont[4 * (size_t)nc + o] = (2.0 * M_PI / s.NF) * s.r[i] * sp * s.gw[i];
+        }
+    }
+    std::vector<TableBody> tb;
+    std::vector<int64_t> bo;
+    std::vector<int32_t> bk(1, 0);
     c.ring_base.clear();
-    int nr = 0;
     c.max_nf = 0;
-    for (size_t bi = 0; bi < c.bodies.size(); ++bi) {
-        const auto &b = c.bodies[bi];
+    int nr = 0, maxng = 0;
+    int64_t ent = 0, maxn = 0;
+    for (auto &b : c.bodies) {
         const Shape &s = c.shapes[b.shape];
         c.ring_base.push_back(nr);
+        tb.push_back(TableBody{b.offset, ent, s.NG, s.NF, nr, coff[b.shape]});
         nr += s.NG;
+        ent += (int64_t)s.NG * (s.NF / 2 + 1);
+        maxng = std::max(maxng, s.NG);
+        maxn = std::max(maxn, b.n);
         c.max_nf = std::max(c.max_nf, s.NF);
         for (int a = 0; a < 3; ++a) fr.push_back(b.centre[a]);
         for (int a = 0; a < 9; ++a) fr.push_back(b.rot[a]);
         fr.push_back(b.bound_radius);
         for (int a = 13; a < FRAME; ++a) fr.push_back(0.0);
-        for (int l = 0; l < s.NF; ++l) {
-            const double th = 2.0 * M_PI * l / s.NF;
-            for (int i = 0; i < s.NG; ++i) {
-                const int64_t j = b.offset + (int64_t)i * s.NF + l;
-                csv[j] = std::cos(th);
-                csv[N + j] = std::sin(th);
-            }
-        }
+        bo.push_back(b.offset);
+        bk.push_back(bk.back() + (int32_t)ceil_div(b.n, (int64_t)32));
     }
+    bo.push_back(N);
     c.nrings = nr;
+    c.nblk = bk.back();
     // phases less whole revolutions stay below 2 (r_t + r_s) k/2pi + 1 revolutions
     double rmax = 0;
     for (auto &b : c.bodies) rmax = std::max(rmax, b.bound_radius);
     c.near_phase_ok = 4.0 * rmax * c.kappa / (2.0 * M_PI) + 2.0 < 256.0;
-    // every pair of nodes closer than 255 wavelengths: the point order's FP32
-    // phase stays inside the hardware sin/cos input range
-    double dmax = 0;
+    // dmax: every pair of nodes closer than 255 wavelengths, and the point
+    // order's FP32 phase stays inside the hardware sin/cos input range.
+    // dmin: every inter-body pair is at least the smallest gap between bounding
+    // balls apart
+    double dmax = 0, dmin = 1e300;
     for (size_t a = 0; a < c.bodies.size(); ++a)
         for (size_t b = a; b < c.bodies.size(); ++b) {
             const auto &A = c.bodies[a], &B = c.bodies[b];
             const double dx = A.centre[0] - B.centre[0], dy = A.centre[1] - B.centre[1], dz = A.centre[2] - B.centre[2];
-            dmax = std::max(dmax, std::sqrt(dx * dx + dy * dy + dz * dz) + A.bound_radius + B.bound_radius);
+            const double d = std::sqrt(dx * dx + dy * dy + dz * dz);
+            dmax = std::max(dmax, d + A.bound_radius + B.bound_radius);
+            if (b > a) dmin = std::min(dmin, d - A.bound_radius - B.bound_radius);
         }
     c.scene_phase_ok = dmax * c.kappa / (2.0 * M_PI) < 255.0;
-    std::vector<int32_t> off(nr), nf(nr), body(nr), eoff(nr + 1, 0);
-    std::vector<int2> pairs;
-    std::vector<double> g(5 * (size_t)nr);
-    AXS_REQUIRE(N < (int64_t)INT32_MAX, AXS_EINVAL, "node count beyond 32-bit ring tables");
-    for (size_t bi = 0; bi < c.bodies.size(); ++bi) {
-        const auto &b = c.bodies[bi];
-        const Shape &s = c.shapes[b.shape];
-        for (int i = 0; i < s.NG; ++i) {
-            const int id = (int)c.ring_base[bi] + i;
-            off[id] = (int32_t)(b.offset + (int64_t)i * s.NF);
-            nf[id] = s.NF;
-            body[id] = (int32_t)bi;
-            // mirror-pair entries e = 0 .. N_F/2: azimuth e and N_F - e
-            eoff[id] = (int32_t)pairs.size();
-            for (int e = 0; e <= s.NF / 2; ++e) {
-                const int mir = (e == 0 || 2 * e == s.NF) ? -1 : off[id] + s.NF - e;
-                pairs.push_back(make_int2(off[id] + e, mir));
-            }
-            const double sp = std::hypot(s.dr[i], s.dz[i]);
-            g[id] = s.r[i];
-            g[nr + id] = s.z[i];
-            g[2 * nr + id] = -s.dz[i] / sp;
-            g[3 * nr + id] = s.dr[i] / sp;
-            g[4 * nr + id] = s.r[i] > 0 ? -0.5 * g[2 * nr + id] / s.r[i] : 0.0;
-        }
-    }
-    ri.insert(ri.end(), off.begin(), off.end());
-    ri.insert(ri.end(), nf.begin(), nf.end());
-    ri.insert(ri.end(), body.begin(), body.end());
-    eoff[nr] = (int32_t)pairs.size();
-    ri.insert(ri.end(), eoff.begin(), eoff.end());
-    c.ring_i = (int32_t *)c.dalloc(ri.size() * sizeof(int32_t));
-    AXS_HIP(hipMemcpy(c.ring_i, ri.data(), ri.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    c.ring_pair = (int2 *)c.dalloc(pairs.size() * sizeof(int2));
-    AXS_HIP(hipMemcpy(c.ring_pair, pairs.data(), pairs.size() * sizeof(int2), hipMemcpyHostToDevice));
-    auto up = [&](const std::vector<double> &h, double *&d64, float *&d32) {
-        std::vector<float> f(h.begin(), h.end());
-        d64 = (double *)c.dalloc(h.size() * sizeof(double));
-        d32 = (float *)c.dalloc(h.size() * sizeof(float));
-        AXS_HIP(hipMemcpy(d64, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
-        AXS_HIP(hipMemcpy(d32, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice));
-    };
-    up(g, c.ring_g64, c.ring_g32);
-    up(fr, c.frame64, c.frame32);
-    up(csv, c.cs64, c.cs32);
-
-    // (cos, sin)(2 pi k / 1024) for the FP64 sin/cos of the inter-body kernels
-    std::vector<double> tab(2 * SC_N);
-    for (int k = 0; k < SC_N; ++k) {
-        tab[2 * k] = std::cos(2.0 * M_PI * k / SC_N);
-        tab[2 * k + 1] = std::sin(2.0 * M_PI * k / SC_N);
-    }
-    c.sctab = (double2 *)c.dalloc(tab.size() * sizeof(double));
-    AXS_HIP(hipMemcpy(c.sctab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice));
-
-    std::vector<int64_t> bo;
-    for (auto &b : c.bodies) bo.push_back(b.offset);
-    bo.push_back(N);
-    c.body_off = (int64_t *)c.dalloc(bo.size() * sizeof(int64_t));
-    AXS_HIP(hipMemcpy(c.body_off, bo.data(), bo.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-    std::vector<int32_t> bk(1, 0);
-    for (auto &b : c.bodies) bk.push_back(bk.back() + (int32_t)ceil_div(b.n, (int64_t)32));
-    c.nblk = bk.back();
-    c.blk_off = (int32_t *)c.dalloc(bk.size() * sizeof(int32_t));
-    AXS_HIP(hipMemcpy(c.blk_off, bk.data(), bk.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    // FP16 multiply-accumulate: every inter-body pair is at least dmin apart
-    // (the smallest gap between bounding balls), so |4 pi G| <= 1/dmin^2 +
-    // (|eta| + kappa)/dmin; S_G = 2^gexp brings that bound to at most 8192
-    double dmin = 1e300;
-    for (size_t a = 0; a < c.bodies.size(); ++a)
-        for (size_t b2 = a + 1; b2 < c.bodies.size(); ++b2) {
-            const auto &A = c.bodies[a], &Bb = c.bodies[b2];
-            const double dx = A.centre[0] - Bb.centre[0], dy = A.centre[1] - Bb.centre[1],
-                         dz = A.centre[2] - Bb.centre[2];
-            dmin = std::min(dmin, std::sqrt(dx * dx + dy * dy + dz * dz) - A.bound_radius - Bb.bound_radius);
-        }
+    // FP16 multiply-accumulate: |4 pi G| <= 1/dmin^2 + (|eta| + kappa)/dmin;
+    // S_G = 2^gexp brings that bound to at most 8192
     c.mf16_ok = false;
     if (c.bodies.size() > 1 && dmin > 1e-3) {
         const double gb = 1.0 / (dmin * dmin) + (std::fabs(c.eta) + c.kappa) / dmin;
         c.mf16_gexp = (int)std::floor(std::log2(8192.0 / gb));
         c.mf16_ok = c.mf16_gexp > -60 && c.mf16_gexp < 60;
     }
-    if (c.kappa > 0) {
-        // MFMA source operands in each body's frame, scaled so that the
-        // products give R'^2 and nd' of the ring order directly
-        const double k2pi = c.kappa / (2.0 * M_PI), s2 = k2pi * k2pi, c1 = s2 * k2pi;
-        std::vector<double> mf64(8 * (size_t)N);
-        for (size_t bi = 0; bi < c.bodies.size(); ++bi) {
-            const auto &b = c.bodies[bi];
-            const Shape &s = c.shapes[b.shape];
-            for (int i = 0; i < s.NG; ++i) {
-                const double sp = std::hypot(s.dr[i], s.dz[i]);
-                const double nr = -s.dz[i] / sp, nz = s.dr[i] / sp;
-                for (int l = 0; l < s.NF; ++l) {
-                    const double th = 2.0 * M_PI * l / s.NF, ct = std::cos(th), st = std::sin(th);
-                    const double y[3] = {s.r[i] * ct, s.r[i] * st, s.z[i]};
-                    const double n[3] = {nr * ct, nr * st, nz};
-                    const int64_t j = b.offset + (int64_t)i * s.NF + l;
-                    double *a = &mf64[4 * j], *d = &mf64[4 * (N + j)];
-                    for (int k = 0; k < 3; ++k) {
-                        a[k] = -2.0 * s2 * y[k];
-                        d[k] = c1 * n[k];
-                    }
-                    a[3] = s2 * (y[0] * y[0] + y[1] * y[1] + y[2] * y[2]);
-                    d[3] = -c1 * (n[0] * y[0] + n[1] * y[1] + n[2] * y[2]);
-                }
-            }
+    // (cos, sin)(2 pi k / 1024) for the FP64 sin/cos of the inter-body kernels
+    static const std::vector<double> sctab = [] {
+        std::vector<double> tab(2 * SC_N);
+        for (int k = 0; k < SC_N; ++k) {
+            tab[2 * k] = std::cos(2.0 * M_PI * k / SC_N);
+            tab[2 * k + 1] = std::sin(2.0 * M_PI * k / SC_N);
         }
-        const std::vector<float> mf(mf64.begin(), mf64.end());
-        c.mf_src = (float *)c.dalloc(mf.size() * sizeof(float));
-        AXS_HIP(hipMemcpy(c.mf_src, mf.data(), mf.size() * sizeof(float), hipMemcpyHostToDevice));
-        c.mf_src64 = (double *)c.dalloc(mf64.size() * sizeof(double));
-        AXS_HIP(hipMemcpy(c.mf_src64, mf64.data(), mf64.size() * sizeof(double), hipMemcpyHostToDevice));
+        return tab;
+    }();
+    auto up = [&](const void *h, size_t bytes) {
+        void *d = c.dalloc(bytes);
+        AXS_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, c.stream));
+        return d;
+    };
+    const std::vector<float> fr32(fr.begin(), fr.end());
+    c.frame64 = (double *)up(fr.data(), fr.size() * sizeof(double));
+    c.frame32 = (float *)up(fr32.data(), fr32.size() * sizeof(float));
+    c.sctab = (double2 *)up(sctab.data(), sctab.size() * sizeof(double));
+    c.body_off = (int64_t *)up(bo.data(), bo.size() * sizeof(int64_t));
+    c.blk_off = (int32_t *)up(bk.data(), bk.size() * sizeof(int32_t));
+    double *d_cont = (double *)up(cont.data(), cont.size() * sizeof(double));
+    TableBody *d_tb = (TableBody *)up(tb.data(), tb.size() * sizeof(TableBody));
+    NodeOut o{};
+    o.g64 = c.g64 = (double *)c.dalloc(7 * N * sizeof(double));
+    o.g32 = c.g32 = (float *)c.dalloc(6 * N * sizeof(float));
+    o.cs64 = c.cs64 = (double *)c.dalloc(2 * N * sizeof(double));
+    o.cs32 = c.cs32 = (float *)c.dalloc(2 * N * sizeof(float));
+    if (c.kappa > 0) {
+        o.mf64 = c.mf_src64 = (double *)c.dalloc(8 * N * sizeof(double));
+        o.mf32 = c.mf_src = (float *)c.dalloc(8 * N * sizeof(float));
     }
+    c.ring_i = (int32_t *)c.dalloc((4 * (size_t)nr + 1) * sizeof(int32_t));
+    c.ring_pair = (int2 *)c.dalloc(ent * sizeof(int2));
+    c.ring_g64 = (double *)c.dalloc(5 * (size_t)nr * sizeof(double));
+    c.ring_g32 = (float *)c.dalloc(5 * (size_t)nr * sizeof(float));
+    constexpr int YMAX = 65535;   // grid limit: more bodies take several launches
+    for (int b0 = 0; b0 < (int)c.bodies.size(); b0 += YMAX) {
+        const unsigned ny = (unsigned)std::min<size_t>(YMAX, c.bodies.size() - b0);
+        hipLaunchKernelGGL(node_tables_kernel, dim3((unsigned)ceil_div(maxn, 256), ny), dim3(256), 0, c.stream, d_tb,
+                           d_cont, nc, c.frame64, N, b0, c.kappa / (2.0 * M_PI), o);
+        hipLaunchKernelGGL(ring_tables_kernel, dim3((unsigned)maxng, ny), dim3(64), 0, c.stream, d_tb, d_cont, nc, b0,
+                           nr, c.ring_i, c.ring_g64, c.ring_g32, c.ring_pair);
+        AXS_HIP(hipGetLastError());
+    }
+    AXS_HIP(hipStreamSynchronize(c.stream));   // the uploads come from pageable host memory
+    c.dfree(d_cont);
+    c.dfree(d_tb);
 }
 
 template <typename R, int TPT, int BS, bool LAP>

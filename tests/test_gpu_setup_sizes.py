@@ -49,3 +49,37 @@ def test_inverse_of_shapes_of_different_sizes_together():
     for b, c in enumerate(shapes):
         _check_inverse(ctx, b, 2, c.NG)
     ctx.close()
+
+
+@pytest.mark.parametrize("M,kappa", [(0, 1.0), (1, 0.0), (20, 3.0), (40, 0.5)])
+def test_node_geometry_at_small_and_ragged_sizes(M, kappa):
+    """Node positions, normals and weights of rotated bodies of different shapes against their
+    closed form in numpy; positions of mirrored azimuths of an unrotated body mirror exactly."""
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    rng = np.random.default_rng(2)
+    shapes = [geo.sphere(1.0, 1, 3), geo.prolate(0.7, 1.4, 7, 11), geo.bowl(2, 2, 3, 8)]
+    poses = [(np.array([5.0 * k, -1.0, 0.3]), np.eye(3) if k == 0 else geo.random_rotation(rng)) for k in range(3)]
+    ctx = Context(0)
+    for c, (x0, rot) in zip(shapes, poses):
+        ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.0, M, x0, rot)
+    ctx.precompute_scattering()
+    got = ctx.node_geometry()
+    NF, rows = 2 * M + 1, []
+    for c, (x0, rot) in zip(shapes, poses):
+        th = 2 * math.pi * np.arange(NF) / NF
+        r, z = c.rz[:, :1], c.rz[:, 1:]
+        sp = np.hypot(c.drz[:, :1], c.drz[:, 1:])
+        nr, nz = -c.drz[:, 1:] / sp, c.drz[:, :1] / sp
+        one = np.ones((1, NF))
+        loc = np.stack([r * np.cos(th), r * np.sin(th), z * one], -1).reshape(-1, 3)
+        nl = np.stack([nr * np.cos(th), nr * np.sin(th), nz * one], -1).reshape(-1, 3)
+        w = ((2 * math.pi / NF) * r * sp * c.gw[:, None] * one).reshape(-1, 1)
+        rows.append(np.concatenate([loc @ rot.T + x0, nl @ rot.T, w], 1))
+    ref = np.concatenate(rows)
+    # a handful of roundings at the size of the coordinates (up to 12)
+    assert np.max(np.abs(got - ref)) < 12 * 8 * np.finfo(np.float64).eps
+    first = got[:shapes[0].NG * NF].reshape(-1, NF, 7)
+    if M:
+        assert np.array_equal(first[:, 1:, 0], first[:, :0:-1, 0])
+    ctx.close()
