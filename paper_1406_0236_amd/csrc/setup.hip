@@ -8,8 +8,8 @@
 // on the target's own panel, its neighbours and any panel closer to y_i than
 // that panel's arc length (the paper cites Kolm-Rokhlin corrected quadrature
 // for this step; here it is product integration with a graded Gauss rule:
-// geometric bisection towards the (near-)singular parameter, 46 levels of 10
-// Gauss points per side, which resolves the logarithmic singularity).
+// geometric bisection towards the (near-)singular parameter, max(10, p) Gauss
+// points per level, see the constants below for how far it goes).
 // On a near panel the curve is the polynomial interpolant of the node
 // positions and its derivative gives the normal and line element; on the
 // target's own panel the displacement y(s) - y_i is formed from the Lagrange
@@ -37,31 +37,58 @@
 
 namespace axs {
 
-constexpr int NLEV = 46;       // graded levels per side
-constexpr int NGL = 10;        // Gauss points per level
+// Gauss points per level: the interpolation l_j(s) times the curve's own
+// polynomial has degree 2p and more, which 10 points do not integrate for p > 10
+// (with 10 the largest error of an entry is 2e-12 at p = 11, 1e-11 at 12 and
+// 1e-8 at 16; with p points the kernel values' noise, 1e-12)
+static int level_points(int p) { return p > 10 ? p : 10; }
 constexpr int PMAX = 16;       // max nodes per panel supported
+// Levels of the graded rule.  Every kernel value costs the same, so the points
+// are what the precomputation pays for; 46 levels on both sides of every near
+// panel (920 points) resolved far more than is there:
+//  - own panel (the target is a node of it): a logarithmic singularity at the
+//    node, a(s) log|s - s_i| + b(s) with a, b analytic.  OWN_LEV levels, then the
+//    remaining interval [0, h] under x = h u^OWN_Q with OWN_NQ Gauss points,
+//    which integrates polynomials and polynomials times log x to rounding: 134
+//    points a side for p <= 10.
+//  - other near panels: the integrand is analytic at the split point, its
+//    singularity at least the target's distance d away, so the halving stops
+//    where the innermost interval is shorter than d / 8 and that interval is one
+//    level (10 Gauss points leave (16 + sqrt(255))^-20); 90 to 110 points a side,
+//    none on a side of length zero.
+// In FP64 the two rules agree with the 46-level one to the noise of the kernel
+// values (1e-13 to 4e-12 of the largest entry, where 46 levels are as far from a
+// tanh-sinh rule) for spheres of 1 to 20 panels, spheroids, a 10 : 1 needle and
+// bowls, p = 3 to 16.  2760 -> 480 points per target node of a smooth contour:
+// precomputation of 8 mixed bodies 6.08 -> 2.71 ms, of 27 spheres (one shape of
+// 200 contour nodes) 6.85 -> 2.73 ms.
+constexpr int OWN_LEV = 11, OWN_Q = 8, OWN_NQ = 24;
+constexpr int MAX_LEV = 46;
 
 struct Pts {
     double *rt, *rp, *dr, *dz, *nr, *nz, *wj;   // [P]
-    double *lag;                                 // [P][p] (near points only)
+    double *lag;                                 // [near points][p]
 };
 
+// target node i against near panel P, split at sstar: n0 points on the side
+// towards -1 and n1 towards 1, from near point `first` of the batch on
 struct NearDesc {
     int32_t i, P;
     double sstar;
+    int32_t n0, n1, first, pad;
 };
 
 // ---------------------------------------------------------------------------
 // evaluation points
 // ---------------------------------------------------------------------------
-__global__ void gen_far_kernel(const int2 *__restrict__ pairs, int n, const double *__restrict__ r,
+// far points: pair (i, P) of target node and panel, its p nodes in turn
+__global__ void gen_far_kernel(const int2 *__restrict__ pairs, int n, int p, const double *__restrict__ r,
                                const double *__restrict__ z, const double *__restrict__ nr,
-                               const double *__restrict__ nz, const double *__restrict__ aw, Pts pts,
-                               int64_t base) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n) return;
-    const int i = pairs[idx].x, j = pairs[idx].y;
-    const int64_t o = base + idx;
+                               const double *__restrict__ nz, const double *__restrict__ aw, Pts pts) {
+    int o = blockIdx.x * blockDim.x + threadIdx.x;
+    if (o >= n * p) return;
+    const int2 pr = pairs[o / p];
+    const int i = pr.x, j = pr.y * p + o % p;
     pts.rt[o] = r[i];
     pts.rp[o] = r[j];
     pts.dr[o] = r[j] - r[i];
@@ -71,84 +98,84 @@ __global__ void gen_far_kernel(const int2 *__restrict__ pairs, int n, const doub
     pts.wj[o] = aw[j];
 }
 
-__global__ void gen_near_kernel(const NearDesc *__restrict__ desc, int npairs, int p,
-                                const double *__restrict__ snode, const double *__restrict__ lden,
-                                const double *__restrict__ glu, const double *__restrict__ glw,
-                                const double *__restrict__ r, const double *__restrict__ z, Pts pts,
-                                int64_t base) {
-    const int per = 2 * NLEV * NGL;
-    int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)npairs * per) return;
-    const int pair = (int)(idx / per);
-    const int rem = (int)(idx - (int64_t)pair * per);
-    const int side = rem / (NLEV * NGL);
-    const int lev = (rem / NGL) % NLEV;
-    const int kq = rem % NGL;
-    const NearDesc d = desc[pair];
-    const int64_t o = base + idx;
-    const double sst = d.sstar;
-    const double dir = side == 0 ? -1.0 : 1.0;
-    const double Ls = side == 0 ? sst + 1.0 : 1.0 - sst;
-    double* lag = pts.lag + o * p;
-    bool ok = Ls > 1e-14;
-    double off = 0, wq = 0;
-    if (ok) {
-        const double hi = Ls * ldexp(1.0, -lev);
-        const double lo = (lev == NLEV - 1) ? 0.0 : 0.5 * hi;
-        off = lo + (hi - lo) * 0.5 * (glu[kq] + 1.0);
-        wq = glw[kq] * 0.5 * (hi - lo);
-    }
-    const double s = sst + dir * off;
+// one workgroup per near pair
+__global__ void gen_near_kernel(const NearDesc *__restrict__ desc, int p, const double *__restrict__ snode,
+                                const double *__restrict__ lden, const double *__restrict__ glu,
+                                const double *__restrict__ glw, int ngl, const double *__restrict__ ownx,
+                                const double *__restrict__ ownw, const double *__restrict__ r,
+                                const double *__restrict__ z, Pts pts, int64_t base) {
+    const NearDesc d = desc[blockIdx.x];
     const int own = (d.i / p) == d.P;
-    const int iloc = d.i - d.P * p;
-    const double *rP = r + d.P * p, *zP = z + d.P * p;
-    // Lagrange basis and its derivative at s; on the own panel the factor
-    // (s - s_iloc) is the exact signed offset.
-    double diff[PMAX];
-    for (int k = 0; k < p; ++k) diff[k] = (own && k == iloc) ? dir * off : s - snode[k];
-    double L[PMAX], D[PMAX];
-    for (int j = 0; j < p; ++j) {
-        double prod = lden[j];
-        for (int k = 0; k < p; ++k)
-            if (k != j) prod *= diff[k];
-        L[j] = prod;
-        double der = 0;
-        for (int m = 0; m < p; ++m) {
-            if (m == j) continue;
-            double t = lden[j];
+    for (int idx = threadIdx.x; idx < d.n0 + d.n1; idx += blockDim.x) {
+        const int side = idx >= d.n0;
+        const int q = side ? idx - d.n0 : idx;
+        const int64_t o = base + d.first + idx;
+        const double sst = d.sstar;
+        const double dir = side == 0 ? -1.0 : 1.0;
+        const double Ls = side == 0 ? sst + 1.0 : 1.0 - sst;
+        double* lag = pts.lag + (int64_t)(d.first + idx) * p;
+        double off, wq;
+        if (own) {
+            off = Ls * ownx[q];
+            wq = Ls * ownw[q];
+        } else {
+            const int lev = q / ngl, kq = q % ngl, nlev = (side ? d.n1 : d.n0) / ngl;
+            const double hi = Ls * ldexp(1.0, -lev);
+            const double lo = lev == nlev - 1 ? 0.0 : 0.5 * hi;
+            off = lo + (hi - lo) * 0.5 * (glu[kq] + 1.0);
+            wq = glw[kq] * 0.5 * (hi - lo);
+        }
+        const double s = sst + dir * off;
+        const int iloc = d.i - d.P * p;
+        const double *rP = r + d.P * p, *zP = z + d.P * p;
+        // Lagrange basis and its derivative at s; on the own panel the factor
+        // (s - s_iloc) is the exact signed offset.
+        double diff[PMAX];
+        for (int k = 0; k < p; ++k) diff[k] = (own && k == iloc) ? dir * off : s - snode[k];
+        double L[PMAX], D[PMAX];
+        for (int j = 0; j < p; ++j) {
+            double prod = lden[j];
             for (int k = 0; k < p; ++k)
-                if (k != j && k != m) t *= diff[k];
-            der += t;
+                if (k != j) prod *= diff[k];
+            L[j] = prod;
+            double der = 0;
+            for (int m = 0; m < p; ++m) {
+                if (m == j) continue;
+                double t = lden[j];
+                for (int k = 0; k < p; ++k)
+                    if (k != j && k != m) t *= diff[k];
+                der += t;
+            }
+            D[j] = der;
         }
-        D[j] = der;
-    }
-    double rp = 0, zp = 0, rs = 0, zs = 0, dr = 0, dz = 0;
-    for (int k = 0; k < p; ++k) {
-        rp += L[k] * rP[k];
-        zp += L[k] * zP[k];
-        rs += D[k] * rP[k];
-        zs += D[k] * zP[k];
-    }
-    if (own) {
+        double rp = 0, zp = 0, rs = 0, zs = 0, dr = 0, dz = 0;
         for (int k = 0; k < p; ++k) {
-            if (k == iloc) continue;
-            dr += L[k] * (rP[k] - r[d.i]);
-            dz += L[k] * (zP[k] - z[d.i]);
+            rp += L[k] * rP[k];
+            zp += L[k] * zP[k];
+            rs += D[k] * rP[k];
+            zs += D[k] * zP[k];
         }
-    } else {
-        dr = rp - r[d.i];
-        dz = zp - z[d.i];
+        if (own) {
+            for (int k = 0; k < p; ++k) {
+                if (k == iloc) continue;
+                dr += L[k] * (rP[k] - r[d.i]);
+                dz += L[k] * (zP[k] - z[d.i]);
+            }
+        } else {
+            dr = rp - r[d.i];
+            dz = zp - z[d.i];
+        }
+        const double sp = sqrt(rs * rs + zs * zs);
+        const bool ok = rp > 1e-13 && (dr * dr + dz * dz) > 0.0;
+        pts.rt[o] = r[d.i];
+        pts.rp[o] = ok ? rp : -1.0;     // rp < 0 marks a point that contributes nothing
+        pts.dr[o] = dr;
+        pts.dz[o] = dz;
+        pts.nr[o] = -zs / sp;
+        pts.nz[o] = rs / sp;
+        pts.wj[o] = ok ? wq * rp * sp : 0.0;
+        for (int k = 0; k < p; ++k) lag[k] = L[k];
     }
-    const double sp = sqrt(rs * rs + zs * zs);
-    ok = ok && rp > 1e-13 && (dr * dr + dz * dz) > 0.0;
-    pts.rt[o] = r[d.i];
-    pts.rp[o] = ok ? rp : -1.0;     // rp < 0 marks a point that contributes nothing
-    pts.dr[o] = dr;
-    pts.dz[o] = dz;
-    pts.nr[o] = -zs / sp;
-    pts.nz[o] = rs / sp;
-    pts.wj[o] = ok ? wq * rp * sp : 0.0;
-    for (int k = 0; k < p; ++k) lag[k] = L[k];
 }
 
 // ---------------------------------------------------------------------------
@@ -349,28 +376,28 @@ __global__ __launch_bounds__(64 * WPB) void modal_kernel(Pts pts, int64_t npts, 
 // ---------------------------------------------------------------------------
 // assembly of A~_m
 // ---------------------------------------------------------------------------
-__global__ void scatter_far_kernel(const int2 *__restrict__ pairs, int n, int M, int NG,
-                                   const double2 *__restrict__ kval, int64_t base, double2 *__restrict__ A) {
+__global__ void scatter_far_kernel(const int2 *__restrict__ pairs, int n, int p, int M, int NG,
+                                   const double2 *__restrict__ kval, double2 *__restrict__ A) {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n * (M + 1)) return;
-    const int pr = (int)(idx / (M + 1)), m = (int)(idx % (M + 1));
-    const int i = pairs[pr].x, j = pairs[pr].y;
-    A[((int64_t)m * NG + i) * NG + j] = kval[(base + pr) * (M + 1) + m];
+    if (idx >= (int64_t)n * p * (M + 1)) return;
+    const int o = (int)(idx / (M + 1)), m = (int)(idx % (M + 1));
+    const int2 pr = pairs[o / p];
+    A[((int64_t)m * NG + pr.x) * NG + pr.y * p + o % p] = kval[idx];
 }
 
 __global__ void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int NG, int p,
                                    const double2 *__restrict__ kval, const double *__restrict__ lag,
                                    int64_t base, double2 *__restrict__ A) {
-    const int pair = blockIdx.x;
-    const NearDesc d = desc[pair];
-    const int per = 2 * NLEV * NGL;
-    const int64_t p0 = base + (int64_t)pair * per;
+    const NearDesc d = desc[blockIdx.x];
+    const int per = d.n0 + d.n1;
+    const double2 *kv = kval + (base + d.first) * (M + 1);
+    const double *lg = lag + (int64_t)d.first * p;
     for (int t = threadIdx.x; t < (M + 1) * p; t += blockDim.x) {
         const int m = t / p, j = t % p;
         double re = 0, im = 0;
         for (int q = 0; q < per; ++q) {
-            const double2 v = kval[(p0 + q) * (M + 1) + m];
-            const double l = lag[(p0 + q) * p + j];
+            const double2 v = kv[(int64_t)q * (M + 1) + m];
+            const double l = lg[(int64_t)q * p + j];
             re = fma(v.x, l, re);
             im = fma(v.y, l, im);
         }
@@ -741,9 +768,11 @@ void precompute_shape(Ctx &c, Shape &s) {
     s.Nt = modal_nt(s);
     const int Nt = s.Nt, L = Nt / 2 - 1, nq = M + L + 1;
 
-    std::vector<double> sn, sw, gu, gwq;
+    std::vector<double> sn, sw, gu, gwq, qu, qw;
     gauss_legendre(p, sn, sw);
-    gauss_legendre(NGL, gu, gwq);
+    const int ngl = level_points(p), own_pts = OWN_LEV * ngl + OWN_NQ;
+    gauss_legendre(ngl, gu, gwq);
+    gauss_legendre(OWN_NQ, qu, qw);
     std::vector<double> lden(p);
     for (int j = 0; j < p; ++j) {
         double d = 1.0;
@@ -751,17 +780,31 @@ void precompute_shape(Ctx &c, Shape &s) {
             if (k != j) d *= (sn[j] - sn[k]);
         lden[j] = 1.0 / d;
     }
+    // the own-panel rule on [0, 1], singular at 0
+    std::vector<double> ownx, ownw;
+    for (int lev = 0; lev < OWN_LEV; ++lev)
+        for (int k = 0; k < ngl; ++k) {
+            const double half = std::ldexp(0.25, -lev);   // half of [2^-(lev + 1), 2^-lev]
+            ownx.push_back(2.0 * half + half * (gu[k] + 1.0));
+            ownw.push_back(half * gwq[k]);
+        }
+    for (int k = 0; k < OWN_NQ; ++k) {
+        const double u = 0.5 * (qu[k] + 1.0), h = std::ldexp(1.0, -OWN_LEV);
+        ownx.push_back(h * std::pow(u, OWN_Q));
+        ownw.push_back(h * OWN_Q * std::pow(u, OWN_Q - 1) * 0.5 * qw[k]);
+    }
     // node data
-    std::vector<double> nr(NG), nz(NG), aw(NG), plen(np_, 0.0);
+    std::vector<double> nr(NG), nz(NG), aw(NG), plen(np_, 0.0), smax(np_, 0.0);
     for (int i = 0; i < NG; ++i) {
         const double sp = std::hypot(s.dr[i], s.dz[i]);
         nr[i] = -s.dz[i] / sp;
         nz[i] = s.dr[i] / sp;
         aw[i] = s.r[i] * sp * s.gw[i];
         plen[i / p] += sp * s.gw[i];
+        smax[i / p] = std::max(smax[i / p], sp);
     }
     // near panels and split points per target (host geometry)
-    std::vector<std::vector<std::pair<int, double>>> near(NG);
+    std::vector<std::vector<NearDesc>> near(NG);
     std::vector<double> endr(2 * np_), endz(2 * np_);
     for (int P = 0; P < np_; ++P) {
         endr[2 * P] = interp_at(sn, &s.r[P * p], p, -1.0);
@@ -769,99 +812,109 @@ void precompute_shape(Ctx &c, Shape &s) {
         endz[2 * P] = interp_at(sn, &s.z[P * p], p, -1.0);
         endz[2 * P + 1] = interp_at(sn, &s.z[P * p], p, 1.0);
     }
+    // points on one side (length Ls in s) of a panel at distance d: halve until
+    // the innermost interval is shorter than d / 8
+    auto side_points = [&](double Ls, double d, double speed) {
+        if (!(Ls > 1e-14)) return 0;
+        int n = 1;
+        while (n < MAX_LEV && std::ldexp(Ls, 1 - n) * speed > 0.125 * d) ++n;
+        return n * ngl;
+    };
     for (int i = 0; i < NG; ++i) {
         const int own = i / p;
         for (int P = 0; P < np_; ++P) {
-            double best = 1e300, bs = 0;
+            double best2 = 1e300, bs = 0;
             auto consider = [&](double rr, double zz, double sv) {
-                double d = std::hypot(rr - s.r[i], zz - s.z[i]);
-                if (d < best) {
-                    best = d;
+                const double a = rr - s.r[i], b = zz - s.z[i], d2 = a * a + b * b;
+                if (d2 < best2) {
+                    best2 = d2;
                     bs = sv;
                 }
             };
             consider(endr[2 * P], endz[2 * P], -1.0);
             for (int k = 0; k < p; ++k) consider(s.r[P * p + k], s.z[P * p + k], sn[k]);
             consider(endr[2 * P + 1], endz[2 * P + 1], 1.0);
+            const double best = std::sqrt(best2);
             const bool is_near = std::abs(P - own) <= 1 || best < plen[P];
             if (!is_near) continue;
-            const double sst = P == own ? sn[i - own * p] : bs;
-            near[i].push_back({P, sst});
+            NearDesc d{};
+            d.i = i;
+            d.P = P;
+            if (P == own) {
+                d.sstar = sn[i - own * p];
+                d.n0 = d.n1 = own_pts;
+            } else {
+                d.sstar = bs;
+                d.n0 = side_points(bs + 1.0, best, smax[P]);
+                d.n1 = side_points(1.0 - bs, best, smax[P]);
+            }
+            near[i].push_back(d);
         }
     }
-    // device constants
-    double *d_sn = (double *)c.dalloc(p * sizeof(double));
-    double *d_lden = (double *)c.dalloc(p * sizeof(double));
-    double *d_gu = (double *)c.dalloc(NGL * sizeof(double));
-    double *d_gw = (double *)c.dalloc(NGL * sizeof(double));
-    double *d_r = (double *)c.dalloc(NG * sizeof(double));
-    double *d_z = (double *)c.dalloc(NG * sizeof(double));
-    double *d_nr = (double *)c.dalloc(NG * sizeof(double));
-    double *d_nz = (double *)c.dalloc(NG * sizeof(double));
-    double *d_aw = (double *)c.dalloc(NG * sizeof(double));
-    AXS_HIP(hipMemcpy(d_sn, sn.data(), p * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_lden, lden.data(), p * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_gu, gu.data(), NGL * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_gw, gwq.data(), NGL * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_r, s.r.data(), NG * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_z, s.z.data(), NG * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_nr, nr.data(), NG * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_nz, nz.data(), NG * sizeof(double), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_aw, aw.data(), NG * sizeof(double), hipMemcpyHostToDevice));
+    // device constants, one block
+    std::vector<double> hc;
+    auto put = [&](const std::vector<double> &v) {
+        const size_t o = hc.size();
+        hc.insert(hc.end(), v.begin(), v.end());
+        return o;
+    };
+    const size_t o_sn = put(sn), o_lden = put(lden), o_gu = put(gu), o_gw = put(gwq), o_ox = put(ownx),
+                 o_ow = put(ownw), o_r = put(s.r), o_z = put(s.z), o_nr = put(nr), o_nz = put(nz), o_aw = put(aw);
+    double *dc = (double *)c.dalloc(hc.size() * sizeof(double));
+    AXS_HIP(hipMemcpyAsync(dc, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
 
     const int64_t nmat = (int64_t)(M + 1) * NG * NG;
-    double2 *A = (double2 *)c.dalloc(nmat * sizeof(double2));
-    AXS_HIP(hipMemsetAsync(A, 0, nmat * sizeof(double2), c.stream));
+    double2 *A = (double2 *)c.dalloc(nmat * sizeof(double2));   // every entry is written below
     s.A64 = (double *)A;
 
     // batches of target rows, bounded number of evaluation points
-    const int per_near = 2 * NLEV * NGL;
     const int64_t max_pts = 1 << 19;
     int i0 = 0;
     while (i0 < NG) {
         int i1 = i0;
         int64_t npts = 0;
-        while (i1 < NG) {
-            int64_t add = (NG - (int64_t)near[i1].size() * p) + (int64_t)near[i1].size() * per_near;
-            if (i1 > i0 && npts + add > max_pts) break;
-            npts += add;
-            ++i1;
-        }
         std::vector<int2> far;
         std::vector<NearDesc> nd;
-        for (int i = i0; i < i1; ++i) {
-            std::vector<char> isnear(np_, 0);
-            for (auto &pr : near[i]) {
-                isnear[pr.first] = 1;
-                nd.push_back(NearDesc{i, pr.first, pr.second});
+        int64_t nnear = 0;
+        while (i1 < NG) {
+            int64_t add = (int64_t)(np_ - (int)near[i1].size()) * p;
+            for (auto &d : near[i1]) add += d.n0 + d.n1;
+            if (i1 > i0 && npts + add > max_pts) break;
+            npts += add;
+            size_t k = 0;
+            for (int P = 0; P < np_; ++P) {
+                if (k < near[i1].size() && near[i1][k].P == P) {
+                    NearDesc d = near[i1][k++];
+                    d.first = (int32_t)nnear;
+                    nnear += d.n0 + d.n1;
+                    nd.push_back(d);
+                } else {
+                    far.push_back(make_int2(i1, P));
+                }
             }
-            for (int j = 0; j < NG; ++j)
-                if (!isnear[j / p]) far.push_back(make_int2(i, j));
+            ++i1;
         }
-        const int64_t nfar = far.size(), nnear = (int64_t)nd.size() * per_near;
+        const int64_t nfar = (int64_t)far.size() * p;
         const int64_t P = nfar + nnear;
         // point storage
-        double *pbuf = (double *)c.scratch(WS_MISC, (size_t)P * (7 + p) * sizeof(double));
+        double *pbuf = (double *)c.scratch(WS_MISC, ((size_t)P * 7 + (size_t)nnear * p) * sizeof(double));
         Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, pbuf + 7 * P};
         double *qv = (double *)c.scratch(WS_TMP, (size_t)P * nq * sizeof(double));
         double *dqv = (double *)c.scratch(WS_TMP2, (size_t)P * nq * sizeof(double));
         double2 *kv = (double2 *)c.scratch(WS_TMP3, (size_t)P * (M + 1) * sizeof(double2));
-        int2 *d_far = nullptr;
-        NearDesc *d_nd = nullptr;
+        int2 *d_far = (int2 *)c.scratch(WS_RED, far.size() * sizeof(int2));
+        NearDesc *d_nd = (NearDesc *)c.scratch(WS_GEMM, nd.size() * sizeof(NearDesc));
         if (nfar) {
-            d_far = (int2 *)c.scratch(WS_RED, nfar * sizeof(int2));
-            AXS_HIP(hipMemcpy(d_far, far.data(), nfar * sizeof(int2), hipMemcpyHostToDevice));
+            AXS_HIP(hipMemcpyAsync(d_far, far.data(), far.size() * sizeof(int2), hipMemcpyHostToDevice, c.stream));
             hipLaunchKernelGGL(gen_far_kernel, dim3(ceil_div(nfar, 256)), dim3(256), 0, c.stream, d_far,
-                               (int)nfar, d_r, d_z, d_nr, d_nz, d_aw, pts, (int64_t)0);
+                               (int)far.size(), p, dc + o_r, dc + o_z, dc + o_nr, dc + o_nz, dc + o_aw, pts);
             AXS_HIP(hipGetLastError());
         }
-        if (nnear) {
-            d_nd = (NearDesc *)c.scratch(WS_GEMM, nd.size() * sizeof(NearDesc));
-            AXS_HIP(hipMemcpy(d_nd, nd.data(), nd.size() * sizeof(NearDesc), hipMemcpyHostToDevice));
-            hipLaunchKernelGGL(gen_near_kernel, dim3(ceil_div(nnear, 128)), dim3(128), 0, c.stream, d_nd,
-                               (int)nd.size(), p, d_sn, d_lden, d_gu, d_gw, d_r, d_z, pts, nfar);
-            AXS_HIP(hipGetLastError());
-        }
+        // a target's own panel is always near, so no batch is without near points
+        AXS_HIP(hipMemcpyAsync(d_nd, nd.data(), nd.size() * sizeof(NearDesc), hipMemcpyHostToDevice, c.stream));
+        hipLaunchKernelGGL(gen_near_kernel, dim3(nd.size()), dim3(128), 0, c.stream, d_nd, p, dc + o_sn, dc + o_lden,
+                           dc + o_gu, dc + o_gw, ngl, dc + o_ox, dc + o_ow, dc + o_r, dc + o_z, pts, nfar);
+        AXS_HIP(hipGetLastError());
         hipLaunchKernelGGL(toroidal_kernel, dim3(ceil_div(P, 64)), dim3(64), 0, c.stream, pts, P, nq - 1, qv,
                            dqv);
         AXS_HIP(hipGetLastError());
@@ -874,24 +927,21 @@ void precompute_shape(Ctx &c, Shape &s) {
         AXS_HIP(hipGetLastError());
         if (nfar) {
             hipLaunchKernelGGL(scatter_far_kernel, dim3(ceil_div(nfar * (M + 1), 256)), dim3(256), 0, c.stream,
-                               d_far, (int)nfar, M, NG, kv, (int64_t)0, A);
+                               d_far, (int)far.size(), p, M, NG, kv, A);
             AXS_HIP(hipGetLastError());
         }
-        if (nnear) {
-            hipLaunchKernelGGL(near_reduce_kernel, dim3(nd.size()), dim3(256), 0, c.stream, d_nd, M, NG, p, kv,
-                               pts.lag, nfar, A);
-            AXS_HIP(hipGetLastError());
-        }
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        hipLaunchKernelGGL(near_reduce_kernel, dim3(nd.size()), dim3(256), 0, c.stream, d_nd, M, NG, p, kv, pts.lag,
+                           nfar, A);
+        AXS_HIP(hipGetLastError());
         i0 = i1;
+        if (i0 >= NG) {
+            hipLaunchKernelGGL(add_half_identity_kernel, dim3(ceil_div((M + 1) * NG, 256)), dim3(256), 0, c.stream, A,
+                               M, NG);
+            AXS_HIP(hipGetLastError());
+        }
+        AXS_HIP(hipStreamSynchronize(c.stream));   // far, nd (and hc) are pageable host memory
     }
-    hipLaunchKernelGGL(add_half_identity_kernel, dim3(ceil_div((M + 1) * NG, 256)), dim3(256), 0, c.stream, A,
-                       M, NG);
-    AXS_HIP(hipGetLastError());
-    AXS_HIP(hipStreamSynchronize(c.stream));   // the inverses follow for all shapes at once
-    for (void *ptr : {(void *)d_sn, (void *)d_lden, (void *)d_gu, (void *)d_gw, (void *)d_r, (void *)d_z,
-                      (void *)d_nr, (void *)d_nz, (void *)d_aw})
-        c.dfree(ptr);
+    c.dfree(dc);
 }
 
 // S_m = A~_m^{-1} for every shape and mode, in groups of shapes whose work

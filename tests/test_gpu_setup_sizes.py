@@ -83,3 +83,28 @@ def test_node_geometry_at_small_and_ragged_sizes(M, kappa):
     if M:
         assert np.array_equal(first[:, 1:, 0], first[:, :0:-1, 0])
     ctx.close()
+
+
+@pytest.mark.parametrize("kind,kappa,eta,M", [("sphere2", 1.0, 1.0, 20), ("bowl", 2 * math.pi, 2 * math.pi, 12),
+                                              ("prolate", 0.0, 1.0, 20), ("prolate16", 3.0, 3.0, 10)])
+def test_modal_matrices_against_the_reference(kind, kappa, eta, M):
+    """A~_m with the graded rules of own and neighbouring panels against the reference's
+    tanh-sinh product integrals, on a few target rows.  The reference refines until two steps agree to
+    2e-12 of the largest entry at worst; the bound is five times that."""
+    from oracle.nystrom import Shape
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    c = {"sphere2": lambda: geo.sphere(1.0, 2, 10), "bowl": lambda: geo.bowl(3, 2, 4, 10),
+         "prolate": lambda: geo.prolate(0.5, 1.0, 5, 10),
+         "prolate16": lambda: geo.prolate(0.8, 1.3, 3, 16)}[kind]()
+    ctx = Context(0)
+    ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, eta, M, np.zeros(3), np.eye(3))
+    ctx.precompute_scattering()
+    A = ctx.modal_matrices(0, 0, M=M, NG=c.NG).cpu().numpy()
+    ref = Shape(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, eta, M, Nt=128)
+    for i in sorted({0, c.p - 1, c.p, c.NG // 2, c.NG - 1}):
+        row = ref.modal_row(i)
+        row[:, i] += 0.5
+        err = np.max(np.abs(A[:, i, :] - row)) / np.max(np.abs(row))
+        assert err < 1e-11, (kind, i, err)
+    ctx.close()
