@@ -650,6 +650,17 @@ axs_status axs_incident_point_sources(axs_ctx *ctx, const double *src, const dou
     });
 }
 
+// max |p_i| of n host points (NaN if any coordinate is)
+static double largest_norm(const double *p, int n) {
+    double m = 0;
+    for (int i = 0; i < n; ++i) {
+        const double d = p[3 * i] * p[3 * i] + p[3 * i + 1] * p[3 * i + 1] + p[3 * i + 2] * p[3 * i + 2];
+        if (!(d <= m)) m = d;
+        if (m != m) break;
+    }
+    return std::sqrt(m);
+}
+
 axs_status axs_eval_field(axs_ctx *ctx, const void *sigma, int nrhs, const double *tgt, int nt, void *u) {
     return guarded(ctx, [&](Ctx &c) -> axs_status {
         AXS_REQUIRE(c.precomputed, AXS_ESTATE, "call axs_precompute_scattering first");
@@ -657,7 +668,7 @@ axs_status axs_eval_field(axs_ctx *ctx, const void *sigma, int nrhs, const doubl
                     "bad arguments");
         double *d = (double *)c.scratch(axs::WS_EVAL, 3 * nt * sizeof(double));
         AXS_HIP(hipMemcpy(d, tgt, 3 * nt * sizeof(double), hipMemcpyHostToDevice));
-        axs::eval_field_launch(c, sigma, nrhs, d, nt, u);
+        axs::eval_field_launch(c, sigma, nrhs, d, nt, largest_norm(tgt, nt), u);
         AXS_HIP(hipStreamSynchronize(c.stream));
         return AXS_OK;
     });
@@ -671,7 +682,7 @@ axs_status axs_far_field(axs_ctx *ctx, const void *sigma, int nrhs, const double
         AXS_REQUIRE(c.kappa > 0, AXS_EINVAL, "no far field at kappa = 0");
         double *d = (double *)c.scratch(axs::WS_EVAL, 3 * nd * sizeof(double));
         AXS_HIP(hipMemcpy(d, xhat, 3 * nd * sizeof(double), hipMemcpyHostToDevice));
-        axs::far_field_launch(c, sigma, nrhs, d, nd, out);
+        axs::far_field_launch(c, sigma, nrhs, d, nd, largest_norm(xhat, nd), out);
         AXS_HIP(hipStreamSynchronize(c.stream));
         return AXS_OK;
     });

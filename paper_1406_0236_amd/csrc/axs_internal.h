@@ -310,12 +310,11 @@ void interbody_partials(Ctx &c, const void *sigma, int nrhs, int prec);   // -> 
 int64_t interbody_scratch_bytes(Ctx &c, int prec, int nrhs);
 void interbody_reduce_to_c128(Ctx &c, void *y, int nrhs, int prec, bool add = false);  // WS_PART -> (+)y
 int interbody_splits(Ctx &c, int prec, int nrhs);
-void eval_field_launch(Ctx &c, const void *sigma, int nrhs, const double *tgt_dev, int nt,
-                       void *u);
-void far_field_launch(Ctx &c, const void *sigma, int nrhs, const double *xh_dev, int nd,
-                      void *u);
 void incident_plane_launch(Ctx &c, const double *dirs_dev, int nrhs, void *v);
 void incident_point_launch(Ctx &c, const double *src_dev, const double *amp_dev, int ns, void *v);
+// field.hip: tmax, xmax: the largest |target|, |direction| (from the caller's host copy)
+void eval_field_launch(Ctx &c, const void *sigma, int nrhs, const double *tgt_dev, int nt, double tmax, void *u);
+void far_field_launch(Ctx &c, const void *sigma, int nrhs, const double *xh_dev, int nd, double xmax, void *u);
 // modal.hip
 // forward DFT from partial sums (src = 0) or from a complex128 vector (src = 1)
 void dft_forward(Ctx &c, int prec, int from_vec, const void *vec, int nrhs, int splits);

@@ -1,5 +1,5 @@
-// Inter-body operator B (Sec. 3.3 naive-rule blocks, applied in Sec. 4), field
-// evaluation (eq. "intHelm1") and incident fields, hand-written for gfx950.
+// Inter-body operator B (Sec. 3.3 naive-rule blocks, applied in Sec. 4) and
+// incident fields, hand-written for gfx950.
 //
 // B sigma is a direct sum over every (target, source) pair on different bodies,
 //   (B sigma)_i = sum_{j notin body(i)} G(x_i, x_j) q_j,   q_j = w_j sigma_j / (4 pi)
@@ -29,6 +29,7 @@
 //     those constants so that R * kappa / 2 pi (the phase in revolutions)
 //     is R^2 * rsq(R^2) with no further multiply.
 #include "axs_internal.h"
+#include "fp64_math.h"
 
 namespace axs {
 
@@ -48,36 +49,6 @@ __device__ __forceinline__ void sincos_rev_near(float ph, float &s, float &c) {
     c = __builtin_amdgcn_cosf(ph);
 }
 
-// sin and cos of 2 pi t in FP64 for |t| < 2^40 revolutions, with a 1024-entry
-// table of (cos, sin)(2 pi j / 1024) held in LDS:
-//   y = t + 1.5 * 2^42 (one add; the sum has an ulp of 1/1024) rounds t to the
-//   nearest multiple j / 1024, and the low word of y is j, which indexes the
-//   table; y - 1.5 * 2^42 is j / 1024 exactly, and so is r = t - j / 1024, in
-//   [-1/2048, 1/2048];
-//   with x = 2 pi r, |x| <= h = pi / 1024: cos x to x^4 (Taylor; the first
-//   dropped term below 1.2e-18) and sin x to x^3, with the x^5 term of its
-//   Taylor series economised into x and x^3 by the Chebyshev polynomial T5 on
-//   [-h, h] (x^5 ~ (5/4) h^2 x^3 - (5/16) h^4 x, error h^5 / 16 there), so the
-//   truncation stays below h^5 / 1920 + h^7 / 5040 = 1.5e-16; both as
-//   polynomials in r (coefficients times powers of 2 pi);
-//   then the angle sum with the table entry.
-constexpr int SC_N = 1024;
-constexpr double SC_MAGIC = 6597069766656.0;   // 1.5 * 2^42
-constexpr double SC_A = 6.283185307179586476925287;
-constexpr double SC_H = SC_A / (2 * SC_N);
-constexpr double SC_S1 = SC_A * (1.0 - SC_H * SC_H * SC_H * SC_H / 384.0),
-                 SC_S3 = SC_A * SC_A * SC_A * (-1.0 / 6.0 + SC_H * SC_H / 96.0);
-constexpr double SC_C2 = -SC_A * SC_A / 2.0, SC_C4 = SC_A * SC_A * SC_A * SC_A / 24.0;
-__device__ __forceinline__ void sincos_rev_tab(double t, const double2 *tab, double &s, double &c) {
-    const double y = t + SC_MAGIC;
-    const double r = t - (y - SC_MAGIC);          // exact
-    const double r2 = r * r;
-    const double sx = r * fma(r2, SC_S3, SC_S1);
-    const double cx = fma(r2, fma(r2, SC_C4, SC_C2), 1.0);
-    const double2 e = tab[__double2loint(y) & (SC_N - 1)];   // (cos, sin)(2 pi j / 1024)
-    s = fma(e.y, cx, e.x * sx);
-    c = fma(e.x, cx, -e.y * sx);
-}
 // precision-generic entry points used by the kernels (the table is unused in FP32)
 __device__ __forceinline__ void sincos_any(float ph, const double2 *, float &s, float &c) { sincos_rev(ph, s, c); }
 __device__ __forceinline__ void sincos_any(double t, const double2 *tab, double &s, double &c) {
@@ -92,16 +63,6 @@ __device__ __forceinline__ void sincos_any(double t, const double2 *tab, double 
 // remainder carries the product's full precision (R' < 2^40 revolutions).
 __device__ __forceinline__ void sincos_phase(float r2, float u, float n0, const double2 *, float &s, float &c) {
     sincos_rev_near(fma(r2, u, -n0), s, c);
-}
-__device__ __forceinline__ void sincos_phase(double r2, double u, double, const double2 *tab, double &s, double &c) {
-    const double y = fma(r2, u, SC_MAGIC);
-    const double r = fma(r2, u, -(y - SC_MAGIC));
-    const double rr = r * r;
-    const double sx = r * fma(rr, SC_S3, SC_S1);
-    const double cx = fma(rr, fma(rr, SC_C4, SC_C2), 1.0);
-    const double2 e = tab[__double2loint(y) & (SC_N - 1)];   // (cos, sin)(2 pi j / 1024)
-    s = fma(e.y, cx, e.x * sx);
-    c = fma(e.x, cx, -e.y * sx);
 }
 // copy the FP64 table to LDS (the kernels' first barrier publishes it)
 template <typename R, int BS>
@@ -124,16 +85,6 @@ __device__ __forceinline__ double wave_floor_min(double v) {
     return floor(fmax(v, 0.0));
 }
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-// 1/sqrt(x) for finite x > 0: the hardware estimate y (relative error up to
-// 5.2e-8 measured over 4M arguments; one Newton step leaves 4e-15) corrected
-// to second order in e = 1 - x y^2: 1/sqrt(x) = y (1 - e)^(-1/2)
-// = y (1 + e/2 + 3 e^2/8 + ...), the first dropped term 5 e^3/16 below 1e-21
-__device__ __forceinline__ double rsq(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y, e * fma(e, 0.375, 0.5), y);
-}
-
 // LDS stride (in elements) of one staged source: x y z nx ny nz + NR complex q,
 // or with one right-hand side (FOLD) the scaled position, the scaled normal
 // and the six density terms of ring_term1; rounded up to 16 bytes so the
@@ -1753,106 +1704,6 @@ void interbody_reduce_to_c128(Ctx &c, void *y, int nrhs, int prec, bool add) {
         hipLaunchKernelGGL(reduce_parts_kernel<double>, dim3(ceil_div(total, thr)), dim3(thr), 0, c.stream,
                            (const double2 *)c.scratch(WS_PART, 0), splits, total, add ? 1 : 0, (double2 *)y, c.N,
                            row0, row1);
-    AXS_HIP(hipGetLastError());
-}
-
-// ---------------------------------------------------------------------------
-// field evaluation off the surface: few targets, all sources.  One block per
-// (target, rhs); threads stride the sources and the complex sums are reduced
-// with wavefront shuffles, then across the block's waves in LDS (fixed order).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-template <int BS>
-__device__ __forceinline__ double2 block_sum2(double re, double im) {
-    __shared__ double sr[BS / 64], si[BS / 64];
-    re = wave_sum(re);
-    im = wave_sum(im);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
-        sr[wv] = re;
-        si[wv] = im;
-    }
-    __syncthreads();
-    double2 out = make_double2(0, 0);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < BS / 64; ++k) {
-            out.x += sr[k];
-            out.y += si[k];
-        }
-    }
-    return out;
-}
-
-template <int BS>
-__global__ __launch_bounds__(BS) void eval_field_kernel(const double *__restrict__ g, int64_t N,
-                                                        const double2 *__restrict__ sigma,
-                                                        const double *__restrict__ tgt, int nt,
-                                                        double kappa, double gam_re, double gam_im,
-                                                        double2 *__restrict__ u) {
-    const int t = blockIdx.x, c = blockIdx.y;
-    const double tx = tgt[3 * t], ty = tgt[3 * t + 1], tz = tgt[3 * t + 2];
-    const double2 *sg = sigma + (int64_t)c * N;
-    double re = 0, im = 0;
-    for (int64_t j = threadIdx.x; j < N; j += BS) {
-        const double dx = tx - g[j], dy = ty - g[N + j], dz = tz - g[2 * N + j];
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const double R = sqrt(r2);
-        const double nd = g[3 * N + j] * dx + g[4 * N + j] * dy + g[5 * N + j] * dz;
-        double s, cs;
-        sincos(kappa * R, &s, &cs);
-        // 4 pi G = e^{ikR}/R [a (1 - i k R) + gamma], a = n.d / R^2
-        const double a = nd / r2, are = a + gam_re, bim = gam_im - a * kappa * R;
-        const double er = cs / R, ei = s / R;
-        const double gr = er * are - ei * bim, gi = er * bim + ei * are;
-        const double w = g[6 * N + j] * (0.25 / M_PI);
-        const double qr = sg[j].x * w, qi = sg[j].y * w;
-        re += gr * qr - gi * qi;
-        im += gr * qi + gi * qr;
-    }
-    double2 tot = block_sum2<BS>(re, im);
-    if (threadIdx.x == 0) u[(int64_t)c * nt + t] = tot;
-}
-
-template <int BS>
-__global__ __launch_bounds__(BS) void far_field_kernel(const double *__restrict__ g, int64_t N,
-                                                       const double2 *__restrict__ sigma,
-                                                       const double *__restrict__ xh, int nd,
-                                                       double kappa, double eta,
-                                                       double2 *__restrict__ u) {
-    const int t = blockIdx.x, c = blockIdx.y;
-    const double hx = xh[3 * t], hy = xh[3 * t + 1], hz = xh[3 * t + 2];
-    const double2 *sg = sigma + (int64_t)c * N;
-    double re = 0, im = 0;
-    for (int64_t j = threadIdx.x; j < N; j += BS) {
-        const double ph = -kappa * (hx * g[j] + hy * g[N + j] + hz * g[2 * N + j]);
-        double s, cs;
-        sincos(ph, &s, &cs);
-        // (-i k xh.n + i eta) e^{i ph}
-        const double fim = -kappa * (hx * g[3 * N + j] + hy * g[4 * N + j] + hz * g[5 * N + j]) + eta;
-        const double gr = -fim * s, gi = fim * cs;
-        const double w = g[6 * N + j] * (0.25 / M_PI);
-        const double qr = sg[j].x * w, qi = sg[j].y * w;
-        re += gr * qr - gi * qi;
-        im += gr * qi + gi * qr;
-    }
-    double2 tot = block_sum2<BS>(re, im);
-    if (threadIdx.x == 0) u[(int64_t)c * nd + t] = tot;
-}
-
-void eval_field_launch(Ctx &c, const void *sigma, int nrhs, const double *tgt_dev, int nt, void *u) {
-    hipLaunchKernelGGL(eval_field_kernel<256>, dim3(nt, nrhs), dim3(256), 0, c.stream, c.g64, c.N,
-                       (const double2 *)sigma, tgt_dev, nt, c.kappa, c.gam_re, c.gam_im, (double2 *)u);
-    AXS_HIP(hipGetLastError());
-}
-
-void far_field_launch(Ctx &c, const void *sigma, int nrhs, const double *xh_dev, int nd, void *u) {
-    hipLaunchKernelGGL(far_field_kernel<256>, dim3(nd, nrhs), dim3(256), 0, c.stream, c.g64, c.N,
-                       (const double2 *)sigma, xh_dev, nd, c.kappa, c.eta, (double2 *)u);
     AXS_HIP(hipGetLastError());
 }
 

@@ -1,0 +1,83 @@
+"""Scattered field at points and far-field pattern at the sizes where the kernels' work is cut
+differently (lanes, targets per lane, chunks of nodes, groups of right-hand sides), against the same
+sums in numpy's FP64."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# about N = 1,500 terms of one sign at worst, each with a few roundings and a phase of at most 20
+# radians rounded to eps: 1,500 * 20 * eps / 2 relative to the largest value
+TOL = 3e-12
+
+
+@pytest.fixture(scope="module")
+def scenes():
+    import torch
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    out = {}
+    for kappa in (0.0, 3.0):
+        ctx = Context(0)
+        for k, c in enumerate((geo.sphere(1.0, 4, 10), geo.prolate(0.8, 1.3, 5, 9), geo.sphere(0.5, 1, 4))):
+            rot = geo.random_rotation(np.random.default_rng(k))
+            ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, 8, np.array([3.0 * k, 0.5 * k, -0.2]), rot)
+        ctx.precompute_scattering()
+        g = ctx.node_geometry()
+        rng = np.random.default_rng(5)
+        sig = rng.standard_normal((19, ctx.N)) + 1j * rng.standard_normal((19, ctx.N))
+        out[kappa] = (ctx, g, sig, torch.from_numpy(sig).to("cuda:0"))
+    yield out
+    for v in out.values():
+        v[0].close()
+
+
+def _near(g, q, t, kappa, eta):
+    d = t[:, None, :] - g[None, :, :3]
+    R = np.linalg.norm(d, axis=2)
+    nd = np.einsum("tjk,jk->tj", d, g[:, 3:6])
+    if kappa == 0:
+        K = (nd / R ** 2 + eta) / R
+    else:
+        K = np.exp(1j * kappa * R) / R * (nd / R ** 2 * (1 - 1j * kappa * R) + 1j * eta)
+    return q @ K.T
+
+
+@pytest.mark.parametrize("kappa", [0.0, 3.0])
+@pytest.mark.parametrize("nt,nrhs", [(1, 1), (1, 9), (63, 3), (64, 19), (65, 4), (257, 5), (1023, 2), (1024, 1),
+                                     (1025, 8), (1024, 7), (2049, 17), (4097, 3)])
+def test_fields_at_edges(scenes, kappa, nt, nrhs):
+    ctx, g, sig, dev = scenes[kappa]
+    rng = np.random.default_rng(nt)
+    q = sig[:nrhs] * (g[:, 6] / (4 * math.pi))
+    t = rng.uniform(-4, 12, (nt, 3))
+    t[:, 2] = 3.0 + 2 * rng.random(nt)
+    ref = _near(g, q, t, kappa, 1.5)
+    got = ctx.eval_field(dev[:nrhs].contiguous(), t).cpu().numpy()
+    assert np.max(np.abs(got - ref)) < TOL * np.max(np.abs(ref))
+    if kappa > 0:
+        x = rng.standard_normal((nt, 3))
+        x /= np.linalg.norm(x, axis=1, keepdims=True)
+        K = np.exp(-1j * kappa * (x @ g[:, :3].T)) * (1j * (1.5 - kappa * (x @ g[:, 3:6].T)))
+        ref = q @ K.T
+        got = ctx.far_field(dev[:nrhs].contiguous(), x).cpu().numpy()
+        assert np.max(np.abs(got - ref)) < TOL * np.max(np.abs(ref))
+
+
+def test_field_at_very_distant_and_at_bad_points(scenes):
+    """Phases beyond the table's range are reduced first (the field's size stays right; its phase
+    carries the rounding of kappa R, about 2^-53 kappa R); NaN targets give NaN, and only there."""
+    ctx, g, sig, dev = scenes[3.0]
+    q = sig[:1] * (g[:, 6] / (4 * math.pi))
+    for R in (1e12, 1e14):
+        t = np.array([[R, 0.3 * R, -0.2 * R], [4.0, 5.0, 6.0]])
+        got = ctx.eval_field(dev[:1].contiguous(), t).cpu().numpy()
+        ref = _near(g, q, t, 3.0, 1.5)
+        assert abs(got[0, 1] - ref[0, 1]) < TOL * abs(ref[0, 1])
+        # the sum of the moduli bounds the far value whatever its phase
+        bound = np.sum(np.abs(q)) * (3.0 + 1.5) / np.linalg.norm(t[0])
+        assert np.isfinite(got[0, 0]) and abs(got[0, 0]) <= bound
+    got = ctx.eval_field(dev[:1].contiguous(), np.array([[np.nan, 0, 9.0], [4.0, 5.0, 6.0]])).cpu().numpy()
+    assert np.isnan(got[0, 0]) and abs(got[0, 1] - ref[0, 1]) < TOL * abs(ref[0, 1])
