@@ -142,8 +142,8 @@ struct Ctx {
     // [precision][0: point / ring orders, 1: MFMA order (node units),
     // 2: MFMA order with the FP16 multiply-accumulate (32-node block units)],
     // so that alternating single and batched calls do not rebuild them
-    IBWork *ib_work[2][3] = {{nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}};
-    int ib_nwork[2][3] = {{0, 0, 0}, {0, 0, 0}};
+    IBWork *ib_work[2][3] = {};
+    int ib_nwork[2][3] = {};
     int ib_key[2][3][6] = {};   // launch shape and target range of the cached table
 
     // launch configuration of the inter-body sum (0 = library default)

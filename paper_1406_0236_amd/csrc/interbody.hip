@@ -134,12 +134,15 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
     constexpr bool FOLD = NR == 1 && !LAP;
     constexpr int ST = SrcStride<R, NR, FOLD>::value;
     __shared__ __align__(16) R tile[BS * ST];
-    __shared__ double2 s_tab[sizeof(R) == 8 ? SC_N : 1];
-    load_sctab<R, BS>(s_tab, sctab);
+    __shared__ double2 s_tab[sizeof(R) == 8 && !LAP ? SC_N : 1];
+    if constexpr (!LAP) load_sctab<R, BS>(s_tab, sctab);
 
     const IBWork w = work[blockIdx.x];
     const int tid = threadIdx.x;
     const int cb = c0 + blockIdx.y * NR;   // first rhs of this block's group
+    // a wavefront's targets are consecutive, so that in a tile that is not full
+    // whole wavefronts have none and only help to stage the sources
+    const int wt = __builtin_amdgcn_readfirstlane(tid >> 6) * 64 * TPT, tl = wt + (tid & 63);
     const R *gx = geo, *gy = geo + N, *gz = geo + 2 * N;
     const R *gnx = geo + 3 * N, *gny = geo + 4 * N, *gnz = geo + 5 * N;
 
@@ -147,7 +150,7 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
     R ar[TPT][NR], ai[TPT][NR];
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-        int t = tid + k * BS;
+        int t = tl + k * 64;
         int64_t gi = w.t0 + (t < w.tn ? t : 0);
         tx[k] = gx[gi];
         ty[k] = gy[gi];
@@ -199,6 +202,7 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
                 }
             }
             __syncthreads();
+            if (wt >= w.tn) continue;
             if constexpr (FOLD) {
 #pragma unroll 2
                 for (int js = 0; js < cnt; ++js) {
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
     }
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-        int t = tid + k * BS;
+        int t = tl + k * 64;
         if (t < w.tn) {
 #pragma unroll
             for (int c = 0; c < NR; ++c) {
@@ -360,12 +364,13 @@ __global__ __launch_bounds__(BS) void interbody_ring_kernel(
     constexpr int ST = RingStride<R, NR, FOLD>::value;
     constexpr int QB = FOLD ? 8 : 2 + 2 * NR;   // offset of the mirror's densities in an entry
     __shared__ __align__(16) R tile[BS * ST];
-    __shared__ double2 s_tab[sizeof(R) == 8 ? SC_N : 1];
-    load_sctab<R, BS>(s_tab, sctab);
+    __shared__ double2 s_tab[sizeof(R) == 8 && !LAP ? SC_N : 1];
+    if constexpr (!LAP) load_sctab<R, BS>(s_tab, sctab);
 
     const IBWork w = work[blockIdx.x];
     const int tid = threadIdx.x;
     const int cb = c0 + blockIdx.y * NR;   // first rhs of this block's group
+    const int wt = __builtin_amdgcn_readfirstlane(tid >> 6) * 64 * TPT, tl = wt + (tid & 63);   // as in the point order
     const R *gx = geo, *gy = geo + N, *gz = geo + 2 * N;
     const R *gc = cs, *gs = cs + N;
     const R *rr_ = rg, *rz_ = rg + nrings, *rnr = rg + 2 * nrings, *rnz = rg + 3 * nrings;
@@ -378,7 +383,7 @@ __global__ __launch_bounds__(BS) void interbody_ring_kernel(
     R ar[TPT][NR], ai[TPT][NR];
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-        int t = tid + k * BS;
+        int t = tl + k * 64;
         int64_t gi = w.t0 + (t < w.tn ? t : 0);
         tx[k] = gx[gi];
         ty[k] = gy[gi];
@@ -428,8 +433,11 @@ __global__ __launch_bounds__(BS) void interbody_ring_kernel(
                 }
             }
             __syncthreads();
+            const int rfirst = r0;
+            r0 = r1;
+            if (wt >= w.tn) continue;   // no targets in this wavefront
 #pragma unroll 1
-            for (int ring = r0; ring < r1; ++ring) {
+            for (int ring = rfirst; ring < r1; ++ring) {
                 const int b = rt.body[ring];
                 if (b != prev_body) {
                     // targets in the source body's frame: p = Rot^T (x - c).  Every
@@ -533,12 +541,11 @@ __global__ __launch_bounds__(BS) void interbody_ring_kernel(
                     }
                 }
             }
-            r0 = r1;
         }
     }
 #pragma unroll
     for (int k = 0; k < TPT; ++k) {
-        int t = tid + k * BS;
+        int t = tl + k * 64;
         if (t < w.tn) {
 #pragma unroll
             for (int c = 0; c < NR; ++c) {
@@ -649,6 +656,7 @@ __global__ __launch_bounds__(256) void interbody_mfma_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int col = lane & 15, kq = lane >> 4;
     const int cb = c0 + blockIdx.y * NR;
+    const bool live = __builtin_amdgcn_readfirstlane(wv) * G * 16 < w.tn;   // else the wavefront only stages
     const R *gx = geo, *gy = geo + N, *gz = geo + 2 * N;
     const V zero4 = {R(0), R(0), R(0), R(0)};
 
@@ -723,7 +731,7 @@ __global__ __launch_bounds__(256) void interbody_mfma_kernel(
             }
             __syncthreads();
 #pragma unroll 1
-            for (int j = 0; j < n16; j += 16) {
+            for (int j = live ? 0 : n16; j < n16; j += 16) {
                 const R a1 = ((const R *)s_sr)[(j + col) * 4 + kq];
                 const R a2 = ((const R *)s_sn)[(j + col) * 4 + kq];
                 if constexpr (!MACC) {
@@ -916,7 +924,7 @@ __global__ __launch_bounds__(64) void qmax_final_kernel(const unsigned *__restri
 // six FP16 planes per 32-source block and rhs group (B-operand order)
 __global__ __launch_bounds__(256) void q16_kernel(const float2 *__restrict__ q, const unsigned *__restrict__ qmax,
                                                   const int64_t *__restrict__ boff, const int32_t *__restrict__ bblk,
-                                                  int nbodies, int64_t N, int64_t nblk, int groups,
+                                                  int nbodies, int64_t N, int64_t nblk, int groups, int nrhs,
                                                   _Float16 *__restrict__ q16) {
     const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x;   // ((grp * nblk + B) * 16 + c) * 32 + k
     if (item >= (int64_t)groups * nblk * 512) return;
@@ -935,7 +943,7 @@ __global__ __launch_bounds__(256) void q16_kernel(const float2 *__restrict__ q, 
     const int64_t node = boff[b] + 32 * (B - bblk[b]) + r;
     const int rhs = grp * 16 + c;
     float2 v = make_float2(0.f, 0.f);
-    if (node < boff[b + 1]) {
+    if (node < boff[b + 1] && rhs < nrhs) {   // padding nodes and right-hand sides: zero
         v = q[(int64_t)rhs * N + node];
         const float s = ldexpf(1.f, qscale_exp(qmax[rhs]));
         v.x *= s;
@@ -964,6 +972,7 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int col = lane & 15, kq = lane >> 4;
     const int grp = blockIdx.y, cb = grp * 16;
+    const bool live = __builtin_amdgcn_readfirstlane(wv) * G * 16 < w.tn;   // else the wavefront only stages
     const float *gx = geo, *gy = geo + N, *gz = geo + 2 * N;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
 
@@ -1037,7 +1046,7 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
 #pragma unroll
             for (int g = 0; g < G; ++g) accR[g] = accI[g] = zero4;
 #pragma unroll 1
-            for (int jb = 0; jb < nb; ++jb) {
+            for (int jb = live ? 0 : nb; jb < nb; ++jb) {
                 const h8 *qb = s_q + jb * MF16_BLK;
                 const h8 qrh = qb[(0 * 16 + col) * 4 + kq], qrl = qb[(1 * 16 + col) * 4 + kq];
                 const h8 qih = qb[(2 * 16 + col) * 4 + kq], qil = qb[(3 * 16 + col) * 4 + kq];
@@ -1082,6 +1091,7 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
         }
     }
     // lane (kq, col) holds targets 4kq + v of each group for rhs cb + col
+    if (cb + col >= nrhs) return;   // padding of the last group
     const float inv = ldexpf(1.f, -(gexp + qscale_exp(qmax[cb + col])));
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -1145,24 +1155,99 @@ struct IBShape {
 // targets per work item: TPT x block, or for the MFMA orders 16 x G x 4 waves
 static int ib_tile(const IBShape &s) { return s.variant >= 3 ? 64 * s.tpt : s.tpt * s.bs; }
 
+enum class Units { nodes, rings, blocks };
+static Units ib_units(const IBShape &s) {
+    return s.variant == 2 ? Units::rings : s.variant == 4 ? Units::blocks : Units::nodes;
+}
+static int64_t body_units(const Ctx &c, size_t bi, Units u) {
+    const Body &b = c.bodies[bi];
+    return u == Units::rings ? c.shapes[b.shape].NG : u == Units::blocks ? ceil_div(b.n, (int64_t)32) : b.n;
+}
+static bool is_target(const Ctx &c, size_t bi) {
+    return c.tgt_count < 0 || ((int)bi >= c.tgt_first && (int)bi < c.tgt_first + c.tgt_count);
+}
+// tiles of `tile` targets over the target rows computed (all bodies, or the set range)
+static int64_t count_tiles(const Ctx &c, int tile) {
+    int64_t tiles = 0;
+    for (size_t bi = 0; bi < c.bodies.size(); ++bi)
+        if (is_target(c, bi)) tiles += ceil_div(c.bodies[bi].n, (int64_t)tile);
+    return tiles;
+}
+
+// Defaults from launch-shape sweeps on MI355X (order x targets per thread x
+// splits; scenes of 4,408 to 437,400 nodes, 1 to 64 rhs; inter-body ms or us
+// below).
+//  order: below 16 rhs the ring order, from 16 on the MFMA order (in FP32 with
+//    the FP16 multiply-accumulate where the kernel values have a bound); the
+//    point order where neither applies.  A compressed system of single nodes
+//    has no rings: in FP32 its padded group of 16 (342 us on 20,090 nodes
+//    whatever the rhs) beats the point order from 5 rhs (376), in FP64 the MFMA
+//    order beats it at the widths it has groups of (1: 481 against 522; 4: 661
+//    against 701; at 5, with groups of 4 and 1, 1139 against 768).
+//  targets per thread: FP32 rings 1 (20,090 nodes: 216 us, 2: 250), at zero
+//    frequency 2 from 3 rhs (136,350 nodes: 4.52 ms, 1: 4.86).  FP64 rings: 4
+//    pays only where bodies have many tiles of 1,024 targets (129,600 nodes: 4
+//    16.1 ms, 1 17.5; 20,090 nodes: 4 550 us, 1 506; 8,200: 103 and 87), groups
+//    of 5 to 7 rhs hold too much at 4 (129,600 nodes, 12 rhs: 60.5 ms, 2
+//    53.9), and at zero frequency 2 serves small bodies best (41,310 nodes: 4
+//    976 us, 2 836, 1 860).  FP64 points 2 (83,640 nodes: 8.36 ms, 4 8.56).
+//    MFMA orders: 2 groups of 16 targets per wavefront; FP64 4 where there are
+//    256 tiles of that size (129,600 nodes, 16 rhs: 39.7 ms, 2 40.5; 20,090
+//    nodes 1141 and 1051 us), and 1 in small systems (8,200 nodes, 1 rhs: 116, 2
+//    122).
+static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
+    const int width = (int)ceil_div(nrhs, ceil_div(nrhs, 8));   // of a VALU rhs group
+    const bool large = count_tiles(c, 1024) >= 64;
+    if (variant == 4) return 2;
+    if (variant == 3) {
+        if (prec == AXS_FP32) return 2;
+        const int64_t groups = ceil_div(nrhs, 16);
+        if (count_tiles(c, 256) * groups >= 256) return 4;
+        return nrhs < 16 && count_tiles(c, 128) < 128 ? 1 : 2;
+    }
+    if (variant == 1) return prec == AXS_FP32 ? 1 : 2;
+    if (prec == AXS_FP32) return c.kappa == 0 && nrhs >= 3 ? 2 : 1;
+    if (c.kappa == 0) return large && width <= 4 ? 4 : 2;
+    return !large ? 1 : width >= 5 && width <= 7 ? 2 : 4;
+}
+
+//  splits: as many source chunks as give every CU several workgroups (tiles x
+//    splits x rhs groups), and no more, since each chunk's partial sums cross
+//    memory twice: 64 rhs on 20,090 nodes take 1.27 ms with 8, 1.35 with 32,
+//    one rhs on 8,200 nodes 49 us with 16 or 32, 55 with 64.  The FP32 ring order
+//    (8 resident workgroups per CU) takes 16K so that the last, partly filled
+//    round is a small share of the launch.
+static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
+    const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
+    const int64_t tiles = count_tiles(c, ib_tile(s)) * (mf ? ceil_div(nrhs, 16) : 1);
+    const int64_t want = ring32 ? 16384 : s.variant == 4 ? 8192 : 4096;
+    const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : ring32 || (s.variant == 2 && s.tpt == 1) ? 32 : 64;
+    int splits = 1;
+    while (tiles * splits < want && splits < most) splits *= 2;
+    // no empty chunks: 100 rings in 32 chunks are 25 chunks of 4
+    const Units u = ib_units(s);
+    int64_t total = 0, used = 1;
+    for (size_t bi = 0; bi < c.bodies.size(); ++bi) total += body_units(c, bi, u);
+    for (size_t bi = 0; bi < c.bodies.size(); ++bi) {
+        const int64_t others = std::max<int64_t>(1, total - body_units(c, bi, u));
+        used = std::max(used, ceil_div(others, ceil_div(others, (int64_t)splits)));
+    }
+    return (int)used;
+}
+
 static IBShape launch_shape(Ctx &c, int prec, int nrhs) {
     const int pi = prec == AXS_FP32 ? 1 : 0;
     IBShape s;
-    // Defaults from the launch-shape sweeps on MI355X (27-sphere lattice, one
-    // rhs; 8 mixed bodies, 1-64 rhs; 64 mixed bodies, 16 rhs): below 16 rhs
-    // the ring order (1 target per thread in FP32, 4 in FP64), from 16 rhs on
-    // the MFMA order (2 groups of 16 targets per wavefront in FP32, with the
-    // FP16 multiply-accumulate where the kernel values have a bound; 4 groups
-    // in FP64); the point order where neither applies.
     s.bs = c.ib_block[pi] > 0 ? c.ib_block[pi] : 256;
     const bool ring_ok = !c.no_rings && c.max_nf / 2 + 1 <= s.bs && (c.kappa == 0 || c.near_phase_ok);
     const bool mf_ok = c.kappa > 0 && c.mf_src && c.near_phase_ok && s.bs == 256 &&
                        (c.ib_tpt[pi] == 0 || c.ib_tpt[pi] <= 4);
     const bool mf16_ok = mf_ok && prec == AXS_FP32 && c.mf16_ok;
+    // (c.no_rings: the compressed system of single nodes)
+    const bool few16 = c.no_rings && nrhs >= 5, few = c.no_rings && prec == AXS_FP64 && (nrhs & (nrhs - 1)) == 0;
     s.variant = c.ib_variant[pi] > 0 ? c.ib_variant[pi]
-                : (nrhs >= 16 && mf16_ok) ? 4 : (nrhs >= 16 && mf_ok) ? 3 : ring_ok ? 2 : 1;
-    const int dflt = prec == AXS_FP32 ? (s.variant == 2 ? 1 : 2) : 4;
-    s.tpt = c.ib_tpt[pi] > 0 ? c.ib_tpt[pi] : dflt;
+                : ((nrhs >= 16 || few16) && mf16_ok) ? 4 : ((nrhs >= 16 || few) && mf_ok) ? 3 : ring_ok ? 2 : 1;
+    s.tpt = c.ib_tpt[pi] > 0 ? c.ib_tpt[pi] : default_tpt(c, prec, s.variant, nrhs);
     AXS_REQUIRE(s.variant != 2 || ring_ok, AXS_EINVAL,
                 "ring variant needs N_F/2 + 1 <= threads per block and bodies under 127 wavelengths across");
     if (s.variant == 4)
@@ -1175,20 +1260,7 @@ static IBShape launch_shape(Ctx &c, int prec, int nrhs) {
                     "MFMA variant: 1, 2 or 4 groups of 16 targets per wave");
         AXS_REQUIRE(s.bs == 256, AXS_EINVAL, "MFMA variant uses 256-thread blocks");
     }
-    if (c.ib_splits[pi] > 0) {
-        s.splits = c.ib_splits[pi];
-    } else {
-        // enough blocks to fill 256 CUs several times over; the FP32 ring order
-        // (8 resident blocks per CU) takes 16K so that the last, partly filled
-        // round of blocks is a small share of the launch
-        int64_t tiles = 0;   // of the target rows computed (all bodies, or the set range)
-        for (size_t bi = 0; bi < c.bodies.size(); ++bi)
-            if (c.tgt_count < 0 || ((int)bi >= c.tgt_first && (int)bi < c.tgt_first + c.tgt_count))
-                tiles += ceil_div(c.bodies[bi].n, (int64_t)ib_tile(s));
-        const int64_t want = (prec == AXS_FP32 && s.variant == 2) ? 16384 : 4096;
-        s.splits = 1;
-        while (tiles * s.splits < want && s.splits < 64) s.splits *= 2;
-    }
+    s.splits = c.ib_splits[pi] > 0 ? c.ib_splits[pi] : default_splits(c, prec, s, nrhs);
     return s;
 }
 
@@ -1203,7 +1275,6 @@ void interbody_shape(Ctx &c, int prec, int nrhs, int out[4]) {
 }
 
 // Work items (worktable.h) in units of nodes, rings or 32-node blocks
-enum class Units { nodes, rings, blocks };
 static std::vector<IBWork> build_work(Ctx &c, int tile, int splits, Units units) {
     std::vector<WorkBody> wb;
     int64_t boff = 0;
@@ -1211,11 +1282,10 @@ static std::vector<IBWork> build_work(Ctx &c, int tile, int splits, Units units)
         const auto &b = c.bodies[bi];
         const int64_t nbk = ceil_div(b.n, (int64_t)32);
         const int64_t uoff = units == Units::rings ? c.ring_base[bi] : units == Units::blocks ? boff : b.offset;
-        const int64_t un = units == Units::rings ? c.shapes[b.shape].NG : units == Units::blocks ? nbk : b.n;
+        const int64_t un = body_units(c, bi, units);
         boff += nbk;
         // bodies outside the target range keep their sources, lose their targets
-        const bool own = c.tgt_count < 0 || ((int)bi >= c.tgt_first && (int)bi < c.tgt_first + c.tgt_count);
-        wb.push_back(WorkBody{b.offset, own ? b.n : 0, uoff, un});
+        wb.push_back(WorkBody{b.offset, is_target(c, bi) ? b.n : 0, uoff, un});
     }
     const int64_t U = units == Units::rings ? c.nrings : units == Units::blocks ? c.nblk : c.N;
     return build_work_table(wb, U, tile, splits);
@@ -1461,6 +1531,7 @@ static void launch_ib(Ctx &c, int variant, const IBWork *work, int nwork, const 
                       const R *rg, const R *frame, const typename C2T<R>::T *q, int nrhs,
                       typename C2T<R>::T *part) {
     // at kappa = 0 the ring order runs unscaled (k/2pi replaced by 1, no phase)
+    constexpr bool ANY = BS == 256 && TPT <= 4;
     const R kappa = (R)c.kappa, k2pi = LAP ? R(1) : (R)(c.kappa / (2.0 * M_PI)), eta = (R)c.eta;
     const RingTabs rt{c.ring_i, c.ring_i + c.nrings, c.ring_i + 2 * c.nrings, c.ring_i + 3 * c.nrings,
                       c.ring_pair};
@@ -1469,10 +1540,15 @@ static void launch_ib(Ctx &c, int variant, const IBWork *work, int nwork, const 
     // at 8: with mirror pairs a 16- or 32-wide group doubles the LDS tile and
     // the registers of the densities, and ran slower than groups of 8 (64 rhs
     // beyond 16 take the MFMA order anyway).
+    // Where groups of any width are built (the shapes the library chooses by
+    // itself) the groups are as equal as they can be: 3 right-hand sides are one
+    // launch instead of 2 + 1, 11 are 6 + 5 instead of 8 + 2 + 1, which shares every
+    // kernel value more evenly (3 at zero frequency in FP64, 9 of 27 bodies'
+    // rows of 41,310 nodes: 410 us, with the default of 2 targets per thread, against 880).
     int c0 = 0;
     while (c0 < nrhs) {
         const int left = nrhs - c0;
-        const int nr = left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
+        const int nr = ANY ? (int)ceil_div(left, ceil_div(left, 8)) : left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1;
         const int groups = left / nr;
 #define AXS_IB_NR(NR_)                                                                                     \
     if (nr == NR_) {                                                                                       \
@@ -1489,6 +1565,12 @@ static void launch_ib(Ctx &c, int variant, const IBWork *work, int nwork, const 
         AXS_IB_NR(4)
         AXS_IB_NR(2)
         AXS_IB_NR(1)
+        if constexpr (ANY) {
+            AXS_IB_NR(7)
+            AXS_IB_NR(6)
+            AXS_IB_NR(5)
+            AXS_IB_NR(3)
+        }
 #undef AXS_IB_NR
         AXS_HIP(hipGetLastError());
         c0 += nr * groups;
@@ -1589,12 +1671,15 @@ static const IBWork *get_work(Ctx &c, int pi, int wi, const IBShape &s, Units un
     return c.ib_work[pi][wi];
 }
 
-// MFMA order with the FP16 multiply-accumulate: full groups of 16 rhs over
-// 32-node source blocks; a remainder of fewer than 16 rhs takes the FP32 MFMA
-// order (node units).  Both write the same [splits][nrhs][N] partial sums.
+// MFMA order with the FP16 multiply-accumulate: groups of 16 rhs over 32-node
+// source blocks.  A remainder of 1 or 2 rhs takes the FP32 MFMA order; from 3 on it
+// pads a last group with zero densities (83,640 nodes: a group takes 5.0 ms
+// whatever its rhs, the FP32 MFMA order 7.2 ms for 8).  Both write the same
+// [splits][nrhs][N] partial sums.
 static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, float2 *part) {
-    const int groups = nrhs / 16;
-    if (groups > 0) {
+    const bool apart = nrhs % 16 == 1 || nrhs % 16 == 2;
+    const int groups = apart ? nrhs / 16 : (int)ceil_div(nrhs, 16);
+    {
         int nwork = 0;
         const IBWork *work = get_work(c, 1, 2, s, Units::blocks, nwork);
         // slices of at least 16K nodes per block, at most QMAX_SLICES per rhs
@@ -1606,7 +1691,7 @@ static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, flo
         const int64_t items = (int64_t)groups * c.nblk * 512;
         _Float16 *q16 = (_Float16 *)c.scratch(WS_Q16, (size_t)items * 6 * sizeof(_Float16));
         hipLaunchKernelGGL(q16_kernel, dim3(ceil_div(items, (int64_t)256)), dim3(256), 0, c.stream, q, qmax,
-                           c.body_off, c.blk_off, (int)c.bodies.size(), c.N, c.nblk, groups, q16);
+                           c.body_off, c.blk_off, (int)c.bodies.size(), c.N, c.nblk, groups, nrhs, q16);
         AXS_HIP(hipGetLastError());
         const float k2pi = (float)(c.kappa / (2.0 * M_PI));
         const float s2 = k2pi * k2pi;
@@ -1625,15 +1710,14 @@ static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, flo
 #undef AXS_MF16
         AXS_HIP(hipGetLastError());
     }
-    if (16 * groups < nrhs) {
-        int nwork = 0;
-        IBShape s3 = s;
-        s3.variant = 3;
-        const IBWork *work = get_work(c, 1, 1, s3, Units::nodes, nwork);
-        if (s.tpt == 1) launch_mf<float, 1>(c, work, nwork, q, nrhs, part, 16 * groups);
-        else if (s.tpt == 2) launch_mf<float, 2>(c, work, nwork, q, nrhs, part, 16 * groups);
-        else launch_mf<float, 4>(c, work, nwork, q, nrhs, part, 16 * groups);
-    }
+    if (!apart) return;
+    int nwork = 0;
+    IBShape r = s;
+    r.variant = 3;
+    const IBWork *work = get_work(c, 1, 1, r, Units::nodes, nwork);
+    if (s.tpt == 1) launch_mf<float, 1>(c, work, nwork, q, nrhs, part, 16 * groups);
+    else if (s.tpt == 2) launch_mf<float, 2>(c, work, nwork, q, nrhs, part, 16 * groups);
+    else launch_mf<float, 4>(c, work, nwork, q, nrhs, part, 16 * groups);
 }
 
 int64_t interbody_scratch_bytes(Ctx &c, int prec, int nrhs) {
@@ -1647,7 +1731,7 @@ int64_t interbody_scratch_bytes(Ctx &c, int prec, int nrhs) {
     const bool cached = c.ib_work[pi][0] && key[0] == s.tpt && key[1] == s.bs && key[2] == s.splits &&
                         key[3] == s.variant && key[4] == c.tgt_first && key[5] == c.tgt_count;
     if (!cached)
-        bytes += r256((int64_t)build_work(c, ib_tile(s), s.splits, s.variant == 2 ? Units::rings : Units::nodes).size() *
+        bytes += r256((int64_t)build_work(c, ib_tile(s), s.splits, ib_units(s)).size() *
                       (int64_t)sizeof(IBWork));
     return bytes;
 }
@@ -1667,8 +1751,7 @@ void interbody_partials(Ctx &c, const void *sigma, int nrhs, int prec) {
         return;
     }
     int nwork = 0;
-    const IBWork *dwork = get_work(c, pi, s.variant == 3 ? 1 : 0, s,
-                                   s.variant == 2 ? Units::rings : Units::nodes, nwork);
+    const IBWork *dwork = get_work(c, pi, s.variant == 3 ? 1 : 0, s, ib_units(s), nwork);
     if (prec == AXS_FP32) {
         float2 *q = (float2 *)c.scratch(WS_Q, total * sizeof(float2));
         float2 *part = (float2 *)c.scratch(WS_PART, (size_t)s.splits * total * sizeof(float2));
