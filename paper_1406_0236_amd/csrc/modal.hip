@@ -4,7 +4,10 @@
 //   (2) per Fourier mode, apply the stored S_|m| = A~_|m|^{-1} (A~_{-m} = A~_m),
 //   (3) inverse DFT, optionally adding the identity term of eq. "precond".
 // N_F = 2M + 1 is odd and small (41, 81), so the DFT is a direct sum with the
-// twiddle table and the input rows staged in LDS (same result as an FFT).
+// twiddle table and the input rows staged in LDS (same result as an FFT).  The
+// nodes l and N_F - l share their cosine and have opposite sines, and so do the
+// modes k and -k: with a_l = w_l + w_{N_F - l}, b_l = w_l - w_{N_F - l} both modes come
+// from the same M products a_l cos, b_l sin, a quarter of the plain sum's.
 // Step (2) is a batched complex GEMM on the matrix cores: for each shape and
 // |m| the columns are (+m, -m) x (bodies of that shape) x (right-hand sides),
 // and the complex product is four real MFMA products on planar operands.
@@ -16,7 +19,10 @@ template <typename R> struct CT;
 template <> struct CT<float> { using T = float2; };
 template <> struct CT<double> { using T = double2; };
 
-constexpr int DFT_GI = 16;     // contour nodes per DFT block
+// Contour nodes per DFT block: 16, or 4 where 16 would leave fewer than 1,024
+// workgroups.  The forward transform also adds up the partial inter-body sums, which for
+// a small system is most of its time: 8,200 nodes, FP64, 25 partial sums 5.4 us
+// (a pass over 64 of them in 14 workgroups: 55 us).
 constexpr int DFT_BS = 256;
 
 __device__ __forceinline__ int64_t xelem(const BodyDev &b, int nrhs, int k, int c, int i) {
@@ -31,21 +37,22 @@ __device__ __forceinline__ int64_t xelem(const BodyDev &b, int nrhs, int k, int 
 // X[k][i] = sum_l w[i][l] e^{-2 pi i k l / N_F} for the body's contour nodes
 // [i0, i0 + GI) and rhs c.  Input: sum over `splits` partial inter-body sums
 // (from_vec = 0) or a complex128 vector (from_vec = 1).
-template <typename R>
+template <typename R, int GI>
 __global__ __launch_bounds__(DFT_BS) void dft_forward_kernel(
     const BodyDev *__restrict__ bodies, const typename CT<R>::T *__restrict__ part, int splits,
     const double2 *__restrict__ vec, int from_vec, int64_t N, int nrhs, const R *__restrict__ tw,
     R *__restrict__ Xr, R *__restrict__ Xi) {
     using R2 = typename CT<R>::T;
+    constexpr int P = GI + 1;                   // row pitch: the rows are written along l
     extern __shared__ __align__(16) unsigned char smem[];
-    R2 *w = (R2 *)smem;                         // [GI][NF]
+    R2 *w = (R2 *)smem;                         // [NF][P]
     const BodyDev b = bodies[blockIdx.z];
     const int c = blockIdx.y;
-    const int i0 = blockIdx.x * DFT_GI;
+    const int i0 = blockIdx.x * GI;
     if (i0 >= b.NG) return;
-    const int ni = min(DFT_GI, b.NG - i0);
-    const int NF = b.NF;
-    R2 *t = w + DFT_GI * NF;                    // [NF] twiddles (cos, sin)(2 pi j / NF)
+    const int ni = min(GI, b.NG - i0);
+    const int NF = b.NF, M = b.M;
+    R2 *t = w + P * NF;                         // [NF] twiddles (cos, sin)(2 pi j / NF)
     for (int j = threadIdx.x; j < NF; j += DFT_BS) {
         t[j].x = tw[2 * (b.twoff + j)];
         t[j].y = tw[2 * (b.twoff + j) + 1];
@@ -60,78 +67,108 @@ __global__ __launch_bounds__(DFT_BS) void dft_forward_kernel(
         } else {
             v.x = R(0);
             v.y = R(0);
-            for (int s = 0; s < splits; ++s) {
-                R2 p = part[((int64_t)s * nrhs + c) * N + base + idx];
+            const R2 *src = part + (int64_t)c * N + base + idx;
+            const int64_t step = (int64_t)nrhs * N;
+            int s = 0;
+            for (; s + 8 <= splits; s += 8) {   // loads first, then the sum in order
+                R2 p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) p[u] = src[(s + u) * step];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    v.x += p[u].x;
+                    v.y += p[u].y;
+                }
+            }
+            for (; s < splits; ++s) {
+                const R2 p = src[s * step];
                 v.x += p.x;
                 v.y += p.y;
             }
         }
-        w[idx] = v;
+        w[(idx % NF) * P + idx / NF] = v;
     }
     __syncthreads();
-    for (int idx = threadIdx.x; idx < ni * NF; idx += DFT_BS) {
-        const int k = idx / ni, i = idx - k * ni;
-        R re = 0, im = 0;
+    for (int idx = threadIdx.x; idx < M * GI; idx += DFT_BS) {
+        const int l = 1 + idx / GI, i = idx % GI;
+        if (i >= ni) continue;
+        const R2 x = w[l * P + i], y = w[(NF - l) * P + i];
+        R2 s, d;
+        s.x = x.x + y.x;
+        s.y = x.y + y.y;
+        d.x = x.x - y.x;
+        d.y = x.y - y.y;
+        w[l * P + i] = s;
+        w[(NF - l) * P + i] = d;
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < (M + 1) * GI; idx += DFT_BS) {
+        const int k = idx / GI, i = idx % GI;
+        if (i >= ni) continue;
+        R cr = w[i].x, ci = w[i].y, sr = 0, si = 0;
         int tj = 0;
-        const R2 *row = w + i * NF;
-        for (int l = 0; l < NF; ++l) {
-            const R2 x = row[l], e = t[tj];
-            // x * conj(e)
-            re = fma(x.x, e.x, fma(x.y, e.y, re));
-            im = fma(x.y, e.x, fma(-x.x, e.y, im));
+        for (int l = 1; l <= M; ++l) {
             tj += k;
             if (tj >= NF) tj -= NF;
+            const R2 s = w[l * P + i], d = w[(NF - l) * P + i], e = t[tj];
+            cr = fma(s.x, e.x, cr);
+            ci = fma(s.y, e.x, ci);
+            sr = fma(d.x, e.y, sr);
+            si = fma(d.y, e.y, si);
         }
         const int64_t o = xelem(b, nrhs, k, c, i0 + i);
-        Xr[o] = re;
-        Xi[o] = im;
+        Xr[o] = cr + si;
+        Xi[o] = ci - sr;
+        if (k > 0) {
+            const int64_t o2 = xelem(b, nrhs, NF - k, c, i0 + i);
+            Xr[o2] = cr - si;
+            Xi[o2] = ci + sr;
+        }
     }
 }
 
 // y[c][node] = alpha sigma[c][node] + beta / N_F sum_k Y[k][i] e^{+2 pi i k l / N_F}
-template <typename R>
+template <typename R, int GI>
 __global__ __launch_bounds__(DFT_BS) void dft_inverse_kernel(
     const BodyDev *__restrict__ bodies, const R *__restrict__ Yr, const R *__restrict__ Yi, int64_t N,
     int nrhs, const R *__restrict__ tw, const double2 *__restrict__ sigma, double alpha, double beta,
     double2 *__restrict__ y) {
     using R2 = typename CT<R>::T;
     extern __shared__ __align__(16) unsigned char smem[];
-    R2 *yh = (R2 *)smem;                        // [GI][NF] (i-major)
+    R2 *yh = (R2 *)smem;                        // [GI][NF]: Y_0, then Y_k + Y_-k at k, Y_k - Y_-k at N_F - k
     const BodyDev b = bodies[blockIdx.z];
     const int c = blockIdx.y;
-    const int i0 = blockIdx.x * DFT_GI;
+    const int i0 = blockIdx.x * GI;
     if (i0 >= b.NG) return;
-    const int ni = min(DFT_GI, b.NG - i0);
-    const int NF = b.NF;
-    R2 *t = yh + DFT_GI * NF;
+    const int ni = min(GI, b.NG - i0);
+    const int NF = b.NF, M = b.M;
+    R2 *t = yh + (GI + 1) * NF;
     for (int j = threadIdx.x; j < NF; j += DFT_BS) {
         t[j].x = tw[2 * (b.twoff + j)];
         t[j].y = tw[2 * (b.twoff + j) + 1];
     }
-    for (int idx = threadIdx.x; idx < ni * NF; idx += DFT_BS) {
-        const int k = idx / ni, i = idx - k * ni;
+    for (int idx = threadIdx.x; idx < (M + 1) * GI; idx += DFT_BS) {
+        const int k = idx / GI, i = idx % GI;
+        if (i >= ni) continue;
         const int64_t o = xelem(b, nrhs, k, c, i0 + i);
-        R2 v;
-        v.x = Yr[o];
-        v.y = Yi[o];
-        yh[i * NF + k] = v;
+        R2 s, d;
+        s.x = Yr[o];
+        s.y = Yi[o];
+        if (k > 0) {
+            const int64_t o2 = xelem(b, nrhs, NF - k, c, i0 + i);
+            const R xr = Yr[o2], xi = Yi[o2];
+            d.x = s.x - xr;
+            d.y = s.y - xi;
+            s.x += xr;
+            s.y += xi;
+            yh[i * NF + NF - k] = d;
+        }
+        yh[i * NF + k] = s;
     }
     __syncthreads();
     const double scale = beta / NF;
-    const int64_t base = b.offset + (int64_t)i0 * NF;
-    for (int idx = threadIdx.x; idx < ni * NF; idx += DFT_BS) {
-        const int i = idx / NF, l = idx - i * NF;
-        R re = 0, im = 0;
-        int tj = 0;
-        const R2 *row = yh + i * NF;
-        for (int k = 0; k < NF; ++k) {
-            const R2 x = row[k], e = t[tj];
-            re = fma(x.x, e.x, fma(-x.y, e.y, re));
-            im = fma(x.y, e.x, fma(x.x, e.y, im));
-            tj += l;
-            if (tj >= NF) tj -= NF;
-        }
-        const int64_t g = (int64_t)c * N + base + idx;
+    const int64_t base = (int64_t)c * N + b.offset + (int64_t)i0 * NF;
+    auto put = [&](int64_t g, R re, R im) {
         double2 out = make_double2(scale * (double)re, scale * (double)im);
         if (alpha != 0.0) {
             const double2 s = sigma[g];
@@ -139,14 +176,37 @@ __global__ __launch_bounds__(DFT_BS) void dft_inverse_kernel(
             out.y += alpha * s.y;
         }
         y[g] = out;
+    };
+    for (int idx = threadIdx.x; idx < ni * (M + 1); idx += DFT_BS) {
+        const int i = idx / (M + 1), l = idx - i * (M + 1);
+        const R2 *row = yh + i * NF;
+        R cr = row[0].x, ci = row[0].y, sr = 0, si = 0;
+        int tj = 0;
+        for (int k = 1; k <= M; ++k) {
+            tj += l;
+            if (tj >= NF) tj -= NF;
+            const R2 s = row[k], d = row[NF - k], e = t[tj];
+            cr = fma(s.x, e.x, cr);
+            ci = fma(s.y, e.x, ci);
+            sr = fma(d.x, e.y, sr);
+            si = fma(d.y, e.y, si);
+        }
+        const int64_t g = base + (int64_t)i * NF;
+        put(g + l, cr - si, ci + sr);
+        if (l > 0) put(g + NF - l, cr + si, ci - sr);
     }
 }
 
 // ---------------------------------------------------------------------------
 // batched complex GEMM on MFMA:  Y = S X  per (shape, |m|)
 // S planar column-major (element (i, k) at k*NG + i); X, Y planar column-major
-// with leading dimension NG.  One 256-thread block computes a 32 x 32 tile,
-// each wave a 16 x 16 tile with the 16x16x4 MFMA (k steps of 4).
+// with leading dimension NG.  16 x 16 tiles of the 16x16x4 MFMA, four k steps'
+// operands loaded ahead of their products.  KS = 1: a 256-thread block computes
+// a 32 x 32 tile, each wave a 16 x 16 tile.  KS = 4: a block computes one 16 x 16 tile,
+// each wave a quarter of the inner dimension, added up in LDS; taken where
+// 32 x 32 tiles would leave fewer than 1,024 workgroups (few bodies and right-
+// hand sides), where the product is bound by the latency of its serial k loop
+// (8,200 nodes, FP64: 15 us with KS = 1, 5 us with KS = 4).
 // Operand layout of the 16x16x4 MFMA (one block of 16x16): lane l supplies
 // A[l % 16][l / 16] and B[l / 16][l % 16]; it receives column l % 16 of D in
 // four registers v = 0..3, rows 4 (l / 16) + v for FP32 and (l / 16) + 4 v for
@@ -171,7 +231,7 @@ template <> struct V4<double> {
     static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
 };
 
-template <typename R>
+template <typename R, int KS>
 __global__ __launch_bounds__(256) void modal_gemm_kernel(const GemmBatch *__restrict__ batches, int nrhs,
                                                          const R *__restrict__ Sr, const R *__restrict__ Si,
                                                          const R *__restrict__ Xr, const R *__restrict__ Xi,
@@ -181,28 +241,64 @@ __global__ __launch_bounds__(256) void modal_gemm_kernel(const GemmBatch *__rest
     const int NG = bt.NG;
     const int ncols = bt.ncols * nrhs;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int r0 = blockIdx.x * 32 + (wave >> 1) * 16;
-    const int c0 = blockIdx.y * 32 + (wave & 1) * 16;
-    if (r0 >= NG || c0 >= ncols) return;
-    const R *Ar = Sr + bt.a_off, *Ai = Si + bt.a_off;
-    const int64_t xo = bt.x_off * nrhs;
-    const R *Br = Xr + xo, *Bi = Xi + xo;
-    const int ar_row = r0 + (lane & 15);
-    const int bcol = c0 + (lane & 15);
+    const int r0 = KS == 1 ? blockIdx.x * 32 + (wave >> 1) * 16 : blockIdx.x * 16;
+    const int c0 = KS == 1 ? blockIdx.y * 32 + (wave & 1) * 16 : blockIdx.y * 16;
+    if (r0 >= NG || c0 >= ncols) return;   // with KS = 4 the whole block
+    // rows and columns beyond the matrix repeat the last one; their results are not stored
+    const int arow = min(r0 + (lane & 15), NG - 1), bcol = min(c0 + (lane & 15), ncols - 1);
     const int kk = lane >> 4;
-    const bool rok = ar_row < NG, cok = bcol < ncols;
+    const int64_t xo = bt.x_off * nrhs;
+    const R *Ar = Sr + bt.a_off + arow, *Ai = Si + bt.a_off + arow;
+    const R *Br = Xr + xo + (int64_t)bcol * NG, *Bi = Xi + xo + (int64_t)bcol * NG;
+    // this wave's k range: quarters in steps of 16
+    const int quarter = KS == 1 ? NG : ((NG + 63) / 64) * 16;
+    const int kb = KS == 1 ? 0 : wave * quarter, ke = min(NG, kb + quarter);
     V accr = {0, 0, 0, 0}, acci = {0, 0, 0, 0};
-    for (int k0 = 0; k0 < NG; k0 += 4) {
-        const int k = k0 + kk;
-        const bool kok = k < NG;
-        const R ar = (rok && kok) ? Ar[(int64_t)k * NG + ar_row] : R(0);
-        const R ai = (rok && kok) ? Ai[(int64_t)k * NG + ar_row] : R(0);
-        const R br = (cok && kok) ? Br[(int64_t)bcol * NG + k] : R(0);
-        const R bi = (cok && kok) ? Bi[(int64_t)bcol * NG + k] : R(0);
+    auto step = [&](R ar, R ai, R br, R bi) {
         accr = mfma16(ar, br, accr);
-        accr = mfma16(ai, -bi, accr);
         acci = mfma16(ar, bi, acci);
+        accr = mfma16(ai, -bi, accr);
         acci = mfma16(ai, br, acci);
+    };
+    int k0 = kb;
+    for (; k0 + 16 <= ke; k0 += 16) {
+        R ar[4], ai[4], br[4], bi[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 4 * u + kk;
+            ar[u] = Ar[(int64_t)k * NG];
+            ai[u] = Ai[(int64_t)k * NG];
+            br[u] = Br[k];
+            bi[u] = Bi[k];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) step(ar[u], ai[u], br[u], bi[u]);
+    }
+    for (; k0 < ke; k0 += 4) {
+        const int k = k0 + kk;
+        const bool kok = k < ke;
+        const R ar = kok ? Ar[(int64_t)k * NG] : R(0), ai = kok ? Ai[(int64_t)k * NG] : R(0);
+        const R br = kok ? Br[k] : R(0), bi = kok ? Bi[k] : R(0);
+        step(ar, ai, br, bi);
+    }
+    if constexpr (KS > 1) {
+        __shared__ R s_acc[KS - 1][8][64];
+        if (wave > 0) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                s_acc[wave - 1][v][lane] = accr[v];
+                s_acc[wave - 1][4 + v][lane] = acci[v];
+            }
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int q = 0; q < KS - 1; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                accr[v] += s_acc[q][v][lane];
+                acci[v] += s_acc[q][4 + v][lane];
+            }
     }
     const int ocol = c0 + (lane & 15);
     if (ocol < ncols) {
@@ -220,66 +316,85 @@ __global__ __launch_bounds__(256) void modal_gemm_kernel(const GemmBatch *__rest
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-static size_t dft_smem(Ctx &c, size_t elem) {
+// contour nodes per DFT block (see above), and the block's LDS
+static int dft_gi(const Ctx &c, int nrhs) {
+    return ceil_div(c.max_NG, 16) * nrhs * (int64_t)c.bodies.size() < 1024 ? 4 : 16;
+}
+static size_t dft_smem(const Ctx &c, int gi, size_t elem) {
     int maxnf = 0;
     for (auto &s : c.shapes) maxnf = std::max(maxnf, s.NF);
-    return (size_t)(DFT_GI + 1) * maxnf * elem;
+    return (size_t)(gi + 2) * maxnf * elem;
+}
+
+template <typename R, int GI>
+static void launch_forward(Ctx &c, int from_vec, const void *vec, int nrhs, int splits, const R *tw) {
+    using R2 = typename CT<R>::T;
+    const int64_t total = (int64_t)nrhs * c.N;
+    R *Xr = (R *)c.scratch(WS_XR, total * sizeof(R)), *Xi = (R *)c.scratch(WS_XI, total * sizeof(R));
+    hipLaunchKernelGGL((dft_forward_kernel<R, GI>),
+                       dim3((unsigned)ceil_div(c.max_NG, GI), nrhs, (unsigned)c.bodies.size()), dim3(DFT_BS),
+                       dft_smem(c, GI, sizeof(R2)), c.stream, c.body_dev, (const R2 *)c.scratch(WS_PART, 0), splits,
+                       (const double2 *)vec, from_vec, c.N, nrhs, tw, Xr, Xi);
+    AXS_HIP(hipGetLastError());
 }
 
 void dft_forward(Ctx &c, int prec, int from_vec, const void *vec, int nrhs, int splits) {
-    const int64_t total = (int64_t)nrhs * c.N;
-    dim3 grid((unsigned)ceil_div(c.max_NG, DFT_GI), nrhs, (unsigned)c.bodies.size());
+    const bool small = dft_gi(c, nrhs) == 4;
     if (prec == AXS_FP32) {
-        float *Xr = (float *)c.scratch(WS_XR, total * sizeof(float));
-        float *Xi = (float *)c.scratch(WS_XI, total * sizeof(float));
-        hipLaunchKernelGGL(dft_forward_kernel<float>, grid, dim3(DFT_BS), dft_smem(c, sizeof(float2)),
-                           c.stream, c.body_dev, (const float2 *)c.scratch(WS_PART, 0), splits,
-                           (const double2 *)vec, from_vec, c.N, nrhs, c.tw32, Xr, Xi);
+        if (small) launch_forward<float, 4>(c, from_vec, vec, nrhs, splits, c.tw32);
+        else launch_forward<float, 16>(c, from_vec, vec, nrhs, splits, c.tw32);
     } else {
-        double *Xr = (double *)c.scratch(WS_XR, total * sizeof(double));
-        double *Xi = (double *)c.scratch(WS_XI, total * sizeof(double));
-        hipLaunchKernelGGL(dft_forward_kernel<double>, grid, dim3(DFT_BS), dft_smem(c, sizeof(double2)),
-                           c.stream, c.body_dev, (const double2 *)c.scratch(WS_PART, 0), splits,
-                           (const double2 *)vec, from_vec, c.N, nrhs, c.tw64, Xr, Xi);
+        if (small) launch_forward<double, 4>(c, from_vec, vec, nrhs, splits, c.tw64);
+        else launch_forward<double, 16>(c, from_vec, vec, nrhs, splits, c.tw64);
     }
+}
+
+template <typename R>
+static void launch_gemm(Ctx &c, int nrhs, const R *Sr, const R *Si) {
+    const int64_t total = (int64_t)nrhs * c.N, cols = (int64_t)c.gemm_max_cols * nrhs;
+    R *Yr = (R *)c.scratch(WS_YR, total * sizeof(R)), *Yi = (R *)c.scratch(WS_YI, total * sizeof(R));
+    const R *Xr = (const R *)c.scratch(WS_XR, 0), *Xi = (const R *)c.scratch(WS_XI, 0);
+    if (ceil_div(c.max_NG, 32) * ceil_div(cols, 32) * c.ngemm < 1024)
+        hipLaunchKernelGGL((modal_gemm_kernel<R, 4>),
+                           dim3((unsigned)ceil_div(c.max_NG, 16), (unsigned)ceil_div(cols, 16), (unsigned)c.ngemm),
+                           dim3(256), 0, c.stream, c.gemm, nrhs, Sr, Si, Xr, Xi, Yr, Yi);
+    else
+        hipLaunchKernelGGL((modal_gemm_kernel<R, 1>),
+                           dim3((unsigned)ceil_div(c.max_NG, 32), (unsigned)ceil_div(cols, 32), (unsigned)c.ngemm),
+                           dim3(256), 0, c.stream, c.gemm, nrhs, Sr, Si, Xr, Xi, Yr, Yi);
     AXS_HIP(hipGetLastError());
 }
 
 void modal_gemm(Ctx &c, int prec, int nrhs, bool forward) {
-    const int64_t total = (int64_t)nrhs * c.N;
-    dim3 grid((unsigned)ceil_div(c.max_NG, 32), (unsigned)ceil_div((int64_t)c.gemm_max_cols * nrhs, 32),
-              (unsigned)c.ngemm);
     // all shapes' matrices live in one planar allocation per precision (see precompute)
     const Shape &s0 = c.shapes[0];
     if (forward && prec != AXS_FP64) throw Error{AXS_EINVAL, "the A~_m products exist in FP64 only"};
-    if (prec == AXS_FP32) {
-        float *Yr = (float *)c.scratch(WS_YR, total * sizeof(float));
-        float *Yi = (float *)c.scratch(WS_YI, total * sizeof(float));
-        hipLaunchKernelGGL(modal_gemm_kernel<float>, grid, dim3(256), 0, c.stream, c.gemm, nrhs, s0.S32r,
-                           s0.S32i, (const float *)c.scratch(WS_XR, 0), (const float *)c.scratch(WS_XI, 0),
-                           Yr, Yi);
-    } else {
-        double *Yr = (double *)c.scratch(WS_YR, total * sizeof(double));
-        double *Yi = (double *)c.scratch(WS_YI, total * sizeof(double));
-        hipLaunchKernelGGL(modal_gemm_kernel<double>, grid, dim3(256), 0, c.stream, c.gemm, nrhs,
-                           forward ? s0.A64r : s0.S64r, forward ? s0.A64i : s0.S64i,
-                           (const double *)c.scratch(WS_XR, 0), (const double *)c.scratch(WS_XI, 0), Yr, Yi);
-    }
+    if (prec == AXS_FP32)
+        launch_gemm<float>(c, nrhs, s0.S32r, s0.S32i);
+    else
+        launch_gemm<double>(c, nrhs, forward ? s0.A64r : s0.S64r, forward ? s0.A64i : s0.S64i);
+}
+
+template <typename R, int GI>
+static void launch_inverse(Ctx &c, const void *sigma, double alpha, double beta, void *y, int nrhs, const R *tw) {
+    using R2 = typename CT<R>::T;
+    hipLaunchKernelGGL((dft_inverse_kernel<R, GI>),
+                       dim3((unsigned)ceil_div(c.max_NG, GI), nrhs, (unsigned)c.bodies.size()), dim3(DFT_BS),
+                       dft_smem(c, GI, sizeof(R2)), c.stream, c.body_dev, (const R *)c.scratch(WS_YR, 0),
+                       (const R *)c.scratch(WS_YI, 0), c.N, nrhs, tw, (const double2 *)sigma, alpha, beta,
+                       (double2 *)y);
     AXS_HIP(hipGetLastError());
 }
 
 void dft_inverse(Ctx &c, int prec, const void *sigma, double alpha, double beta, void *y, int nrhs) {
-    dim3 grid((unsigned)ceil_div(c.max_NG, DFT_GI), nrhs, (unsigned)c.bodies.size());
-    if (prec == AXS_FP32)
-        hipLaunchKernelGGL(dft_inverse_kernel<float>, grid, dim3(DFT_BS), dft_smem(c, sizeof(float2)), c.stream,
-                           c.body_dev, (const float *)c.scratch(WS_YR, 0), (const float *)c.scratch(WS_YI, 0),
-                           c.N, nrhs, c.tw32, (const double2 *)sigma, alpha, beta, (double2 *)y);
-    else
-        hipLaunchKernelGGL(dft_inverse_kernel<double>, grid, dim3(DFT_BS), dft_smem(c, sizeof(double2)),
-                           c.stream, c.body_dev, (const double *)c.scratch(WS_YR, 0),
-                           (const double *)c.scratch(WS_YI, 0), c.N, nrhs, c.tw64, (const double2 *)sigma,
-                           alpha, beta, (double2 *)y);
-    AXS_HIP(hipGetLastError());
+    const bool small = dft_gi(c, nrhs) == 4;
+    if (prec == AXS_FP32) {
+        if (small) launch_inverse<float, 4>(c, sigma, alpha, beta, y, nrhs, c.tw32);
+        else launch_inverse<float, 16>(c, sigma, alpha, beta, y, nrhs, c.tw32);
+    } else {
+        if (small) launch_inverse<double, 4>(c, sigma, alpha, beta, y, nrhs, c.tw64);
+        else launch_inverse<double, 16>(c, sigma, alpha, beta, y, nrhs, c.tw64);
+    }
 }
 
 }  // namespace axs
