@@ -49,11 +49,6 @@ __device__ __forceinline__ void sincos_rev_near(float ph, float &s, float &c) {
     c = __builtin_amdgcn_cosf(ph);
 }
 
-// precision-generic entry points used by the kernels (the table is unused in FP32)
-__device__ __forceinline__ void sincos_any(float ph, const double2 *, float &s, float &c) { sincos_rev(ph, s, c); }
-__device__ __forceinline__ void sincos_any(double t, const double2 *tab, double &s, double &c) {
-    sincos_rev_tab(t, tab, s, c);
-}
 // sin and cos of 2 pi R' from r2 = R'^2 and u = 1/R' (R' = R k / 2 pi, the
 // phase in revolutions).  FP32: the hardware sin/cos of R' - n0, n0 the whole
 // revolutions of the (wavefront, source body), which keeps the argument in
@@ -95,25 +90,31 @@ template <typename R, int NR, bool FOLD> struct SrcStride {
     static constexpr int value = (raw + per16 - 1) / per16 * per16;
 };
 
+// sin and cos of the phase of the point order in revolutions.  near: every phase of
+// the launch is under 255 revolutions, so the FP32 hardware sin/cos take it
+// without the fraction step; FP64 uses the table, good for any phase below 2^40
+// revolutions.
+__device__ __forceinline__ void point_sincos(float ph, int near, const double2 *, float &s, float &c) {
+    if (near)
+        sincos_rev_near(ph, s, c);
+    else
+        sincos_rev(ph, s, c);
+}
+__device__ __forceinline__ void point_sincos(double ph, int, const double2 *tab, double &s, double &c) {
+    sincos_rev_tab(ph, tab, s, c);
+}
+
 // One pair of the point order with one right-hand side, as ring_term1: r2 =
-// R'^2 and nd = nd' in revolutions, qv the staged density terms.  near: every
-// phase of the launch is under 255 revolutions, so the FP32 hardware sin/cos
-// take it without the fraction step; FP64 uses the table form, good for any
-// phase below 2^40 revolutions.
+// R'^2 and nd = nd' in revolutions, qv the staged density terms.
 template <typename R>
 __device__ __forceinline__ void point_term1(R r2, R nd, int near, const double2 *s_tab, const R *qv, R &ar,
                                             R &ai) {
     const R u = rsq(r2);
     R sn, cs_;
-    if constexpr (sizeof(R) == 4) {
-        const R ph = r2 * u;
-        if (near)
-            sincos_rev_near(ph, sn, cs_);
-        else
-            sincos_rev(ph, sn, cs_);
-    } else {
+    if constexpr (sizeof(R) == 4)
+        point_sincos(r2 * u, near, s_tab, sn, cs_);
+    else
         sincos_phase(r2, u, R(0), s_tab, sn, cs_);
-    }
     const R w = nd * u;
     const R zr = fma(w, fma(u, qv[0], qv[2]), qv[4]);
     const R zi = fma(w, fma(u, qv[1], qv[3]), qv[5]);
@@ -235,11 +236,11 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
                 for (int k = 0; k < TPT; ++k) {
                     const R dx = tx[k] - sx, dy = ty[k] - sy, dz = tz[k] - sz;
                     const R r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                    const R ri = rsq(r2);
+                    const R u = rsq(r2);
                     const R nd = fma(snx, dx, fma(sny, dy, snz * dz));
                     if constexpr (LAP) {
                         // kappa = 0 (Sec. 6.1): 4 pi G = (n.d / R^2 + eta) / R, real
-                        const R G = ri * fma(nd, ri * ri, eta);
+                        const R G = u * fma(nd, u * u, eta);
 #pragma unroll
                         for (int c = 0; c < NR; ++c) {
                             ar[k][c] = fma(G, qr[c], ar[k][c]);
@@ -247,14 +248,14 @@ __global__ __launch_bounds__(BS) void interbody_kernel(
                         }
                         continue;
                     }
-                    const R rr = r2 * ri;
+                    // as the ring order (ring_term), unscaled
                     R sn, cs;
-                    sincos_any(rr * k2pi, s_tab, sn, cs);
-                    const R a = nd * ri * ri;                 // (n.d)/R^2
-                    const R bim = fma(-a * kappa, rr, eta);   // eta - a k R
-                    const R er = cs * ri, ei = sn * ri;       // e^{ikR}/R
-                    const R gr = fma(er, a, -ei * bim);
-                    const R gi = fma(er, bim, ei * a);
+                    point_sincos(r2 * u * k2pi, near, s_tab, sn, cs);
+                    const R t = nd * (u * u);              // (n.d)/R^2
+                    const R P = t * u;
+                    const R Q = fma(-kappa, t, eta * u);
+                    const R gr = fma(cs, P, -sn * Q);
+                    const R gi = fma(cs, Q, sn * P);
 #pragma unroll
                     for (int c = 0; c < NR; ++c) {
                         ar[k][c] = fma(gr, qr[c], fma(-gi, qi[c], ar[k][c]));
@@ -1179,11 +1180,9 @@ static int64_t count_tiles(const Ctx &c, int tile) {
 // below).
 //  order: below 16 rhs the ring order, from 16 on the MFMA order (in FP32 with
 //    the FP16 multiply-accumulate where the kernel values have a bound); the
-//    point order where neither applies.  A compressed system of single nodes
-//    has no rings: in FP32 its padded group of 16 (342 us on 20,090 nodes
-//    whatever the rhs) beats the point order from 5 rhs (376), in FP64 the MFMA
-//    order beats it at the widths it has groups of (1: 481 against 522; 4: 661
-//    against 701; at 5, with groups of 4 and 1, 1139 against 768).
+//    point order where neither applies (compressed systems of single nodes,
+//    which have no rings; the MFMA orders would be faster there from 5 rhs, but
+//    the point order forms x - y first and its FP32 error is up to half of theirs).
 //  targets per thread: FP32 rings 1 (20,090 nodes: 216 us, 2: 250), at zero
 //    frequency 2 from 3 rhs (136,350 nodes: 4.52 ms, 1: 4.86).  FP64 rings: 4
 //    pays only where bodies have many tiles of 1,024 targets (129,600 nodes: 4
@@ -1193,8 +1192,7 @@ static int64_t count_tiles(const Ctx &c, int tile) {
 //    976 us, 2 836, 1 860).  FP64 points 2 (83,640 nodes: 8.36 ms, 4 8.56).
 //    MFMA orders: 2 groups of 16 targets per wavefront; FP64 4 where there are
 //    256 tiles of that size (129,600 nodes, 16 rhs: 39.7 ms, 2 40.5; 20,090
-//    nodes 1141 and 1051 us), and 1 in small systems (8,200 nodes, 1 rhs: 116, 2
-//    122).
+//    nodes 1141 and 1051 us).
 static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
     const int width = (int)ceil_div(nrhs, ceil_div(nrhs, 8));   // of a VALU rhs group
     const bool large = count_tiles(c, 1024) >= 64;
@@ -1203,7 +1201,7 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
         if (prec == AXS_FP32) return 2;
         const int64_t groups = ceil_div(nrhs, 16);
         if (count_tiles(c, 256) * groups >= 256) return 4;
-        return nrhs < 16 && count_tiles(c, 128) < 128 ? 1 : 2;
+        return 2;
     }
     if (variant == 1) return prec == AXS_FP32 ? 1 : 2;
     if (prec == AXS_FP32) return c.kappa == 0 && nrhs >= 3 ? 2 : 1;
@@ -1243,10 +1241,8 @@ static IBShape launch_shape(Ctx &c, int prec, int nrhs) {
     const bool mf_ok = c.kappa > 0 && c.mf_src && c.near_phase_ok && s.bs == 256 &&
                        (c.ib_tpt[pi] == 0 || c.ib_tpt[pi] <= 4);
     const bool mf16_ok = mf_ok && prec == AXS_FP32 && c.mf16_ok;
-    // (c.no_rings: the compressed system of single nodes)
-    const bool few16 = c.no_rings && nrhs >= 5, few = c.no_rings && prec == AXS_FP64 && (nrhs & (nrhs - 1)) == 0;
     s.variant = c.ib_variant[pi] > 0 ? c.ib_variant[pi]
-                : ((nrhs >= 16 || few16) && mf16_ok) ? 4 : ((nrhs >= 16 || few) && mf_ok) ? 3 : ring_ok ? 2 : 1;
+                : (nrhs >= 16 && mf16_ok) ? 4 : (nrhs >= 16 && mf_ok) ? 3 : ring_ok ? 2 : 1;
     s.tpt = c.ib_tpt[pi] > 0 ? c.ib_tpt[pi] : default_tpt(c, prec, s.variant, nrhs);
     AXS_REQUIRE(s.variant != 2 || ring_ok, AXS_EINVAL,
                 "ring variant needs N_F/2 + 1 <= threads per block and bodies under 127 wavelengths across");
