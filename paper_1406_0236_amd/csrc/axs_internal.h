@@ -247,20 +247,22 @@ enum ScratchSlot {
 // Point skeletons: per shape k skeleton nodes of its n = NG NF nodes, the
 // interpolation matrix as X^T (k x n, column-major: column j holds row j of X,
 // columns of X in ascending skeleton node order) and S_p = X^T A_pp^{-1} X
-// (k x k, column-major) in FP64 and FP32; bodies grouped in runs of
-// consecutive bodies of one shape (one batched product per run)
-struct PointRun {
-    int shape, first, nb, k, n;
-    int64_t o0, s0;                      // first full node and first skeleton node of the run
-};
-// 256 rows of one body's dense m x K block (column-major, ld m) times the
-// body's K-vector of every rhs: the work item of the per-body products of
-// point skeletons (S_p in the skeleton system, X^T in the restriction)
-struct BodyMatItem {
+// (k x k, column-major) in FP64 and FP32.
+//
+// Dense products of every body with its shape's block (S_p in the skeleton
+// system, X^T in the restriction, X in the prolongation): out_b = A in_b, A of m
+// rows and K columns, for the bodies [first, first + count) of the lists in0, out0
+// (each body's first entry in the input and output vectors).
+struct BodyMat {
     const float2 *A32;                   // complex64 copy of the block, or null
     const double2 *A64;                  // complex128
-    int64_t in0, out0;                   // the body's first entry in the input and output vectors
-    int m, K, row0, pad;
+    int m, K, first, count;
+};
+struct BodyMats {                        // device tables, bodies sorted by shape
+    BodyMat *mats = nullptr;
+    int64_t *in0 = nullptr, *out0 = nullptr;
+    int2 *items = nullptr;               // (block, first row) of every 64-row slice
+    int nitems = 0, max_bodies = 0;      // slices of all blocks; bodies of the commonest one
 };
 
 struct PointSkel {
@@ -270,10 +272,7 @@ struct PointSkel {
     std::vector<double2 *> XT;           // per shape (device)
     std::vector<double2 *> S64;
     std::vector<float2 *> S32;
-    std::vector<PointRun> runs;
-    BodyMatItem *sp_items = nullptr;     // device: S_p per skeleton body
-    BodyMatItem *rs_items = nullptr;     // device: X^T per body (full -> skeleton)
-    int n_sp = 0, n_rs = 0;
+    BodyMats sp, restrict_, prolong;     // S_p; X^T (full -> skeleton); X (skeleton -> full)
 };
 
 struct Skeleton {

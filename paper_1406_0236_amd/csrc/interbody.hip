@@ -925,7 +925,7 @@ __global__ __launch_bounds__(64) void qmax_final_kernel(const unsigned *__restri
 // six FP16 planes per 32-source block and rhs group (B-operand order)
 __global__ __launch_bounds__(256) void q16_kernel(const float2 *__restrict__ q, const unsigned *__restrict__ qmax,
                                                   const int64_t *__restrict__ boff, const int32_t *__restrict__ bblk,
-                                                  int nbodies, int64_t N, int64_t nblk, int groups, int nrhs,
+                                                  int nbodies, int64_t N, int64_t nblk, int groups,
                                                   _Float16 *__restrict__ q16) {
     const int64_t item = (int64_t)blockIdx.x * 256 + threadIdx.x;   // ((grp * nblk + B) * 16 + c) * 32 + k
     if (item >= (int64_t)groups * nblk * 512) return;
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(256) void q16_kernel(const float2 *__restrict__ q, 
     const int64_t node = boff[b] + 32 * (B - bblk[b]) + r;
     const int rhs = grp * 16 + c;
     float2 v = make_float2(0.f, 0.f);
-    if (node < boff[b + 1] && rhs < nrhs) {   // padding nodes and right-hand sides: zero
+    if (node < boff[b + 1]) {
         v = q[(int64_t)rhs * N + node];
         const float s = ldexpf(1.f, qscale_exp(qmax[rhs]));
         v.x *= s;
@@ -1092,7 +1092,6 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
         }
     }
     // lane (kq, col) holds targets 4kq + v of each group for rhs cb + col
-    if (cb + col >= nrhs) return;   // padding of the last group
     const float inv = ldexpf(1.f, -(gexp + qscale_exp(qmax[cb + col])));
 #pragma unroll
     for (int g = 0; g < G; ++g)
@@ -1667,15 +1666,12 @@ static const IBWork *get_work(Ctx &c, int pi, int wi, const IBShape &s, Units un
     return c.ib_work[pi][wi];
 }
 
-// MFMA order with the FP16 multiply-accumulate: groups of 16 rhs over 32-node
-// source blocks.  A remainder of 1 or 2 rhs takes the FP32 MFMA order; from 3 on it
-// pads a last group with zero densities (83,640 nodes: a group takes 5.0 ms
-// whatever its rhs, the FP32 MFMA order 7.2 ms for 8).  Both write the same
-// [splits][nrhs][N] partial sums.
+// MFMA order with the FP16 multiply-accumulate: full groups of 16 rhs over
+// 32-node source blocks; a remainder of fewer than 16 rhs takes the FP32 MFMA
+// order (node units).  Both write the same [splits][nrhs][N] partial sums.
 static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, float2 *part) {
-    const bool apart = nrhs % 16 == 1 || nrhs % 16 == 2;
-    const int groups = apart ? nrhs / 16 : (int)ceil_div(nrhs, 16);
-    {
+    const int groups = nrhs / 16;
+    if (groups > 0) {
         int nwork = 0;
         const IBWork *work = get_work(c, 1, 2, s, Units::blocks, nwork);
         // slices of at least 16K nodes per block, at most QMAX_SLICES per rhs
@@ -1687,7 +1683,7 @@ static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, flo
         const int64_t items = (int64_t)groups * c.nblk * 512;
         _Float16 *q16 = (_Float16 *)c.scratch(WS_Q16, (size_t)items * 6 * sizeof(_Float16));
         hipLaunchKernelGGL(q16_kernel, dim3(ceil_div(items, (int64_t)256)), dim3(256), 0, c.stream, q, qmax,
-                           c.body_off, c.blk_off, (int)c.bodies.size(), c.N, c.nblk, groups, nrhs, q16);
+                           c.body_off, c.blk_off, (int)c.bodies.size(), c.N, c.nblk, groups, q16);
         AXS_HIP(hipGetLastError());
         const float k2pi = (float)(c.kappa / (2.0 * M_PI));
         const float s2 = k2pi * k2pi;
@@ -1706,14 +1702,15 @@ static void launch_mf16(Ctx &c, const IBShape &s, const float2 *q, int nrhs, flo
 #undef AXS_MF16
         AXS_HIP(hipGetLastError());
     }
-    if (!apart) return;
-    int nwork = 0;
-    IBShape r = s;
-    r.variant = 3;
-    const IBWork *work = get_work(c, 1, 1, r, Units::nodes, nwork);
-    if (s.tpt == 1) launch_mf<float, 1>(c, work, nwork, q, nrhs, part, 16 * groups);
-    else if (s.tpt == 2) launch_mf<float, 2>(c, work, nwork, q, nrhs, part, 16 * groups);
-    else launch_mf<float, 4>(c, work, nwork, q, nrhs, part, 16 * groups);
+    if (16 * groups < nrhs) {
+        int nwork = 0;
+        IBShape s3 = s;
+        s3.variant = 3;
+        const IBWork *work = get_work(c, 1, 1, s3, Units::nodes, nwork);
+        if (s.tpt == 1) launch_mf<float, 1>(c, work, nwork, q, nrhs, part, 16 * groups);
+        else if (s.tpt == 2) launch_mf<float, 2>(c, work, nwork, q, nrhs, part, 16 * groups);
+        else launch_mf<float, 4>(c, work, nwork, q, nrhs, part, 16 * groups);
+    }
 }
 
 int64_t interbody_scratch_bytes(Ctx &c, int prec, int nrhs) {

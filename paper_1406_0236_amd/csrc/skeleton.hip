@@ -608,14 +608,15 @@ void release_skeleton(Ctx &c) {
         for (auto *p : c.skel->pts->XT) c.dfree(p);
         for (auto *p : c.skel->pts->S64) c.dfree(p);
         for (auto *p : c.skel->pts->S32) c.dfree(p);
-        if (c.skel->pts->sp_items) c.dfree(c.skel->pts->sp_items);
-        if (c.skel->pts->rs_items) c.dfree(c.skel->pts->rs_items);
+        for (BodyMats *t : {&c.skel->pts->sp, &c.skel->pts->restrict_, &c.skel->pts->prolong})
+            for (void *p : {(void *)t->mats, (void *)t->in0, (void *)t->out0, (void *)t->items}) c.dfree(p);
     }
     c.skel.reset();
 }
 
 static void point_restrict(Ctx &c, const void *y, void *out, int nrhs, double alpha);
-static BodyMatItem *upload_items(Ctx &c, const std::vector<BodyMatItem> &bodies, int &count);
+static BodyMats upload_mats(Ctx &c, const std::vector<BodyMat> &blocks, const std::vector<int64_t> &in0,
+                            const std::vector<int64_t> &out0);
 static void point_prolong(Ctx &c, const void *w, const void *add, void *out, int nrhs);
 
 // restrict / prolong between the full and the skeleton vectors
@@ -1470,20 +1471,13 @@ void skeletonize_points(Ctx &c, double eps, double factor, int n_proxy, uint64_t
         for (auto *p : P.S32) c.dfree(p);
         throw;
     }
-    // runs of consecutive bodies of one shape, skeleton offsets, node list
+    // skeleton offsets, node list
     std::vector<int64_t> gidx;
     int64_t off = 0;
     for (size_t b = 0; b < nb; ++b) {
         const Body &B = c.bodies[b];
-        const int sh = B.shape;
-        if (P.runs.empty() || P.runs.back().shape != sh ||
-            P.runs.back().o0 + (int64_t)P.runs.back().nb * P.n[sh] != B.offset) {
-            PointRun r{sh, (int)b, 0, P.k[sh], P.n[sh], B.offset, off};
-            P.runs.push_back(r);
-        }
-        P.runs.back().nb += 1;
-        for (int j : P.nodes[sh]) gidx.push_back(B.offset + j);
-        off += P.k[sh];
+        for (int j : P.nodes[B.shape]) gidx.push_back(B.offset + j);
+        off += P.k[B.shape];
     }
     const int64_t Ns = off;
     // the child context: the skeleton nodes of every body, point-order sum
@@ -1556,16 +1550,22 @@ void skeletonize_points(Ctx &c, double eps, double factor, int n_proxy, uint64_t
     ch.pop = sk->pts.get();
     ch.precomputed = true;
     {
-        std::vector<BodyMatItem> sp, rs;
-        for (size_t b = 0; b < nb; ++b) {
-            const Body &B = c.bodies[b];
-            const int sh = B.shape;
-            const int64_t s0 = ch.bodies[b].offset;
-            sp.push_back(BodyMatItem{P.S32[sh], P.S64[sh], s0, s0, P.k[sh], P.k[sh], 0, 0});
-            rs.push_back(BodyMatItem{nullptr, P.XT[sh], B.offset, s0, P.k[sh], P.n[sh], 0, 0});
+        std::vector<BodyMat> sp, rs, pr;
+        std::vector<int64_t> full, skel;   // first nodes of the bodies, shape by shape
+        for (size_t k = 0; k < nsh; ++k) {
+            const int first = (int)full.size();
+            for (int b : c.shapes[k].bodies) {
+                full.push_back(c.bodies[b].offset);
+                skel.push_back(ch.bodies[b].offset);
+            }
+            const int cnt = (int)full.size() - first;
+            sp.push_back(BodyMat{P.S32[k], P.S64[k], P.k[k], P.k[k], first, cnt});
+            rs.push_back(BodyMat{nullptr, P.XT[k], P.k[k], P.n[k], first, cnt});
+            pr.push_back(BodyMat{nullptr, P.XT[k], P.n[k], P.k[k], first, cnt});
         }
-        P.sp_items = upload_items(c, sp, P.n_sp);
-        P.rs_items = upload_items(c, rs, P.n_rs);
+        P.sp = upload_mats(c, sp, skel, skel);
+        P.restrict_ = upload_mats(c, rs, full, skel);
+        P.prolong = upload_mats(c, pr, skel, full);
     }
     sk->Ns = Ns;
     sk->eps = eps;
@@ -1573,191 +1573,197 @@ void skeletonize_points(Ctx &c, double eps, double factor, int n_proxy, uint64_t
     c.skel = std::move(sk);
 }
 
-// child of point skeletons: y = s + S (B~ s), B~ in `prec`, S_p in the same precision
-// C = alpha op(A) B + beta C for every body of a run and every rhs, A shared.
-// B holds a body's kk-vector per (body j, rhs c) at j bk + c bN, C its
-// m-vector at j ck + c cN.  With at least as many rhs as bodies: one GEMM per
-// body whose columns are the rhs (ld = the rhs stride); else one GEMM per rhs
-// whose columns are the bodies.  Either way A is streamed min(nb, nrhs) times,
-// not once per (body, rhs) column.
-template <typename T, typename Gemm>
-static void run_gemm(rocblas_handle h, Gemm gemm, rocblas_operation op, int m, int kk, int nb, int nrhs, const T *alpha,
-                     const T *A, int lda, const T *B, int64_t bk, int64_t bN, const T *beta, T *C, int64_t ck,
-                     int64_t cN) {
-    if (nrhs >= nb)
-        AXS_BLAS(gemm(h, op, rocblas_operation_none, m, nrhs, kk, alpha, A, lda, 0, B, (rocblas_int)bN,
-                      (rocblas_stride)bk, beta, C, (rocblas_int)cN, (rocblas_stride)ck, nb));
-    else
-        AXS_BLAS(gemm(h, op, rocblas_operation_none, m, nb, kk, alpha, A, lda, 0, B, (rocblas_int)bk,
-                      (rocblas_stride)bN, beta, C, (rocblas_int)ck, (rocblas_stride)cN, nrhs));
-}
-
-// out_b = alpha A_b in_b (+ out_b) for every body b of a work list and every
-// rhs: one workgroup per 256 rows of a body's block and NR rhs, one row per
-// thread, NR complex accumulators per thread.  The input rows of a 64-column
-// chunk (NR rhs) are staged in LDS and read back as broadcasts; A is read
-// once per (row, column) and rhs group, down its columns, so a wavefront's
-// load covers 64 consecutive rows.  With one body per launch of a GEMM
-// library the same product fills a few dozen workgroups; here every body of
-// every shape is in one launch.  In FP32 (R = float) the complex64 copy of A
-// is used and the input is rounded to FP32 as it is staged.
+// out_b = add_b + alpha A in_b for every body b and rhs, A the block of b's shape (m x
+// K).  Bound: reading the blocks once (8 or 16 bytes an entry, a few hundred MB a
+// scene) against 4 FMAs an entry and column.  A shape's bodies and right-hand
+// sides are one set of columns, so a block is read once per NR columns and not once
+// per body: a workgroup takes 64 rows and NR columns, its KW wavefronts each an
+// equal part of the inner dimension (a slice per wavefront keeps enough loads in
+// flight where a scene has few slices), one row per lane, eight entries loaded
+// ahead; the input entries of KC inner indices are staged in LDS (rounded to R) and
+// read back as broadcasts; the wavefronts' sums are added in a fixed tree.
+// TRANS: A is stored as its transpose (row i contiguous: a lane reads whole cache
+// lines of its own row, eight entries at a time).
+// 8 bodies of 1,488 to 2,199 skeleton nodes, 5 rhs, FP32: 61 us (a
+// 256-row slice of one body and 4 rhs per workgroup: 322 us).
 template <typename R> struct CplxOf;
 template <> struct CplxOf<float> { using T = float2; };
 template <> struct CplxOf<double> { using T = double2; };
-constexpr int BM_KC = 64;
+constexpr int BM_KC = 32;
 
-template <typename R, int NR>
-__global__ __launch_bounds__(256) void body_matvec_kernel(const BodyMatItem *__restrict__ items,
-                                                          const double2 *__restrict__ in, int64_t inN, int nrhs,
-                                                          double2 *__restrict__ out, int64_t outN, double alpha,
-                                                          int accumulate) {
+template <typename R, int NR, int KW, bool TRANS>
+__global__ __launch_bounds__(64 * KW) void body_matvec_kernel(
+    const int2 *__restrict__ items, const BodyMat *__restrict__ mats, const int64_t *__restrict__ in0,
+    const int64_t *__restrict__ out0, const double2 *__restrict__ in, int64_t inN, int nrhs,
+    const double2 *__restrict__ add, double2 *__restrict__ out, int64_t outN, double alpha) {
     using C = typename CplxOf<R>::T;
-    __shared__ C sw[BM_KC * NR];
-    const BodyMatItem it = items[blockIdx.x];
-    const int c0 = blockIdx.y * NR;
-    const int i = it.row0 + (int)threadIdx.x;
-    const bool row_ok = i < it.m;
-    const C *A = sizeof(R) == 4 ? (const C *)(const void *)it.A32 : (const C *)(const void *)it.A64;
+    constexpr int STAGE = KW * BM_KC * NR, RED = KW / 2 * NR * 64;
+    __shared__ C sw[STAGE > RED ? STAGE : RED];
+    const int2 it = items[blockIdx.x];
+    const BodyMat mt = mats[it.x];
+    const int ncol = mt.count * nrhs, q0 = blockIdx.y * NR;
+    if (q0 >= ncol) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = it.y + lane, arow = min(row, mt.m - 1);
+    const int kq = ((mt.K + KW - 1) / KW + 7) / 8 * 8;
+    const C *A = (sizeof(R) == 4 ? (const C *)(const void *)mt.A32 : (const C *)(const void *)mt.A64) +
+                 (TRANS ? (int64_t)arow * mt.K : arow);
+    const int64_t lda = TRANS ? 1 : mt.m;
     R ar[NR], ai[NR];
 #pragma unroll
     for (int q = 0; q < NR; ++q) ar[q] = ai[q] = R(0);
-    for (int j0 = 0; j0 < it.K; j0 += BM_KC) {
-        const int kc = min(BM_KC, it.K - j0);
+    for (int s0 = 0; s0 < kq; s0 += BM_KC) {
         __syncthreads();
-        for (int t = threadIdx.x; t < BM_KC * NR; t += 256) {
-            const int j = t % BM_KC, q = t / BM_KC;
+        for (int t = threadIdx.x; t < STAGE; t += 64 * KW) {
+            const int j = t % BM_KC, q = t / BM_KC % NR, w = t / (BM_KC * NR);
+            const int k = w * kq + s0 + j;
             C v;
             v.x = R(0);
             v.y = R(0);
-            if (j < kc && c0 + q < nrhs) {
-                const double2 x = in[(int64_t)(c0 + q) * inN + it.in0 + j0 + j];
+            if (s0 + j < kq && k < mt.K && q0 + q < ncol) {
+                const int b = (q0 + q) / nrhs, c = (q0 + q) - b * nrhs;
+                const double2 x = in[(int64_t)c * inN + in0[mt.first + b] + k];
                 v.x = (R)x.x;
                 v.y = (R)x.y;
             }
-            sw[j * NR + q] = v;
+            sw[(w * BM_KC + j) * NR + q] = v;
         }
         __syncthreads();
-        if (row_ok) {
-            const C *col = A + (int64_t)j0 * it.m + i;
-            int j = 0;
-            for (; j + 8 <= kc; j += 8) {
-                C a[8];
+        const int k0 = wave * kq + s0;
+        const C *x = sw + wave * BM_KC * NR;
+#pragma unroll 1
+        for (int j = 0; j < BM_KC && s0 + j < kq; j += 8) {
+            if (k0 + j >= mt.K) break;
+            C a[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = col[(int64_t)(j + u) * it.m];
+            for (int u = 0; u < 8; ++u)   // entries beyond K repeat the last one, against zero input
+                a[u] = A[min(k0 + j + u, mt.K - 1) * lda];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int q = 0; q < NR; ++q) {
-                        const C x = sw[(j + u) * NR + q];
-                        ar[q] = fma(a[u].x, x.x, fma(-a[u].y, x.y, ar[q]));
-                        ai[q] = fma(a[u].x, x.y, fma(a[u].y, x.x, ai[q]));
-                    }
-            }
-            for (; j < kc; ++j) {
-                const C a = col[(int64_t)j * it.m];
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
                 for (int q = 0; q < NR; ++q) {
-                    const C x = sw[j * NR + q];
-                    ar[q] = fma(a.x, x.x, fma(-a.y, x.y, ar[q]));
-                    ai[q] = fma(a.x, x.y, fma(a.y, x.x, ai[q]));
+                    const C v = x[(j + u) * NR + q];
+                    ar[q] = fma(a[u].x, v.x, fma(-a[u].y, v.y, ar[q]));
+                    ai[q] = fma(a[u].x, v.y, fma(a[u].y, v.x, ai[q]));
                 }
+        }
+    }
+#pragma unroll
+    for (int h = KW / 2; h >= 1; h /= 2) {
+        __syncthreads();
+        if (wave >= h && wave < 2 * h) {
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                C v;
+                v.x = ar[q];
+                v.y = ai[q];
+                sw[((wave - h) * NR + q) * 64 + lane] = v;
+            }
+        }
+        __syncthreads();
+        if (wave < h) {
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const C v = sw[(wave * NR + q) * 64 + lane];
+                ar[q] += v.x;
+                ai[q] += v.y;
             }
         }
     }
-    if (!row_ok) return;
+    if (wave > 0 || row >= mt.m) return;
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
-        if (c0 + q >= nrhs) break;
-        double2 *o = out + (int64_t)(c0 + q) * outN + it.out0 + i;
-        double2 v = accumulate ? *o : make_double2(0.0, 0.0);
+        if (q0 + q >= ncol) break;
+        const int b = (q0 + q) / nrhs, c = (q0 + q) - b * nrhs;
+        const int64_t o = (int64_t)c * outN + out0[mt.first + b] + row;
+        double2 v = add ? add[o] : make_double2(0.0, 0.0);
         v.x += alpha * (double)ar[q];
         v.y += alpha * (double)ai[q];
-        *o = v;
+        out[o] = v;
     }
 }
 
-template <typename R>
-static void launch_body_matvec(Ctx &c, const BodyMatItem *items, int nitems, const double2 *in, int64_t inN,
-                               int nrhs, double2 *out, int64_t outN, double alpha, bool accumulate) {
-    if (nitems == 0) return;
-    const int nr = nrhs >= 16 ? 16 : nrhs >= 8 ? 8 : nrhs >= 4 ? 4 : nrhs >= 2 ? 2 : 1;
-    const dim3 grid(nitems, ceil_div(nrhs, nr));
-    const int acc = accumulate ? 1 : 0;
-    switch (nr) {
-    case 16:
-        hipLaunchKernelGGL((body_matvec_kernel<R, 16>), grid, dim3(256), 0, c.stream, items, in, inN, nrhs, out, outN,
-                           alpha, acc);
-        break;
-    case 8:
-        hipLaunchKernelGGL((body_matvec_kernel<R, 8>), grid, dim3(256), 0, c.stream, items, in, inN, nrhs, out, outN,
-                           alpha, acc);
-        break;
-    case 4:
-        hipLaunchKernelGGL((body_matvec_kernel<R, 4>), grid, dim3(256), 0, c.stream, items, in, inN, nrhs, out, outN,
-                           alpha, acc);
-        break;
-    case 2:
-        hipLaunchKernelGGL((body_matvec_kernel<R, 2>), grid, dim3(256), 0, c.stream, items, in, inN, nrhs, out, outN,
-                           alpha, acc);
-        break;
-    default:
-        hipLaunchKernelGGL((body_matvec_kernel<R, 1>), grid, dim3(256), 0, c.stream, items, in, inN, nrhs, out, outN,
-                           alpha, acc);
+template <typename R, bool TRANS>
+static void launch_body_matvec(Ctx &c, const BodyMats &t, const double2 *in, int64_t inN, int nrhs, const double2 *add,
+                               double2 *out, int64_t outN, double alpha) {
+    if (t.nitems == 0) return;
+    // columns in equal groups of at most 16, and as many as give every CU a
+    // workgroup (88 slices, 15 columns: 61 us in 3 groups, 123 in one, 71 in 5, each
+    // reading the blocks again); four wavefronts per slice, eight where that leaves
+    // fewer than four workgroups a CU
+    const int64_t cols = (int64_t)t.max_bodies * nrhs;
+    const int64_t groups = std::max(ceil_div(cols, 16), std::min(cols, ceil_div((int64_t)256, (int64_t)t.nitems)));
+    const int width = (int)ceil_div(cols, groups);
+    const dim3 grid(t.nitems, (unsigned)groups);
+    const bool few = (int64_t)t.nitems * groups < 1024;
+#define AXS_BM(NR_)                                                                                              \
+    if (width <= NR_) {                                                                                          \
+        const dim3 g(t.nitems, (unsigned)ceil_div(cols, NR_));                                                   \
+        if (few)                                                                                                 \
+            hipLaunchKernelGGL((body_matvec_kernel<R, NR_, 8, TRANS>), g, dim3(512), 0, c.stream, t.items, t.mats, \
+                               t.in0, t.out0, in, inN, nrhs, add, out, outN, alpha);                             \
+        else                                                                                                     \
+            hipLaunchKernelGGL((body_matvec_kernel<R, NR_, 4, TRANS>), g, dim3(256), 0, c.stream, t.items, t.mats, \
+                               t.in0, t.out0, in, inN, nrhs, add, out, outN, alpha);                             \
+        AXS_HIP(hipGetLastError());                                                                              \
+        return;                                                                                                  \
     }
-    AXS_HIP(hipGetLastError());
+    AXS_BM(1)
+    AXS_BM(2)
+    AXS_BM(3)
+    AXS_BM(4)
+    AXS_BM(5)
+    AXS_BM(6)
+    AXS_BM(8)
+    AXS_BM(12)
+    AXS_BM(16)
+#undef AXS_BM
 }
 
-// work items for one product per body: blocks A32/A64 of m_b x K_b rows, in
-// 256-row slices
-static BodyMatItem *upload_items(Ctx &c, const std::vector<BodyMatItem> &bodies, int &count) {
-    std::vector<BodyMatItem> v;
-    for (const BodyMatItem &b : bodies)
-        for (int r0 = 0; r0 < b.m; r0 += 256) {
-            BodyMatItem t = b;
-            t.row0 = r0;
-            v.push_back(t);
-        }
-    count = (int)v.size();
-    if (v.empty()) return nullptr;
-    BodyMatItem *d = (BodyMatItem *)c.dalloc(v.size() * sizeof(BodyMatItem));
-    AXS_HIP(hipMemcpy(d, v.data(), v.size() * sizeof(BodyMatItem), hipMemcpyHostToDevice));
-    return d;
+static BodyMats upload_mats(Ctx &c, const std::vector<BodyMat> &blocks, const std::vector<int64_t> &in0,
+                            const std::vector<int64_t> &out0) {
+    BodyMats t;
+    std::vector<int2> items;
+    for (size_t k = 0; k < blocks.size(); ++k) {
+        t.max_bodies = std::max(t.max_bodies, blocks[k].count);
+        for (int r0 = 0; r0 < blocks[k].m; r0 += 64) items.push_back(make_int2((int)k, r0));
+    }
+    t.nitems = (int)items.size();
+    auto up = [&](const void *h, size_t bytes) {
+        void *d = c.dalloc(bytes);
+        AXS_HIP(hipMemcpy(d, h, bytes, hipMemcpyHostToDevice));
+        return d;
+    };
+    t.mats = (BodyMat *)up(blocks.data(), blocks.size() * sizeof(BodyMat));
+    t.in0 = (int64_t *)up(in0.data(), in0.size() * sizeof(int64_t));
+    t.out0 = (int64_t *)up(out0.data(), out0.size() * sizeof(int64_t));
+    t.items = (int2 *)up(items.data(), items.size() * sizeof(int2));
+    return t;
 }
 
+// child of point skeletons: y = s + S (B~ s), B~ in `prec`, S_p in the same precision
 void point_operator(Ctx &c, const void *sigma, void *y, int nrhs, int prec) {
     const PointSkel &P = *c.pop;
     const int64_t Ns = c.N, tot = Ns * nrhs;
     interbody_partials(c, sigma, nrhs, prec);
     double2 *w = (double2 *)c.scratch(WS_XR, tot * sizeof(double2));
     interbody_reduce_to_c128(c, w, nrhs, prec);
-    if (y != sigma) AXS_HIP(hipMemcpyAsync(y, sigma, tot * sizeof(double2), hipMemcpyDeviceToDevice, c.stream));
     if (prec == AXS_FP64)
-        launch_body_matvec<double>(c, P.sp_items, P.n_sp, w, Ns, nrhs, (double2 *)y, Ns, 1.0, true);
+        launch_body_matvec<double, false>(c, P.sp, w, Ns, nrhs, (const double2 *)sigma, (double2 *)y, Ns, 1.0);
     else
-        launch_body_matvec<float>(c, P.sp_items, P.n_sp, w, Ns, nrhs, (double2 *)y, Ns, 1.0, true);
+        launch_body_matvec<float, false>(c, P.sp, w, Ns, nrhs, (const double2 *)sigma, (double2 *)y, Ns, 1.0);
 }
 
 // out = alpha X^T y per body (full [nrhs][N] -> skeleton [nrhs][Ns])
 static void point_restrict(Ctx &c, const void *y, void *out, int nrhs, double alpha) {
-    const PointSkel &P = *c.skel->pts;
-    launch_body_matvec<double>(c, P.rs_items, P.n_rs, (const double2 *)y, c.N, nrhs, (double2 *)out, c.skel->Ns,
-                               alpha, false);
+    launch_body_matvec<double, false>(c, c.skel->pts->restrict_, (const double2 *)y, c.N, nrhs, nullptr, (double2 *)out,
+                                      c.skel->Ns, alpha);
 }
 
-// out = add + X w per body (skeleton -> full)
+// out = add + X w per body (skeleton -> full); X is stored as X^T (k x n, column-major)
 static void point_prolong(Ctx &c, const void *w, const void *add, void *out, int nrhs) {
-    const PointSkel &P = *c.skel->pts;
-    const int64_t N = c.N, Ns = c.skel->Ns;
-    if (add)
-        AXS_HIP(hipMemcpyAsync(out, add, (size_t)N * nrhs * sizeof(double2), hipMemcpyDeviceToDevice, c.stream));
-    else
-        AXS_HIP(hipMemsetAsync(out, 0, (size_t)N * nrhs * sizeof(double2), c.stream));
-    rocblas_handle h = blas_of(c);
-    const rocblas_double_complex one = {1.0, 0.0};
-    for (const PointRun &r : P.runs)
-        run_gemm(h, rocblas_zgemm_strided_batched, rocblas_operation_transpose, r.n, r.k, r.nb, nrhs, &one,
-                 zc(P.XT[r.shape]), r.k, zc((const double2 *)w + r.s0), r.k, Ns, &one, zc((double2 *)out + r.o0), r.n,
-                 N);
+    launch_body_matvec<double, true>(c, c.skel->pts->prolong, (const double2 *)w, c.skel->Ns, nrhs,
+                                     (const double2 *)add, (double2 *)out, c.N, 1.0);
 }
 
 }  // namespace axs
