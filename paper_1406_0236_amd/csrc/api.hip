@@ -62,8 +62,28 @@ void *Ctx::scratch(int slot, size_t bytes) {
     return b.ptr;
 }
 
+void *Ctx::pinned(size_t bytes) {
+    if (bytes > pin_bytes) {
+        if (pin) {
+            AXS_HIP(hipStreamSynchronize(stream));   // a kernel may still write to the old block
+            (void)hipHostFree(pin);
+            pin = nullptr;
+            pin_bytes = 0;
+        }
+        const size_t n = std::max<size_t>(2 * bytes, 16384);
+        const hipError_t e = hipHostMalloc(&pin, n, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            pin = nullptr;
+            throw Error{AXS_ENOMEM, std::string("hipHostMalloc failed: ") + hipGetErrorString(e)};
+        }
+        pin_bytes = n;
+    }
+    return pin;
+}
+
 Ctx::~Ctx() {
-    if (stream) (void)hipStreamSynchronize(stream);
+    if (stream || pin) (void)hipStreamSynchronize(stream);
+    if (pin) (void)hipHostFree(pin);
     skel.reset();   // the child context first (it borrows this context's tables)
     destroy_blas(*this);
     for (void *p : std::vector<void *>(owned)) dfree(p);
@@ -71,32 +91,25 @@ Ctx::~Ctx() {
         if (e) (void)hipEventDestroy(e);
 }
 
-// p[0..n) = value (a kernel, not a memset, so that graph-captured callers record no memset node)
-__global__ void fill_int_kernel(int *__restrict__ p, int n, int value) {
-    for (int t = threadIdx.x; t < n; t += blockDim.x) p[t] = value;
-}
-
-// flag = 1 if any component of v[0..n) is NaN or Inf (integer OR, order-free)
+// *flag = 1 if any component of v[0..n) is NaN or Inf
 __global__ void nonfinite_kernel(const double2 *__restrict__ v, int64_t n, int *__restrict__ flag) {
     int bad = 0;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
         const double2 a = v[t];
         bad |= !(isfinite(a.x) && isfinite(a.y));
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, 1);
+    if (__any(bad) && (threadIdx.x & 63) == 0) *flag = 1;   // every writer stores the same value
 }
 
 void require_finite(Ctx &c, const void *v, int64_t n, const char *what) {
-    int *flag = (int *)c.scratch(WS_FLAG, sizeof(int));
-    hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, c.stream, flag, 1, 0);
-    AXS_HIP(hipGetLastError());
+    // the flag is pinned host memory: no kernel to clear it and no copy back
+    volatile int *flag = (volatile int *)c.pinned(sizeof(int));
+    *flag = 0;
     const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>(2048, ceil_div(n, 256)));
-    hipLaunchKernelGGL(nonfinite_kernel, dim3(nblk), dim3(256), 0, c.stream, (const double2 *)v, n, flag);
+    hipLaunchKernelGGL(nonfinite_kernel, dim3(nblk), dim3(256), 0, c.stream, (const double2 *)v, n, (int *)flag);
     AXS_HIP(hipGetLastError());
-    int host = 0;
-    AXS_HIP(hipMemcpyAsync(&host, flag, sizeof(int), hipMemcpyDeviceToHost, c.stream));
     AXS_HIP(hipStreamSynchronize(c.stream));
-    AXS_REQUIRE(host == 0, AXS_ENONFINITE, std::string("non-finite value (NaN or Inf) in ") + what);
+    AXS_REQUIRE(*flag == 0, AXS_ENONFINITE, std::string("non-finite value (NaN or Inf) in ") + what);
 }
 
 // ---------------------------------------------------------------------------
@@ -310,7 +323,7 @@ struct ArenaScope {
         c.arena = (char *)base;
         c.arena_cap = cap;
         c.arena_top = 0;
-        for (int k = 0; k < 19; ++k) {
+        for (int k = 0; k < 18; ++k) {
             c.arena_slot[k] = nullptr;
             c.arena_slot_bytes[k] = 0;
         }

@@ -208,13 +208,19 @@ struct Ctx {
     // device allocations owned by the context
     std::vector<void *> owned;
     // named scratch buffers (grow-only)
-    Buffer ws[19];
+    Buffer ws[18];
     // while `arena` is set, scratch() hands out slices of that caller-supplied
     // region instead (one slice per slot, bump order) and allocates nothing
     char *arena = nullptr;
     size_t arena_cap = 0, arena_top = 0;
-    void *arena_slot[19] = {};
-    size_t arena_slot_bytes[19] = {};
+    void *arena_slot[18] = {};
+    size_t arena_slot_bytes[18] = {};
+
+    // pinned host memory that kernels write small results to (grow-only; the
+    // contents are good until the next call)
+    void *pin = nullptr;
+    size_t pin_bytes = 0;
+    void *pinned(size_t bytes);
 
     void *dalloc(size_t bytes);
     void dfree(void *p);
@@ -241,7 +247,6 @@ enum ScratchSlot {
     WS_EVAL = 15,
     WS_Q16 = 16,     // FP16 density planes of the FP16 multiply-accumulate
     WS_QMAX = 17,    // per-rhs max |q| (float bits), then the per-slice partial maxima
-    WS_FLAG = 18,    // one int: set when an input vector holds NaN or Inf
 };
 
 // Point skeletons: per shape k skeleton nodes of its n = NG NF nodes, the

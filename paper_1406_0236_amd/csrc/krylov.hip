@@ -22,76 +22,228 @@ namespace axs {
 using cd = std::complex<double>;
 constexpr int KR_BS = 256;
 
-// partial[c][blk][i] = sum_{n in blk} conj(V_i[c][n]) w[c][n]
-__global__ __launch_bounds__(KR_BS) void cdot_many_kernel(const double2 *__restrict__ V, int64_t ldv, int nvec,
-                                                          const double2 *__restrict__ w, int64_t N,
-                                                          double2 *__restrict__ partial) {
-    const int c = blockIdx.y, nblk = gridDim.x, blk = blockIdx.x;
-    const int64_t chunk = (N + nblk - 1) / nblk;
-    const int64_t n0 = (int64_t)blk * chunk, n1 = min(N, n0 + chunk);
-    __shared__ double sr[KR_BS / 64], si[KR_BS / 64];
-    for (int i = 0; i < nvec; ++i) {
-        const double2 *v = V + (int64_t)i * ldv + (int64_t)c * N;
-        const double2 *ww = w + (int64_t)c * N;
-        double re = 0, im = 0;
-        for (int64_t n = n0 + threadIdx.x; n < n1; n += KR_BS) {
-            const double2 a = v[n], b = ww[n];
-            re += a.x * b.x + a.y * b.y;
-            im += a.x * b.y - a.y * b.x;
-        }
+// ---------------------------------------------------------------------------
+// Gram-Schmidt kernels.  Bound: reading the basis (16 bytes an entry and pass) in
+// large systems, launches and the latency of the reductions in small ones.  One
+// Arnoldi step (classical Gram-Schmidt twice) is four launches and three passes
+// over the basis:
+//   dots_kernel             h  = V^H w, partial sums per tile of w
+//   update_kernel<DOTS>     w -= V h  and, tile by tile, partial sums of V^H w
+//   update_kernel<NORM>     w -= V h' and partial sums of |w|^2
+//   normalize_kernel        w /= |w|
+// each adding up the partial sums of the one before it for itself, in a fixed
+// order.  A workgroup holds a tile of KR_BS x E entries of w in registers; E is 8, or
+// as small as it takes to make 512 workgroups.  The coefficients and the norm go
+// straight to pinned host memory.  (Separate dot, reduction, update and scaling
+// kernels were nine launches and four passes.  7 steps for one rhs on 8,200 nodes: 365 us
+// of kernels before, 139 now; a mixed solve of 64 rhs on 18,860 nodes to 1e-10:
+// 5.9 ms before, 3.7 now, at 4 TB/s in the dot products.)
+// ---------------------------------------------------------------------------
+struct KrTile {
+    int64_t n0;   // first entry of the thread; entries n0 + e KR_BS
+    int64_t N;
+    __device__ __forceinline__ bool in(int e) const { return n0 + (int64_t)e * KR_BS < N; }
+    __device__ __forceinline__ int64_t at(int e) const { return n0 + (int64_t)e * KR_BS; }
+};
+
+__device__ __forceinline__ double2 wave_sum2(double re, double im) {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            re += __shfl_xor(re, o, 64);
-            im += __shfl_xor(im, o, 64);
+    for (int o = 32; o > 0; o >>= 1) {
+        re += __shfl_xor(re, o, 64);
+        im += __shfl_xor(im, o, 64);
+    }
+    return make_double2(re, im);
+}
+
+// partial[(c nblk + blk) nvec + i] = sum over the tile of conj(V_i) w, i in [i0, i1)
+template <int E>
+__device__ __forceinline__ void tile_dots(const double2 *__restrict__ V, int64_t ldv, int i0, int i1, int nvec,
+                                          const double2 (&w)[E], const KrTile &t, double2 *__restrict__ partial) {
+    __shared__ double2 s_dot[64][KR_BS / 64];
+    const int wave = threadIdx.x >> 6;
+    for (int b0 = i0; b0 < i1; b0 += 64) {
+        const int cnt = min(64, i1 - b0);
+        __syncthreads();
+#pragma unroll 2
+        for (int i = 0; i < cnt; ++i) {
+            const double2 *v = V + (int64_t)(b0 + i) * ldv;
+            double re = 0, im = 0;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const double2 a = t.in(e) ? v[t.at(e)] : make_double2(0.0, 0.0);
+                re = fma(a.x, w[e].x, fma(a.y, w[e].y, re));
+                im = fma(a.x, w[e].y, fma(-a.y, w[e].x, im));
+            }
+            const double2 s = wave_sum2(re, im);
+            if ((threadIdx.x & 63) == 0) s_dot[i][wave] = s;
         }
-        if ((threadIdx.x & 63) == 0) {
-            sr[threadIdx.x >> 6] = re;
-            si[threadIdx.x >> 6] = im;
+        __syncthreads();
+        if ((int)threadIdx.x < cnt) {
+            double2 s = s_dot[threadIdx.x][0];
+#pragma unroll
+            for (int k = 1; k < KR_BS / 64; ++k) {
+                s.x += s_dot[threadIdx.x][k].x;
+                s.y += s_dot[threadIdx.x][k].y;
+            }
+            partial[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * nvec + b0 + threadIdx.x] = s;
         }
+    }
+}
+
+// vectors whose coefficients a workgroup holds in LDS at a time, and most of an
+// augmentation (a run of 60 steps, plus one)
+constexpr int KR_CH = 32, KR_AUG = 64;
+
+// h[i] = sum_b partial[(c nin + b) nvec + i0 + i], i < cnt, in a fixed
+// order: up to 16 threads a coefficient, each every so many-th tile, then those
+__device__ __forceinline__ void gather_coef(const double2 *__restrict__ partial, int nin, int nvec, int i0, int cnt,
+                                            double2 *h) {
+    __shared__ double2 s_part[KR_BS];
+    const double2 *p = partial + (int64_t)blockIdx.y * nin * nvec + i0;
+    const int slices = max(1, min(min(16, nin), KR_BS / cnt));
+    const int i = slices == 1 ? threadIdx.x : threadIdx.x % cnt, sl = slices == 1 ? 0 : threadIdx.x / cnt;
+    for (int b0 = 0; b0 < cnt; b0 += KR_BS) {
+        double2 s = make_double2(0.0, 0.0);
+        if (b0 + i < cnt && sl < slices)
+            for (int b = sl; b < nin; b += slices) {
+                const double2 v = p[(int64_t)b * nvec + b0 + i];
+                s.x += v.x;
+                s.y += v.y;
+            }
+        s_part[threadIdx.x] = s;
+        __syncthreads();
+        if (sl == 0 && b0 + i < cnt) {
+            for (int k = 1; k < slices; ++k) {
+                s.x += s_part[k * cnt + i].x;
+                s.y += s_part[k * cnt + i].y;
+            }
+            h[b0 + i] = s;
+        }
+        __syncthreads();
+    }
+}
+
+template <int E>
+__global__ __launch_bounds__(KR_BS) void dots_kernel(const double2 *__restrict__ V, int64_t ldv, int nvec, int vb,
+                                                     const double2 *__restrict__ w, int64_t N,
+                                                     double2 *__restrict__ partial) {
+    const KrTile t{(int64_t)blockIdx.x * KR_BS * E + threadIdx.x, N};
+    const int64_t c0 = (int64_t)blockIdx.y * N;
+    double2 x[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = t.in(e) ? w[c0 + t.at(e)] : make_double2(0.0, 0.0);
+    const int i0 = blockIdx.z * vb;
+    tile_dots<E>(V + c0, ldv, i0, min(nvec, i0 + vb), nvec, x, t, partial);
+}
+
+// h_out = the summed coefficients, `vb` of them a workgroup and rhs
+__global__ __launch_bounds__(KR_BS) void coef_kernel(const double2 *__restrict__ partial, int nin, int nvec, int vb,
+                                                     double2 *__restrict__ h_out) {
+    __shared__ double2 h[KR_CH];
+    const int i0 = blockIdx.x * vb, cnt = min(vb, nvec - i0);
+    gather_coef(partial, nin, nvec, i0, cnt, h);
+    if ((int)threadIdx.x < cnt) h_out[(int64_t)blockIdx.y * nvec + i0 + threadIdx.x] = h[threadIdx.x];
+}
+
+// h_out = the summed coefficients and p = M h (M: nvec x nvec per rhs, row-major),
+// one workgroup per rhs; nvec <= KR_AUG
+__global__ __launch_bounds__(KR_BS) void coef_product_kernel(const double2 *__restrict__ partial, int nin, int nvec,
+                                                             const double2 *__restrict__ M, double2 *__restrict__ p,
+                                                             double2 *__restrict__ h_out) {
+    __shared__ double2 h[KR_AUG];
+    gather_coef(partial, nin, nvec, 0, nvec, h);
+    const int c = blockIdx.y;
+    for (int i = threadIdx.x; i < nvec; i += KR_BS) {
+        h_out[(int64_t)c * nvec + i] = h[i];
+        const double2 *m = M + ((int64_t)c * nvec + i) * nvec;
+        double re = 0, im = 0;
+        for (int l = 0; l < nvec; ++l) {
+            re += m[l].x * h[l].x - m[l].y * h[l].y;
+            im += m[l].x * h[l].y + m[l].y * h[l].x;
+        }
+        p[(int64_t)c * nvec + i] = make_double2(re, im);
+    }
+}
+
+// w += sign V h with h the sum of `nin` partial coefficients per vector (1: h
+// itself), written to h_out where that is given; then per tile with MODE DOTS the
+// partial sums of V^H w, with NORM those of |w|^2
+enum KrMode { KR_PLAIN = 0, KR_DOTS = 1, KR_NORM = 2 };
+template <int E, int MODE>
+__global__ __launch_bounds__(KR_BS) void update_kernel(const double2 *__restrict__ V, int64_t ldv, int nvec,
+                                                       const double2 *__restrict__ coef, int nin, double sign,
+                                                       double2 *__restrict__ w, int64_t N,
+                                                       double2 *__restrict__ h_out, double2 *__restrict__ partial) {
+    __shared__ double2 h[KR_CH];
+    const KrTile t{(int64_t)blockIdx.x * KR_BS * E + threadIdx.x, N};
+    const int64_t c0 = (int64_t)blockIdx.y * N;
+    V += c0;
+    w += c0;
+    double2 x[E], s[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        x[e] = t.in(e) ? w[t.at(e)] : make_double2(0.0, 0.0);
+        s[e] = make_double2(0.0, 0.0);
+    }
+    for (int i0 = 0; i0 < nvec; i0 += KR_CH) {
+        const int cnt = min(KR_CH, nvec - i0);
+        if (i0 > 0) __syncthreads();   // the last chunk's coefficients have been used
+        gather_coef(coef, nin, nvec, i0, cnt, h);
+        if (h_out && blockIdx.x == 0)
+            for (int i = threadIdx.x; i < cnt; i += KR_BS) h_out[(int64_t)blockIdx.y * nvec + i0 + i] = h[i];
+#pragma unroll 2
+        for (int i = 0; i < cnt; ++i) {
+            const double2 *v = V + (int64_t)(i0 + i) * ldv;
+            const double2 f = h[i];
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const double2 a = t.in(e) ? v[t.at(e)] : make_double2(0.0, 0.0);
+                s[e].x = fma(a.x, f.x, fma(-a.y, f.y, s[e].x));
+                s[e].y = fma(a.x, f.y, fma(a.y, f.x, s[e].y));
+            }
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        x[e].x += sign * s[e].x;
+        x[e].y += sign * s[e].y;
+        if (t.in(e)) w[t.at(e)] = x[e];
+    }
+    if constexpr (MODE == KR_DOTS) tile_dots<E>(V, ldv, 0, nvec, nvec, x, t, partial);
+    if constexpr (MODE == KR_NORM) {
+        __shared__ double s_nrm[KR_BS / 64];
+        double r = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) r = fma(x[e].x, x[e].x, fma(x[e].y, x[e].y, r));
+        const double2 q = wave_sum2(r, 0.0);
+        if ((threadIdx.x & 63) == 0) s_nrm[threadIdx.x >> 6] = q.x;
         __syncthreads();
         if (threadIdx.x == 0) {
-            double tr = 0, ti = 0;
-            for (int k = 0; k < KR_BS / 64; ++k) {
-                tr += sr[k];
-                ti += si[k];
-            }
-            partial[((int64_t)c * nblk + blk) * nvec + i] = make_double2(tr, ti);
+            double a = s_nrm[0];
+#pragma unroll
+            for (int k = 1; k < KR_BS / 64; ++k) a += s_nrm[k];
+            partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = make_double2(a, 0.0);
         }
-        __syncthreads();
     }
 }
 
-__global__ void reduce_dots_kernel(const double2 *__restrict__ partial, int nblk, int nvec, int nrhs,
-                                   double2 *__restrict__ out) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nvec * nrhs) return;
-    const int c = t / nvec, i = t % nvec;
-    double re = 0, im = 0;
-    for (int b = 0; b < nblk; ++b) {
-        const double2 v = partial[((int64_t)c * nblk + b) * nvec + i];
-        re += v.x;
-        im += v.y;
-    }
-    out[t] = make_double2(re, im);
-}
-
-// w[c][n] += sign * sum_i V_i[c][n] h[c][i]
-__global__ void caxpy_many_kernel(const double2 *__restrict__ V, int64_t ldv, int nvec,
-                                  const double2 *__restrict__ h, double sign, double2 *__restrict__ w,
-                                  int64_t N, int nrhs) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N * nrhs) return;
-    const int c = (int)(t / N);
-    double re = 0, im = 0;
-    for (int i = 0; i < nvec; ++i) {
-        const double2 v = V[(int64_t)i * ldv + t], hh = h[c * nvec + i];
-        re += v.x * hh.x - v.y * hh.y;
-        im += v.x * hh.y + v.y * hh.x;
-    }
-    double2 o = w[t];
-    o.x += sign * re;
-    o.y += sign * im;
-    w[t] = o;
+// w /= |w|, or 0 where that norm is 0 (the new Arnoldi vector); |w|^2 to n_out
+template <int E>
+__global__ __launch_bounds__(KR_BS) void normalize_kernel(double2 *__restrict__ w, const double2 *__restrict__ partial,
+                                                          int nin, int64_t N, double2 *__restrict__ n_out) {
+    __shared__ double2 h[KR_CH];
+    gather_coef(partial, nin, 1, 0, 1, h);
+    const double n2 = h[0].x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) n_out[blockIdx.y] = make_double2(n2, 0.0);
+    const double f = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
+    const KrTile t{(int64_t)blockIdx.x * KR_BS * E + threadIdx.x, N};
+    w += (int64_t)blockIdx.y * N;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (t.in(e)) {
+            const double2 v = w[t.at(e)];
+            w[t.at(e)] = make_double2(v.x * f, v.y * f);
+        }
 }
 
 // out[c][n] = in[c][n] * s[c]  (s real)
@@ -117,38 +269,12 @@ __global__ void cadd_scaled_kernel(const double2 *__restrict__ a, const double *
     out[t] = o;
 }
 
-// w[c][n] /= sqrt(nrm[c].x), or 0 where that norm is 0 (the new Arnoldi vector)
-__global__ void cnormalize_kernel(double2 *__restrict__ w, const double2 *__restrict__ nrm, int64_t N, int nrhs) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N * nrhs) return;
-    const double n2 = nrm[t / N].x;
-    const double f = n2 > 0.0 ? 1.0 / sqrt(n2) : 0.0;
-    const double2 v = w[t];
-    w[t] = make_double2(v.x * f, v.y * f);
-}
-
 // out = a - b
 __global__ void csub_kernel(const double2 *__restrict__ a, const double2 *__restrict__ b, double2 *__restrict__ out,
                             int64_t n) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
     out[t] = make_double2(a[t].x - b[t].x, a[t].y - b[t].y);
-}
-
-// p[c][i] = sum_l M[c][i][l] a[c][l]  (K x K per right-hand side, row-major)
-__global__ void cmatvec_small_kernel(const double2 *__restrict__ M, const double2 *__restrict__ a, int K, int nrhs,
-                                     double2 *__restrict__ p) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= K * nrhs) return;
-    const int c = t / K, i = t % K;
-    const double2 *m = M + ((int64_t)c * K + i) * K;
-    const double2 *x = a + (int64_t)c * K;
-    double re = 0, im = 0;
-    for (int l = 0; l < K; ++l) {
-        re += m[l].x * x[l].x - m[l].y * x[l].y;
-        im += m[l].x * x[l].y + m[l].y * x[l].x;
-    }
-    p[t] = make_double2(re, im);
 }
 
 // ---------------------------------------------------------------------------
@@ -158,65 +284,131 @@ __global__ void cmatvec_small_kernel(const double2 *__restrict__ M, const double
 // checks below see them), a tiny negative rounding becomes 0
 static double norm_from_sq(double s) { return std::isfinite(s) ? std::sqrt(std::max(0.0, s)) : NAN; }
 
-struct Dots {
+// Gram-Schmidt over nrhs vectors of N entries: the tile size, the partial sums'
+// buffers and the launches
+struct Ortho {
     Ctx &c;
     int64_t N;
-    int nrhs;
-    int nblk;
+    int nrhs, E, nblk;
     int cap = 0;                 // vectors per rhs the buffers hold (grown on demand)
-    double2 *partial = nullptr, *dev = nullptr;
-    std::vector<double2> host;
-    Dots(Ctx &c_, int64_t N_, int nrhs_, int maxvec) : c(c_), N(N_), nrhs(nrhs_) {
-        nblk = (int)std::min<int64_t>(512, std::max<int64_t>(1, ceil_div(N, 4096)));
+    double2 *pa = nullptr, *pb = nullptr;   // partial sums [nrhs][nblk][vectors], and [nrhs] [vectors] sums behind
+    Ortho(Ctx &c_, int64_t N_, int nrhs_, int maxvec) : c(c_), N(N_), nrhs(nrhs_) {
+        E = 8;
+        while (E > 1 && ceil_div(N, (int64_t)KR_BS * E) * nrhs < 512) E /= 2;
+        nblk = (int)ceil_div(N, (int64_t)KR_BS * E);
         reserve(std::min(maxvec, 16));
     }
-    ~Dots() {
-        c.dfree(partial);
-        c.dfree(dev);
+    Ortho(const Ortho &) = delete;
+    Ortho &operator=(const Ortho &) = delete;
+    ~Ortho() {
+        c.dfree(pa);
+        c.dfree(pb);
     }
     // room for nvec coefficients per rhs; the old buffers are released in
     // stream order (their last readers were queued on c.stream before)
     void reserve(int nvec) {
         if (nvec <= cap) return;
         const int nc = std::max(nvec, 2 * cap);
-        c.dfree(partial);
-        c.dfree(dev);
-        partial = nullptr;
-        dev = nullptr;
-        partial = (double2 *)c.dalloc((size_t)nrhs * nblk * nc * sizeof(double2));
-        dev = (double2 *)c.dalloc((size_t)nrhs * nc * sizeof(double2));
+        c.dfree(pa);
+        c.dfree(pb);
+        pa = pb = nullptr;
+        pa = (double2 *)c.dalloc((size_t)nrhs * (nblk + 1) * nc * sizeof(double2));
+        pb = (double2 *)c.dalloc((size_t)nrhs * (nblk + 1) * nc * sizeof(double2));
         cap = nc;
     }
-    // out[c][i] = V_i^H w on the device (stream-ordered, no host copy)
-    void launch(const double2 *V, int64_t ldv, int nvec, const double2 *w, double2 *out) {
-        reserve(nvec);
-        hipLaunchKernelGGL(cdot_many_kernel, dim3(nblk, nrhs), dim3(KR_BS), 0, c.stream, V, ldv, nvec, w, N,
-                           partial);
-        AXS_HIP(hipGetLastError());
-        hipLaunchKernelGGL(reduce_dots_kernel, dim3(ceil_div(nvec * nrhs, 128)), dim3(128), 0, c.stream, partial,
-                           nblk, nvec, nrhs, out);
+    dim3 grid(int z = 1) const { return dim3(nblk, nrhs, z); }
+#define AXS_KR_E(call)             \
+    do {                           \
+        if (E == 8) { constexpr int E_ = 8; call; }        \
+        else if (E == 4) { constexpr int E_ = 4; call; }   \
+        else if (E == 2) { constexpr int E_ = 2; call; }   \
+        else { constexpr int E_ = 1; call; }               \
+        AXS_HIP(hipGetLastError()); \
+    } while (0)
+    // partial sums of V^H w into `part`
+    void dots(const double2 *V, int64_t ldv, int nvec, const double2 *w, double2 *part) {
+        // few tiles: several workgroups share one, each a part of the vectors
+        const int z = std::max(1, std::min(nvec, 512 / (nblk * nrhs)));
+        const int vb = (int)ceil_div(nvec, z);
+        AXS_KR_E(hipLaunchKernelGGL((dots_kernel<E_>), grid((int)ceil_div(nvec, vb)), dim3(KR_BS), 0, c.stream, V, ldv,
+                                    nvec, vb, w, N, part));
+    }
+    // the coefficients [nrhs][nvec] of `part` into out, 16 a workgroup
+    void coefs(const double2 *part, int nvec, double2 *out) {
+        hipLaunchKernelGGL(coef_kernel, dim3(ceil_div(nvec, 16), nrhs), dim3(KR_BS), 0, c.stream, part, nblk, nvec, 16,
+                           out);
         AXS_HIP(hipGetLastError());
     }
-    // h[c][i] = V_i^H w (device + host copies)
-    void run(const double2 *V, int64_t ldv, int nvec, const double2 *w) {
+    // the partial sums of `part` as update_kernel and normalize_kernel take them:
+    // summed first (into its tail) where every workgroup would otherwise add up
+    // more than 128 of them
+    const double2 *summed(double2 *part, int nvec, int &nin) {
+        nin = nblk;
+        if (nblk <= 128) return part;
+        double2 *sum = part + (size_t)nrhs * nblk * cap;
+        coefs(part, nvec, sum);
+        nin = 1;
+        return sum;
+    }
+    // w += sign V h, h the summed partial coefficients (or [nrhs][nvec] with nin = 1)
+    template <int MODE>
+    void update(const double2 *V, int64_t ldv, int nvec, const double2 *coef, int nin, double sign, double2 *w,
+                double2 *h_out, double2 *part) {
+        AXS_KR_E(hipLaunchKernelGGL((update_kernel<E_, MODE>), grid(), dim3(KR_BS), 0, c.stream, V, ldv, nvec, coef, nin,
+                                    sign, w, N, h_out, part));
+    }
+    // one Arnoldi step: w against V[0, nvec) twice, its norm, normalised; h0, h1
+    // [nrhs][nvec] and n2 [nrhs] are host-visible.  before(pass): work ahead of
+    // each pass that changes w (the second pass's dots are then taken apart)
+    template <class F>
+    void step(const double2 *V, int64_t ldv, int nvec, double2 *w, double2 *h0, double2 *h1, double2 *n2, bool apart,
+              F before) {
         reserve(nvec);
-        launch(V, ldv, nvec, w, dev);
-        host.resize((size_t)nrhs * nvec);
-        AXS_HIP(hipMemcpyAsync(host.data(), dev, (size_t)nvec * nrhs * sizeof(double2), hipMemcpyDeviceToHost,
-                               c.stream));
+        int nin = 0;
+        before(0);
+        dots(V, ldv, nvec, w, pa);
+        const double2 *h = summed(pa, nvec, nin);
+        if (apart) {
+            update<KR_PLAIN>(V, ldv, nvec, h, nin, -1.0, w, h0, nullptr);
+            before(1);
+            dots(V, ldv, nvec, w, pb);
+        } else {
+            update<KR_DOTS>(V, ldv, nvec, h, nin, -1.0, w, h0, pb);
+        }
+        h = summed(pb, nvec, nin);
+        update<KR_NORM>(V, ldv, nvec, h, nin, -1.0, w, h1, pa);
+        h = summed(pa, 1, nin);
+        AXS_KR_E(hipLaunchKernelGGL((normalize_kernel<E_>), grid(), dim3(KR_BS), 0, c.stream, w, h, nin, N, n2));
+    }
+    // acoef = V^H w ([nrhs][nvec]) and w -= V (M acoef); p: [nrhs][nvec] scratch
+    void project_out(const double2 *V, int64_t ldv, int nvec, const double2 *M, double2 *p, double2 *w, double2 *acoef) {
+        AXS_REQUIRE(nvec <= KR_AUG, AXS_EINVAL, "augmentation beyond its limit");
+        reserve(nvec);
+        dots(V, ldv, nvec, w, pa);
+        hipLaunchKernelGGL(coef_product_kernel, dim3(1, nrhs), dim3(KR_BS), 0, c.stream, pa, nblk, nvec, M, p, acoef);
+        AXS_HIP(hipGetLastError());
+        update<KR_PLAIN>(V, ldv, nvec, p, 1, -1.0, w, nullptr, nullptr);
+    }
+    // |v|^2 per rhs, on the host
+    std::vector<double> sumsq(const double2 *v) {
+        double2 *out = (double2 *)c.pinned(nrhs * sizeof(double2));
+        dots(v, 0, 1, v, pa);
+        coefs(pa, 1, out);
         AXS_HIP(hipStreamSynchronize(c.stream));
+        std::vector<double> r(nrhs);
+        for (int k = 0; k < nrhs; ++k) r[k] = out[k].x;
+        return r;
     }
-    cd get(int c_, int i, int nvec) const { return cd(host[c_ * nvec + i].x, host[c_ * nvec + i].y); }
+#undef AXS_KR_E
 };
 
-static void axpy_many(Ctx &c, const double2 *V, int64_t ldv, int nvec, const std::vector<cd> &h, int nrhs,
-                      double sign, double2 *w, int64_t N, double2 *hdev) {
+// w += sign V h for host coefficients h[nrhs][nvec]
+static void axpy_many(Ctx &c, Ortho &O, const double2 *V, int64_t ldv, int nvec, const std::vector<cd> &h, double sign,
+                      double2 *w, double2 *hdev) {
     std::vector<double2> hh(h.size());
     for (size_t k = 0; k < h.size(); ++k) hh[k] = make_double2(h[k].real(), h[k].imag());
     AXS_HIP(hipMemcpyAsync(hdev, hh.data(), hh.size() * sizeof(double2), hipMemcpyHostToDevice, c.stream));
-    hipLaunchKernelGGL(caxpy_many_kernel, dim3(ceil_div(N * nrhs, 256)), dim3(256), 0, c.stream, V, ldv, nvec,
-                       hdev, sign, w, N, nrhs);
-    AXS_HIP(hipGetLastError());
+    O.update<KR_PLAIN>(V, ldv, nvec, hdev, 1, sign, w, nullptr, nullptr);
     AXS_HIP(hipStreamSynchronize(c.stream));   // hh is pageable host memory
 }
 
@@ -381,35 +573,24 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
     const int64_t ldv = N * nrhs;
     Gmres G(nrhs, maxit);
     G.bnorm = bnorm;
-    Dots D(c, N, nrhs, maxit + 1);
+    Ortho O(c, N, nrhs, maxit + 1);
     double *sdev = (double *)c.dalloc(nrhs * sizeof(double));
-    // per Arnoldi step: both Gram-Schmidt passes' coefficients [nrhs][j+1] and
-    // the squared norm of the new vector [nrhs], read back in one copy; the
-    // device buffer grows with the step (doubling), like the host copy
-    double2 *cdev = nullptr;
-    int64_t cdev_cap = 0;
-    std::vector<double2> chost;
+    // per Arnoldi step: both Gram-Schmidt passes' coefficients [nrhs][j+1] and the
+    // squared norm of the new vector [nrhs], written by the kernels to pinned host memory
     if (rec) {
         rec->H.assign(nrhs, {});
         rec->breakdown.assign(nrhs, 0);
         rec->steps = 0;
     }
     // augmentation: coefficients against the earlier basis, two passes [2][nrhs][K]
+    // (pinned host memory behind the step's)
     const int K = rc ? rc->k + 1 : 0;
-    std::unique_ptr<Dots> DR;
-    double2 *adev = nullptr, *pdev = nullptr;
-    std::vector<double2> ahost;
+    double2 *pdev = nullptr;
     std::vector<std::vector<cd>> Bm;   // per rhs: B = C^H A V_j, k x maxit column-major
     std::vector<std::vector<cd>> cr0;  // per rhs: C^H r0
     auto project_out = [&](double2 *w, double2 *acoef) {
         // w -= C C^H w = V_rc (Q Q^H) (V_rc^H w); acoef receives V_rc^H w
-        DR->launch(rc->V, ldv, K, w, acoef);
-        hipLaunchKernelGGL(cmatvec_small_kernel, dim3(ceil_div(K * nrhs, 128)), dim3(128), 0, c.stream, rc->M,
-                           acoef, K, nrhs, pdev);
-        AXS_HIP(hipGetLastError());
-        hipLaunchKernelGGL(caxpy_many_kernel, dim3(ceil_div(N * nrhs, 256)), dim3(256), 0, c.stream, rc->V, ldv, K,
-                           pdev, -1.0, w, N, nrhs);
-        AXS_HIP(hipGetLastError());
+        O.project_out(rc->V, ldv, K, rc->M, pdev, w, acoef);
     };
     // C^H w from the two passes' V_rc^H w
     auto qh = [&](int cc, const double2 *a0, const double2 *a1) {
@@ -428,34 +609,29 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
     };
     const double2 *start = r0;
     if (rc) {
-        DR.reset(new Dots(c, N, nrhs, K));
-        adev = (double2 *)c.dalloc((size_t)2 * nrhs * K * sizeof(double2));
         pdev = (double2 *)c.dalloc((size_t)nrhs * K * sizeof(double2));
-        ahost.resize((size_t)2 * nrhs * K);
         Bm.assign(nrhs, std::vector<cd>((size_t)rc->k * maxit, 0.0));
         // start vector: r0 less its component in range(C), twice
         V.reserve(2, 0);
+        double2 *ahost = (double2 *)c.pinned((size_t)2 * nrhs * K * sizeof(double2));
         AXS_HIP(hipMemcpyAsync(V.vec(0), r0, (size_t)ldv * sizeof(double2), hipMemcpyDeviceToDevice, c.stream));
-        for (int pass = 0; pass < 2; ++pass) project_out(V.vec(0), adev + (size_t)pass * nrhs * K);
-        AXS_HIP(hipMemcpyAsync(ahost.data(), adev, ahost.size() * sizeof(double2), hipMemcpyDeviceToHost, c.stream));
+        for (int pass = 0; pass < 2; ++pass) project_out(V.vec(0), ahost + (size_t)pass * nrhs * K);
         AXS_HIP(hipStreamSynchronize(c.stream));
         cr0.resize(nrhs);
-        for (int cc = 0; cc < nrhs; ++cc) cr0[cc] = qh(cc, ahost.data(), ahost.data() + (size_t)nrhs * K);
+        for (int cc = 0; cc < nrhs; ++cc) cr0[cc] = qh(cc, ahost, ahost + (size_t)nrhs * K);
         start = V.vec(0);
     }
     auto release = [&]() {
         c.dfree(sdev);
-        c.dfree(cdev);
-        c.dfree(adev);
         c.dfree(pdev);
     };
     // beta = ||r0|| (of the projected start vector with rc)
-    D.run(start, ldv, 1, start);
+    const std::vector<double> beta2 = O.sumsq(start);
     std::vector<double> beta(nrhs), inv(nrhs);
     rel_est.assign(nrhs, 0.0);
     bool all_done = true;
     for (int cc = 0; cc < nrhs; ++cc) {
-        beta[cc] = norm_from_sq(D.get(cc, 0, 1).real());
+        beta[cc] = norm_from_sq(beta2[cc]);
         AXS_REQUIRE(std::isfinite(beta[cc]), AXS_ENONFINITE, "non-finite residual");
         G.g[cc][0] = beta[cc];
         inv[cc] = beta[cc] > 0 ? 1.0 / beta[cc] : 0.0;
@@ -482,36 +658,15 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
             }
             // classical Gram-Schmidt, twice (against range(C) first with rc), then
             // the norm and the normalisation of the new vector, all stream-ordered
-            // on the device; the coefficients come to the host in one copy, the
-            // only synchronisation of the step
+            // on the device; one synchronisation per step
             const int nv = j + 1;
             const int64_t nh = (int64_t)nrhs * nv;
-            if (2 * nh + nrhs > cdev_cap) {
-                const int64_t cap = std::max<int64_t>(2 * nh + nrhs, 2 * cdev_cap);
-                c.dfree(cdev);
-                cdev = nullptr;
-                cdev = (double2 *)c.dalloc((size_t)cap * sizeof(double2));
-                cdev_cap = cap;
-            }
-            chost.resize((size_t)(2 * nh + nrhs));
+            double2 *chost = (double2 *)c.pinned((size_t)(2 * nh + nrhs + 2 * (int64_t)nrhs * K) * sizeof(double2));
+            double2 *ahost = chost + 2 * nh + nrhs;
             G.open_column(j);
-            for (int pass = 0; pass < 2; ++pass) {
-                if (rc) project_out(w, adev + (size_t)pass * nrhs * K);
-                double2 *hc = cdev + pass * nh;
-                D.launch(V.p, ldv, nv, w, hc);
-                hipLaunchKernelGGL(caxpy_many_kernel, dim3(ceil_div(N * nrhs, 256)), dim3(256), 0, c.stream, V.p,
-                                   ldv, nv, hc, -1.0, w, N, nrhs);
-                AXS_HIP(hipGetLastError());
-            }
-            D.launch(w, ldv, 1, w, cdev + 2 * nh);
-            hipLaunchKernelGGL(cnormalize_kernel, dim3(ceil_div(N * nrhs, 256)), dim3(256), 0, c.stream, w,
-                               cdev + 2 * nh, N, nrhs);
-            AXS_HIP(hipGetLastError());
-            AXS_HIP(hipMemcpyAsync(chost.data(), cdev, (size_t)(2 * nh + nrhs) * sizeof(double2),
-                                   hipMemcpyDeviceToHost, c.stream));
-            if (rc)
-                AXS_HIP(hipMemcpyAsync(ahost.data(), adev, ahost.size() * sizeof(double2), hipMemcpyDeviceToHost,
-                                       c.stream));
+            O.step(V.p, ldv, nv, w, chost, chost + nh, chost + 2 * nh, rc != nullptr, [&](int pass) {
+                if (rc) project_out(w, ahost + (size_t)pass * nrhs * K);
+            });
             AXS_HIP(hipStreamSynchronize(c.stream));
             all_done = true;
             for (int cc = 0; cc < nrhs; ++cc) {
@@ -528,7 +683,7 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
                     if (hn == 0.0) rec->breakdown[cc] = 1;
                 }
                 if (rc) {
-                    const std::vector<cd> bcol = qh(cc, ahost.data(), ahost.data() + (size_t)nrhs * K);
+                    const std::vector<cd> bcol = qh(cc, ahost, ahost + (size_t)nrhs * K);
                     for (int i = 0; i < rc->k; ++i) Bm[cc][(size_t)j * rc->k + i] = bcol[i];
                 }
                 if (G.done_at[cc] < 0) {
@@ -566,7 +721,7 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
         for (int cc = 0; cc < nrhs; ++cc)
             for (int i = 0; i < iters[cc]; ++i) y[(size_t)cc * kmax + i] = ys[cc][i];
         double2 *ydev = (double2 *)c.dalloc(y.size() * sizeof(double2));
-        axpy_many(c, basis, ldv, kmax, y, nrhs, 1.0, x, N, ydev);
+        axpy_many(c, O, basis, ldv, kmax, y, 1.0, x, ydev);
         c.dfree(ydev);
     }
     if (rc) {
@@ -586,7 +741,7 @@ static std::vector<int> gmres_core(Ctx &c, int64_t N, int nrhs, int maxit, doubl
             }
         }
         double2 *ddev = (double2 *)c.dalloc(d.size() * sizeof(double2));
-        axpy_many(c, rc->V, ldv, k, d, nrhs, 1.0, x, N, ddev);
+        axpy_many(c, O, rc->V, ldv, k, d, 1.0, x, ddev);
         c.dfree(ddev);
     }
     release();
@@ -641,10 +796,9 @@ static void build_recycle(Ctx &c, const ArnoldiRecord &rec, int maxit, const dou
 }
 
 static std::vector<double> norms(Ctx &c, const double2 *v, int64_t N, int nrhs) {
-    Dots D(c, N, nrhs, 1);
-    D.run(v, N * nrhs, 1, v);
-    std::vector<double> out(nrhs);
-    for (int cc = 0; cc < nrhs; ++cc) out[cc] = norm_from_sq(D.get(cc, 0, 1).real());
+    Ortho O(c, N, nrhs, 1);
+    std::vector<double> out = O.sumsq(v);
+    for (double &q : out) q = norm_from_sq(q);
     return out;
 }
 
