@@ -8,8 +8,10 @@ SOURCES = ["api.hip", "interbody.hip", "field.hip", "modal.hip", "setup.hip", "k
 LIB = os.path.join(HERE, "libaxs.so")
 # MFMA results of the inter-body kernels feed VALU arithmetic at once: keep
 # them in ordinary VGPRs instead of accumulation registers (saves two
-# v_accvgpr_read per pair in the inner loop)
-EXTRA = {"interbody.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# v_accvgpr_read per pair in the inner loop); the network's products otherwise
+# park prefetched tiles in accumulation registers and move them back (3-5 %)
+_VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
+EXTRA = {"interbody.hip": _VGPR_FORM, "mlp.hip": _VGPR_FORM}
 
 
 def build(verbose: bool = False, jobs: int = 8) -> str:

@@ -6,8 +6,8 @@
 // Network: y = L_D(... GELU(L_1(x))), L_k(h) = h W_k + b_k, W_k row-major with
 // the input index first; parameters packed as [W_1, b_1, W_2, b_2, ...].
 // Loss: mean squared error over the batch and outputs; optimiser: Adam.
-// GEMMs run on the matrix cores (16x16x4 FP32 MFMA) with 64x64 block tiles
-// staged through LDS; the bias and GELU are fused into the GEMM epilogue.
+// GEMMs run on the matrix cores (16x16x4 FP32 MFMA) with block tiles staged
+// through LDS; bias, GELU, its derivative and the loss are fused into their epilogues.
 //
 // Warm-start encoding (the network's output).  From eq. "precond" the solution
 // satisfies sigma* = b~ - D^{-1} B sigma*, b~ = -D^{-1} v, and b~ (the
@@ -40,10 +40,10 @@ struct Mlp {
     int64_t step = 0;
     // activations for a batch (grown on demand)
     int cap_batch = 0;
-    std::vector<float *> H, Z;       // H[k]: input to layer k (B x sizes[k]); Z[k]: pre-activation (B x sizes[k+1])
+    std::vector<float *> H, Z;       // H[k]: input to layer k (B x sizes[k]); Z[k]: its pre-activation (hidden layers)
     float *G0 = nullptr, *G1 = nullptr, *loss_part = nullptr;
-    float *Tb = nullptr;             // gathered targets of one batch (B x n_out)
     double *loss_dev = nullptr;
+    int64_t cap_part = 0;
     int32_t *order = nullptr;        // row order of one epoch (device copy)
     int64_t cap_order = 0;
     float *ws = nullptr;             // split-K partial products (grown on demand)
@@ -51,184 +51,331 @@ struct Mlp {
 };
 
 // ---------------------------------------------------------------------------
-// GEMM: C[M x N] = op(A)[M x K] op(B)[K x N] (+ bias[N]) with optional GELU.
-// TA: A stored as K x M (transposed); TB: B stored as N x K.  All row-major.
-// out_z (if set) receives the pre-activation, out_h the activation.
+// GEMM: C[M x N] = op(A)[M x K] op(B)[K x N] on the 16x16x4 FP32 MFMA, with what
+// follows it fused into the epilogue.  TA: A stored as K x M (transposed); TB: B
+// stored as N x K.  All row-major.
+//
+// Bound: the matrix cores (149 TFLOP/s measured in FP32) for the products with
+// the output layer at a batch of 256, its weights' memory traffic at small
+// batches, latency for the hidden layers.  A workgroup is four wavefronts on a BM x BN
+// tile; the next K tile of both operands is loaded into registers while this one
+// is multiplied from LDS (two buffers, one barrier a tile).  An operand whose rows
+// run along k is kept as [m][KT + 4], any other as [k][BM + 4]: with either
+// stride 16-byte writes and fragment reads hit each bank once.  Lane group g of a
+// fragment takes k = 4 g + step, so [m][k] gives four steps in one 16-byte read.
+// The operands of the instruction are swapped, which leaves four consecutive n of
+// one m with a lane: 16-byte stores.  Loads and stores of 16 bytes need 4-byte
+// alignment only; rows and columns past the edges are read as zero.
+// Network 4 -> 512 x 4 -> 116,620 at a batch of 256, products with the output layer:
+// forward with loss 364 us (84 TFLOP/s), weights' gradient 298 (103), inputs'
+// 280 (109), the whole gradient 1.00 ms; 64 x 64 tiles without a prefetch ran at 35
+// TFLOP/s with separate passes for loss, sums and GELU', and took 3.15.  The 128 x 128
+// tiles' depth: 16 where B is read along n, with three workgroups a CU (32, with
+// two: 392 and 331 us), 32 where both run along k (16: 295).
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int GBM = 64, GBN = 64, GKT = 16;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+enum GemmMode {
+    GM_STORE = 0,   // out = acc
+    GM_LINEAR,      // out = acc + bias
+    GM_GELU,        // out_z = acc + bias, out = GELU(out_z)
+    GM_LOSS,        // d = acc + bias - T: out = 2 d scale, part[tile] = sum of d^2
+    GM_DGELU,       // out = acc GELU'(Z)
+};
+
+struct GemmArgs {
+    int M = 0, N = 0, K = 0;
+    const float *A = nullptr, *B = nullptr;
+    int lda = 0, ldb = 0;
+    int mode = GM_STORE;
+    const float *bias = nullptr;    // [N]
+    const float *aux = nullptr;     // T (GM_LOSS) or Z (GM_DGELU), rows of N
+    const int32_t *rows = nullptr;  // GM_LOSS: row of T of output row m (null: m)
+    float scale = 0.f;
+    float *out_z = nullptr, *out = nullptr;   // rows of N
+    float *part = nullptr;
+    float *colsum = nullptr;        // [N]: sums over k of op(B) (unsplit K only)
+    // filled in by gemm()
+    int kc = 0, splits = 1, mt = 0, nt = 0;
+};
 
 __device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 __device__ __forceinline__ float gelu_grad_f(float x) {
     return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * expf(-0.5f * x * x) * 0.39894228040143268f;
 }
 
-// With gridDim.z > 1 (split K) block z sums k in [z kc, min(K, (z+1) kc)) and
-// writes its partial product, without bias or activation, to out_h + z M ldc.
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void gemm_mfma_kernel(int M, int N, int K, int kc, const float *__restrict__ A,
-                                                        int lda, const float *__restrict__ B, int ldb,
-                                                        const float *__restrict__ bias, int act, float beta,
-                                                        float *__restrict__ out_z, float *__restrict__ out_h, int ldc) {
-    __shared__ float As[GBM][GKT + 1];
-    __shared__ float Bs[GKT][GBN + 1];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int m0 = blockIdx.y * GBM, n0 = blockIdx.x * GBN;
-    const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-    f32x4 acc[2][2];
+// p[0..4), of which the first n are in range
+__device__ __forceinline__ f32x4 load4(const float *p, int n) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (n >= 4) {
+        v = *(const f32x4u *)p;
+    } else {
+        if (n > 0) v[0] = p[0];
+        if (n > 1) v[1] = p[1];
+        if (n > 2) v[2] = p[2];
+    }
+    return v;
+}
+
+__device__ __forceinline__ void store4(float *p, int n, f32x4 v) {
+    if (n >= 4) {
+        *(f32x4u *)p = v;
+    } else {
+        if (n > 0) p[0] = v[0];
+        if (n > 1) p[1] = v[1];
+        if (n > 2) p[2] = v[2];
+    }
+}
+
+// one operand's tile: R rows (m or n) x KT; KC: stored with k contiguous
+template <bool KC, int R, int KT>
+struct Tile {
+    static constexpr int NE = R * KT / 1024;   // 16-byte pieces per thread
+    static_assert(R * KT % 1024 == 0 && 256 % (KC ? KT / 4 : R / 4) == 0, "");
+    static constexpr int LD = KC ? KT + 4 : R + 4, SIZE = KC ? R * LD : KT * LD;
+    f32x4 reg[NE];
+    __device__ __forceinline__ void load(const float *__restrict__ P, int ld, int r0, int rows, int k0, int ke) {
+        if (r0 + R <= rows && k0 + KT <= ke) {   // inside: no branch between the loads
+            const float *p = KC ? P + (int64_t)(r0 + threadIdx.x / (KT / 4)) * ld + k0 + threadIdx.x % (KT / 4) * 4
+                                : P + (int64_t)(k0 + threadIdx.x / (R / 4)) * ld + r0 + threadIdx.x % (R / 4) * 4;
+            const int64_t step = (int64_t)(256 / (KC ? KT / 4 : R / 4)) * ld;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int kb = blockIdx.z * kc, ke = min(K, kb + kc);
-    if (gridDim.z > 1) out_h += (int64_t)blockIdx.z * M * ldc;
-    for (int k0 = kb; k0 < ke; k0 += GKT) {
-        // stage A tile (GBM x GKT) and B tile (GKT x GBN), 4 elements per thread each
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = tid + e * 256;
-            int mm, kk;
-            if (TA) {            // stored K x M: consecutive threads walk m
-                mm = idx % GBM;
-                kk = idx / GBM;
-            } else {             // stored M x K: consecutive threads walk k
-                kk = idx % GKT;
-                mm = idx / GKT;
-            }
-            const int gm = m0 + mm, gk = k0 + kk;
-            float val = 0.f;
-            if (gm < M && gk < ke) val = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
-            As[mm][kk] = val;
-            int nn, kb;
-            if (TB) {            // stored N x K: consecutive threads walk k
-                kb = idx % GKT;
-                nn = idx / GKT;
-            } else {             // stored K x N: consecutive threads walk n
-                nn = idx % GBN;
-                kb = idx / GBN;
-            }
-            const int gn = n0 + nn, gkb = k0 + kb;
-            float vb = 0.f;
-            if (gn < N && gkb < ke) vb = TB ? B[(int64_t)gn * ldb + gkb] : B[(int64_t)gkb * ldb + gn];
-            Bs[kb][nn] = vb;
+            for (int e = 0; e < NE; ++e) reg[e] = *(const f32x4u *)(p + e * step);
+            return;
         }
-        __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < GKT; kk += 4) {
-            float a[2], b[2];
+        for (int e = 0; e < NE; ++e) {
+            const int idx = threadIdx.x + e * 256;
+            if (KC) {
+                const int r = r0 + idx / (KT / 4), k = k0 + idx % (KT / 4) * 4;
+                reg[e] = load4(P + (int64_t)r * ld + k, r < rows ? ke - k : 0);
+            } else {
+                const int r = r0 + idx % (R / 4) * 4, k = k0 + idx / (R / 4);
+                reg[e] = load4(P + (int64_t)k * ld + r, k < ke ? rows - r : 0);
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float *S) const {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = As[wm + i * 16 + (lane & 15)][kk + (lane >> 4)];
+        for (int e = 0; e < NE; ++e) {
+            const int idx = threadIdx.x + e * 256;
+            float *q = KC ? S + idx / (KT / 4) * LD + idx % (KT / 4) * 4 : S + idx / (R / 4) * LD + idx % (R / 4) * 4;
+            *(f32x4 *)q = reg[e];
+        }
+    }
+    // k = k0 + 4 g + step of row r, step 0..3
+    static __device__ __forceinline__ f32x4 frag(const float *S, int r, int k) {
+        if (KC) return *(const f32x4 *)(S + r * LD + k);
+        f32x4 v;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = Bs[kk + (lane >> 4)][wn + j * 16 + (lane & 15)];
+        for (int j = 0; j < 4; ++j) v[j] = S[(k + j) * LD + r];
+        return v;
+    }
+};
+
+// sum over the workgroup (256 threads) in a fixed order, valid in thread 0
+template <class T>
+__device__ __forceinline__ T block_sum(T v) {
+    __shared__ T s_sum[4];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+}
+
+// BM x BN per workgroup, WM x (4 / WM) wavefronts.  With splits > 1 block s of a tile sums k
+// in [s kc, min(K, (s + 1) kc)) and writes its partial product to out + s M N.
+// Workgroups go to the eight XCDs in turn: each XCD takes a contiguous run of tiles
+// (m fastest), so that the tiles of one column panel share its L2.
+template <bool TA, bool TB, int BM, int BN, int KT, int WM>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmArgs a) {
+    using TileA = Tile<!TA, BM, KT>;
+    using TileB = Tile<TB, BN, KT>;
+    constexpr int WN = 4 / WM, FM = BM / WM / 16, FN = BN / WN / 16;
+    __shared__ __attribute__((aligned(16))) float s_a[2][TileA::SIZE], s_b[2][TileB::SIZE];
+    const int nb = gridDim.x, xcd = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+    int t = xcd * per + min(xcd, rem) + blockIdx.x / 8;
+    const int mi = t % a.mt;
+    t /= a.mt;
+    const int ni = t % a.nt, split = t / a.nt;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
+    const int m0 = mi * BM, n0 = ni * BN;
+    const int wm = wave / WN * (BM / WM), wn = wave % WN * (BN / WN);
+    const int kb = split * a.kc, ke = min(a.K, kb + a.kc);
+    f32x4 acc[FM][FN];
 #pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const bool sums = a.colsum && mi == 0 && wm == 0;
+    float cs[FN] = {};
+    TileA ta;
+    TileB tb;
+    ta.load(a.A, a.lda, m0, a.M, kb, ke);
+    tb.load(a.B, a.ldb, n0, a.N, kb, ke);
+    ta.store(s_a[0]);
+    tb.store(s_b[0]);
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = kb; k0 < ke; k0 += KT, buf ^= 1) {
+        const bool more = k0 + KT < ke;
+        if (more) {
+            ta.load(a.A, a.lda, m0, a.M, k0 + KT, ke);
+            tb.load(a.B, a.ldb, n0, a.N, k0 + KT, ke);
+        }
+#pragma unroll
+        for (int kq = 0; kq < KT; kq += 16) {
+            f32x4 fa[FM], fb[FN];
+#pragma unroll
+            for (int i = 0; i < FM; ++i) fa[i] = TileA::frag(s_a[buf], wm + 16 * i + l16, kq + 4 * g);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) fb[j] = TileB::frag(s_b[buf], wn + 16 * j + l16, kq + 4 * g);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j][q], fa[i][q], acc[i][j], 0, 0, 0);
+            if (sums)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) cs[j] += (fb[j][0] + fb[j][1]) + (fb[j][2] + fb[j][3]);
+        }
+        if (more) {
+            ta.store(s_a[buf ^ 1]);
+            tb.store(s_b[buf ^ 1]);
         }
         __syncthreads();
     }
+    if (sums)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < FN; ++j) {
+            cs[j] += __shfl_xor(cs[j], 16, 64);
+            cs[j] += __shfl_xor(cs[j], 32, 64);
+            const int n = n0 + wn + 16 * j + l16;
+            if (g == 0 && n < a.N) a.colsum[n] = cs[j];
+        }
+    float *out = a.out + (int64_t)split * a.M * a.N;
+    const int mode = a.splits > 1 ? GM_STORE : a.mode;
+    float loss = 0.f;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < FN; ++j) {
+        const int n = n0 + wn + 16 * j + 4 * g, cnt = a.N - n;
+        if (cnt <= 0) continue;
+        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
+        if (mode == GM_LINEAR || mode == GM_GELU || mode == GM_LOSS) bias = load4(a.bias + n, cnt);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int gm = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-                const int gn = n0 + wn + j * 16 + (lane & 15);
-                if (gm < M && gn < N) {
-                    float z = acc[i][j][r];
-                    if (bias) z += bias[gn];
-                    const int64_t o = (int64_t)gm * ldc + gn;
-                    if (beta != 0.f) z += beta * out_z[o];
-                    if (out_z) out_z[o] = z;
-                    if (out_h) out_h[o] = act ? gelu_f(z) : z;
-                }
+        for (int i = 0; i < FM; ++i) {
+            const int m = m0 + wm + 16 * i + l16;
+            if (m >= a.M) continue;
+            const int64_t o = (int64_t)m * a.N + n;
+            f32x4 z = acc[i][j] + bias;
+            if (mode == GM_GELU) {
+                store4(a.out_z + o, cnt, z);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = gelu_f(z[r]);
+            } else if (mode == GM_DGELU) {
+                const f32x4 zz = load4(a.aux + o, cnt);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] *= gelu_grad_f(zz[r]);
+            } else if (mode == GM_LOSS) {
+                z -= load4(a.aux + (int64_t)(a.rows ? a.rows[m] : m) * a.N + n, cnt);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r < cnt) loss += z[r] * z[r];
+                z *= 2.f * a.scale;
             }
+            store4(out + o, cnt, z);
+        }
+    }
+    if (mode == GM_LOSS) {
+        loss = block_sum(loss);
+        if (threadIdx.x == 0) a.part[ni * a.mt + mi] = loss;
+    }
 }
 
-// out[m][n] = sum_s part[s][m][n] (fixed order) + bias[n], GELU with act
-__global__ void splitk_reduce_kernel(const float *__restrict__ part, int S, int M, int N,
-                                     const float *__restrict__ bias, int act, float *__restrict__ out_z,
-                                     float *__restrict__ out_h) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, mn = (int64_t)M * N;
+// out = sum_s part[s] (fixed order), with GM_DGELU times GELU'(Z)
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ part, int S, int64_t mn, int mode,
+                                                            const float *__restrict__ Z, float *__restrict__ out) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (t >= mn) return;
     float z = 0.f;
+#pragma unroll 8
     for (int s = 0; s < S; ++s) z += part[s * mn + t];
-    if (bias) z += bias[t % N];
-    if (out_z) out_z[t] = z;
-    if (out_h) out_h[t] = act ? gelu_f(z) : z;
+    out[t] = mode == GM_DGELU ? z * gelu_grad_f(Z[t]) : z;
 }
 
-// K splits for a GEMM whose output has too few 64 x 64 tiles to fill the
-// GPU (at least 1024 k per split, up to about 1024 blocks in all); 1 = none
-static int splitk_count(int M, int N, int K) {
-    const int64_t tiles = ceil_div(M, GBM) * ceil_div(N, GBN);
-    if (tiles >= 256 || K < 2048) return 1;
-    return (int)std::max<int64_t>(1, std::min<int64_t>(K / 1024, 1024 / tiles));
-}
-
-// C = op(A) op(B) (+ bias, GELU); ws: workspace of splitk_count(M, N, K) M N
-// floats when that count exceeds 1 (ldc must then be N)
-template <bool TA, bool TB>
-static void gemm(Ctx &c, int M, int N, int K, const float *A, int lda, const float *B, int ldb, const float *bias,
-                 int act, float *out_z, float *out_h, int ldc, float *ws = nullptr) {
-    const int S = ws && ldc == N ? splitk_count(M, N, K) : 1;
-    const int kc = S > 1 ? (int)(ceil_div(ceil_div(K, S), GKT) * GKT) : K;
-    const int Sg = S > 1 ? (int)ceil_div(K, kc) : 1;
-    dim3 grid((unsigned)ceil_div(N, GBN), (unsigned)ceil_div(M, GBM), (unsigned)Sg);
-    if (Sg > 1) {
-        hipLaunchKernelGGL((gemm_mfma_kernel<TA, TB>), grid, dim3(256), 0, c.stream, M, N, K, kc, A, lda, B, ldb,
-                           nullptr, 0, 0.f, nullptr, ws, N);
-        AXS_HIP(hipGetLastError());
-        hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div((int64_t)M * N, 256)), dim3(256), 0,
-                           c.stream, ws, Sg, M, N, bias, act, out_z, out_h);
-    } else {
-        hipLaunchKernelGGL((gemm_mfma_kernel<TA, TB>), grid, dim3(256), 0, c.stream, M, N, K, K, A, lda, B, ldb, bias,
-                           act, 0.f, out_z, out_h, ldc);
+// The tile of a product and its K splits.  128 x 128 where that makes a workgroup
+// a CU (K split into parts of at least 1024 if it may be); 64 x 64 where it does not, or where
+// padding M to 128 costs more than the smaller tile; 32 x 128 for at most 32
+// rows; 32 x 32 with deep K tiles for the small products, which are all latency.
+enum GemmShape { GS_LARGE, GS_MID, GS_THIN, GS_SMALL };
+static GemmShape gemm_shape(int M, int N, int K, bool can_split, int &splits) {
+    const int64_t smax = can_split && K >= 2048 ? K / 1024 : 1;
+    auto tiles = [&](int bm, int bn) { return ceil_div(M, bm) * (int64_t)ceil_div(N, bn); };
+    GemmShape g = GS_SMALL;
+    int64_t t = tiles(32, 32);
+    if (M <= 32) {
+        if (tiles(32, 128) * smax >= 256) g = GS_THIN, t = tiles(32, 128);
+    } else if (tiles(128, 128) * smax >= 256 && 4 * ceil_div(M, 128) * 128 <= 5 * ceil_div(M, 64) * 64) {
+        g = GS_LARGE, t = tiles(128, 128);
+    } else if (tiles(64, 64) * smax >= 256) {
+        g = GS_MID, t = tiles(64, 64);
     }
+    splits = (int)std::max<int64_t>(1, std::min<int64_t>(smax, (g == GS_LARGE ? 512 : 1024) / t));
+    return g;
+}
+
+// workspace floats of a product whose K may be split (0: not split)
+static int64_t gemm_ws(int M, int N, int K) {
+    int S = 1;
+    gemm_shape(M, N, K, true, S);
+    return S > 1 ? (int64_t)S * M * N : 0;
+}
+
+template <bool TA, bool TB, int BM, int BN, int KT, int WM>
+static int gemm_launch(Ctx &c, GemmArgs a, float *ws) {
+    a.mt = (int)ceil_div(a.M, BM);
+    a.nt = (int)ceil_div(a.N, BN);
+    a.kc = (int)(ceil_div(ceil_div(a.K, a.splits), KT) * KT);
+    a.splits = (int)ceil_div(a.K, a.kc);
+    float *const out = a.out;
+    if (a.splits > 1) a.out = ws;
+    const int64_t nb = (int64_t)a.mt * a.nt * a.splits;
+    AXS_REQUIRE(nb <= INT32_MAX, AXS_EINVAL, "product too large");
+    hipLaunchKernelGGL((gemm_mfma_kernel<TA, TB, BM, BN, KT, WM>), dim3((unsigned)nb), dim3(256), 0, c.stream, a);
     AXS_HIP(hipGetLastError());
+    if (a.splits == 1) return a.mt * a.nt;
+    const int64_t mn = (int64_t)a.M * a.N;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)ceil_div(mn, 256)), dim3(256), 0, c.stream, ws, a.splits, mn,
+                       a.mode, a.aux, out);
+    AXS_HIP(hipGetLastError());
+    return a.mt * a.nt;
 }
 
-// G <- G * GELU'(Z)
-__global__ void gelu_backward_kernel(float *__restrict__ G, const float *__restrict__ Z, int64_t n) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n) G[t] *= gelu_grad_f(Z[t]);
-}
-
-// db[j] = sum_b G[b][j]   (fixed order over the batch)
-__global__ void colsum_kernel(const float *__restrict__ G, int B, int n, float *__restrict__ db) {
-    int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s += G[(int64_t)b * n + j];
-    db[j] = s;
-}
-
-// G = 2 (Y - T) / (B n); per-block partial sums of (Y - T)^2 in double
-__global__ __launch_bounds__(256) void mse_kernel(const float *__restrict__ Y, const float *__restrict__ T, int64_t n,
-                                                  float scale, float *__restrict__ G, float *__restrict__ part) {
-    __shared__ float red[256];
-    float s = 0.f;
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)gridDim.x * 256) {
-        const float d = Y[t] - T[t];
-        G[t] = 2.f * d * scale;
-        s += d * d;
+// ws: gemm_ws(M, N, K) floats, or null (K not split); returns the output tiles
+template <bool TA, bool TB>
+static int gemm(Ctx &c, GemmArgs a, float *ws = nullptr) {
+    switch (gemm_shape(a.M, a.N, a.K, ws != nullptr, a.splits)) {
+        case GS_LARGE: return gemm_launch<TA, TB, 128, 128, TB ? 32 : 16, 2>(c, a, ws);
+        case GS_MID: return gemm_launch<TA, TB, 64, 64, 32, 2>(c, a, ws);
+        case GS_THIN: return gemm_launch<TA, TB, 32, 128, 32, 1>(c, a, ws);
+        default: return gemm_launch<TA, TB, 32, 32, 64, 2>(c, a, ws);
     }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void sum_parts_kernel(const float *__restrict__ part, int n, double scale, double *__restrict__ out) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0;
-        for (int i = 0; i < n; ++i) s += part[i];
-        *out = s * scale;
-    }
+// at most this many partial sums with GM_LOSS (one an output tile)
+static int64_t loss_tiles(int M, int N) { return ceil_div(M, 32) * ceil_div(N, 32); }
+
+// out = scale * sum of part[0..n)
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float *__restrict__ part, int n, double scale,
+                                                        double *__restrict__ out) {
+    double s = 0;
+    for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+    s = block_sum(s);
+    if (threadIdx.x == 0) *out = s * scale;
 }
 
 // dst[r][:] = src[idx[r]][:] for r < batch; idx already checked against the source rows
@@ -258,44 +405,68 @@ __global__ void adam_kernel(float *__restrict__ p, float *__restrict__ m, float 
 // ---------------------------------------------------------------------------
 // host
 // ---------------------------------------------------------------------------
+// activations for a batch: inputs of every layer, pre-activations of the hidden
+// ones, and two gradients (the first also as wide as the output)
 static void ensure_batch(Mlp &n, int B) {
     if (B <= n.cap_batch) return;
     Ctx &c = *n.ctx;
+    n.cap_batch = 0;
     for (auto *p : n.H) c.dfree(p);
     for (auto *p : n.Z) c.dfree(p);
     c.dfree(n.G0);
     c.dfree(n.G1);
-    c.dfree(n.Tb);
+    n.G0 = n.G1 = nullptr;
     const int L = (int)n.sizes.size() - 1;
-    n.H.assign(L + 1, nullptr);
-    n.Z.assign(L, nullptr);
+    n.H.assign(L, nullptr);
+    n.Z.assign(L - 1, nullptr);
     int wmax = 0;
     for (int s : n.sizes) wmax = std::max(wmax, s);
-    for (int k = 0; k <= L; ++k) n.H[k] = (float *)c.dalloc((size_t)B * n.sizes[k] * sizeof(float));
-    for (int k = 0; k < L; ++k) n.Z[k] = (float *)c.dalloc((size_t)B * n.sizes[k + 1] * sizeof(float));
+    for (int k = 0; k < L; ++k) n.H[k] = (float *)c.dalloc((size_t)B * n.sizes[k] * sizeof(float));
+    for (int k = 0; k < L - 1; ++k) n.Z[k] = (float *)c.dalloc((size_t)B * n.sizes[k + 1] * sizeof(float));
     n.G0 = (float *)c.dalloc((size_t)B * wmax * sizeof(float));
-    n.G1 = (float *)c.dalloc((size_t)B * wmax * sizeof(float));
-    n.Tb = (float *)c.dalloc((size_t)B * n.sizes[L] * sizeof(float));
+    n.G1 = (float *)c.dalloc((size_t)B * n.sizes[1] * sizeof(float));   // gradients of the hidden layers only
     n.cap_batch = B;
 }
 
-// forward pass from the input already in H[0]; H[L] = output
-static void mlp_forward_h0(Mlp &n, int B) {
-    Ctx &c = *n.ctx;
+// layer k's product H[k] W_k (bias and epilogue to be filled in)
+static GemmArgs layer_args(const Mlp &n, int k, int B) {
+    GemmArgs g;
+    g.M = B;
+    g.N = n.sizes[k + 1];
+    g.K = n.sizes[k];
+    g.A = n.H[k];
+    g.lda = g.K;
+    g.B = n.p + n.woff[k];
+    g.ldb = g.N;
+    g.bias = n.p + n.boff[k];
+    return g;
+}
+
+// the hidden layers from the input already in H[0]
+static void mlp_hidden(Mlp &n, int B) {
     const int L = (int)n.sizes.size() - 1;
-    for (int k = 0; k < L; ++k) {
-        const int a = n.sizes[k], b = n.sizes[k + 1];
-        gemm<false, false>(c, B, b, a, n.H[k], a, n.p + n.woff[k], b, n.p + n.boff[k], k < L - 1 ? 1 : 0, n.Z[k],
-                           n.H[k + 1], b);
+    for (int k = 0; k < L - 1; ++k) {
+        GemmArgs g = layer_args(n, k, B);
+        g.mode = GM_GELU;
+        g.out_z = n.Z[k];
+        g.out = n.H[k + 1];
+        gemm<false, false>(*n.ctx, g);
     }
 }
 
-// forward pass: H[0] = X (copied), H[L] = output
-static void mlp_forward(Mlp &n, const float *X, int B) {
-    Ctx &c = *n.ctx;
+static void load_input(Mlp &n, const float *X, int B) {
     ensure_batch(n, B);
-    AXS_HIP(hipMemcpyAsync(n.H[0], X, (size_t)B * n.sizes[0] * sizeof(float), hipMemcpyDeviceToDevice, c.stream));
-    mlp_forward_h0(n, B);
+    AXS_HIP(hipMemcpyAsync(n.H[0], X, (size_t)B * n.sizes[0] * sizeof(float), hipMemcpyDeviceToDevice, n.ctx->stream));
+}
+
+// forward pass of X (copied) into Y (null: into G0)
+static void mlp_forward(Mlp &n, const float *X, int B, float *Y) {
+    load_input(n, X, B);
+    mlp_hidden(n, B);
+    GemmArgs g = layer_args(n, (int)n.sizes.size() - 2, B);
+    g.mode = GM_LINEAR;
+    g.out = Y ? Y : n.G0;
+    gemm<false, false>(*n.ctx, g);
 }
 
 // bias-corrected Adam update of the packed parameters from the gradient in n.g
@@ -315,51 +486,76 @@ static void gather_rows(Ctx &c, const float *src, int ncol, const int32_t *idx, 
     AXS_HIP(hipGetLastError());
 }
 
-// loss and gradient of the packed parameters into n.g
-static void mlp_backward(Mlp &n, const float *T, int B) {
+// loss and its gradient in the packed parameters, into `grad`, for the inputs
+// already in H[0] and the rows of T (row rows[r] for batch row r; null: row r).
+// The loss and the gradient of the outputs come with the output layer's product, the bias
+// gradients with the weights', GELU' with the product back through the weights.
+static void mlp_backward(Mlp &n, const float *T, const int32_t *rows, int B, float *grad) {
     Ctx &c = *n.ctx;
     const int L = (int)n.sizes.size() - 1;
     const int nout = n.sizes[L];
-    const int64_t ny = (int64_t)B * nout;
-    const int nblk = (int)std::min<int64_t>(1024, ceil_div(ny, 256));
-    if (!n.loss_part) {
-        n.loss_part = (float *)c.dalloc(1024 * sizeof(float));
-        n.loss_dev = (double *)c.dalloc(sizeof(double));
+    const int64_t ny = (int64_t)B * nout, nparts = loss_tiles(B, nout);
+    if (nparts > n.cap_part) {
+        c.dfree(n.loss_part);
+        n.loss_part = nullptr;
+        n.cap_part = 0;
+        n.loss_part = (float *)c.dalloc((size_t)nparts * sizeof(float));
+        n.cap_part = nparts;
     }
-    hipLaunchKernelGGL(mse_kernel, dim3(nblk), dim3(256), 0, c.stream, n.H[L], T, ny, 1.f / (float)ny, n.G0,
-                       n.loss_part);
-    AXS_HIP(hipGetLastError());
-    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(64), 0, c.stream, n.loss_part, nblk, 1.0 / (double)ny,
+    if (!n.loss_dev) n.loss_dev = (double *)c.dalloc(sizeof(double));
+    mlp_hidden(n, B);
+    GemmArgs f = layer_args(n, L - 1, B);
+    f.mode = GM_LOSS;
+    f.aux = T;
+    f.rows = rows;
+    f.scale = 1.f / (float)ny;
+    f.out = n.G0;
+    f.part = n.loss_part;
+    const int tiles = gemm<false, false>(c, f);
+    hipLaunchKernelGGL(sum_parts_kernel, dim3(1), dim3(256), 0, c.stream, n.loss_part, tiles, 1.0 / (double)ny,
                        n.loss_dev);
     AXS_HIP(hipGetLastError());
     float *G = n.G0, *Gn = n.G1;
     for (int k = L - 1; k >= 0; --k) {
         const int a = n.sizes[k], b = n.sizes[k + 1];
-        if (k < L - 1) {
-            hipLaunchKernelGGL(gelu_backward_kernel, dim3(ceil_div((int64_t)B * b, 256)), dim3(256), 0, c.stream, G,
-                               n.Z[k], (int64_t)B * b);
-            AXS_HIP(hipGetLastError());
-        }
         // dW = H^T G  (a x b),  db = colsum(G),  dH = G W^T (B x a)
-        gemm<true, false>(c, a, b, B, n.H[k], a, G, b, nullptr, 0, nullptr, n.g + n.woff[k], b);
-        hipLaunchKernelGGL(colsum_kernel, dim3(ceil_div(b, 256)), dim3(256), 0, c.stream, G, B, b, n.g + n.boff[k]);
-        AXS_HIP(hipGetLastError());
-        if (k > 0) {
-            // dH has few output tiles and, for the output layer, a long k range: split K
-            const int64_t need = (int64_t)splitk_count(B, a, b) * B * a;
-            if (need > (int64_t)B * a && need > n.cap_ws) {
-                AXS_HIP(hipStreamSynchronize(c.stream));
-                c.dfree(n.ws);
-                n.ws = nullptr;
-                n.ws = (float *)c.dalloc((size_t)need * sizeof(float));
-                n.cap_ws = need;
-            }
-            gemm<false, true>(c, B, a, b, G, b, n.p + n.woff[k], b, nullptr, 0, nullptr, Gn, a, n.ws);
-            std::swap(G, Gn);
+        GemmArgs w;
+        w.M = a;
+        w.N = b;
+        w.K = B;
+        w.A = n.H[k];
+        w.lda = a;
+        w.B = G;
+        w.ldb = b;
+        w.out = grad + n.woff[k];
+        w.colsum = grad + n.boff[k];
+        gemm<true, false>(c, w);
+        if (k == 0) break;
+        // dH has few output tiles and, for the output layer, a long k range: split K
+        const int64_t need = gemm_ws(B, a, b);
+        if (need > n.cap_ws) {
+            AXS_HIP(hipStreamSynchronize(c.stream));
+            c.dfree(n.ws);
+            n.ws = nullptr;
+            n.cap_ws = 0;
+            n.ws = (float *)c.dalloc((size_t)need * sizeof(float));
+            n.cap_ws = need;
         }
+        GemmArgs h;
+        h.M = B;
+        h.N = a;
+        h.K = b;
+        h.A = G;
+        h.lda = b;
+        h.B = n.p + n.woff[k];
+        h.ldb = b;
+        h.mode = GM_DGELU;
+        h.aux = n.Z[k - 1];
+        h.out = Gn;
+        gemm<false, true>(c, h, need > 0 ? n.ws : nullptr);
+        std::swap(G, Gn);
     }
 }
-
 
 // copy one epoch's row order (host, already checked) to the device; the copy is
 // complete on return, so the caller may reuse the host array
@@ -384,13 +580,10 @@ static void queue_steps(Mlp &n, const float *X, const float *T, int batch, int s
                         double b2, double eps) {
     Ctx &c = *n.ctx;
     ensure_batch(n, batch);
-    const int L = (int)n.sizes.size() - 1;
     for (int s = 0; s < steps; ++s) {
         const int32_t *idx = n.order + (int64_t)s * batch;
         gather_rows(c, X, n.sizes[0], idx, batch, n.H[0]);
-        gather_rows(c, T, n.sizes[L], idx, batch, n.Tb);
-        mlp_forward_h0(n, batch);
-        mlp_backward(n, n.Tb, batch);
+        mlp_backward(n, T, idx, batch, n.g);
         adam_update(n, lr[s], b1, b2, eps);
     }
 }
@@ -467,7 +660,7 @@ axs_status axs_mlp_destroy(axs_mlp *h) {
         for (auto *p : n.H) n.ctx->dfree(p);
         for (auto *p : n.Z) n.ctx->dfree(p);
         for (void *p : {(void *)n.p, (void *)n.m, (void *)n.v, (void *)n.g, (void *)n.G0, (void *)n.G1,
-                        (void *)n.Tb, (void *)n.loss_part, (void *)n.loss_dev, (void *)n.order, (void *)n.ws})
+                        (void *)n.loss_part, (void *)n.loss_dev, (void *)n.order, (void *)n.ws})
             n.ctx->dfree(p);
     }
     delete h;
@@ -504,10 +697,7 @@ axs_status axs_mlp_get_params(axs_mlp *h, float *host) {
 axs_status axs_mlp_forward(axs_mlp *h, const float *X, float *Y, int batch) {
     return mlp_guarded(h, [&](Mlp &n, Ctx &c) -> axs_status {
         AXS_REQUIRE(X && Y && batch >= 1, AXS_EINVAL, "bad arguments");
-        axs::mlp_forward(n, X, batch);
-        const int L = (int)n.sizes.size() - 1;
-        AXS_HIP(hipMemcpyAsync(Y, n.H[L], (size_t)batch * n.sizes[L] * sizeof(float), hipMemcpyDeviceToDevice,
-                               c.stream));
+        axs::mlp_forward(n, X, batch, Y);
         return AXS_OK;
     });
 }
@@ -515,10 +705,8 @@ axs_status axs_mlp_forward(axs_mlp *h, const float *X, float *Y, int batch) {
 axs_status axs_mlp_gradient(axs_mlp *h, const float *X, const float *T, int batch, double *loss, float *grad) {
     return mlp_guarded(h, [&](Mlp &n, Ctx &c) -> axs_status {
         AXS_REQUIRE(X && T && batch >= 1, AXS_EINVAL, "bad arguments");
-        axs::mlp_forward(n, X, batch);
-        axs::mlp_backward(n, T, batch);
-        if (grad)
-            AXS_HIP(hipMemcpyAsync(grad, n.g, n.nparams * sizeof(float), hipMemcpyDeviceToDevice, c.stream));
+        axs::load_input(n, X, batch);
+        axs::mlp_backward(n, T, nullptr, batch, grad ? grad : n.g);
         if (loss) {
             AXS_HIP(hipMemcpyAsync(loss, n.loss_dev, sizeof(double), hipMemcpyDeviceToHost, c.stream));
             AXS_HIP(hipStreamSynchronize(c.stream));
@@ -532,8 +720,8 @@ axs_status axs_mlp_adam_step(axs_mlp *h, const float *X, const float *T, int bat
     return mlp_guarded(h, [&](Mlp &n, Ctx &c) -> axs_status {
         AXS_REQUIRE(X && T && batch >= 1 && lr > 0 && b1 >= 0 && b1 < 1 && b2 >= 0 && b2 < 1 && eps > 0,
                     AXS_EINVAL, "bad arguments");
-        axs::mlp_forward(n, X, batch);
-        axs::mlp_backward(n, T, batch);
+        axs::load_input(n, X, batch);
+        axs::mlp_backward(n, T, nullptr, batch, n.g);
         axs::adam_update(n, lr, b1, b2, eps);
         if (loss) {
             AXS_HIP(hipMemcpyAsync(loss, n.loss_dev, sizeof(double), hipMemcpyDeviceToHost, c.stream));
@@ -1105,7 +1293,7 @@ axs_status axs_mlp_predict(axs_mlp *h, axs_ctx *ctx, const double *dirs, const d
         }
         float *xd = (float *)n.ctx->dalloc(xf.size() * sizeof(float));
         AXS_HIP(hipMemcpy(xd, xf.data(), xf.size() * sizeof(float), hipMemcpyHostToDevice));
-        axs::mlp_forward(n, xd, nrhs);
+        axs::mlp_forward(n, xd, nrhs, nullptr);
         AXS_HIP(hipStreamSynchronize(n.ctx->stream));
         n.ctx->dfree(xd);
         // sigma0 = b~ = -D^{-1} v, then the decoded multiple-scattering part on top
@@ -1115,7 +1303,7 @@ axs_status axs_mlp_predict(axs_mlp *h, axs_ctx *ctx, const double *dirs, const d
         double2 *v = (double2 *)c.dalloc((size_t)nrhs * c.N * sizeof(double2));
         axs::incident_plane_launch(c, T.dirs, nrhs, v);
         axs::apply_precond(c, v, sigma0, nrhs, AXS_FP64, -1.0);
-        axs::ws_decode(c, T, n.H[L], P, mmax, nrhs, true, (double2 *)sigma0);
+        axs::ws_decode(c, T, n.G0, P, mmax, nrhs, true, (double2 *)sigma0);
         AXS_HIP(hipStreamSynchronize(c.stream));
         c.dfree(v);
         return AXS_OK;

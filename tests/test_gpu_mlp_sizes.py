@@ -1,0 +1,56 @@
+"""The network's products at the sizes where their tiles, K splits and edges change (one to 257
+rows, rows of odd length, so that nothing is 16-byte aligned), layer by layer against the FP64
+reference."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("width,depth,n_out,B", [
+    (24, 1, 1, 1), (31, 3, 33, 5),       # 32 x 32 tiles
+    (33, 1, 32771, 32),                  # 32 x 128 forward, 64 x 64 weights' gradient
+    (512, 2, 70001, 20),                 # 32 x 128 both ways, K split
+    (64, 1, 6001, 130),                  # 64 x 64 forward
+    (512, 1, 8203, 250),                 # 64 x 64 with K split
+    (130, 2, 16390, 257),                # 128 x 128 forward, 32 x 32 with K split
+    (512, 1, 32770, 255),                # 128 x 128 throughout
+])
+def test_products_at_edges(width, depth, n_out, B):
+    from oracle import mlp as ref
+    from paper_1406_0236_amd import Context, Mlp
+    print(f"[gpu] {width} x {depth} -> {n_out}, batch {B}", flush=True)
+    ctx = Context(0)
+    rng = np.random.default_rng(width + B)
+    sizes = ref.layer_sizes(4, width, depth, n_out)
+    p = ref.init_params(sizes, rng).astype(np.float32).astype(np.float64)
+    p += (0.05 * rng.standard_normal(p.size)).astype(np.float32)
+    p = p.astype(np.float32).astype(np.float64)
+    net = Mlp(ctx, 4, width, depth, n_out)
+    net.set_params(p)
+    X = rng.standard_normal((B, 4)).astype(np.float32)
+    T = rng.standard_normal((B, n_out)).astype(np.float32)
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    # rounding of sums of up to max(sizes, B) terms of random sign, relative in the 2-norm,
+    # through at most depth + 1 layers each way
+    tol = 4 * (depth + 1) * np.finfo(np.float32).eps * np.sqrt(max(max(sizes), B))
+    Yr, _ = ref.forward(p, sizes, X.astype(np.float64))
+    Y = net.forward(Xd).cpu().numpy()
+    assert np.linalg.norm(Y - Yr) <= tol * np.linalg.norm(Yr)
+    lr, gr = ref.loss_and_grad(p, sizes, X.astype(np.float64), T.astype(np.float64))
+    loss, g = net.gradient(Xd, Td)
+    g = g.cpu().numpy()
+    assert abs(loss - lr) <= tol * lr
+    o = 0
+    for a, b in zip(sizes, sizes[1:]):
+        for n in (a * b, b):
+            e = np.linalg.norm(g[o:o + n] - gr[o:o + n]) / np.linalg.norm(gr[o:o + n])
+            assert e <= tol, (a, b, n, e, tol)
+            o += n
+    # the rows of a batch taken from a larger set on the device
+    order = rng.permutation(B).astype(np.int32)
+    l2 = net.train_epoch(Xd, Td, order, B, [1e-12])
+    assert abs(l2 - lr) <= tol * lr
+    net.close()
+    ctx.close()
