@@ -8,8 +8,8 @@
 // on the target's own panel, its neighbours and any panel closer to y_i than
 // that panel's arc length (the paper cites Kolm-Rokhlin corrected quadrature
 // for this step; here it is product integration with a graded Gauss rule:
-// geometric bisection towards the (near-)singular parameter, max(10, p) Gauss
-// points per level, see the constants below for how far it goes).
+// geometric bisection towards the (near-)singular parameter, 10 Gauss points or
+// more per level, see the constants below for how far it goes).
 // On a near panel the curve is the polynomial interpolant of the node
 // positions and its derivative gives the normal and line element; on the
 // target's own panel the displacement y(s) - y_i is formed from the Lagrange
@@ -22,26 +22,32 @@
 //   entire functions cos(kR(t)) and sin(kR)/R (sampled at Nt points),
 //   q_m = 2 Q_{|m|-1/2}(chi) / sqrt(r r') with Q the toroidal harmonic
 //   (AGM elliptic integrals, then the three-term recurrence: forward near
-//   chi = 1, backward continued fraction otherwise);
+//   chi = 1, backward otherwise);
 //   k^D_m = normal derivative at the source of the same expression.
 // Pipeline per batch of target rows:
 //   gen_far / gen_near  -> evaluation points (source data + weight)
-//   toroidal_kernel     -> q_mu, n.grad q_mu per point            (thread per point)
-//   modal_kernel        -> k^G_m * weight per point, m = 0..M    (wavefront per point)
+//   toroidal_kernel     -> q_mu per point                        (thread per point)
+//   modal_kernel        -> k^G_m * weight per point, m = 0..M    (16 points a workgroup)
 //   scatter / near_reduce -> entries of A~_m
 // then 1/2 on the diagonal and S_m = A~_m^{-1} by Gauss-Jordan elimination
 // with partial pivoting (one workgroup per mode).
+#include <algorithm>
 #include <cmath>
 
 #include "axs_internal.h"
+#include "fp64_math.h"
 
 namespace axs {
 
 // Gauss points per level: the interpolation l_j(s) times the curve's own
 // polynomial has degree 2p and more, which 10 points do not integrate for p > 10
 // (with 10 the largest error of an entry is 2e-12 at p = 11, 1e-11 at 12 and
-// 1e-8 at 16; with p points the kernel values' noise, 1e-12)
-static int level_points(int p) { return p > 10 ? p : 10; }
+// 1e-8 at 16; with p points the kernel values' noise, 1e-12).  kl: the longest panel in
+// units of 1/kappa; the kernel's own oscillation takes one more for every two
+// beyond 5 (with 10 the error is 1e-10 at kl = 9).
+static int level_points(int p, double kl) {
+    return std::max(p, 10 + (int)std::ceil(std::min(std::max(0.0, 0.5 * (kl - 5.0)), 54.0)));
+}
 constexpr int PMAX = 16;       // max nodes per panel supported
 // Levels of the graded rule.  Every kernel value costs the same, so the points
 // are what the precomputation pays for; 46 levels on both sides of every near
@@ -64,6 +70,8 @@ constexpr int PMAX = 16;       // max nodes per panel supported
 // 200 contour nodes) 6.85 -> 2.73 ms.
 constexpr int OWN_LEV = 11, OWN_Q = 8, OWN_NQ = 24;
 constexpr int MAX_LEV = 46;
+
+typedef double gj_f64x4 __attribute__((ext_vector_type(4)));
 
 struct Pts {
     double *rt, *rp, *dr, *dz, *nr, *nz, *wj;   // [P]
@@ -98,14 +106,24 @@ __global__ void gen_far_kernel(const int2 *__restrict__ pairs, int n, int p, con
     pts.wj[o] = aw[j];
 }
 
-// one workgroup per near pair
-__global__ void gen_near_kernel(const NearDesc *__restrict__ desc, int p, const double *__restrict__ snode,
-                                const double *__restrict__ lden, const double *__restrict__ glu,
-                                const double *__restrict__ glw, int ngl, const double *__restrict__ ownx,
-                                const double *__restrict__ ownw, const double *__restrict__ r,
-                                const double *__restrict__ z, Pts pts, int64_t base) {
+// one workgroup per near pair.  rd, zd: derivative of each panel's interpolant at its
+// nodes, so that the curve and its tangent both come from the Lagrange basis.  The
+// basis is formed from running products kept in registers (p <= PMAX, unrolled).
+// A quarter of the time went into scratch memory for them, the rest into p^3
+// products for the derivatives: FIGN.
+__global__ __launch_bounds__(128) void gen_near_kernel(const NearDesc *__restrict__ desc, int p,
+                                                       const double *__restrict__ snode,
+                                                       const double *__restrict__ lden,
+                                                       const double *__restrict__ glu, const double *__restrict__ glw,
+                                                       int ngl, const double *__restrict__ ownx,
+                                                       const double *__restrict__ ownw, const double *__restrict__ r,
+                                                       const double *__restrict__ z, const double *__restrict__ rd,
+                                                       const double *__restrict__ zd, Pts pts, int64_t base) {
     const NearDesc d = desc[blockIdx.x];
     const int own = (d.i / p) == d.P;
+    const int iloc = own ? d.i - d.P * p : -1;
+    const double *rP = r + d.P * p, *zP = z + d.P * p, *rdP = rd + d.P * p, *zdP = zd + d.P * p;
+    const double ri = r[d.i], zi = z[d.i];
     for (int idx = threadIdx.x; idx < d.n0 + d.n1; idx += blockDim.x) {
         const int side = idx >= d.n0;
         const int q = side ? idx - d.n0 : idx;
@@ -113,7 +131,7 @@ __global__ void gen_near_kernel(const NearDesc *__restrict__ desc, int p, const 
         const double sst = d.sstar;
         const double dir = side == 0 ? -1.0 : 1.0;
         const double Ls = side == 0 ? sst + 1.0 : 1.0 - sst;
-        double* lag = pts.lag + (int64_t)(d.first + idx) * p;
+        double *lag = pts.lag + (int64_t)(d.first + idx) * p;
         double off, wq;
         if (own) {
             off = Ls * ownx[q];
@@ -126,167 +144,251 @@ __global__ void gen_near_kernel(const NearDesc *__restrict__ desc, int p, const 
             wq = glw[kq] * 0.5 * (hi - lo);
         }
         const double s = sst + dir * off;
-        const int iloc = d.i - d.P * p;
-        const double *rP = r + d.P * p, *zP = z + d.P * p;
-        // Lagrange basis and its derivative at s; on the own panel the factor
-        // (s - s_iloc) is the exact signed offset.
-        double diff[PMAX];
-        for (int k = 0; k < p; ++k) diff[k] = (own && k == iloc) ? dir * off : s - snode[k];
-        double L[PMAX], D[PMAX];
-        for (int j = 0; j < p; ++j) {
-            double prod = lden[j];
-            for (int k = 0; k < p; ++k)
-                if (k != j) prod *= diff[k];
-            L[j] = prod;
-            double der = 0;
-            for (int m = 0; m < p; ++m) {
-                if (m == j) continue;
-                double t = lden[j];
-                for (int k = 0; k < p; ++k)
-                    if (k != j && k != m) t *= diff[k];
-                der += t;
+        // Lagrange basis at s; on the own panel the factor (s - s_iloc) is the
+        // exact signed offset.  L[k]: first the product of the factors before k.
+        double L[PMAX], diff[PMAX], run = 1.0;
+#pragma unroll
+        for (int k = 0; k < PMAX; ++k)
+            if (k < p) {
+                diff[k] = k == iloc ? dir * off : s - snode[k];
+                L[k] = run;
+                run *= diff[k];
             }
-            D[j] = der;
-        }
         double rp = 0, zp = 0, rs = 0, zs = 0, dr = 0, dz = 0;
-        for (int k = 0; k < p; ++k) {
-            rp += L[k] * rP[k];
-            zp += L[k] * zP[k];
-            rs += D[k] * rP[k];
-            zs += D[k] * zP[k];
-        }
-        if (own) {
-            for (int k = 0; k < p; ++k) {
-                if (k == iloc) continue;
-                dr += L[k] * (rP[k] - r[d.i]);
-                dz += L[k] * (zP[k] - z[d.i]);
+        run = 1.0;
+#pragma unroll
+        for (int k = PMAX - 1; k >= 0; --k)
+            if (k < p) {
+                const double l = L[k] * run * lden[k];
+                run *= diff[k];
+                lag[k] = l;
+                rp = fma(l, rP[k], rp);
+                zp = fma(l, zP[k], zp);
+                rs = fma(l, rdP[k], rs);
+                zs = fma(l, zdP[k], zs);
+                dr = fma(l, rP[k] - ri, dr);   // own panel: the target node's term is exactly 0
+                dz = fma(l, zP[k] - zi, dz);
             }
-        } else {
-            dr = rp - r[d.i];
-            dz = zp - z[d.i];
+        if (!own) {
+            dr = rp - ri;
+            dz = zp - zi;
         }
         const double sp = sqrt(rs * rs + zs * zs);
         const bool ok = rp > 1e-13 && (dr * dr + dz * dz) > 0.0;
-        pts.rt[o] = r[d.i];
+        pts.rt[o] = ri;
         pts.rp[o] = ok ? rp : -1.0;     // rp < 0 marks a point that contributes nothing
         pts.dr[o] = dr;
         pts.dz[o] = dz;
         pts.nr[o] = -zs / sp;
         pts.nz[o] = rs / sp;
         pts.wj[o] = ok ? wq * rp * sp : 0.0;
-        for (int k = 0; k < p; ++k) lag[k] = L[k];
     }
 }
 
 // ---------------------------------------------------------------------------
-// toroidal harmonics: q_mu = 2 Q_{mu-1/2}(chi)/sqrt(r r') and its normal derivative
+// toroidal harmonics: q_mu = 2 Q_{mu-1/2}(chi)/sqrt(r r') = scale e^{-decay mu} f_mu
 // ---------------------------------------------------------------------------
-__global__ void toroidal_kernel(Pts pts, int64_t npts, int nmax, double *__restrict__ qv,
-                                double *__restrict__ dqv) {
-    int64_t pt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (pt >= npts) return;
-    const int nq = nmax + 1;
-    double *q = qv + pt * nq, *dq = dqv + pt * nq;
-    const double rp = pts.rp[pt];
-    if (!(rp > 0.0)) {
-        for (int mu = 0; mu < nq; ++mu) q[mu] = dq[mu] = 0.0;
-        return;
+// lane j's value of x, in scalar registers
+__device__ __forceinline__ double lane_value(double x, int j) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), j),
+                            __builtin_amdgcn_readlane(__double2loint(x), j));
+}
+
+// One point per thread, f[mu][point].  Bound: the serial recurrence, up to 10 nq
+// steps of two dependent multiply-adds in some wavefront or other.
+//  - nq eta <= 2 (chi = cosh eta): forward from the elliptic integrals, which
+//    amplifies rounding by e^2 at most.  With c = chi - 1 and e_mu = (mu - 1/2)
+//    (f_mu - f_{mu-1}) the three-term recurrence is
+//      e_{mu+1} = e_mu + 2 mu c f_mu,   f_{mu+1} = f_mu + e_{mu+1} / (mu + 1/2),
+//    free of the rounding of 1 + c, which at small c is most of the error.
+//  - otherwise backward, with the decay taken out, Q_{mu-1/2} ~ t^mu g_mu, t = e^{-eta}
+//    (and 2 chi t = 1 + t^2), and h_mu = (mu - 1/2) (g_{mu-1} - g_mu):
+//      h_mu = t^2 h_{mu+1} + (1 - t^2) g_mu / 2,   g_{mu-1} = g_mu + h_mu / (mu - 1/2),
+//    all terms positive and no size beyond a power of mu; started at h = g / 2,
+//    its limit, 18 / eta steps above nq (an error there shrinks by t^2 a step).
+// All lanes of a wavefront take the same mu, each from its own start on, so the
+// reciprocals come from one division per 64 steps.  38,000 points, nq = 84: 233 us
+// with a division a step and rows of f per point, FIGT now.
+__global__ __launch_bounds__(64) void toroidal_kernel(Pts pts, int64_t npts, int nq, double *__restrict__ f,
+                                                      double *__restrict__ scale, double *__restrict__ decay) {
+    const int64_t pt = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int lane = threadIdx.x;
+    const double rp = pt < npts ? pts.rp[pt] : -1.0;
+    const bool active = rp > 0.0;
+    double chim1 = 1.0, eta = 1.0, Q0 = 0.0, d1 = 0.0, srr = 1.0;
+    if (active) {
+        const double rt = pts.rt[pt], dr = pts.dr[pt], dz = pts.dz[pt];
+        const double rr = rt * rp;
+        srr = sqrt(rr);
+        chim1 = (dr * dr + dz * dz) / (2.0 * rr);
+        const double chi = 1.0 + chim1;
+        const double pm = chim1 / (chi + 1.0);           // 1 - m, m = 2/(chi+1)
+        // complete elliptic integrals K(m), E(m) by the arithmetic-geometric mean
+        double a = 1.0, b = sqrt(pm), csum = 0.5 * (1.0 - pm), pw = 0.5;
+        for (int it = 0; it < 64; ++it) {
+            const double an = 0.5 * (a + b), cn = 0.5 * (a - b);
+            b = sqrt(a * b);
+            a = an;
+            pw *= 2.0;
+            csum += pw * cn * cn;
+            if (fabs(cn) <= 1e-17 * a) break;
+        }
+        const double K = M_PI / (2.0 * a);
+        const double E = K * (1.0 - csum);
+        Q0 = sqrt(2.0 / (chi + 1.0)) * K;
+        d1 = chim1 * Q0 - sqrt(2.0 * (chi + 1.0)) * E;   // Q_{1/2} - Q_{-1/2}
+        eta = 2.0 * asinh(sqrt(0.5 * chim1));
     }
-    const double rt = pts.rt[pt], dr = pts.dr[pt], dz = pts.dz[pt], nrp = pts.nr[pt], nzp = pts.nz[pt];
-    const double rr = rt * rp;
-    const double d0sq = dr * dr + dz * dz;
-    const double chim1 = d0sq / (2.0 * rr);
-    const double chi = 1.0 + chim1;
-    const double pm = chim1 / (chi + 1.0);           // 1 - m, m = 2/(chi+1)
-    // complete elliptic integrals K(m), E(m) by the arithmetic-geometric mean
-    double a = 1.0, b = sqrt(pm), csum = 0.5 * (1.0 - pm), pw = 0.5;
-    for (int it = 0; it < 64; ++it) {
-        const double an = 0.5 * (a + b), cn = 0.5 * (a - b);
-        b = sqrt(a * b);
-        a = an;
-        pw *= 2.0;
-        csum += pw * cn * cn;
-        if (fabs(cn) <= 1e-17 * a) break;
+    double *q = f + pt;
+    const bool backward = active && nq * eta > 2.0, forward = active && !backward;   // a NaN goes forward
+    // backward starts: whole blocks of 64 above nq
+    const int first = backward ? (int)(ceil(18.0 / eta) + 20.0 + 63.0) / 64 : 0;
+    int wfirst = first;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) wfirst = max(wfirst, __shfl_xor(wfirst, o, 64));
+    wfirst = __builtin_amdgcn_readfirstlane(wfirst);
+    double norm = 1.0;
+    if (wfirst > 0) {
+        const double t2 = exp(-2.0 * eta), w = -0.5 * expm1(-2.0 * eta);
+        double v = 1.0, h = 0.5;
+        for (int blk = wfirst; blk > 0; --blk) {
+            const int mu0 = nq + 64 * blk;
+            if (blk == first) {   // what a lane did ahead of its start is not used
+                v = 1.0;
+                h = 0.5;
+            }
+            const double rec = 1.0 / ((mu0 - lane) - 0.5);
+#pragma unroll 16
+            for (int j = 0; j < 64; ++j) {
+                h = fma(w, v, t2 * h);
+                v = fma(h, lane_value(rec, j), v);
+            }
+        }
+        for (int mu0 = nq; mu0 >= 1; mu0 -= 64) {
+            const double rec = 1.0 / ((mu0 - lane) - 0.5);
+            for (int j = 0; j < min(64, mu0); ++j) {
+                h = fma(w, v, t2 * h);
+                v = fma(h, lane_value(rec, j), v);
+                if (backward) q[(mu0 - j - 1) * npts] = v;
+            }
+        }
+        norm = Q0 / v;
     }
-    const double K = M_PI / (2.0 * a);
-    const double E = K * (1.0 - csum);
-    const double kk = sqrt(2.0 / (chi + 1.0));
-    const double Q0 = kk * K;
-    const double eta = chim1 < 1e-3 ? 2.0 * asinh(sqrt(0.5 * chim1)) : acosh(chi);
-    q[0] = Q0;
-    if (nq > 1) {
-        if (!(2.0 * nq * eta > 2.0)) {       // forward recurrence (also taken for a NaN argument)
-            double qa = Q0, qb = chi * kk * K - sqrt(2.0 * (chi + 1.0)) * E;
-            q[1] = qb;
-            for (int mu = 1; mu + 1 < nq; ++mu) {
-                const double qc = (2.0 * mu * chi * qb - (mu - 0.5) * qa) / (mu + 0.5);
-                q[mu + 1] = qc;
-                qa = qb;
-                qb = qc;
+    if (__any(forward)) {
+        double v = Q0 + d1, e = 0.5 * d1;
+        if (forward) {
+            q[0] = Q0;
+            q[npts] = v;
+        }
+        for (int mu0 = 1; mu0 + 1 < nq; mu0 += 64) {
+            const double rec = 1.0 / ((mu0 + lane) + 0.5);
+            for (int j = 0; j < min(64, nq - 1 - mu0); ++j) {
+                e = fma(2.0 * (mu0 + j) * chim1, v, e);
+                v = fma(e, lane_value(rec, j), v);
+                if (forward) q[(mu0 + j + 1) * npts] = v;
             }
-        } else {
-            // rho_mu = Q_{mu+1/2}/Q_{mu-1/2} by the backward recurrence
-            // rho_{mu-1} = (mu - 1/2) / (2 mu chi - (mu + 1/2) rho_mu), started at e^{-eta}
-            const int top = nq + (int)ceil(20.0 / eta) + 20;
-            double rho = 1.0 / (chi + sqrt(chim1 * (chi + 1.0)));
-            for (int mu = top; mu >= 1; --mu) {
-                rho = (mu - 0.5) / (2.0 * mu * chi - (mu + 0.5) * rho);
-                if (mu < nq) q[mu] = rho;            // slot mu holds rho_{mu-1}
-            }
-            for (int mu = 1; mu < nq; ++mu) q[mu] = q[mu - 1] * q[mu];
         }
     }
-    const double c2m1 = chim1 * (chi + 1.0);
-    const double srr = sqrt(rr);
-    const double ndel = nrp * dr + nzp * dz;
-    const double ndchi = ndel / rr - nrp * d0sq / (2.0 * rr * rp);
-    const double q1 = nq > 1 ? q[1] : 0.0;   // Q_{-3/2} = Q_{1/2}
-    double prev = q1;
-    for (int mu = 0; mu < nq; ++mu) {
-        const double Qm = q[mu];
-        const double dQ = (mu - 0.5) * (chi * Qm - prev) / c2m1;
-        prev = Qm;
-        const double qq = 2.0 * Qm / srr;
-        q[mu] = qq;
-        dq[mu] = 2.0 * dQ * ndchi / srr - nrp * qq / (2.0 * rp);
+    if (active) {
+        scale[pt] = 2.0 / srr * (backward ? norm : 1.0);
+        decay[pt] = backward ? eta : 0.0;
     }
 }
 
 // ---------------------------------------------------------------------------
-// modal kernel values per point: one wavefront per point
+// modal kernel values
 // ---------------------------------------------------------------------------
-__device__ double tcos_series(double x) {
-    // (x cos x - sin x) / x^3 = sum_{k>=1} (-1)^k 2k x^{2k-2} / (2k+1)!
-    double x2 = x * x, term = 1.0, sum = 0.0;
-    double fact = 6.0;  // (2k+1)! for k = 1
-    for (int k = 1; k <= 11; ++k) {
-        sum += ((k & 1) ? -1.0 : 1.0) * (2.0 * k) * term / fact;
-        term *= x2;
-        fact *= (2.0 * k + 2.0) * (2.0 * k + 3.0);
-    }
-    return sum;
+// (x cos x - sin x) / x^3 = sum_{k>=1} (-1)^k 2k x^{2k-2} / (2k+1)!  for |x| <= 0.2
+// (the first term left out is below 2e-21)
+__device__ __forceinline__ double tcos_series(double x) {
+    const double y = x * x;
+    double t = 1.0 / 518918400.0;
+    t = fma(t, y, -1.0 / 3991680.0);
+    t = fma(t, y, 1.0 / 45360.0);
+    t = fma(t, y, -1.0 / 840.0);
+    t = fma(t, y, 1.0 / 30.0);
+    return fma(t, y, -1.0 / 3.0);
 }
 
-template <int WPB>
-__global__ __launch_bounds__(64 * WPB) void modal_kernel(Pts pts, int64_t npts, int Nt, int M,
-                                                         const double *__restrict__ qv,
-                                                         const double *__restrict__ dqv, double kappa,
-                                                         double gam_re, double gam_im,
-                                                         double2 *__restrict__ kout) {
-    extern __shared__ double sm[];
-    const int Nh = Nt / 2 + 1, L = Nt / 2 - 1, nq = M + L + 1;
-    const int per = 4 * Nh + 2 * (L + 1) + 2 * (M + 1) + 2 * nq;
-    double *cosT = sm;                               // [Nt]
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    double *base = sm + Nt + wave * per;
-    double *Cs = base, *Ss = Cs + Nh, *Dc = Ss + Nh, *Ds = Dc + Nh;
-    double *cl = Ds + Nh, *dcl = cl + (L + 1), *sm_ = dcl + (L + 1), *dsm = sm_ + (M + 1);
-    double *ql = dsm + (M + 1), *dql = ql + nq;
-    for (int j = threadIdx.x; j < Nt; j += 64 * WPB) cosT[j] = cospi(2.0 * j / Nt);
-    const int64_t pt = (int64_t)blockIdx.x * WPB + wave;
-    const bool inrange = pt < npts;
-    const double rp = inrange ? pts.rp[pt] : -1.0;
-    const bool active = rp > 0.0;       // rp <= 0 marks a point without contribution
+// sin x and cos x for 0 <= x < 1e5: x less the nearest multiple n of pi/2, whose second part
+// leaves n 1.5e-33, and the Taylor series on [-pi/4, pi/4] (first terms left out below 9e-20 and 4e-21)
+__device__ __forceinline__ void sincos_small(double x, double &s, double &c) {
+    const double n = rint(x * 0.636619772367581343);
+    double r = fma(-n, 1.5707963267948966, x);
+    r = fma(-n, 6.123233995736766e-17, r);
+    const double y = r * r;
+    double a = 1.0 / 355687428096000.0, b = -1.0 / 6402373705728000.0;
+    a = fma(a, y, -1.0 / 1307674368000.0);
+    b = fma(b, y, 1.0 / 20922789888000.0);
+    a = fma(a, y, 1.0 / 6227020800.0);
+    b = fma(b, y, -1.0 / 87178291200.0);
+    a = fma(a, y, -1.0 / 39916800.0);
+    b = fma(b, y, 1.0 / 479001600.0);
+    a = fma(a, y, 1.0 / 362880.0);
+    b = fma(b, y, -1.0 / 3628800.0);
+    a = fma(a, y, -1.0 / 5040.0);
+    b = fma(b, y, 1.0 / 40320.0);
+    a = fma(a, y, 1.0 / 120.0);
+    b = fma(b, y, -1.0 / 720.0);
+    a = fma(a, y, -1.0 / 6.0);
+    b = fma(b, y, 1.0 / 24.0);
+    b = fma(b, y, -0.5);
+    const double sn = fma(a * y, r, r), cs = fma(b, y, 1.0);
+    const int q = (int)n;
+    s = (q & 1) ? cs : sn;
+    c = (q & 1) ? sn : cs;
+    if (q & 2) s = -s;
+    if ((q + 1) & 2) c = -c;
+}
+
+// Sizes and LDS of modal_kernel for PT points a workgroup (in doubles)
+struct ModalSize {
+    int Nt, M, H, KP, L, nq, Lc;
+    __host__ __device__ ModalSize(int Nt_, int M_)
+        : Nt(Nt_), M(M_), H(Nt_ / 2), KP((H / 2 + 4) / 4 * 4), L(H - 1), nq(M_ + H), Lc(L > M_ ? L : M_) {}
+    __host__ __device__ int shared(int PT) const {
+        return Nt + H + 2 + PT * ((8 * KP > 2 * nq ? 8 * KP : 2 * nq) + 2 * (L + 1) + 2 * (M + 1));
+    }
+};
+
+// k^G_m (times the point's weight) for m = 0..M of PT points per workgroup, in three parts:
+//  - the four even functions of t (cos kR, sin(kR)/R and their normal
+//    derivatives) at t_k = 2 pi k / Nt, k = 0..H = Nt/2, weighted for the cosine series
+//      f_l = sum_k g_k cos(2 pi l k / Nt)
+//    and folded at H/2, where cos changes by (-1)^l: e_k = g_k + g_{H-k} for even
+//    l, o_k = g_k - g_{H-k} for odd;
+//  - the series as a product on the FP64 matrix cores: the cosines of 16 l of
+//    one parity times the folded samples of 4 PT columns;
+//  - the convolution over l with q_{m-l}, per thread one point and MB values of
+//    m: c_0 q_m + sum_l c_l (q_{|m-l|} + q_{m+l}), the MB pairs (q, dq) on either side
+//    kept in registers and moved on by one per l.
+// Bound by the multiply-adds of the last part and the sines of the first, about half and half
+// of the time each.  FIGM
+template <int PT, int MB>
+__global__ __launch_bounds__(256) void modal_kernel(Pts pts, int64_t npts, int Nt, int M, const double *__restrict__ f,
+                                                    const double *__restrict__ scale, const double *__restrict__ decay,
+                                                    double kappa, double gam_re, double gam_im,
+                                                    double2 *__restrict__ kout) {
+    extern __shared__ __attribute__((aligned(16))) double sm[];
+    const ModalSize z(Nt, M);
+    const int H = z.H, KP = z.KP, L = z.L, nq = z.nq;
+    constexpr int CW = 4 * PT, CT = PT / 4, NPAR = 256 / PT;
+    double *cosT = sm, *s2T = sm + Nt;               // cos(2 pi j / Nt); sin^2(pi j / Nt), j <= H
+    double *ev = s2T + H + 2, *od = ev + KP * CW;    // folded samples [KP][CW]
+    double2 *qd = (double2 *)ev;                     // later (q_mu, dq_mu) [nq][PT]
+    const int un = 8 * KP > 2 * nq ? 8 * KP : 2 * nq;
+    double2 *cd = (double2 *)(ev + PT * un);         // series of cos and its derivative [L + 1][PT]
+    double2 *ss = cd + (L + 1) * PT;                 // of sin / R and its derivative [M + 1][PT], then the results
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 4, l16 = lane & 15;
+    const int pl = tid % PT, par = tid / PT;         // this thread's point and its share of the work on it
+    const int64_t pt0 = (int64_t)blockIdx.x * PT, pt = pt0 + pl;
+    for (int j = tid; j < Nt; j += 256) cosT[j] = cospi(2.0 * j / Nt);
+    for (int j = tid; j <= H; j += 256) {
+        const double sh = sinpi((double)j / Nt);
+        s2T[j] = sh * sh;
+    }
+    const double rp = pt < npts ? pts.rp[pt] : -1.0;
+    const bool active = rp > 0.0;                    // rp <= 0 marks a point without contribution
     double rt = 0, dr = 0, dz = 0, nrp = 0, nzp = 0, wj = 0;
     if (active) {
         rt = pts.rt[pt];
@@ -296,81 +398,186 @@ __global__ __launch_bounds__(64 * WPB) void modal_kernel(Pts pts, int64_t npts, 
         nzp = pts.nz[pt];
         wj = pts.wj[pt];
     }
-    const double d0sq = dr * dr + dz * dz, ndel = nrp * dr + nzp * dz;
-    // samples t_k = 2 pi k / Nt, k = 0..Nt/2 (all factors are even in t)
-    if (active) {
-        for (int k = lane; k < Nh; k += 64) {
-            const double sh = sinpi((double)k / Nt);
-            const double s2 = sh * sh;                   // sin^2(t/2)
-            const double R = sqrt(d0sq + 4.0 * rt * rp * s2);
-            const double x = kappa * R;
-            double sn, cs;
-            sincos(x, &sn, &cs);
-            const double sd = R > 0.0 ? sn / R : kappa;
-            const double T = x > 0.2 ? (x * cs - sn) / (R * R * R) : kappa * kappa * kappa * tcos_series(x);
-            const double g = ndel + 2.0 * nrp * rt * s2;
-            Cs[k] = cs;
-            Ss[k] = sd;
-            Dc[k] = -kappa * sd * g;
-            Ds[k] = T * g;
-        }
-        for (int mu = lane; mu < nq; mu += 64) {
-            ql[mu] = qv[pt * nq + mu];
-            dql[mu] = dqv[pt * nq + mu];
+    const double rr = rt * rp, d0sq = dr * dr + dz * dz, ndel = nrp * dr + nzp * dz;
+    __syncthreads();
+    // samples (all factors are even in t)
+    for (int k = par; k < KP; k += NPAR) {
+        double e[4] = {0, 0, 0, 0}, o[4] = {0, 0, 0, 0};
+        if (active && 2 * k <= H)
+            for (int side = 0; side < (2 * k < H ? 2 : 1); ++side) {
+                const int kk = side ? H - k : k;
+                const double s2 = s2T[kk];               // sin^2(t/2)
+                const double d2 = fma(4.0 * rr, s2, d0sq);
+                const double inv = rsq(d2);
+                double R = d2 * inv;
+                R = d2 > 0.0 ? fma(0.5 * inv, fma(-R, R, d2), R) : 0.0;
+                const double x = kappa * R;
+                double sn, cs;
+                if (x < 1e5) sincos_small(x, sn, cs);
+                else sincos(x, &sn, &cs);
+                const double sd = R > 0.0 ? sn * inv : kappa;
+                const double T = x > 0.2 ? (x * cs - sn) * (inv * inv * inv) : kappa * kappa * kappa * tcos_series(x);
+                const double gg = ndel + 2.0 * nrp * rt * s2;
+                const double w = (k == 0 ? 1.0 : 2.0) / Nt;
+                const double v[4] = {cs * w, sd * w, -kappa * sd * gg * w, T * gg * w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    e[c] += v[c];
+                    o[c] += side ? -v[c] : (2 * k < H ? v[c] : 0.0);   // cos(pi l / 2) = 0 for odd l
+                }
+            }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            // rows 128 bytes apart in the banks, so that the four k of a fragment do not collide
+            const int col = PT == 16 ? 16 * (c ^ (k & 1)) + pl : PT * c + pl;
+            ev[k * CW + col] = e[c];
+            od[k * CW + col] = o[c];
         }
     }
     __syncthreads();
-    // cosine-series coefficients:  f_l = (1/Nt) [f_0 + (-1)^l f_{Nt/2} + 2 sum_{k=1}^{Nt/2-1} f_k cos(2 pi l k / Nt)]
-    if (active) {
-        const int Lc = L > M ? L : M;
-        for (int l = lane; l <= Lc; l += 64) {
-            const double sgn = (l & 1) ? -1.0 : 1.0;
-            double a0 = Cs[0] + sgn * Cs[Nh - 1], a1 = Ss[0] + sgn * Ss[Nh - 1];
-            double a2 = Dc[0] + sgn * Dc[Nh - 1], a3 = Ds[0] + sgn * Ds[Nh - 1];
-            double b0 = 0, b1 = 0, b2 = 0, b3 = 0;
-            int idx = 0;
-            for (int k = 1; k < Nh - 1; ++k) {
-                idx += l;
-                if (idx >= Nt) idx -= Nt;
-                const double cw = cosT[idx];
-                b0 = fma(Cs[k], cw, b0);
-                b1 = fma(Ss[k], cw, b1);
-                b2 = fma(Dc[k], cw, b2);
-                b3 = fma(Ds[k], cw, b3);
+    // cosine series, 16 l of one parity per wavefront and turn
+    const int ntile = 2 * ((z.Lc / 2 + 16) / 16);
+    for (int tile = wave; tile < ntile; tile += 4) {
+        const int odd = tile & 1, l0 = 32 * (tile >> 1) + odd;
+        const double *src = odd ? od : ev;
+        gj_f64x4 acc[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[c] = (gj_f64x4){0, 0, 0, 0};
+        const int l = l0 + 2 * l16;
+        int idx = l * g % Nt;
+        const int step = 4 * l % Nt;
+        for (int k = 0; k < KP; k += 4) {
+            const double a = cosT[idx];
+            idx += step;
+            if (idx >= Nt) idx -= Nt;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int col = (PT == 16 ? 16 * (c ^ (g & 1)) : 16 * c) + l16;
+                acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, src[(k + g) * CW + col], acc[c], 0, 0, 0);
             }
-            const double inv = 1.0 / Nt;
-            if (l <= L) {
-                cl[l] = (a0 + 2.0 * b0) * inv;
-                dcl[l] = (a2 + 2.0 * b2) * inv;
-            }
-            if (l <= M) {
-                sm_[l] = (a1 + 2.0 * b1) * inv * (2.0 * M_PI);
-                dsm[l] = (a3 + 2.0 * b3) * inv * (2.0 * M_PI);
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int fct = (16 * c + l16) / PT, p2 = (16 * c + l16) % PT;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int ll = l0 + 2 * (g + 4 * v);
+                if (fct % 2 == 0) {
+                    if (ll <= L) (fct ? cd[ll * PT + p2].y : cd[ll * PT + p2].x) = acc[c][v];
+                } else if (ll <= M) {
+                    (fct == 3 ? ss[ll * PT + p2].y : ss[ll * PT + p2].x) = acc[c][v] * (2.0 * M_PI);
+                }
             }
         }
     }
     __syncthreads();
-    if (!inrange) return;
-    double2 *out = kout + pt * (M + 1);
+    // q_mu and its normal derivative
+    {
+        const double chim1 = d0sq / (2.0 * rr), c2m1 = chim1 * (chim1 + 2.0);
+        const double ndchi = ndel / rr - nrp * d0sq / (2.0 * rr * rp);
+        const double ca = ndchi / c2m1, cb = nrp / (2.0 * rp);
+        const double sc = active ? scale[pt] : 0.0, de = active ? decay[pt] : 0.0, t = exp(-de);
+        const double *fp = f + min(pt, npts - 1);
+        // consecutive mu per thread, eight loads in flight
+        const int ch = (nq + NPAR - 1) / NPAR, mu1 = min(nq, (par + 1) * ch);
+        int mu = par * ch;
+        double pw = sc * exp(-de * mu);
+        double prev = mu > 0 ? sc * exp(-de * (mu - 1)) * fp[min(mu - 1, nq - 1) * npts] : sc * t * fp[npts];   // Q_{-3/2} = Q_{1/2}
+        for (; mu < mu1; mu += 8) {
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = fp[min(mu + i, nq - 1) * npts];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (mu + i < mu1) {
+                    const double q = pw * v[i];
+                    const double dq = (mu + i - 0.5) * fma(chim1, q, q - prev) * ca - cb * q;
+                    qd[(mu + i) * PT + pl] = active ? make_double2(q, dq) : make_double2(0.0, 0.0);
+                    prev = q;
+                    pw *= t;
+                }
+        }
+    }
+    __syncthreads();
     const double inv4pi = 0.25 / M_PI;
-    for (int m = lane; m <= M; m += 64) {
-        if (!active) {
-            out[m] = make_double2(0.0, 0.0);
-            continue;
+    for (int m0 = par * MB; m0 <= M; m0 += NPAR * MB) {
+        double2 lo[MB], hi[MB];   // (q, dq) of |m0 + j - l| in slot (j - l) mod MB, of m0 + j + l in (j + l) mod MB
+        double sr[MB], sd[MB];
+        const double2 c0 = cd[pl];
+#pragma unroll
+        for (int j = 0; j < MB; ++j) {
+            lo[j] = hi[j] = qd[min(m0 + j, nq - 1) * PT + pl];
+            sr[j] = c0.x * lo[j].x;
+            sd[j] = fma(c0.y, lo[j].x, c0.x * lo[j].y);
         }
-        double sr = 0.0, dr_ = 0.0;
-        for (int l = -L; l <= L; ++l) {
-            const int al = l < 0 ? -l : l;
-            const int mm = m - l < 0 ? l - m : m - l;
-            sr = fma(cl[al], ql[mm], sr);
-            dr_ = fma(dcl[al], ql[mm], fma(cl[al], dql[mm], dr_));
-        }
-        const double si = sm_[m], di = dsm[m];
-        // (kD + gamma kS) / (4 pi)
-        const double re = (dr_ + gam_re * sr - gam_im * si) * inv4pi;
-        const double im = (di + gam_re * si + gam_im * sr) * inv4pi;
-        out[m] = make_double2(re * wj, im * wj);
+        for (int l0 = 0; l0 < L; l0 += MB)
+#pragma unroll
+            for (int u = 1; u <= MB; ++u) {
+                const int l = l0 + u;
+                if (l > L) break;
+                lo[(MB - u) % MB] = qd[abs(m0 - l) * PT + pl];
+                hi[(MB - 1 + u) % MB] = qd[min(m0 + MB - 1 + l, nq - 1) * PT + pl];
+                const double2 c = cd[l * PT + pl];
+#pragma unroll
+                for (int j = 0; j < MB; ++j) {
+                    const double2 a = lo[(j + MB - u) % MB], b = hi[(j + u) % MB];
+                    const double q = a.x + b.x;
+                    sr[j] = fma(c.x, q, sr[j]);
+                    sd[j] = fma(c.y, q, fma(c.x, a.y + b.y, sd[j]));
+                }
+            }
+#pragma unroll
+        for (int j = 0; j < MB; ++j)
+            if (m0 + j <= M) {
+                double2 &o = ss[(m0 + j) * PT + pl];
+                const double si = o.x, di = o.y;
+                // (kD + gamma kS) / (4 pi)
+                const double re = (sd[j] + gam_re * sr[j] - gam_im * si) * inv4pi;
+                const double im = (di + gam_re * si + gam_im * sr[j]) * inv4pi;
+                o = active ? make_double2(re * wj, im * wj) : make_double2(0.0, 0.0);
+            }
     }
+    __syncthreads();
+    for (int i = tid; i < PT * (M + 1); i += 256) {
+        const int q = i / (M + 1);
+        if (pt0 + q < npts) kout[pt0 * (M + 1) + i] = ss[i % (M + 1) * PT + q];
+    }
+}
+
+// Values of m = 0..M for npts points.  16 points a workgroup while two workgroups
+// share a CU's LDS, else 4 (large kappa r or M); of 2, 3 and 4 values of m a thread the one that leaves the
+// fewest turns idle.
+static void modal_launch(Ctx &c, Pts pts, int64_t npts, int Nt, int M, double *f, double *scale, double *decay,
+                         double kappa, double gam_re, double gam_im, double2 *kout) {
+    const ModalSize z(Nt, M);
+    const int PT = (size_t)z.shared(16) * sizeof(double) <= 80 * 1024 ? 16 : 4;
+    const size_t shm = (size_t)z.shared(PT) * sizeof(double);
+    AXS_REQUIRE(shm <= 160 * 1024, AXS_EINVAL, "mode count or wavenumber too large for the modal kernel");
+    hipLaunchKernelGGL(toroidal_kernel, dim3(ceil_div(npts, 64)), dim3(64), 0, c.stream, pts, npts, z.nq, f, scale,
+                       decay);
+    AXS_HIP(hipGetLastError());
+    int MB = 3;
+    if (PT == 16) {
+        double best = 1e300;
+        for (int b : {4, 3, 2}) {
+            const double cost = (double)ceil_div(M + 1, 16 * b) * (b + 1.5);   // the loads of c and the new pairs cost as much as 1.5 values
+            if (cost < best) best = cost, MB = b;
+        }
+    }
+    const dim3 grid((unsigned)ceil_div(npts, PT)), blk(256);
+    if (PT == 4)
+        hipLaunchKernelGGL((modal_kernel<4, 3>), grid, blk, shm, c.stream, pts, npts, Nt, M, f, scale, decay,
+                           kappa, gam_re, gam_im, kout);
+    else if (MB == 2)
+        hipLaunchKernelGGL((modal_kernel<16, 2>), grid, blk, shm, c.stream, pts, npts, Nt, M, f, scale, decay,
+                           kappa, gam_re, gam_im, kout);
+    else if (MB == 3)
+        hipLaunchKernelGGL((modal_kernel<16, 3>), grid, blk, shm, c.stream, pts, npts, Nt, M, f, scale, decay,
+                           kappa, gam_re, gam_im, kout);
+    else
+        hipLaunchKernelGGL((modal_kernel<16, 4>), grid, blk, shm, c.stream, pts, npts, Nt, M, f, scale, decay,
+                           kappa, gam_re, gam_im, kout);
+    AXS_HIP(hipGetLastError());
 }
 
 // ---------------------------------------------------------------------------
@@ -385,24 +592,37 @@ __global__ void scatter_far_kernel(const int2 *__restrict__ pairs, int n, int p,
     A[((int64_t)m * NG + pr.x) * NG + pr.y * p + o % p] = kval[idx];
 }
 
-__global__ void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int NG, int p,
-                                   const double2 *__restrict__ kval, const double *__restrict__ lag,
-                                   int64_t base, double2 *__restrict__ A) {
+// Entries of the near pairs: sum over a pair's points of the kernel values
+// (M + 1 complex numbers a point: 2 (M + 1) rows) times the p basis values, on the FP64
+// matrix cores, 16 rows per workgroup with the points split between its four
+// wavefronts.  One thread per entry read every kernel value p times: FIGR
+__global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int NG, int p,
+                                                          const double2 *__restrict__ kval,
+                                                          const double *__restrict__ lag, int64_t base,
+                                                          double2 *__restrict__ A) {
+    __shared__ double s_acc[4][16][17];
     const NearDesc d = desc[blockIdx.x];
-    const int per = d.n0 + d.n1;
-    const double2 *kv = kval + (base + d.first) * (M + 1);
+    const int per = d.n0 + d.n1, R = 2 * (M + 1), row0 = blockIdx.y * 16;
+    const double *kv = (const double *)(kval + (base + d.first) * (M + 1));
     const double *lg = lag + (int64_t)d.first * p;
-    for (int t = threadIdx.x; t < (M + 1) * p; t += blockDim.x) {
-        const int m = t / p, j = t % p;
-        double re = 0, im = 0;
-        for (int q = 0; q < per; ++q) {
-            const double2 v = kv[(int64_t)q * (M + 1) + m];
-            const double l = lg[(int64_t)q * p + j];
-            re = fma(v.x, l, re);
-            im = fma(v.y, l, im);
-        }
-        A[((int64_t)m * NG + d.i) * NG + d.P * p + j] = make_double2(re, im);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
+    const bool row_in = row0 + l16 < R, col_in = l16 < p;
+    gj_f64x4 acc = {0, 0, 0, 0};
+#pragma unroll 4
+    for (int q0 = wave * 4; q0 < per; q0 += 16) {
+        const int q = q0 + g;
+        const double a = row_in && q < per ? kv[(int64_t)q * R + row0 + l16] : 0.0;
+        const double b = col_in && q < per ? lg[q * p + l16] : 0.0;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s_acc[wave][g + 4 * v][l16] = acc[v];
+    __syncthreads();
+    const int comp = threadIdx.x & 1, j = (threadIdx.x >> 1) & 15, rl = 2 * (threadIdx.x >> 5) + comp;
+    const int m = (row0 + rl) / 2;
+    if (m <= M && j < p)
+        ((double *)(A + ((int64_t)m * NG + d.i) * NG + d.P * p + j))[comp] =
+            (s_acc[0][rl][j] + s_acc[1][rl][j]) + (s_acc[2][rl][j] + s_acc[3][rl][j]);
 }
 
 __global__ void add_half_identity_kernel(double2 *A, int M, int NG) {
@@ -425,7 +645,8 @@ __global__ void add_half_identity_kernel(double2 *A, int M, int NG) {
 // then need A <- A (pivot rows zeroed) + T A_old[R, :], one product with an
 // inner dimension of 16:
 //   gj_panel_kernel  - one workgroup per matrix, one row per thread held in
-//                      registers; bound by its 16 serial steps (two barriers each);
+//                      registers; bound by its 16 serial steps (one barrier each:
+//                      every wavefront offers its candidate row);
 //   gj_update_kernel - a 16 x 16 tile per wavefront on the FP64 matrix cores,
 //                      read from one copy of the matrix and written to the other
 //                      (the pivot rows are read by every tile).
@@ -443,10 +664,20 @@ struct GJItem {
 constexpr int GJB = 16;
 constexpr int GJ_ROWS = 1024;   // one thread per row: larger matrices take gauss_jordan_kernel
 
-typedef double gj_f64x4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ const double2 *gj_src(const GJItem &it, int step) {
     return step == 0 ? it.A : (step & 1) ? it.b0 : it.b1;
+}
+
+// largest x of the wavefront, by moves between neighbouring lanes (ds_bpermute takes
+// ten times as long in this chain)
+__device__ __forceinline__ int wave_max(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x111, 0xf, 0xf, false));   // row_shr:1
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x112, 0xf, 0xf, false));   // row_shr:2
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xf, false));   // row_shr:4
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x118, 0xf, 0xf, false));   // row_shr:8
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xf, 0xf, false));   // row_bcast:15
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xf, 0xf, false));   // row_bcast:31
+    return __builtin_amdgcn_readlane(x, 63);
 }
 
 template <int BS>
@@ -457,75 +688,75 @@ __global__ __launch_bounds__(BS) void gj_panel_kernel(const GJItem *__restrict__
     const int nb = min(GJB, NG - k0);
     const int r = threadIdx.x, lane = r & 63, wave = r >> 6;
     constexpr int NW = BS / 64;
-    __shared__ double s_max[2][NW];
-    __shared__ int s_row[2][NW];
-    __shared__ double2 s_piv[2][GJB];
+    __shared__ int s_max[2][NW], s_row[2][NW];
+    __shared__ double2 s_cand[2][NW][GJB];   // each wavefront's candidate row
     const bool live = r < NG;
-    const double2 *src = gj_src(it, step) + (int64_t)r * NG + k0;
+    // clamped, not conditional, so that all loads are in flight together
+    const double2 *src = gj_src(it, step) + (int64_t)min(r, NG - 1) * NG + k0;
     double ar[GJB], ai[GJB];
 #pragma unroll
     for (int j = 0; j < GJB; ++j) {
-        double2 v = make_double2(0.0, 0.0);
-        if (live && j < nb) v = src[j];
+        const double2 v = src[min(j, nb - 1)];
         ar[j] = v.x;
         ai[j] = v.y;
     }
-    int mycol = !live ? 0 : step == 0 ? -1 : it.col[r];
-#pragma unroll
+    int mycol = step == 0 ? -1 : it.col[min(r, NG - 1)];
+    if (!live) mycol = 0;
+    // The column of a step is always the first register, and every step moves the row
+    // on by one, in the assignments it makes anyway: a rolled loop with constant
+    // indices (unrolled, its 40 KB of code are fetched as slowly as they are run).
+    // Steps past the last column only move the row.
+#pragma unroll 1
     for (int c = 0; c < GJB; ++c) {
-        if (c >= nb) break;
-        double mag = -1.0;
+        // the upper half of |a|^2 orders the candidates to 1e-6, plenty for a pivot
+        int mag = -1;
         if (mycol < 0) {
-            mag = ar[c] * ar[c] + ai[c] * ai[c];
-            if (!(mag >= 0.0)) mag = 0.0;   // NaN: the result is NaN whatever the pivot
+            const double v = ar[0] * ar[0] + ai[0] * ai[0];
+            mag = v >= 0.0 ? __double2hiint(v) : 0;   // NaN: the result is NaN whatever the pivot
         }
-        double wm = mag;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) wm = fmax(wm, __shfl_xor(wm, o, 64));
+        const int wm = wave_max(mag);
         const int first = __ffsll((unsigned long long)__ballot(mag == wm)) - 1;
-        if (lane == 0) {
+        if (lane == first) {
             s_max[c & 1][wave] = wm;
-            s_row[c & 1][wave] = wave * 64 + first;
+            s_row[c & 1][wave] = r;
+#pragma unroll
+            for (int j = 0; j < GJB; ++j) s_cand[c & 1][wave][j] = make_double2(ar[j], ai[j]);
         }
         __syncthreads();
-        double best = s_max[c & 1][0];
-        int pr = s_row[c & 1][0];
+        int best = s_max[c & 1][0], bw = 0;
 #pragma unroll
         for (int w = 1; w < NW; ++w)
             if (s_max[c & 1][w] > best) {
                 best = s_max[c & 1][w];
-                pr = s_row[c & 1][w];
+                bw = w;
             }
-        if (r == pr) {
-            const double den = ar[c] * ar[c] + ai[c] * ai[c];
-            const double pr_ = ar[c] / den, pi_ = -ai[c] / den;
-            ar[c] = 1.0;
-            ai[c] = 0.0;
-#pragma unroll
-            for (int j = 0; j < GJB; ++j) {
-                const double x = ar[j] * pr_ - ai[j] * pi_, y = ar[j] * pi_ + ai[j] * pr_;
-                ar[j] = x;
-                ai[j] = y;
-                s_piv[c & 1][j] = make_double2(x, y);
-            }
+        const bool step_in = c < nb, mine = step_in && r == s_row[c & 1][bw];
+        const double2 *u = s_cand[c & 1][bw];
+        const double2 pv = u[0];
+        const double den = 1.0 / (pv.x * pv.x + pv.y * pv.y);
+        const double vr = pv.x * den, vi = -pv.y * den;   // 1 / pivot
+        // row r: a - f u with f = a_0 / pivot, -f in the column itself; pivot row:
+        // u / pivot, 1 / pivot in the column, which is 0 - g u with g = -1 / pivot
+        double fr = ar[0] * vr - ai[0] * vi, fi = ar[0] * vi + ai[0] * vr;
+        if (mine) {
+            fr = -vr;
+            fi = -vi;
             mycol = k0 + c;
-            it.prow[k0 + c] = r;
         }
-        __syncthreads();
-        if (r != pr) {
-            const double fr = ar[c], fi = ai[c];
-            ar[c] = 0.0;
-            ai[c] = 0.0;
+        const double a0r = step_in ? -fr : ar[0], a0i = step_in ? -fi : ai[0];
+        if (!step_in) fr = fi = 0.0;
 #pragma unroll
-            for (int j = 0; j < GJB; ++j) {
-                const double2 u = s_piv[c & 1][j];
-                ar[j] = fma(-fr, u.x, fma(fi, u.y, ar[j]));
-                ai[j] = fma(-fr, u.y, fma(-fi, u.x, ai[j]));
-            }
+        for (int j = 1; j < GJB; ++j) {
+            const double2 x = u[j];
+            ar[j - 1] = fma(-fr, x.x, fma(fi, x.y, mine ? 0.0 : ar[j]));
+            ai[j - 1] = fma(-fr, x.y, fma(-fi, x.x, mine ? 0.0 : ai[j]));
         }
+        ar[GJB - 1] = a0r;
+        ai[GJB - 1] = a0i;
     }
     if (!live) return;
     it.col[r] = mycol;
+    if (mycol >= k0) it.prow[mycol] = r;   // here, not in the loop, whose barriers would wait for the store
 #pragma unroll
     for (int j = 0; j < GJB; ++j) it.T[(int64_t)r * GJB + j] = make_double2(ar[j], ai[j]);
 }
@@ -549,26 +780,23 @@ __global__ __launch_bounds__(256) void gj_update_kernel(const GJItem *__restrict
         }
         return;
     }
+    // rows and columns past the edge are clamped and not stored: no load waits for a branch
+    const int colc = min(col, NG - 1);
     gj_f64x4 accr, acci;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const int row = r0 + q + 4 * v;
-        double2 x = make_double2(0.0, 0.0);
-        if (row < NG && col < NG) {
-            const int pc = it.col[row];
-            if (pc < k0) x = src[(int64_t)row * NG + col];   // not a pivot row of this block
-        }
-        accr[v] = x.x;
-        acci[v] = x.y;
+        const int row = min(r0 + q + 4 * v, NG - 1);
+        const bool keep = it.col[row] < k0;   // not a pivot row of this block
+        const double2 x = src[(int64_t)row * NG + colc];
+        accr[v] = keep ? x.x : 0.0;
+        acci[v] = keep ? x.y : 0.0;
     }
-    const int arow = r0 + (lane & 15);
+    const int arow = min(r0 + (lane & 15), NG - 1);
 #pragma unroll
     for (int k = 0; k < GJB; k += 4) {
-        double2 a = make_double2(0.0, 0.0), b = a;
-        if (k + q < nb) {
-            if (arow < NG) a = it.T[(int64_t)arow * GJB + k + q];
-            if (col < NG) b = src[(int64_t)it.prow[k0 + k + q] * NG + col];
-        }
+        double2 a = it.T[(int64_t)arow * GJB + k + q];
+        double2 b = src[(int64_t)it.prow[k0 + min(k + q, nb - 1)] * NG + colc];
+        if (k + q >= nb) a = b = make_double2(0.0, 0.0);
         accr = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, accr, 0, 0, 0);
         acci = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, acci, 0, 0, 0);
         accr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, accr, 0, 0, 0);
@@ -766,13 +994,10 @@ void precompute_shape(Ctx &c, Shape &s) {
     const int NG = s.NG, p = s.p, M = s.M, np_ = s.n_panels;
     AXS_REQUIRE(p <= PMAX, AXS_EINVAL, "at most 16 nodes per panel are supported");
     s.Nt = modal_nt(s);
-    const int Nt = s.Nt, L = Nt / 2 - 1, nq = M + L + 1;
+    const int Nt = s.Nt, nq = M + Nt / 2;
 
-    std::vector<double> sn, sw, gu, gwq, qu, qw;
+    std::vector<double> sn, sw;
     gauss_legendre(p, sn, sw);
-    const int ngl = level_points(p), own_pts = OWN_LEV * ngl + OWN_NQ;
-    gauss_legendre(ngl, gu, gwq);
-    gauss_legendre(OWN_NQ, qu, qw);
     std::vector<double> lden(p);
     for (int j = 0; j < p; ++j) {
         double d = 1.0;
@@ -780,6 +1005,21 @@ void precompute_shape(Ctx &c, Shape &s) {
             if (k != j) d *= (sn[j] - sn[k]);
         lden[j] = 1.0 / d;
     }
+    // node data
+    std::vector<double> nr(NG), nz(NG), aw(NG), plen(np_, 0.0), smax(np_, 0.0);
+    for (int i = 0; i < NG; ++i) {
+        const double sp = std::hypot(s.dr[i], s.dz[i]);
+        nr[i] = -s.dz[i] / sp;
+        nz[i] = s.dr[i] / sp;
+        aw[i] = s.r[i] * sp * s.gw[i];
+        plen[i / p] += sp * s.gw[i];
+        smax[i / p] = std::max(smax[i / p], sp);
+    }
+    std::vector<double> gu, gwq, qu, qw;
+    const int ngl = level_points(p, s.kappa * *std::max_element(plen.begin(), plen.end()));
+    const int own_pts = OWN_LEV * ngl + OWN_NQ;
+    gauss_legendre(ngl, gu, gwq);
+    gauss_legendre(OWN_NQ, qu, qw);
     // the own-panel rule on [0, 1], singular at 0
     std::vector<double> ownx, ownw;
     for (int lev = 0; lev < OWN_LEV; ++lev)
@@ -793,15 +1033,16 @@ void precompute_shape(Ctx &c, Shape &s) {
         ownx.push_back(h * std::pow(u, OWN_Q));
         ownw.push_back(h * OWN_Q * std::pow(u, OWN_Q - 1) * 0.5 * qw[k]);
     }
-    // node data
-    std::vector<double> nr(NG), nz(NG), aw(NG), plen(np_, 0.0), smax(np_, 0.0);
+    // derivative of every panel's interpolant at its nodes
+    std::vector<double> rd(NG, 0.0), zd(NG, 0.0);
     for (int i = 0; i < NG; ++i) {
-        const double sp = std::hypot(s.dr[i], s.dz[i]);
-        nr[i] = -s.dz[i] / sp;
-        nz[i] = s.dr[i] / sp;
-        aw[i] = s.r[i] * sp * s.gw[i];
-        plen[i / p] += sp * s.gw[i];
-        smax[i / p] = std::max(smax[i / p], sp);
+        const int P0 = i / p * p, a = i - P0;
+        for (int k = 0; k < p; ++k) {
+            if (k == a) continue;
+            const double w = lden[k] / (lden[a] * (sn[a] - sn[k]));
+            rd[i] += w * (s.r[P0 + k] - s.r[i]);
+            zd[i] += w * (s.z[P0 + k] - s.z[i]);
+        }
     }
     // near panels and split points per target (host geometry)
     std::vector<std::vector<NearDesc>> near(NG);
@@ -859,7 +1100,8 @@ void precompute_shape(Ctx &c, Shape &s) {
         return o;
     };
     const size_t o_sn = put(sn), o_lden = put(lden), o_gu = put(gu), o_gw = put(gwq), o_ox = put(ownx),
-                 o_ow = put(ownw), o_r = put(s.r), o_z = put(s.z), o_nr = put(nr), o_nz = put(nz), o_aw = put(aw);
+                 o_ow = put(ownw), o_r = put(s.r), o_z = put(s.z), o_nr = put(nr), o_nz = put(nz), o_aw = put(aw),
+                 o_rd = put(rd), o_zd = put(zd);
     double *dc = (double *)c.dalloc(hc.size() * sizeof(double));
     AXS_HIP(hipMemcpyAsync(dc, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
 
@@ -897,10 +1139,9 @@ void precompute_shape(Ctx &c, Shape &s) {
         const int64_t nfar = (int64_t)far.size() * p;
         const int64_t P = nfar + nnear;
         // point storage
-        double *pbuf = (double *)c.scratch(WS_MISC, ((size_t)P * 7 + (size_t)nnear * p) * sizeof(double));
-        Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, pbuf + 7 * P};
+        double *pbuf = (double *)c.scratch(WS_MISC, ((size_t)P * 9 + (size_t)nnear * p) * sizeof(double));
+        Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, pbuf + 9 * P};
         double *qv = (double *)c.scratch(WS_TMP, (size_t)P * nq * sizeof(double));
-        double *dqv = (double *)c.scratch(WS_TMP2, (size_t)P * nq * sizeof(double));
         double2 *kv = (double2 *)c.scratch(WS_TMP3, (size_t)P * (M + 1) * sizeof(double2));
         int2 *d_far = (int2 *)c.scratch(WS_RED, far.size() * sizeof(int2));
         NearDesc *d_nd = (NearDesc *)c.scratch(WS_GEMM, nd.size() * sizeof(NearDesc));
@@ -913,25 +1154,18 @@ void precompute_shape(Ctx &c, Shape &s) {
         // a target's own panel is always near, so no batch is without near points
         AXS_HIP(hipMemcpyAsync(d_nd, nd.data(), nd.size() * sizeof(NearDesc), hipMemcpyHostToDevice, c.stream));
         hipLaunchKernelGGL(gen_near_kernel, dim3(nd.size()), dim3(128), 0, c.stream, d_nd, p, dc + o_sn, dc + o_lden,
-                           dc + o_gu, dc + o_gw, ngl, dc + o_ox, dc + o_ow, dc + o_r, dc + o_z, pts, nfar);
+                           dc + o_gu, dc + o_gw, ngl, dc + o_ox, dc + o_ow, dc + o_r, dc + o_z, dc + o_rd, dc + o_zd, pts,
+                           nfar);
         AXS_HIP(hipGetLastError());
-        hipLaunchKernelGGL(toroidal_kernel, dim3(ceil_div(P, 64)), dim3(64), 0, c.stream, pts, P, nq - 1, qv,
-                           dqv);
-        AXS_HIP(hipGetLastError());
-        constexpr int WPB = 4;
-        const int per = 4 * (Nt / 2 + 1) + 2 * (L + 1) + 2 * (M + 1) + 2 * nq;
-        const size_t shm = (Nt + WPB * per) * sizeof(double);
-        AXS_REQUIRE(shm <= 160 * 1024, AXS_EINVAL, "mode count or wavenumber too large for the modal kernel");
-        hipLaunchKernelGGL(modal_kernel<WPB>, dim3(ceil_div(P, WPB)), dim3(64 * WPB), shm, c.stream, pts, P, Nt,
-                           M, qv, dqv, s.kappa, s.kappa > 0 ? 0.0 : s.eta, s.kappa > 0 ? s.eta : 0.0, kv);
-        AXS_HIP(hipGetLastError());
+        modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, s.kappa, s.kappa > 0 ? 0.0 : s.eta, s.kappa > 0 ? s.eta : 0.0,
+                     kv);
         if (nfar) {
             hipLaunchKernelGGL(scatter_far_kernel, dim3(ceil_div(nfar * (M + 1), 256)), dim3(256), 0, c.stream,
                                d_far, (int)far.size(), p, M, NG, kv, A);
             AXS_HIP(hipGetLastError());
         }
-        hipLaunchKernelGGL(near_reduce_kernel, dim3(nd.size()), dim3(256), 0, c.stream, d_nd, M, NG, p, kv, pts.lag,
-                           nfar, A);
+        hipLaunchKernelGGL(near_reduce_kernel, dim3(nd.size(), (unsigned)ceil_div(2 * (M + 1), 16)), dim3(256), 0, c.stream,
+                           d_nd, M, NG, p, kv, pts.lag, nfar, A);
         AXS_HIP(hipGetLastError());
         i0 = i1;
         if (i0 >= NG) {
@@ -1024,21 +1258,12 @@ void invert_shapes(Ctx &c) {
 
 void modal_values(Ctx &c, double kappa, double gam_re, double gam_im, int M, int Nt,
                   const std::vector<double> &h, int64_t P, double2 *kout) {
-    const int L = Nt / 2 - 1, nq = M + L + 1;
-    double *pbuf = (double *)c.scratch(WS_MISC, (size_t)P * 7 * sizeof(double));
+    const int nq = M + Nt / 2;
+    double *pbuf = (double *)c.scratch(WS_MISC, (size_t)P * 9 * sizeof(double));
     AXS_HIP(hipMemcpy(pbuf, h.data(), (size_t)P * 7 * sizeof(double), hipMemcpyHostToDevice));
     Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, nullptr};
     double *qv = (double *)c.scratch(WS_TMP, (size_t)P * nq * sizeof(double));
-    double *dqv = (double *)c.scratch(WS_TMP2, (size_t)P * nq * sizeof(double));
-    hipLaunchKernelGGL(toroidal_kernel, dim3(ceil_div(P, 64)), dim3(64), 0, c.stream, pts, P, nq - 1, qv, dqv);
-    AXS_HIP(hipGetLastError());
-    constexpr int WPB = 4;
-    const int per = 4 * (Nt / 2 + 1) + 2 * (L + 1) + 2 * (M + 1) + 2 * nq;
-    const size_t shm = (Nt + WPB * per) * sizeof(double);
-    AXS_REQUIRE(shm <= 160 * 1024, AXS_EINVAL, "mode count or wavenumber too large for the modal kernel");
-    hipLaunchKernelGGL(modal_kernel<WPB>, dim3(ceil_div(P, WPB)), dim3(64 * WPB), shm, c.stream, pts, P, Nt, M,
-                       qv, dqv, kappa, gam_re, gam_im, kout);
-    AXS_HIP(hipGetLastError());
+    modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, kappa, gam_re, gam_im, kout);
 }
 
 void split_planar(Ctx &c, Shape &s, const double *src, double *r64, double *i64, float *r32, float *i32) {

@@ -108,3 +108,26 @@ def test_modal_matrices_against_the_reference(kind, kappa, eta, M):
         err = np.max(np.abs(A[:, i, :] - row)) / np.max(np.abs(row))
         assert err < 1e-11, (kind, i, err)
     ctx.close()
+
+
+@pytest.mark.parametrize("panels,kappa,eta,M", [(3, 1.0, 1.0, 0), (3, 2.0, 2.0, 31), (3, 1.0, 1.0, 32), (3, 1.0, 1.0, 47),
+                                                (3, 1.0, 1.0, 50), (2, 0.0, 1.0, 40), (2, 0.0, 1.0, 64),
+                                                (16, 45.0, 45.0, 70)])
+def test_modal_values_at_edges(panels, kappa, eta, M):
+    """The modal kernel at the numbers of modes and samples where its split changes, with more modes
+    than series terms, and with four points a workgroup; bound as above."""
+    from oracle.nystrom import Shape
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    c = geo.sphere(1.0, panels, 10)
+    ctx = Context(0)
+    ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, eta, M, np.zeros(3), np.eye(3))
+    ctx.precompute_scattering()
+    A = ctx.modal_matrices(0, 0, M=M, NG=c.NG).cpu().numpy()
+    ref = Shape(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, eta, M, Nt=512 if kappa > 10 else 256)
+    for i in (0, c.NG // 2 + 3):
+        row = ref.modal_row(i)
+        row[:, i] += 0.5
+        err = np.max(np.abs(A[:, i, :] - row)) / np.max(np.abs(row))
+        assert err < 1e-11, (i, err)
+    ctx.close()
