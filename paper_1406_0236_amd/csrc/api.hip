@@ -13,7 +13,7 @@ namespace axs {
 
 void gauss_legendre_public(int n, std::vector<double> &x, std::vector<double> &w);
 void split_planar(Ctx &c, Shape &s, const double *src, double *r64, double *i64, float *r32, float *i32);
-void build_node_tables(Ctx &c);
+void build_node_tables(Ctx &c, Upload &up);
 void interbody_shape(Ctx &c, int prec, int nrhs, int out[4]);
 
 void *Ctx::dalloc(size_t bytes) {
@@ -184,8 +184,7 @@ void apply_precond(Ctx &c, const void *x, void *y, int nrhs, int prec, double be
 // ---------------------------------------------------------------------------
 static void precompute_all(Ctx &c) {
     AXS_REQUIRE(!c.bodies.empty(), AXS_ESTATE, "no bodies");
-    for (auto &s : c.shapes) precompute_shape(c, s);
-    invert_shapes(c);
+    precompute_shapes(c);
     finish_precompute(c);
 }
 
@@ -242,8 +241,8 @@ void finish_precompute(Ctx &c) {
         xo += (int64_t)nb * s.NF * s.NG;
         c.max_NG = std::max(c.max_NG, s.NG);
     }
-    c.gemm = (GemmBatch *)c.dalloc(gb.size() * sizeof(GemmBatch));
-    AXS_HIP(hipMemcpyAsync(c.gemm, gb.data(), gb.size() * sizeof(GemmBatch), hipMemcpyHostToDevice, c.stream));
+    Upload up(c);
+    const size_t o_gb = up.put(gb);
     c.ngemm = (int)gb.size();
     // twiddles per distinct N_F
     std::map<int, int64_t> twoff;
@@ -258,11 +257,7 @@ void finish_precompute(Ctx &c) {
             tw.push_back(std::sin(a));
         }
     }
-    c.tw64 = (double *)c.dalloc(tw.size() * sizeof(double));
-    c.tw32 = (float *)c.dalloc(tw.size() * sizeof(float));
-    std::vector<float> tw32(tw.begin(), tw.end());
-    AXS_HIP(hipMemcpyAsync(c.tw64, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
-    AXS_HIP(hipMemcpyAsync(c.tw32, tw32.data(), tw32.size() * sizeof(float), hipMemcpyHostToDevice, c.stream));
+    const size_t o_tw64 = up.put(tw), o_tw32 = up.put(std::vector<float>(tw.begin(), tw.end()));
     // body descriptors
     c.body_dev_host.clear();
     for (auto &b : c.bodies) {
@@ -279,11 +274,13 @@ void finish_precompute(Ctx &c) {
         d.shape = b.shape;
         c.body_dev_host.push_back(d);
     }
-    c.body_dev = (BodyDev *)c.dalloc(c.body_dev_host.size() * sizeof(BodyDev));
-    AXS_HIP(hipMemcpyAsync(c.body_dev, c.body_dev_host.data(), c.body_dev_host.size() * sizeof(BodyDev),
-                           hipMemcpyHostToDevice, c.stream));
-    build_node_tables(c);
-    AXS_HIP(hipStreamSynchronize(c.stream));
+    const size_t o_bd = up.put(c.body_dev_host);
+    build_node_tables(c, up);   // adds its own tables and uploads the block
+    c.gemm = up.at<GemmBatch>(o_gb);
+    c.tw64 = up.at<double>(o_tw64);
+    c.tw32 = up.at<float>(o_tw32);
+    c.body_dev = up.at<BodyDev>(o_bd);
+    AXS_HIP(hipStreamSynchronize(c.stream));   // the upload comes from pageable host memory
     c.precomputed = true;
 }
 

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstring>
 #include <cstdio>
 #include <string>
 #include <memory>
@@ -296,8 +297,37 @@ struct Skeleton {
 // launches (defined in the .hip files)
 // ---------------------------------------------------------------------------
 // setup.hip
-void precompute_shape(Ctx &c, Shape &s);   // A~_m of one shape
-void invert_shapes(Ctx &c);                 // S_m = A~_m^{-1} of every shape
+// Host arrays gathered into one block and copied to the device at once (a copy
+// from pageable memory holds the host up for some 10 us whatever its size).  The
+// object has to outlive the copy, until the next synchronisation of c.stream.
+struct Upload {
+    Ctx &c;
+    std::vector<char> host;
+    char *dev = nullptr;
+    explicit Upload(Ctx &c_) : c(c_) {}
+    Upload(const Upload &) = delete;
+    Upload &operator=(const Upload &) = delete;
+    size_t put(const void *p, size_t bytes) {   // offset of the copy in the block
+        const size_t o = (host.size() + 255) / 256 * 256;
+        host.resize(o + bytes);
+        if (bytes) memcpy(host.data() + o, p, bytes);
+        return o;
+    }
+    template <class T>
+    size_t put(const std::vector<T> &v) {
+        return put(v.data(), v.size() * sizeof(T));
+    }
+    void commit() {   // the block belongs to the context (c.dfree(dev) gives it back earlier)
+        dev = (char *)c.dalloc(std::max<size_t>(host.size(), 1));
+        AXS_HIP(hipMemcpyAsync(dev, host.data(), host.size(), hipMemcpyHostToDevice, c.stream));
+    }
+    template <class T>
+    T *at(size_t offset) const {
+        return (T *)(dev + offset);
+    }
+};
+
+void precompute_shapes(Ctx &c);   // A~_m and S_m = A~_m^{-1} of every shape
 void gauss_legendre_rule(int n, std::vector<double> &x, std::vector<double> &w);
 // k^G_m w (m = 0..M) for arbitrary (target ring, source ring) pairs: host arrays
 // pts[7][P] = (r_t, r_s, r_s - r_t, z_s - z_t, n_r, n_z of the source, weight);

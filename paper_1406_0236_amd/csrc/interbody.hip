@@ -1397,7 +1397,7 @@ __global__ __launch_bounds__(64) void ring_tables_kernel(const TableBody *__rest
 }
 
 // node arrays, ring tables, body frames, per-node azimuth cos/sin, MFMA operands
-void build_node_tables(Ctx &c) {
+void build_node_tables(Ctx &c, Upload &up) {
     const int64_t N = c.N;
     AXS_REQUIRE(N < (int64_t)INT32_MAX, AXS_EINVAL, "node count beyond 32-bit ring tables");
     // contour records of the distinct shapes
@@ -1481,19 +1481,16 @@ void build_node_tables(Ctx &c) {
         }
         return tab;
     }();
-    auto up = [&](const void *h, size_t bytes) {
-        void *d = c.dalloc(bytes);
-        AXS_HIP(hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, c.stream));
-        return d;
-    };
-    const std::vector<float> fr32(fr.begin(), fr.end());
-    c.frame64 = (double *)up(fr.data(), fr.size() * sizeof(double));
-    c.frame32 = (float *)up(fr32.data(), fr32.size() * sizeof(float));
-    c.sctab = (double2 *)up(sctab.data(), sctab.size() * sizeof(double));
-    c.body_off = (int64_t *)up(bo.data(), bo.size() * sizeof(int64_t));
-    c.blk_off = (int32_t *)up(bk.data(), bk.size() * sizeof(int32_t));
-    double *d_cont = (double *)up(cont.data(), cont.size() * sizeof(double));
-    TableBody *d_tb = (TableBody *)up(tb.data(), tb.size() * sizeof(TableBody));
+    const size_t o_f64 = up.put(fr), o_f32 = up.put(std::vector<float>(fr.begin(), fr.end())), o_sc = up.put(sctab),
+                 o_bo = up.put(bo), o_bk = up.put(bk), o_cont = up.put(cont), o_tb = up.put(tb);
+    up.commit();
+    c.frame64 = up.at<double>(o_f64);
+    c.frame32 = up.at<float>(o_f32);
+    c.sctab = up.at<double2>(o_sc);
+    c.body_off = up.at<int64_t>(o_bo);
+    c.blk_off = up.at<int32_t>(o_bk);
+    const double *d_cont = up.at<double>(o_cont);
+    const TableBody *d_tb = up.at<TableBody>(o_tb);
     NodeOut o{};
     o.g64 = c.g64 = (double *)c.dalloc(7 * N * sizeof(double));
     o.g32 = c.g32 = (float *)c.dalloc(6 * N * sizeof(float));
@@ -1516,9 +1513,6 @@ void build_node_tables(Ctx &c) {
                            nr, c.ring_i, c.ring_g64, c.ring_g32, c.ring_pair);
         AXS_HIP(hipGetLastError());
     }
-    AXS_HIP(hipStreamSynchronize(c.stream));   // the uploads come from pageable host memory
-    c.dfree(d_cont);
-    c.dfree(d_tb);
 }
 
 template <typename R, int TPT, int BS, bool LAP>

@@ -33,6 +33,7 @@
 // with partial pivoting (one workgroup per mode).
 #include <algorithm>
 #include <cmath>
+#include <memory>
 
 #include "axs_internal.h"
 #include "fp64_math.h"
@@ -990,11 +991,26 @@ static int modal_nt(const Shape &s) {
     return nt;
 }
 
-void precompute_shape(Ctx &c, Shape &s) {
-    const int NG = s.NG, p = s.p, M = s.M, np_ = s.n_panels;
+// a shape's evaluation points: what its launches need, with the offsets of the
+// tables in the upload
+struct ShapePlan {
+    int ngl = 0;
+    size_t tab = 0;   // the doubles below, in one array
+    size_t o_sn = 0, o_lden = 0, o_gu = 0, o_gw = 0, o_ox = 0, o_ow = 0, o_r = 0, o_z = 0, o_nr = 0, o_nz = 0, o_aw = 0,
+           o_rd = 0, o_zd = 0;
+    struct Batch {   // target rows
+        size_t far = 0, near = 0;
+        int nfar = 0, nd = 0;
+        int64_t nnear = 0;
+    };
+    std::vector<Batch> batches;
+};
+
+static ShapePlan plan_shape(Shape &s, Upload &up) {
+    const int NG = s.NG, p = s.p, np_ = s.n_panels;
     AXS_REQUIRE(p <= PMAX, AXS_EINVAL, "at most 16 nodes per panel are supported");
     s.Nt = modal_nt(s);
-    const int Nt = s.Nt, nq = M + Nt / 2;
+    ShapePlan plan;
 
     std::vector<double> sn, sw;
     gauss_legendre(p, sn, sw);
@@ -1016,7 +1032,7 @@ void precompute_shape(Ctx &c, Shape &s) {
         smax[i / p] = std::max(smax[i / p], sp);
     }
     std::vector<double> gu, gwq, qu, qw;
-    const int ngl = level_points(p, s.kappa * *std::max_element(plen.begin(), plen.end()));
+    const int ngl = plan.ngl = level_points(p, s.kappa * *std::max_element(plen.begin(), plen.end()));
     const int own_pts = OWN_LEV * ngl + OWN_NQ;
     gauss_legendre(ngl, gu, gwq);
     gauss_legendre(OWN_NQ, qu, qw);
@@ -1053,6 +1069,17 @@ void precompute_shape(Ctx &c, Shape &s) {
         endz[2 * P] = interp_at(sn, &s.z[P * p], p, -1.0);
         endz[2 * P + 1] = interp_at(sn, &s.z[P * p], p, 1.0);
     }
+    // circles around the panels' nodes and ends: most panels are beyond their length
+    // from a target by these alone
+    std::vector<double> cr(np_), cz(np_), crad(np_, 0.0);
+    for (int P = 0; P < np_; ++P) {
+        cr[P] = 0.5 * (endr[2 * P] + endr[2 * P + 1]);
+        cz[P] = 0.5 * (endz[2 * P] + endz[2 * P + 1]);
+        for (int k = -2; k < p; ++k) {
+            const double a = k < 0 ? endr[2 * P + k + 2] : s.r[P * p + k], b = k < 0 ? endz[2 * P + k + 2] : s.z[P * p + k];
+            crad[P] = std::max(crad[P], std::hypot(a - cr[P], b - cz[P]));
+        }
+    }
     // points on one side (length Ls in s) of a panel at distance d: halve until
     // the innermost interval is shorter than d / 8
     auto side_points = [&](double Ls, double d, double speed) {
@@ -1064,6 +1091,8 @@ void precompute_shape(Ctx &c, Shape &s) {
     for (int i = 0; i < NG; ++i) {
         const int own = i / p;
         for (int P = 0; P < np_; ++P) {
+            const double lim = (plen[P] + crad[P]) * (1.0 + 1e-12), ca = cr[P] - s.r[i], cb = cz[P] - s.z[i];
+            if (std::abs(P - own) > 1 && ca * ca + cb * cb > lim * lim) continue;
             double best2 = 1e300, bs = 0;
             auto consider = [&](double rr, double zz, double sv) {
                 const double a = rr - s.r[i], b = zz - s.z[i], d2 = a * a + b * b;
@@ -1092,23 +1121,16 @@ void precompute_shape(Ctx &c, Shape &s) {
             near[i].push_back(d);
         }
     }
-    // device constants, one block
     std::vector<double> hc;
     auto put = [&](const std::vector<double> &v) {
         const size_t o = hc.size();
         hc.insert(hc.end(), v.begin(), v.end());
         return o;
     };
-    const size_t o_sn = put(sn), o_lden = put(lden), o_gu = put(gu), o_gw = put(gwq), o_ox = put(ownx),
-                 o_ow = put(ownw), o_r = put(s.r), o_z = put(s.z), o_nr = put(nr), o_nz = put(nz), o_aw = put(aw),
-                 o_rd = put(rd), o_zd = put(zd);
-    double *dc = (double *)c.dalloc(hc.size() * sizeof(double));
-    AXS_HIP(hipMemcpyAsync(dc, hc.data(), hc.size() * sizeof(double), hipMemcpyHostToDevice, c.stream));
-
-    const int64_t nmat = (int64_t)(M + 1) * NG * NG;
-    double2 *A = (double2 *)c.dalloc(nmat * sizeof(double2));   // every entry is written below
-    s.A64 = (double *)A;
-
+    plan.o_sn = put(sn), plan.o_lden = put(lden), plan.o_gu = put(gu), plan.o_gw = put(gwq), plan.o_ox = put(ownx),
+    plan.o_ow = put(ownw), plan.o_r = put(s.r), plan.o_z = put(s.z), plan.o_nr = put(nr), plan.o_nz = put(nz),
+    plan.o_aw = put(aw), plan.o_rd = put(rd), plan.o_zd = put(zd);
+    plan.tab = up.put(hc);
     // batches of target rows, bounded number of evaluation points
     const int64_t max_pts = 1 << 19;
     int i0 = 0;
@@ -1136,53 +1158,70 @@ void precompute_shape(Ctx &c, Shape &s) {
             }
             ++i1;
         }
-        const int64_t nfar = (int64_t)far.size() * p;
-        const int64_t P = nfar + nnear;
+        ShapePlan::Batch bt;
+        bt.nfar = (int)far.size();
+        bt.nd = (int)nd.size();
+        bt.nnear = nnear;
+        bt.far = up.put(far);
+        bt.near = up.put(nd);
+        plan.batches.push_back(bt);
+        i0 = i1;
+    }
+    return plan;
+}
+
+// A~_m of one shape (every entry is written), queued without synchronisation
+static void run_shape(Ctx &c, Shape &s, const ShapePlan &plan, const Upload &up) {
+    const int NG = s.NG, p = s.p, M = s.M, Nt = s.Nt, nq = M + Nt / 2;
+    const double *dc = up.at<double>(plan.tab);
+    double2 *A = (double2 *)c.dalloc((size_t)(M + 1) * NG * NG * sizeof(double2));
+    s.A64 = (double *)A;
+    for (auto &bt : plan.batches) {
+        const int64_t nfar = (int64_t)bt.nfar * p, nnear = bt.nnear, P = nfar + nnear;
+        const int2 *d_far = up.at<int2>(bt.far);
+        const NearDesc *d_nd = up.at<NearDesc>(bt.near);
         // point storage
         double *pbuf = (double *)c.scratch(WS_MISC, ((size_t)P * 9 + (size_t)nnear * p) * sizeof(double));
         Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, pbuf + 9 * P};
         double *qv = (double *)c.scratch(WS_TMP, (size_t)P * nq * sizeof(double));
         double2 *kv = (double2 *)c.scratch(WS_TMP3, (size_t)P * (M + 1) * sizeof(double2));
-        int2 *d_far = (int2 *)c.scratch(WS_RED, far.size() * sizeof(int2));
-        NearDesc *d_nd = (NearDesc *)c.scratch(WS_GEMM, nd.size() * sizeof(NearDesc));
         if (nfar) {
-            AXS_HIP(hipMemcpyAsync(d_far, far.data(), far.size() * sizeof(int2), hipMemcpyHostToDevice, c.stream));
-            hipLaunchKernelGGL(gen_far_kernel, dim3(ceil_div(nfar, 256)), dim3(256), 0, c.stream, d_far,
-                               (int)far.size(), p, dc + o_r, dc + o_z, dc + o_nr, dc + o_nz, dc + o_aw, pts);
+            hipLaunchKernelGGL(gen_far_kernel, dim3(ceil_div(nfar, 256)), dim3(256), 0, c.stream, d_far, bt.nfar, p,
+                               dc + plan.o_r, dc + plan.o_z, dc + plan.o_nr, dc + plan.o_nz, dc + plan.o_aw, pts);
             AXS_HIP(hipGetLastError());
         }
         // a target's own panel is always near, so no batch is without near points
-        AXS_HIP(hipMemcpyAsync(d_nd, nd.data(), nd.size() * sizeof(NearDesc), hipMemcpyHostToDevice, c.stream));
-        hipLaunchKernelGGL(gen_near_kernel, dim3(nd.size()), dim3(128), 0, c.stream, d_nd, p, dc + o_sn, dc + o_lden,
-                           dc + o_gu, dc + o_gw, ngl, dc + o_ox, dc + o_ow, dc + o_r, dc + o_z, dc + o_rd, dc + o_zd, pts,
-                           nfar);
+        hipLaunchKernelGGL(gen_near_kernel, dim3(bt.nd), dim3(128), 0, c.stream, d_nd, p, dc + plan.o_sn,
+                           dc + plan.o_lden, dc + plan.o_gu, dc + plan.o_gw, plan.ngl, dc + plan.o_ox, dc + plan.o_ow,
+                           dc + plan.o_r, dc + plan.o_z, dc + plan.o_rd, dc + plan.o_zd, pts, nfar);
         AXS_HIP(hipGetLastError());
-        modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, s.kappa, s.kappa > 0 ? 0.0 : s.eta, s.kappa > 0 ? s.eta : 0.0,
-                     kv);
+        modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, s.kappa, s.kappa > 0 ? 0.0 : s.eta,
+                     s.kappa > 0 ? s.eta : 0.0, kv);
         if (nfar) {
-            hipLaunchKernelGGL(scatter_far_kernel, dim3(ceil_div(nfar * (M + 1), 256)), dim3(256), 0, c.stream,
-                               d_far, (int)far.size(), p, M, NG, kv, A);
+            hipLaunchKernelGGL(scatter_far_kernel, dim3(ceil_div(nfar * (M + 1), 256)), dim3(256), 0, c.stream, d_far,
+                               bt.nfar, p, M, NG, kv, A);
             AXS_HIP(hipGetLastError());
         }
-        hipLaunchKernelGGL(near_reduce_kernel, dim3(nd.size(), (unsigned)ceil_div(2 * (M + 1), 16)), dim3(256), 0, c.stream,
+        hipLaunchKernelGGL(near_reduce_kernel, dim3(bt.nd, (unsigned)ceil_div(2 * (M + 1), 16)), dim3(256), 0, c.stream,
                            d_nd, M, NG, p, kv, pts.lag, nfar, A);
         AXS_HIP(hipGetLastError());
-        i0 = i1;
-        if (i0 >= NG) {
-            hipLaunchKernelGGL(add_half_identity_kernel, dim3(ceil_div((M + 1) * NG, 256)), dim3(256), 0, c.stream, A,
-                               M, NG);
-            AXS_HIP(hipGetLastError());
-        }
-        AXS_HIP(hipStreamSynchronize(c.stream));   // far, nd (and hc) are pageable host memory
     }
-    c.dfree(dc);
+    hipLaunchKernelGGL(add_half_identity_kernel, dim3(ceil_div((M + 1) * NG, 256)), dim3(256), 0, c.stream, A, M, NG);
+    AXS_HIP(hipGetLastError());
+}
+
+// give back blocks that queued kernels may still read
+static void release(Ctx &c, std::vector<void *> &blocks) {
+    AXS_HIP(hipStreamSynchronize(c.stream));
+    for (void *p : blocks) c.dfree(p);
+    blocks.clear();
 }
 
 // S_m = A~_m^{-1} for every shape and mode, in groups of shapes whose work
 // arrays (about NG x 2 NG per matrix) stay within 4 GiB.  Per group one launch
 // sequence over all its matrices: two launches per 16 columns, or one launch of
 // gauss_jordan_kernel where a matrix has more rows than a workgroup has threads.
-void invert_shapes(Ctx &c) {
+static void invert_shapes(Ctx &c, std::vector<std::unique_ptr<Upload>> &keep, std::vector<void *> &done) {
     constexpr size_t WORK_CAP = (size_t)4 << 30;
     auto per = [](const Shape &s) {   // work bytes per matrix
         return ((size_t)2 * s.NG * s.NG + (size_t)GJB * s.NG) * sizeof(double2) + (size_t)2 * s.NG * sizeof(int32_t);
@@ -1226,8 +1265,11 @@ void invert_shapes(Ctx &c) {
             g.col = g.prow + g.NG;
             off += (size_t)2 * g.NG * sizeof(int32_t);
         }
-        GJItem *d_items = (GJItem *)c.dalloc(items.size() * sizeof(GJItem));
-        AXS_HIP(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(GJItem), hipMemcpyHostToDevice, c.stream));
+        keep.emplace_back(new Upload(c));
+        Upload &up = *keep.back();
+        const size_t o_items = up.put(items);
+        up.commit();
+        const GJItem *d_items = up.at<GJItem>(o_items);
         const unsigned n = (unsigned)items.size();
         if (blocked) {
             const unsigned t32 = (unsigned)ceil_div(maxNG, 32);
@@ -1249,11 +1291,25 @@ void invert_shapes(Ctx &c) {
             hipLaunchKernelGGL(gauss_jordan_kernel<256>, dim3(n), dim3(256), maxNG * sizeof(double2), c.stream, d_items);
         }
         AXS_HIP(hipGetLastError());
-        AXS_HIP(hipStreamSynchronize(c.stream));   // items is pageable host memory; the work array is released
-        c.dfree(d_items);
-        c.dfree(work);
+        done.push_back(up.dev);
+        done.push_back(work);
         k = k1;
+        if (k < c.shapes.size()) release(c, done);   // one group's work array at a time
     }
+}
+
+void precompute_shapes(Ctx &c) {
+    std::vector<std::unique_ptr<Upload>> keep;   // host copies and device blocks, until the synchronisation
+    std::vector<void *> done;
+    keep.emplace_back(new Upload(c));
+    Upload &up = *keep.back();
+    std::vector<ShapePlan> plans;
+    for (auto &s : c.shapes) plans.push_back(plan_shape(s, up));
+    up.commit();
+    for (size_t k = 0; k < c.shapes.size(); ++k) run_shape(c, c.shapes[k], plans[k], up);
+    done.push_back(up.dev);
+    invert_shapes(c, keep, done);
+    release(c, done);
 }
 
 void modal_values(Ctx &c, double kappa, double gam_re, double gam_im, int M, int Nt,
