@@ -12,7 +12,6 @@
 namespace axs {
 
 void gauss_legendre_public(int n, std::vector<double> &x, std::vector<double> &w);
-void split_planar(Ctx &c, Shape &s, const double *src, double *r64, double *i64, float *r32, float *i32);
 void build_node_tables(Ctx &c, Upload &up);
 void interbody_shape(Ctx &c, int prec, int nrhs, int out[4]);
 
@@ -213,15 +212,14 @@ void finish_precompute(Ctx &c) {
         s.S64i = i64 + soff[k];
         s.S32r = r32 + soff[k];
         s.S32i = i32 + soff[k];
-        split_planar(c, s, s.S64, s.S64r, s.S64i, s.S32r, s.S32i);
         if (have_A) {
             s.A64r = ar64 + soff[k];
             s.A64i = ai64 + soff[k];
-            split_planar(c, s, s.A64, s.A64r, s.A64i, nullptr, nullptr);
         }
     }
     // DFT workspace layout per shape and the batched GEMM table
     std::vector<GemmBatch> gb;
+    std::vector<PlanarMat> pm;
     int64_t xo = 0;
     c.max_NG = 0;
     c.gemm_max_cols = 0;
@@ -236,13 +234,15 @@ void finish_precompute(Ctx &c) {
             g.NG = s.NG;
             g.ncols = nb * (m == 0 ? 1 : 2);
             gb.push_back(g);
+            const int64_t o = (int64_t)m * s.NG * s.NG;
+            pm.push_back(PlanarMat{(const double2 *)s.S64 + o, have_A ? (const double2 *)s.A64 + o : nullptr, g.a_off, s.NG, 0});
             c.gemm_max_cols = std::max(c.gemm_max_cols, g.ncols);
         }
         xo += (int64_t)nb * s.NF * s.NG;
         c.max_NG = std::max(c.max_NG, s.NG);
     }
     Upload up(c);
-    const size_t o_gb = up.put(gb);
+    const size_t o_gb = up.put(gb), o_pm = up.put(pm);
     c.ngemm = (int)gb.size();
     // twiddles per distinct N_F
     std::map<int, int64_t> twoff;
@@ -276,6 +276,7 @@ void finish_precompute(Ctx &c) {
     }
     const size_t o_bd = up.put(c.body_dev_host);
     build_node_tables(c, up);   // adds its own tables and uploads the block
+    split_planar(c, up.at<PlanarMat>(o_pm), (int)pm.size(), c.max_NG, r64, i64, r32, i32, ar64, ai64);
     c.gemm = up.at<GemmBatch>(o_gb);
     c.tw64 = up.at<double>(o_tw64);
     c.tw32 = up.at<float>(o_tw32);

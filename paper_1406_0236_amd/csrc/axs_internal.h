@@ -327,6 +327,14 @@ struct Upload {
     }
 };
 
+// one matrix S_m (row-major) and its A~_m (or null), and where its planar copies go
+struct PlanarMat {
+    const double2 *S, *A;
+    int64_t off;
+    int32_t NG, pad;
+};
+void split_planar(Ctx &c, const PlanarMat *mats, int n, int max_NG, double *s64r, double *s64i, float *s32r, float *s32i,
+                  double *a64r, double *a64i);
 void precompute_shapes(Ctx &c);   // A~_m and S_m = A~_m^{-1} of every shape
 void gauss_legendre_rule(int n, std::vector<double> &x, std::vector<double> &w);
 // k^G_m w (m = 0..M) for arbitrary (target ring, source ring) pairs: host arrays

@@ -29,8 +29,9 @@
 //   toroidal_kernel     -> q_mu per point                        (thread per point)
 //   modal_kernel        -> k^G_m * weight per point, m = 0..M    (16 points a workgroup)
 //   scatter / near_reduce -> entries of A~_m
-// then 1/2 on the diagonal and S_m = A~_m^{-1} by Gauss-Jordan elimination
-// with partial pivoting (one workgroup per mode).
+// (with the 1/2 on the diagonal), and S_m = A~_m^{-1} by Gauss-Jordan elimination
+// with partial pivoting.  Shapes with the same p, M and Nt go through the pipeline
+// together: three small shapes one after the other leave most of the chip idle.
 #include <algorithm>
 #include <cmath>
 #include <memory>
@@ -84,20 +85,32 @@ struct Pts {
 struct NearDesc {
     int32_t i, P;
     double sstar;
-    int32_t n0, n1, first, pad;
+    int32_t n0, n1, first, shape;
+};
+
+// target node i and panel P, their nodes all taken as far points
+struct FarDesc {
+    int32_t i, P, shape;
+};
+
+// where a shape's matrices go; nodes and panels are numbered through all shapes
+// that are set up together
+struct ShapeRef {
+    double2 *A;
+    int32_t NG, node0;
 };
 
 // ---------------------------------------------------------------------------
 // evaluation points
 // ---------------------------------------------------------------------------
 // far points: pair (i, P) of target node and panel, its p nodes in turn
-__global__ void gen_far_kernel(const int2 *__restrict__ pairs, int n, int p, const double *__restrict__ r,
+__global__ void gen_far_kernel(const FarDesc *__restrict__ pairs, int n, int p, const double *__restrict__ r,
                                const double *__restrict__ z, const double *__restrict__ nr,
                                const double *__restrict__ nz, const double *__restrict__ aw, Pts pts) {
     int o = blockIdx.x * blockDim.x + threadIdx.x;
     if (o >= n * p) return;
-    const int2 pr = pairs[o / p];
-    const int i = pr.x, j = pr.y * p + o % p;
+    const FarDesc pr = pairs[o / p];
+    const int i = pr.i, j = pr.P * p + o % p;
     pts.rt[o] = r[i];
     pts.rp[o] = r[j];
     pts.dr[o] = r[j] - r[i];
@@ -584,23 +597,25 @@ static void modal_launch(Ctx &c, Pts pts, int64_t npts, int Nt, int M, double *f
 // ---------------------------------------------------------------------------
 // assembly of A~_m
 // ---------------------------------------------------------------------------
-__global__ void scatter_far_kernel(const int2 *__restrict__ pairs, int n, int p, int M, int NG,
-                                   const double2 *__restrict__ kval, double2 *__restrict__ A) {
+__global__ void scatter_far_kernel(const FarDesc *__restrict__ pairs, int n, int p, int M,
+                                   const ShapeRef *__restrict__ shapes, const double2 *__restrict__ kval) {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)n * p * (M + 1)) return;
     const int o = (int)(idx / (M + 1)), m = (int)(idx % (M + 1));
-    const int2 pr = pairs[o / p];
-    A[((int64_t)m * NG + pr.x) * NG + pr.y * p + o % p] = kval[idx];
+    const FarDesc pr = pairs[o / p];
+    const ShapeRef sh = shapes[pr.shape];
+    sh.A[((int64_t)m * sh.NG + pr.i - sh.node0) * sh.NG + pr.P * p + o % p - sh.node0] = kval[idx];
 }
 
 // Entries of the near pairs: sum over a pair's points of the kernel values
 // (M + 1 complex numbers a point: 2 (M + 1) rows) times the p basis values, on the FP64
 // matrix cores, 16 rows per workgroup with the points split between its four
-// wavefronts.  One thread per entry read every kernel value p times: FIGR
-__global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int NG, int p,
+// wavefronts.  One thread per entry read every kernel value p times: 75 us for a shape
+// of 80 contour nodes, 10 now.  The target's own entry takes the 1/2 of 1/2 I + K.
+__global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int p,
+                                                          const ShapeRef *__restrict__ shapes,
                                                           const double2 *__restrict__ kval,
-                                                          const double *__restrict__ lag, int64_t base,
-                                                          double2 *__restrict__ A) {
+                                                          const double *__restrict__ lag, int64_t base) {
     __shared__ double s_acc[4][16][17];
     const NearDesc d = desc[blockIdx.x];
     const int per = d.n0 + d.n1, R = 2 * (M + 1), row0 = blockIdx.y * 16;
@@ -621,16 +636,12 @@ __global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__rest
     __syncthreads();
     const int comp = threadIdx.x & 1, j = (threadIdx.x >> 1) & 15, rl = 2 * (threadIdx.x >> 5) + comp;
     const int m = (row0 + rl) / 2;
-    if (m <= M && j < p)
-        ((double *)(A + ((int64_t)m * NG + d.i) * NG + d.P * p + j))[comp] =
-            (s_acc[0][rl][j] + s_acc[1][rl][j]) + (s_acc[2][rl][j] + s_acc[3][rl][j]);
-}
-
-__global__ void add_half_identity_kernel(double2 *A, int M, int NG) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (M + 1) * NG) return;
-    const int m = idx / NG, i = idx % NG;
-    A[((int64_t)m * NG + i) * NG + i].x += 0.5;
+    if (m <= M && j < p) {
+        const ShapeRef sh = shapes[d.shape];
+        double v = (s_acc[0][rl][j] + s_acc[1][rl][j]) + (s_acc[2][rl][j] + s_acc[3][rl][j]);
+        if (comp == 0 && d.i == d.P * p + j) v += 0.5;
+        ((double *)(sh.A + ((int64_t)m * sh.NG + d.i - sh.node0) * sh.NG + d.P * p + j - sh.node0))[comp] = v;
+    }
 }
 
 // Inverses of all matrices (every shape, every mode) by in-place Gauss-Jordan
@@ -906,21 +917,42 @@ __global__ __launch_bounds__(BS) void gauss_jordan_kernel(const GJItem *__restri
     }
 }
 
-// S (complex128 row-major [M+1][NG][NG]) -> planar column-major FP64 and FP32 copies
-__global__ void split_planar_kernel(const double2 *__restrict__ S, int M, int NG, double *__restrict__ r64,
-                                    double *__restrict__ i64, float *__restrict__ r32,
-                                    float *__restrict__ i32) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t nn = (int64_t)NG * NG;
-    if (t >= (M + 1) * nn) return;
-    const int64_t m = t / nn, e = t % nn;
-    const int k = (int)(e / NG), i = (int)(e % NG);      // output (column-major): element (i, k) at k*NG + i
-    const double2 v = S[m * nn + (int64_t)i * NG + k];
-    r64[t] = v.x;
-    i64[t] = v.y;
-    if (r32) {
-        r32[t] = (float)v.x;
-        i32[t] = (float)v.y;
+// Planar column-major copies (element (i, k) at k NG + i) of the matrices, S_m in FP64 and
+// FP32 and A~_m (where given) in FP64: 32 x 32 tiles turned in LDS, so that
+// reads and writes both run along rows (without, the reads of 41 matrices of 200 x 200
+// took 28 us of each 29 us launch).
+__global__ __launch_bounds__(256) void split_planar_kernel(const PlanarMat *__restrict__ mats, double *__restrict__ s64r,
+                                                           double *__restrict__ s64i, float *__restrict__ s32r,
+                                                           float *__restrict__ s32i, double *__restrict__ a64r,
+                                                           double *__restrict__ a64i) {
+    __shared__ double2 tile[32][33];
+    const PlanarMat mt = mats[blockIdx.x];
+    const int NG = mt.NG, nt = (NG + 31) / 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+    for (int t = blockIdx.y; t < nt * nt; t += gridDim.y) {
+        const int i0 = t / nt * 32, k0 = t % nt * 32;
+        for (int which = 0; which < (mt.A ? 2 : 1); ++which) {
+            const double2 *src = which ? mt.A : mt.S;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 32; q += 8)
+                if (i0 + y + q < NG && k0 + x < NG) tile[y + q][x] = src[(int64_t)(i0 + y + q) * NG + k0 + x];
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < 32; q += 8) {
+                if (k0 + y + q >= NG || i0 + x >= NG) continue;
+                const double2 v = tile[x][y + q];
+                const int64_t o = mt.off + (int64_t)(k0 + y + q) * NG + i0 + x;
+                if (which) {
+                    a64r[o] = v.x;
+                    a64i[o] = v.y;
+                } else {
+                    s64r[o] = v.x;
+                    s64i[o] = v.y;
+                    s32r[o] = (float)v.x;
+                    s32i[o] = (float)v.y;
+                }
+            }
+        }
     }
 }
 
@@ -991,11 +1023,12 @@ static int modal_nt(const Shape &s) {
     return nt;
 }
 
-// a shape's evaluation points: what its launches need, with the offsets of the
-// tables in the upload
+// the evaluation points of shapes set up together: what their launches need, with
+// the offsets of the tables in the upload
 struct ShapePlan {
+    Shape all;        // contour nodes of all of them (p, M, Nt, kappa and eta are common)
     int ngl = 0;
-    size_t tab = 0;   // the doubles below, in one array
+    size_t tab = 0, refs = 0;   // the doubles below, in one array; the ShapeRefs
     size_t o_sn = 0, o_lden = 0, o_gu = 0, o_gw = 0, o_ox = 0, o_ow = 0, o_r = 0, o_z = 0, o_nr = 0, o_nz = 0, o_aw = 0,
            o_rd = 0, o_zd = 0;
     struct Batch {   // target rows
@@ -1006,11 +1039,29 @@ struct ShapePlan {
     std::vector<Batch> batches;
 };
 
-static ShapePlan plan_shape(Shape &s, Upload &up) {
-    const int NG = s.NG, p = s.p, np_ = s.n_panels;
-    AXS_REQUIRE(p <= PMAX, AXS_EINVAL, "at most 16 nodes per panel are supported");
-    s.Nt = modal_nt(s);
+static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
     ShapePlan plan;
+    Shape &s = plan.all;
+    s = *shapes[0];
+    std::vector<ShapeRef> refs;
+    std::vector<int> shape_of, first_panel;   // of each panel; of each shape, and one past the last
+    s.NG = s.n_panels = 0;
+    for (auto *v : {&s.r, &s.z, &s.dr, &s.dz, &s.gw}) v->clear();
+    for (auto *q : shapes) {
+        refs.push_back(ShapeRef{(double2 *)q->A64, q->NG, s.NG});
+        first_panel.push_back(s.n_panels);
+        shape_of.resize(s.n_panels + q->n_panels, (int)refs.size() - 1);
+        s.NG += q->NG;
+        s.n_panels += q->n_panels;
+        s.r.insert(s.r.end(), q->r.begin(), q->r.end());
+        s.z.insert(s.z.end(), q->z.begin(), q->z.end());
+        s.dr.insert(s.dr.end(), q->dr.begin(), q->dr.end());
+        s.dz.insert(s.dz.end(), q->dz.begin(), q->dz.end());
+        s.gw.insert(s.gw.end(), q->gw.begin(), q->gw.end());
+    }
+    first_panel.push_back(s.n_panels);
+    plan.refs = up.put(refs);
+    const int NG = s.NG, p = s.p, np_ = s.n_panels;
 
     std::vector<double> sn, sw;
     gauss_legendre(p, sn, sw);
@@ -1089,8 +1140,8 @@ static ShapePlan plan_shape(Shape &s, Upload &up) {
         return n * ngl;
     };
     for (int i = 0; i < NG; ++i) {
-        const int own = i / p;
-        for (int P = 0; P < np_; ++P) {
+        const int own = i / p, sh = shape_of[own];
+        for (int P = first_panel[sh]; P < first_panel[sh + 1]; ++P) {
             const double lim = (plen[P] + crad[P]) * (1.0 + 1e-12), ca = cr[P] - s.r[i], cb = cz[P] - s.z[i];
             if (std::abs(P - own) > 1 && ca * ca + cb * cb > lim * lim) continue;
             double best2 = 1e300, bs = 0;
@@ -1110,6 +1161,7 @@ static ShapePlan plan_shape(Shape &s, Upload &up) {
             NearDesc d{};
             d.i = i;
             d.P = P;
+            d.shape = sh;
             if (P == own) {
                 d.sstar = sn[i - own * p];
                 d.n0 = d.n1 = own_pts;
@@ -1137,23 +1189,24 @@ static ShapePlan plan_shape(Shape &s, Upload &up) {
     while (i0 < NG) {
         int i1 = i0;
         int64_t npts = 0;
-        std::vector<int2> far;
+        std::vector<FarDesc> far;
         std::vector<NearDesc> nd;
         int64_t nnear = 0;
         while (i1 < NG) {
-            int64_t add = (int64_t)(np_ - (int)near[i1].size()) * p;
+            const int sh = shape_of[i1 / p], P0 = first_panel[sh], P1 = first_panel[sh + 1];
+            int64_t add = (int64_t)(P1 - P0 - (int)near[i1].size()) * p;
             for (auto &d : near[i1]) add += d.n0 + d.n1;
             if (i1 > i0 && npts + add > max_pts) break;
             npts += add;
             size_t k = 0;
-            for (int P = 0; P < np_; ++P) {
+            for (int P = P0; P < P1; ++P) {
                 if (k < near[i1].size() && near[i1][k].P == P) {
                     NearDesc d = near[i1][k++];
                     d.first = (int32_t)nnear;
                     nnear += d.n0 + d.n1;
                     nd.push_back(d);
                 } else {
-                    far.push_back(make_int2(i1, P));
+                    far.push_back(FarDesc{i1, P, sh});
                 }
             }
             ++i1;
@@ -1170,15 +1223,15 @@ static ShapePlan plan_shape(Shape &s, Upload &up) {
     return plan;
 }
 
-// A~_m of one shape (every entry is written), queued without synchronisation
-static void run_shape(Ctx &c, Shape &s, const ShapePlan &plan, const Upload &up) {
-    const int NG = s.NG, p = s.p, M = s.M, Nt = s.Nt, nq = M + Nt / 2;
+// A~_m of these shapes (every entry is written), queued without synchronisation
+static void run_shapes(Ctx &c, const ShapePlan &plan, const Upload &up) {
+    const Shape &s = plan.all;
+    const int p = s.p, M = s.M, Nt = s.Nt, nq = M + Nt / 2;
     const double *dc = up.at<double>(plan.tab);
-    double2 *A = (double2 *)c.dalloc((size_t)(M + 1) * NG * NG * sizeof(double2));
-    s.A64 = (double *)A;
+    const ShapeRef *refs = up.at<ShapeRef>(plan.refs);
     for (auto &bt : plan.batches) {
         const int64_t nfar = (int64_t)bt.nfar * p, nnear = bt.nnear, P = nfar + nnear;
-        const int2 *d_far = up.at<int2>(bt.far);
+        const FarDesc *d_far = up.at<FarDesc>(bt.far);
         const NearDesc *d_nd = up.at<NearDesc>(bt.near);
         // point storage
         double *pbuf = (double *)c.scratch(WS_MISC, ((size_t)P * 9 + (size_t)nnear * p) * sizeof(double));
@@ -1199,15 +1252,13 @@ static void run_shape(Ctx &c, Shape &s, const ShapePlan &plan, const Upload &up)
                      s.kappa > 0 ? s.eta : 0.0, kv);
         if (nfar) {
             hipLaunchKernelGGL(scatter_far_kernel, dim3(ceil_div(nfar * (M + 1), 256)), dim3(256), 0, c.stream, d_far,
-                               bt.nfar, p, M, NG, kv, A);
+                               bt.nfar, p, M, refs, kv);
             AXS_HIP(hipGetLastError());
         }
         hipLaunchKernelGGL(near_reduce_kernel, dim3(bt.nd, (unsigned)ceil_div(2 * (M + 1), 16)), dim3(256), 0, c.stream,
-                           d_nd, M, NG, p, kv, pts.lag, nfar, A);
+                           d_nd, M, p, refs, kv, pts.lag, nfar);
         AXS_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(add_half_identity_kernel, dim3(ceil_div((M + 1) * NG, 256)), dim3(256), 0, c.stream, A, M, NG);
-    AXS_HIP(hipGetLastError());
 }
 
 // give back blocks that queued kernels may still read
@@ -1246,8 +1297,7 @@ static void invert_shapes(Ctx &c, std::vector<std::unique_ptr<Upload>> &keep, st
         for (size_t q = k; q < k1; ++q) {
             Shape &s = c.shapes[q];
             const int64_t nn = (int64_t)s.NG * s.NG;
-            double2 *S = (double2 *)c.dalloc((size_t)(s.M + 1) * nn * sizeof(double2));
-            s.S64 = (double *)S;
+            double2 *S = (double2 *)s.S64;
             for (int m = 0; m <= s.M; ++m) {
                 GJItem g{};
                 g.A = (const double2 *)s.A64 + m * nn;
@@ -1303,10 +1353,35 @@ void precompute_shapes(Ctx &c) {
     std::vector<void *> done;
     keep.emplace_back(new Upload(c));
     Upload &up = *keep.back();
+    // the matrices of all shapes in one block each, in the shapes' order
+    size_t total = 0;
+    for (auto &s : c.shapes) {
+        AXS_REQUIRE(s.p <= PMAX, AXS_EINVAL, "at most 16 nodes per panel are supported");
+        s.Nt = modal_nt(s);
+        total += (size_t)(s.M + 1) * s.NG * s.NG;
+    }
+    double2 *A = (double2 *)c.dalloc(total * sizeof(double2)), *S = (double2 *)c.dalloc(total * sizeof(double2));
+    size_t off = 0;
+    for (auto &s : c.shapes) {
+        s.A64 = (double *)(A + off);
+        s.S64 = (double *)(S + off);
+        off += (size_t)(s.M + 1) * s.NG * s.NG;
+    }
     std::vector<ShapePlan> plans;
-    for (auto &s : c.shapes) plans.push_back(plan_shape(s, up));
+    std::vector<char> taken(c.shapes.size(), 0);
+    for (size_t k = 0; k < c.shapes.size(); ++k) {
+        if (taken[k]) continue;
+        std::vector<Shape *> group;
+        for (size_t q = k; q < c.shapes.size(); ++q) {
+            const Shape &a = c.shapes[k], &b = c.shapes[q];
+            if (b.p != a.p || b.M != a.M || b.Nt != a.Nt || b.kappa != a.kappa || b.eta != a.eta) continue;
+            taken[q] = 1;
+            group.push_back(&c.shapes[q]);
+        }
+        plans.push_back(plan_shapes(group, up));
+    }
     up.commit();
-    for (size_t k = 0; k < c.shapes.size(); ++k) run_shape(c, c.shapes[k], plans[k], up);
+    for (auto &plan : plans) run_shapes(c, plan, up);
     done.push_back(up.dev);
     invert_shapes(c, keep, done);
     release(c, done);
@@ -1322,10 +1397,11 @@ void modal_values(Ctx &c, double kappa, double gam_re, double gam_im, int M, int
     modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, kappa, gam_re, gam_im, kout);
 }
 
-void split_planar(Ctx &c, Shape &s, const double *src, double *r64, double *i64, float *r32, float *i32) {
-    const int64_t nmat = (int64_t)(s.M + 1) * s.NG * s.NG;
-    hipLaunchKernelGGL(split_planar_kernel, dim3(ceil_div(nmat, 256)), dim3(256), 0, c.stream,
-                       (const double2 *)src, s.M, s.NG, r64, i64, r32, i32);
+void split_planar(Ctx &c, const PlanarMat *mats, int n, int max_NG, double *s64r, double *s64i, float *s32r, float *s32i,
+                  double *a64r, double *a64i) {
+    const int64_t nt = ceil_div(max_NG, 32);
+    hipLaunchKernelGGL(split_planar_kernel, dim3(n, (unsigned)std::min<int64_t>(nt * nt, 65535)), dim3(256), 0, c.stream,
+                       mats, s64r, s64i, s32r, s32i, a64r, a64i);
     AXS_HIP(hipGetLastError());
 }
 

@@ -131,3 +131,20 @@ def test_modal_values_at_edges(panels, kappa, eta, M):
         err = np.max(np.abs(A[:, i, :] - row)) / np.max(np.abs(row))
         assert err < 1e-11, (i, err)
     ctx.close()
+
+
+@pytest.mark.parametrize("M", [3, 20])
+def test_shapes_together_as_alone(M):
+    """Shapes of one p, M and number of samples are set up in common launches: the same bits as
+    each of them by itself, matrices and inverses."""
+    from workloads import geometry as geo
+    shapes = [geo.sphere(1.0, 1, 10), geo.prolate(0.8, 1.3, 7, 10), geo.sphere(0.9, 4, 10), geo.prolate(0.5, 1.0, 3, 9),
+              geo.bowl(3, 2, 4, 10)]
+    ctx = _context(shapes, 1.5, M)
+    for b, c in enumerate(shapes):
+        one = _context([c], 1.5, M)
+        for which in (0, 1):
+            got = ctx.modal_matrices(b, which, M=M, NG=c.NG).cpu().numpy()
+            assert np.array_equal(got, one.modal_matrices(0, which, M=M, NG=c.NG).cpu().numpy()), (b, which)
+        one.close()
+    ctx.close()
