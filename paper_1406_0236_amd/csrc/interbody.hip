@@ -1213,12 +1213,15 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
 //    memory twice: 64 rhs on 20,090 nodes take 1.27 ms with 8, 1.35 with 32,
 //    one rhs on 8,200 nodes 49 us with 16 or 32, 55 with 64.  The FP32 ring order
 //    (8 resident workgroups per CU) takes 16K so that the last, partly filled
-//    round is a small share of the launch.
+//    round is a small share of the launch; its chunks are also its FP32 sums, added
+//    up in FP64 afterwards, so it keeps 64 where 32 would run as fast (at zero
+//    frequency 32 doubles the error: 77,760 nodes 6.4e-7 and 1.2e-6 of the result).
+//    The MFMA orders add 128 sources at a time and show no such difference.
 static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
     const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
     const int64_t tiles = count_tiles(c, ib_tile(s)) * (mf ? ceil_div(nrhs, 16) : 1);
     const int64_t want = ring32 ? 16384 : s.variant == 4 ? 8192 : 4096;
-    const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : ring32 || (s.variant == 2 && s.tpt == 1) ? 32 : 64;
+    const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : !ring32 && s.variant == 2 && s.tpt == 1 ? 32 : 64;
     int splits = 1;
     while (tiles * splits < want && splits < most) splits *= 2;
     // no empty chunks: 100 rings in 32 chunks are 25 chunks of 4
