@@ -1216,11 +1216,14 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
 //    round is a small share of the launch; its chunks are also its FP32 sums, added
 //    up in FP64 afterwards, so it keeps 64 where 32 would run as fast (at zero
 //    frequency 32 doubles the error: 77,760 nodes 6.4e-7 and 1.2e-6 of the result).
-//    The MFMA orders add 128 sources at a time and show no such difference.
+//    The MFMA orders add 128 sources at a time and show no such difference.  For the
+//    same reason the FP32 VALU orders count tiles of one target per thread (rings)
+//    and two (points) whatever they choose, which also bounds their scratch.
 static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
     const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
-    const int64_t tiles = count_tiles(c, ib_tile(s)) * (mf ? ceil_div(nrhs, 16) : 1);
-    const int64_t want = ring32 ? 16384 : s.variant == 4 ? 8192 : 4096;
+    const int tile = ring32 && c.ib_tpt[1] == 0 ? (s.variant == 2 ? 1 : 2) * s.bs : ib_tile(s);
+    const int64_t tiles = count_tiles(c, tile) * (mf ? ceil_div(nrhs, 16) : 1);
+    const int64_t want = ring32 && s.variant == 2 ? 16384 : s.variant == 4 ? 8192 : 4096;
     const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : !ring32 && s.variant == 2 && s.tpt == 1 ? 32 : 64;
     int splits = 1;
     while (tiles * splits < want && splits < most) splits *= 2;

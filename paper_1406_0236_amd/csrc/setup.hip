@@ -67,9 +67,8 @@ constexpr int PMAX = 16;       // max nodes per panel supported
 // In FP64 the two rules agree with the 46-level one to the noise of the kernel
 // values (1e-13 to 4e-12 of the largest entry, where 46 levels are as far from a
 // tanh-sinh rule) for spheres of 1 to 20 panels, spheroids, a 10 : 1 needle and
-// bowls, p = 3 to 16.  2760 -> 480 points per target node of a smooth contour:
-// precomputation of 8 mixed bodies 6.08 -> 2.71 ms, of 27 spheres (one shape of
-// 200 contour nodes) 6.85 -> 2.73 ms.
+// bowls, p = 3 to 16.
+// 2760 -> 480 points per target node of a smooth contour.
 constexpr int OWN_LEV = 11, OWN_Q = 8, OWN_NQ = 24;
 constexpr int MAX_LEV = 46;
 
@@ -123,8 +122,8 @@ __global__ void gen_far_kernel(const FarDesc *__restrict__ pairs, int n, int p, 
 // one workgroup per near pair.  rd, zd: derivative of each panel's interpolant at its
 // nodes, so that the curve and its tangent both come from the Lagrange basis.  The
 // basis is formed from running products kept in registers (p <= PMAX, unrolled).
-// A quarter of the time went into scratch memory for them, the rest into p^3
-// products for the derivatives: FIGN.
+// With the products in scratch memory and p^3 of them for the tangent the three shapes of
+// 8 mixed bodies took 3 x 153 us, in one launch 15 now.
 __global__ __launch_bounds__(128) void gen_near_kernel(const NearDesc *__restrict__ desc, int p,
                                                        const double *__restrict__ snode,
                                                        const double *__restrict__ lden,
@@ -221,8 +220,9 @@ __device__ __forceinline__ double lane_value(double x, int j) {
 //    all terms positive and no size beyond a power of mu; started at h = g / 2,
 //    its limit, 18 / eta steps above nq (an error there shrinks by t^2 a step).
 // All lanes of a wavefront take the same mu, each from its own start on, so the
-// reciprocals come from one division per 64 steps.  38,000 points, nq = 84: 233 us
-// with a division a step and rows of f per point, FIGT now.
+// reciprocals come from one division per 64 steps.  With a division a step and the
+// values of a point in a row of memory the three shapes of 8 mixed bodies took 3 x 233
+// us, in one launch 54 now; 112,000 points of one shape (nq = 104) 381 and 62.
 __global__ __launch_bounds__(64) void toroidal_kernel(Pts pts, int64_t npts, int nq, double *__restrict__ f,
                                                       double *__restrict__ scale, double *__restrict__ decay) {
     const int64_t pt = (int64_t)blockIdx.x * 64 + threadIdx.x;
@@ -376,8 +376,10 @@ struct ModalSize {
 //  - the convolution over l with q_{m-l}, per thread one point and MB values of
 //    m: c_0 q_m + sum_l c_l (q_{|m-l|} + q_{m+l}), the MB pairs (q, dq) on either side
 //    kept in registers and moved on by one per l.
-// Bound by the multiply-adds of the last part and the sines of the first, about half and half
-// of the time each.  FIGM
+// Bound by VALU issue (69 % of the cycles with two workgroups a CU), about half of it
+// in the last part.  One wavefront per point, with five LDS reads per four
+// multiply-adds of the series, took 3 x 184 us for the three shapes of 8 mixed bodies (M =
+// 20), this 224 in one launch; 112,000 points with M = 40: 677 and 278.
 template <int PT, int MB>
 __global__ __launch_bounds__(256) void modal_kernel(Pts pts, int64_t npts, int Nt, int M, const double *__restrict__ f,
                                                     const double *__restrict__ scale, const double *__restrict__ decay,
@@ -610,8 +612,8 @@ __global__ void scatter_far_kernel(const FarDesc *__restrict__ pairs, int n, int
 // Entries of the near pairs: sum over a pair's points of the kernel values
 // (M + 1 complex numbers a point: 2 (M + 1) rows) times the p basis values, on the FP64
 // matrix cores, 16 rows per workgroup with the points split between its four
-// wavefronts.  One thread per entry read every kernel value p times: 75 us for a shape
-// of 80 contour nodes, 10 now.  The target's own entry takes the 1/2 of 1/2 I + K.
+// wavefronts.  One thread per entry read every kernel value p times: 3 x 75 us for the
+// three shapes of 8 mixed bodies, 14 now.  The target's own entry takes the 1/2 of 1/2 I + K.
 __global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__restrict__ desc, int M, int p,
                                                           const ShapeRef *__restrict__ shapes,
                                                           const double2 *__restrict__ kval,
@@ -623,13 +625,21 @@ __global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__rest
     const double *lg = lag + (int64_t)d.first * p;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
     const bool row_in = row0 + l16 < R, col_in = l16 < p;
+    const int row = min(row0 + l16, R - 1), col = min(l16, p - 1);
     gj_f64x4 acc = {0, 0, 0, 0};
-#pragma unroll 4
-    for (int q0 = wave * 4; q0 < per; q0 += 16) {
-        const int q = q0 + g;
-        const double a = row_in && q < per ? kv[(int64_t)q * R + row0 + l16] : 0.0;
-        const double b = col_in && q < per ? lg[q * p + l16] : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+    for (int q0 = wave * 16; q0 < per; q0 += 64) {
+        double a[4], b[4];   // clamped, not conditional: eight loads in flight
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int q = min(q0 + 4 * u + g, per - 1);
+            a[u] = kv[(int64_t)q * R + row];
+            b[u] = lg[q * p + col];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = q0 + 4 * u + g < per;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(in && row_in ? a[u] : 0.0, in && col_in ? b[u] : 0.0, acc, 0, 0, 0);
+        }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) s_acc[wave][g + 4 * v][l16] = acc[v];
@@ -662,8 +672,9 @@ __global__ __launch_bounds__(256) void near_reduce_kernel(const NearDesc *__rest
 //   gj_update_kernel - a 16 x 16 tile per wavefront on the FP64 matrix cores,
 //                      read from one copy of the matrix and written to the other
 //                      (the pivot rows are read by every tile).
-// 41 matrices of 200 x 200 (MI355X): 26 launches, 0.60 ms (13 x 30 us + 13 x 16
-// us); one workgroup per matrix over global memory took 19.97 ms.
+// 41 matrices of 200 x 200 (MI355X): 26 launches, 0.51 ms (13 x 25 us + 13 x 14
+// us); one workgroup per matrix over global memory took 19.97 ms.  Blocks of 32
+// columns: 7 x 69 + 7 x 19 us (a panel step reads and writes twice as much LDS).
 struct GJItem {
     const double2 *A;   // NG x NG, row-major
     double2 *b0, *b1;   // two copies of NG x NG the blocks alternate between
