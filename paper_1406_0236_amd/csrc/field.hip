@@ -14,7 +14,7 @@
 // instead the kernels took 8 % longer, prefetched or not).  The nodes are cut
 // into chunks so that even a few targets fill the chip; the chunks' partial sums
 // are added in a fixed order.
-// 20,000 directions x 18,860 nodes x 4 densities: 0.66 ms, 65 % of the FP64
+// 20,000 directions x 18,860 nodes x 4 densities: 0.60 ms, 72 % of the FP64
 // issue rate (one workgroup per target and right-hand side with the library
 // sincos: 5.7 ms); 1,024 points x 437,400 nodes: 0.68 ms, 80 % (2.7 ms).
 #include "axs_internal.h"
@@ -173,10 +173,38 @@ __global__ __launch_bounds__(256) void field_reduce_kernel(const double2 *__rest
     u[i] = a;
 }
 
+// targets per lane where there are many: they share a node's LDS reads
+constexpr int field_tpt(int nr) { return nr > 4 ? 2 : 4; }
+
+// workgroups of 256 threads a CU holds at a time with many targets
+template <int KIND, int NR>
+static int field_resident() {
+    static const int n = [] {
+        int r = 0;
+        AXS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, field_kernel<KIND, NR, field_tpt(NR)>, 256, 0));
+        return std::max(1, r);
+    }();
+    return n;
+}
+
+template <int KIND>
+static int field_resident_for(int nr) {
+    switch (nr) {
+        case 1: return field_resident<KIND, 1>();
+        case 2: return field_resident<KIND, 2>();
+        case 3: return field_resident<KIND, 3>();
+        case 4: return field_resident<KIND, 4>();
+        case 5: return field_resident<KIND, 5>();
+        case 6: return field_resident<KIND, 6>();
+        case 7: return field_resident<KIND, 7>();
+        default: return field_resident<KIND, 8>();
+    }
+}
+
 template <int KIND, int NR>
 static void launch_field(Ctx &c, dim3 grid, int bs, bool many, const double *rec, int64_t chunk, const double *tgt, int nt,
                          double st, double eta, int wide, int c0, int nrhs, double2 *part) {
-    constexpr int TPT = NR > 4 ? 2 : 4;
+    constexpr int TPT = field_tpt(NR);
     if (many)
         hipLaunchKernelGGL((field_kernel<KIND, NR, TPT>), grid, dim3(bs), 0, c.stream, rec, c.N, chunk, tgt, nt, st, eta,
                            wide, c.sctab, c0, nrhs, part);
@@ -194,17 +222,30 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
     const size_t rec_group = (size_t)c.N * (6 + 2 * nr) * sizeof(double);
     // records of at most 256 MiB at a time (at least one group)
     const int gb = (int)std::max<size_t>(1, std::min<size_t>(groups, ((size_t)256 << 20) / rec_group));
-    // few targets: one wavefront per workgroup and one target per lane; from 1,024
-    // targets on 4 per lane (2 with more than 4 densities), which share a node's
-    // LDS reads
-    const bool many = nt >= 1024;
-    const int bs = nt > 64 ? 256 : 64, tile = bs * (many ? (nr > 4 ? 2 : 4) : 1);
+    // up to 64 targets: one wavefront per workgroup; from 1,024 targets on 4 per lane
+    // (2 with more than 4 densities), if that leaves three workgroups a CU
+    // (18,860 nodes: 1,024 targets 83 us with 4, 69 with 1; 3,000 targets the same)
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(1024, c.N / 64));   // chunks
+    const bool many = nt >= 1024 && ceil_div(nt, 256 * field_tpt(nr)) * gb * most >= 768;
+    const int bs = nt > 64 ? 256 : 64, tile = bs * (many ? field_tpt(nr) : 1);
     const int tiles = (int)ceil_div(nt, tile);
-    // chunks of at least 64 nodes, as many as make 1,024 workgroups of four
-    // wavefronts (4 per CU), at most 1,024
-    const int64_t want = ceil_div((int64_t)1024 * 256, (int64_t)tiles * gb * bs);
-    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(1024, c.N / 64));
-    const int64_t chunk = ceil_div(c.N, std::max<int64_t>(1, std::min(want, most)));
+    // chunks of at least 64 nodes, at most 1,024.  Few targets: as many as make 1,024
+    // workgroups of four wavefronts (4 per CU; more cost as much as they fill).  Many: as
+    // fill whole rounds of the workgroups the CUs hold at a time, one or up to four
+    // where the tiles do not divide a round well (20,000 directions, 4 densities: 38
+    // chunks, 760 workgroups of the 768 held, 0.68 ms; 52 chunks, a round and a third, 0.76)
+    const int64_t all = (int64_t)tiles * gb;
+    int64_t want = std::max<int64_t>(1, std::min(most, ceil_div((int64_t)1024 * 256, all * bs)));
+    if (many) {
+        const int64_t round = 256 * (int64_t)field_resident_for<KIND>(nr);
+        double fill = 0.0;
+        for (int k = 1; k <= 4; ++k) {
+            const int64_t n = std::max<int64_t>(1, std::min(most, k * round / all));
+            const double f = (double)(all * n) / (double)(ceil_div(all * n, round) * round);
+            if (f > fill + 0.03) fill = f, want = n;
+        }
+    }
+    const int64_t chunk = ceil_div(c.N, want);
     const int nchunk = (int)ceil_div(c.N, chunk);
     double *rec = (double *)c.scratch(WS_TMP, rec_group * gb);
     const int64_t items = (int64_t)nrhs * nt;

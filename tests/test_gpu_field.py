@@ -47,7 +47,8 @@ def _near(g, q, t, kappa, eta):
 
 @pytest.mark.parametrize("kappa", [0.0, 3.0])
 @pytest.mark.parametrize("nt,nrhs", [(1, 1), (1, 9), (63, 3), (64, 19), (65, 4), (257, 5), (1023, 2), (1024, 1),
-                                     (1025, 8), (1024, 7), (2049, 17), (4097, 3)])
+                                     (1025, 8), (1024, 7), (2049, 17), (4097, 3),
+                                     (33793, 1), (34000, 4), (8705, 16), (9000, 11)])   # several targets per lane
 def test_fields_at_edges(scenes, kappa, nt, nrhs):
     ctx, g, sig, dev = scenes[kappa]
     rng = np.random.default_rng(nt)
