@@ -47,8 +47,8 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6
 # from rocprofv3 FETCH_SIZE / WRITE_SIZE passes scaled by a calibration copy
 # (profiles/interbody_sphere_lattice_27_k4pi_pmc.md); valid only for the kernel
 # source they were taken on (source_fingerprint: code, not comments).
-TRAFFIC_BYTES = 115.16e6
-TRAFFIC_SOURCE_SHA = "c2b78089b674c037"
+TRAFFIC_BYTES = 115.17e6
+TRAFFIC_SOURCE_SHA = "ab4004a5e2a72ce1"
 
 
 def source_fingerprint(path):
