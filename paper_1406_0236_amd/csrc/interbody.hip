@@ -1191,15 +1191,17 @@ static int64_t count_tiles(const Ctx &c, int tile) {
 //    976 us, 2 836, 1 860).  FP64 points 2 (83,640 nodes: 8.36 ms, 4 8.56).
 //    MFMA orders: 2 groups of 16 targets per wavefront; FP64 4 where there are
 //    256 tiles of that size (129,600 nodes, 16 rhs: 39.7 ms, 2 40.5; 20,090
-//    nodes 1141 and 1051 us).
+//    nodes 1141 and 1051 us), or as much work in fewer (51,120 targets of 86,904
+//    nodes, 200 tiles, 20 rhs: 18.8 ms, 2 19.3).
 static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
     const int width = (int)ceil_div(nrhs, ceil_div(nrhs, 8));   // of a VALU rhs group
     const bool large = count_tiles(c, 1024) >= 64;
     if (variant == 4) return 2;
     if (variant == 3) {
         if (prec == AXS_FP32) return 2;
-        const int64_t groups = ceil_div(nrhs, 16);
-        if (count_tiles(c, 256) * groups >= 256) return 4;
+        const int64_t groups = std::max(1, nrhs / 16);   // of one launch; a remainder gets its own
+        const int64_t tiles = count_tiles(c, 256) * groups;
+        if (tiles >= 256 || tiles * c.N >= ((int64_t)256 << 16)) return 4;
         return 2;
     }
     if (variant == 1) return prec == AXS_FP32 ? 1 : 2;
@@ -1222,7 +1224,9 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
 static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
     const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
     const int tile = ring32 && c.ib_tpt[1] == 0 ? (s.variant == 2 ? 1 : 2) * s.bs : ib_tile(s);
-    const int64_t tiles = count_tiles(c, tile) * (mf ? ceil_div(nrhs, 16) : 1);
+    // groups of a launch; a remainder's own launch has one
+    const int groups = mf && nrhs % 16 == 0 ? nrhs / 16 : 1;
+    const int64_t tiles = count_tiles(c, tile) * groups;
     const int64_t want = ring32 && s.variant == 2 ? 16384 : s.variant == 4 ? 8192 : 4096;
     const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : !ring32 && s.variant == 2 && s.tpt == 1 ? 32 : 64;
     int splits = 1;
