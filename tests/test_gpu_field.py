@@ -82,3 +82,48 @@ def test_field_at_very_distant_and_at_bad_points(scenes):
         assert np.isfinite(got[0, 0]) and abs(got[0, 0]) <= bound
     got = ctx.eval_field(dev[:1].contiguous(), np.array([[np.nan, 0, 9.0], [4.0, 5.0, 6.0]])).cpu().numpy()
     assert np.isnan(got[0, 0]) and abs(got[0, 1] - ref[0, 1]) < TOL * abs(ref[0, 1])
+
+
+def _near_extended(g, q, t, kappa, eta):
+    """The same sums in extended precision (64-bit significands on this host)."""
+    ld = np.longdouble
+    g, q, t, kappa, eta = g.astype(ld), q.astype(np.clongdouble), t.astype(ld), ld(kappa), ld(eta)
+    out = np.zeros((len(q), len(t)), dtype=np.clongdouble)
+    for i, x in enumerate(t):
+        d = x[None] - g[:, :3]
+        R = np.sqrt((d * d).sum(1))
+        nd = (d * g[:, 3:6]).sum(1)
+        ph = kappa * R
+        K = (np.cos(ph) + 1j * np.sin(ph)) / R * (nd / R ** 2 * (1 - 1j * ph) + 1j * eta)
+        out[:, i] = (q * K[None]).sum(1)
+    return out
+
+
+@pytest.mark.parametrize("kappa", [0.7, 3.0])
+@pytest.mark.parametrize("offset", [0.0, 1000.0])
+def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset):
+    """Points 1e-3 and 1e-2 off the nodes of a scene at the origin and of one far from it: the
+    distances come from the differences of the coordinates as given, so that neither the closeness nor the
+    place costs digits."""
+    import torch
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    ctx = Context(0)
+    for k, c in enumerate((geo.sphere(1.0, 4, 10), geo.prolate(0.8, 1.3, 5, 9))):
+        ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, 8,
+                       np.array([3.0 * k + offset, 0.5 * k + offset, -0.2]), geo.random_rotation(np.random.default_rng(k)))
+    ctx.precompute_scattering()
+    g = ctx.node_geometry()
+    rng = np.random.default_rng(11)
+    sig = rng.standard_normal((2, ctx.N)) + 1j * rng.standard_normal((2, ctx.N))
+    q = sig.astype(np.clongdouble) * (g[:, 6].astype(np.longdouble) / (16 * np.arctan(np.longdouble(1))))
+    for h in (1e-3, 1e-2):
+        j = rng.integers(0, ctx.N, 40)
+        t = g[j, :3] + h * g[j, 3:6]
+        ref = _near_extended(g, q, t, kappa, 1.5)
+        got = ctx.eval_field(torch.from_numpy(sig).to("cuda:0"), t).cpu().numpy()
+        # differences, R and 1/R^3 to about 10 roundings, a phase of at most 20 radians to 3 more
+        # each, sums of chunks of 66 terms: 64 eps of the largest value
+        err = float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
+        assert err < 64 * np.finfo(np.float64).eps, (h, err)
+    ctx.close()
