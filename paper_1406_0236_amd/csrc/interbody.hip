@@ -1218,21 +1218,26 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
 //    round is a small share of the launch; its chunks are also its FP32 sums, added
 //    up in FP64 afterwards, so it keeps 64 where 32 would run as fast (at zero
 //    frequency 32 doubles the error: 77,760 nodes 6.4e-7 and 1.2e-6 of the result).
-//    The MFMA orders add 128 sources at a time and show no such difference.  For the
-//    same reason the FP32 VALU orders count tiles of one target per thread (rings)
-//    and two (points) whatever they choose, which also bounds their scratch.
+//    For the same reason the FP32 VALU orders count tiles of one target per thread
+//    (rings) and two (points) whatever they choose, which also bounds their scratch,
+//    and interbody_mfma_kernel, which adds up a whole chunk in FP32 too, takes in
+//    FP32 up to 64 whatever the number of rhs groups, for the remainder of 16 rhs as well
+//    (17,150 to 45,600 nodes, chunks by the rhs groups, at most 16: error 1.0 to 2.4 times
+//    that, 1.2 on average; the remainder's up to 1.07).  interbody_mfma16_kernel starts
+//    anew every 128 sources.
 static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
     const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
+    const bool mf32 = mf && prec == AXS_FP32 && (s.variant == 3 || nrhs % 16 != 0);
     const int tile = ring32 && c.ib_tpt[1] == 0 ? (s.variant == 2 ? 1 : 2) * s.bs : ib_tile(s);
     // groups of a launch; a remainder's own launch has one
-    const int groups = mf && nrhs % 16 == 0 ? nrhs / 16 : 1;
+    const int groups = mf && !mf32 && nrhs % 16 == 0 ? nrhs / 16 : 1;
     const int64_t tiles = count_tiles(c, tile) * groups;
-    const int64_t want = ring32 && s.variant == 2 ? 16384 : s.variant == 4 ? 8192 : 4096;
-    const int most = s.variant == 4 || (mf && s.tpt <= 2) ? 16 : !ring32 && s.variant == 2 && s.tpt == 1 ? 32 : 64;
+    const int64_t want = ring32 && s.variant == 2 ? 16384 : s.variant == 4 && !mf32 ? 8192 : 4096;
+    const int most = mf32 ? 64 : s.variant == 4 || (mf && s.tpt <= 2) ? 16 : !ring32 && s.variant == 2 && s.tpt == 1 ? 32 : 64;
     int splits = 1;
     while (tiles * splits < want && splits < most) splits *= 2;
     // no empty chunks: 100 rings in 32 chunks are 25 chunks of 4
-    const Units u = ib_units(s);
+    const Units u = mf32 ? Units::nodes : ib_units(s);   // the remainder of 16 rhs counts nodes
     int64_t total = 0, used = 1;
     for (size_t bi = 0; bi < c.bodies.size(); ++bi) total += body_units(c, bi, u);
     for (size_t bi = 0; bi < c.bodies.size(); ++bi) {
