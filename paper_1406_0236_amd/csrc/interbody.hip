@@ -978,7 +978,7 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
 
     float tx[G], ty[G], tz[G], bT[G], n0 = 0.f;
-    f32x4 cR[G], sumR[G], sumI[G];
+    f32x4 cR[G], sumR[G], sumI[G], accR[G], accI[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
         const int t = (wv * G + g) * 16 + col;
@@ -988,7 +988,7 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
         tz[g] = gz[gi];
         bT[g] = 0.f;
         cR[g] = zero4;
-        sumR[g] = sumI[g] = zero4;
+        sumR[g] = sumI[g] = accR[g] = accI[g] = zero4;
     }
     int prev = -1;
 
@@ -1041,11 +1041,12 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
             const h8 *src = q16 + ((int64_t)grp * nblk + B) * MF16_BLK;
             for (int i = tid; i < nb * MF16_BLK; i += 256) s_q[i] = src[i];
             __syncthreads();
-            // the matrix cores accumulate one chunk (at most 128 sources) from
-            // zero; the chunk sums are added on the VALU, rounded to nearest
-            f32x4 accR[G], accI[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) accR[g] = accI[g] = zero4;
+            // the matrix cores accumulate one chunk (at most 128 sources); the chunk
+            // sums are added on the VALU, rounded to nearest, and each chunk starts from
+            // what the addition before it lost (Kahan's summation): the error does not grow
+            // with the chunks an item holds (19,680 sources in one item: 2.9e-7 of the
+            // result, 3.5e-7 without, 2.9e-7 either way in 64), for two more additions a
+            // sum in some 1,800 instructions (64 rhs on 20,090 nodes: 1.208 -> 1.220 ms)
 #pragma unroll 1
             for (int jb = live ? 0 : nb; jb < nb; ++jb) {
                 const h8 *qb = s_q + jb * MF16_BLK;
@@ -1085,8 +1086,11 @@ __global__ __launch_bounds__(256) void interbody_mfma16_kernel(
             }
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                sumR[g] += accR[g];
-                sumI[g] += accI[g];
+                const f32x4 tR = sumR[g] + accR[g], tI = sumI[g] + accI[g];
+                accR[g] -= tR - sumR[g];
+                accI[g] -= tI - sumI[g];
+                sumR[g] = tR;
+                sumI[g] = tI;
             }
             B = e;
         }
@@ -1223,8 +1227,8 @@ static int default_tpt(const Ctx &c, int prec, int variant, int nrhs) {
 //    and interbody_mfma_kernel, which adds up a whole chunk in FP32 too, takes in
 //    FP32 up to 64 whatever the number of rhs groups, for the remainder of 16 rhs as well
 //    (17,150 to 45,600 nodes, chunks by the rhs groups, at most 16: error 1.0 to 2.4 times
-//    that, 1.2 on average; the remainder's up to 1.07).  interbody_mfma16_kernel starts
-//    anew every 128 sources.
+//    that, 1.2 on average; the remainder's up to 1.07).  interbody_mfma16_kernel's
+//    error does not depend on its chunks.
 static int default_splits(const Ctx &c, int prec, const IBShape &s, int nrhs) {
     const bool mf = s.variant >= 3, ring32 = prec == AXS_FP32 && !mf;
     const bool mf32 = mf && prec == AXS_FP32 && (s.variant == 3 || nrhs % 16 != 0);
