@@ -321,6 +321,7 @@ void finish_precompute(Ctx &c) {
     c.tw32 = up.at<float>(o_tw32);
     c.body_dev = up.at<BodyDev>(o_bd);
     AXS_HIP(hipStreamSynchronize(c.stream));   // the upload comes from pageable host memory
+    up.pending = false;
     c.precomputed = true;
 }
 

@@ -299,12 +299,18 @@ struct Skeleton {
 // setup.hip
 // Host arrays gathered into one block and copied to the device at once (a copy
 // from pageable memory holds the host up for some 10 us whatever its size).  The
-// object has to outlive the copy, until the next synchronisation of c.stream.
+// host copy is read until the stream has come that far: an owner that has
+// synchronised c.stream since says so (`pending` = false), and one that has not, as
+// after an error, waits in the destructor before the copy's source goes.
 struct Upload {
     Ctx &c;
     std::vector<char> host;
     char *dev = nullptr;
+    bool pending = false;
     explicit Upload(Ctx &c_) : c(c_) {}
+    ~Upload() {
+        if (pending) (void)hipStreamSynchronize(c.stream);
+    }
     Upload(const Upload &) = delete;
     Upload &operator=(const Upload &) = delete;
     size_t put(const void *p, size_t bytes) {   // offset of the copy in the block
@@ -319,6 +325,7 @@ struct Upload {
     }
     void commit() {   // the block belongs to the context (c.dfree(dev) gives it back earlier)
         dev = (char *)c.dalloc(std::max<size_t>(host.size(), 1));
+        pending = true;
         AXS_HIP(hipMemcpyAsync(dev, host.data(), host.size(), hipMemcpyHostToDevice, c.stream));
     }
     template <class T>

@@ -560,6 +560,11 @@ __global__ __launch_bounds__(256) void modal_kernel(Pts pts, int64_t npts, int N
     }
 }
 
+static void require_modal_size(int Nt, int M) {
+    AXS_REQUIRE(Nt <= 16384 && (size_t)ModalSize(Nt, M).shared(4) * sizeof(double) <= 160 * 1024, AXS_EINVAL,
+                "mode count or wavenumber too large for the modal kernel");
+}
+
 // Values of m = 0..M for npts points.  16 points a workgroup while two workgroups
 // share a CU's LDS, else 4 (large kappa r or M); of 2, 3 and 4 values of m a thread the one that leaves the
 // fewest turns idle.
@@ -568,7 +573,7 @@ static void modal_launch(Ctx &c, Pts pts, int64_t npts, int Nt, int M, double *f
     const ModalSize z(Nt, M);
     const int PT = (size_t)z.shared(16) * sizeof(double) <= 80 * 1024 ? 16 : 4;
     const size_t shm = (size_t)z.shared(PT) * sizeof(double);
-    AXS_REQUIRE(shm <= 160 * 1024, AXS_EINVAL, "mode count or wavenumber too large for the modal kernel");
+    require_modal_size(Nt, M);
     hipLaunchKernelGGL(toroidal_kernel, dim3(ceil_div(npts, 64)), dim3(64), 0, c.stream, pts, npts, z.nq, f, scale,
                        decay);
     AXS_HIP(hipGetLastError());
@@ -1371,6 +1376,7 @@ void precompute_shapes(Ctx &c) {
     for (auto &s : c.shapes) {
         AXS_REQUIRE(s.p <= PMAX, AXS_EINVAL, "at most 16 nodes per panel are supported");
         s.Nt = modal_nt(s);
+        require_modal_size(s.Nt, s.M);   // before anything is allocated or queued
         total += (size_t)(s.M + 1) * s.NG * s.NG;
     }
     double2 *A = (double2 *)c.dalloc(total * sizeof(double2)), *S = (double2 *)c.dalloc(total * sizeof(double2));
@@ -1398,6 +1404,7 @@ void precompute_shapes(Ctx &c) {
     done.push_back(up.dev);
     invert_shapes(c, keep, done);
     release(c, done);
+    for (auto &k : keep) k->pending = false;
 }
 
 void modal_values(Ctx &c, double kappa, double gam_re, double gam_im, int M, int Nt,

@@ -188,3 +188,26 @@ def test_inverses_as_exact_as_row_by_row_elimination():
     ratio = math.exp(np.mean(got) - np.mean(ref))
     print(f"error of the inverses, blocked over column by column: {ratio:.3f}")
     assert ratio <= 1.0, ratio
+
+
+def test_refused_wavenumber_leaves_nothing_behind():
+    """A wavenumber beyond the modal kernel's LDS is refused before anything is allocated or
+    queued, every time, and the device is as it was for another context."""
+    import torch
+    from paper_1406_0236_amd import AxsError, Context
+    from workloads import geometry as geo
+    ctx = Context(0)
+    c = geo.sphere(1.0, 4, 10)
+    for b in range(2):     # a shape that is taken beside one that is not
+        f = 0.01 if b == 0 else 1.0
+        ctx.build_body(c.rz * f, c.drz * f, c.gw, c.n_panels, c.p, 400.0, 400.0, 20, np.array([6.0 * b, 0.0, 0.0]),
+                       np.eye(3))
+    before = torch.cuda.memory_allocated()
+    for _ in range(2):
+        with pytest.raises(AxsError, match="EINVAL.*too large for the modal kernel"):
+            ctx.precompute_scattering()
+        assert torch.cuda.memory_allocated() == before
+    ctx.close()
+    ok = _context([geo.sphere(1.0, 2, 8)], 1.0, 2)
+    _check_inverse(ok, 0, 2, 16)
+    ok.close()
