@@ -27,6 +27,7 @@
 namespace axs {
 
 constexpr int FIELD_TILE = 64;   // node records in LDS at a time
+constexpr size_t FIELD_SCRATCH = (size_t)256 << 20;   // records of one pass over groups of rhs, and its partial sums
 
 enum FieldKind { FIELD_FAR = 0, FIELD_NEAR = 1, FIELD_LAPLACE = 2 };
 
@@ -53,7 +54,8 @@ __global__ __launch_bounds__(256) void field_records_kernel(const double *__rest
     }
 }
 
-// part[chunk][c][t] (or u[c][t] where there is one chunk).  wide: phases may reach
+// part[chunk][c - c0][t] for the pass's nc rhs from c0 on (u[c0 ..][t] where there is
+// one chunk).  wide: phases may reach
 // 2^39 revolutions, reduced to a fraction first.  Near: the distance comes from the
 // differences of the coordinates as given, and k / 2 pi goes into R^2 (one
 // multiplication a pair).  With records and targets scaled by k / 2 pi beforehand each
@@ -64,7 +66,7 @@ template <int KIND, int NR, int TPT>
 __global__ __launch_bounds__(256) void field_kernel(const double *__restrict__ rec, int64_t N, int64_t chunk,
                                                     const double *__restrict__ tgt, int nt, double kappa,
                                                     double k2pi, double eta, int wide,
-                                                    const double2 *__restrict__ sctab, int c0, int nrhs,
+                                                    const double2 *__restrict__ sctab, int nc,
                                                     double2 *__restrict__ part) {
     constexpr int ST = 6 + 2 * NR;
     __shared__ __align__(16) double s_rec[FIELD_TILE * ST];
@@ -150,8 +152,8 @@ __global__ __launch_bounds__(256) void field_kernel(const double *__restrict__ r
         if (t >= nt) continue;
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
-            const int cc = c0 + blockIdx.z * NR + c;
-            if (cc < nrhs) part[((int64_t)blockIdx.y * nrhs + cc) * nt + t] = make_double2(ar[k][c], ai[k][c]);
+            const int cc = blockIdx.z * NR + c;
+            if (cc < nc) part[((int64_t)blockIdx.y * nc + cc) * nt + t] = make_double2(ar[k][c], ai[k][c]);
         }
     }
 }
@@ -211,14 +213,14 @@ static int field_resident_for(int nr) {
 
 template <int KIND, int NR>
 static void launch_field(Ctx &c, dim3 grid, int bs, bool many, const double *rec, int64_t chunk, const double *tgt, int nt,
-                         double eta, int wide, int c0, int nrhs, double2 *part) {
+                         double eta, int wide, int nc, double2 *part) {
     constexpr int TPT = field_tpt(NR);
     if (many)
         hipLaunchKernelGGL((field_kernel<KIND, NR, TPT>), grid, dim3(bs), 0, c.stream, rec, c.N, chunk, tgt, nt,
-                           c.kappa, c.kappa / (2.0 * M_PI), eta, wide, c.sctab, c0, nrhs, part);
+                           c.kappa, c.kappa / (2.0 * M_PI), eta, wide, c.sctab, nc, part);
     else
         hipLaunchKernelGGL((field_kernel<KIND, NR, 1>), grid, dim3(bs), 0, c.stream, rec, c.N, chunk, tgt, nt,
-                           c.kappa, c.kappa / (2.0 * M_PI), eta, wide, c.sctab, c0, nrhs, part);
+                           c.kappa, c.kappa / (2.0 * M_PI), eta, wide, c.sctab, nc, part);
     AXS_HIP(hipGetLastError());
 }
 
@@ -228,8 +230,8 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
     // groups of equal width, at most 8 rhs each
     const int groups = (int)ceil_div(nrhs, 8), nr = (int)ceil_div(nrhs, groups);
     const size_t rec_group = (size_t)c.N * (6 + 2 * nr) * sizeof(double);
-    // records of at most 256 MiB at a time (at least one group)
-    const int gb = (int)std::max<size_t>(1, std::min<size_t>(groups, ((size_t)256 << 20) / rec_group));
+    // groups of one pass: as many as have their records within FIELD_SCRATCH (at least one)
+    const int gb = (int)std::max<size_t>(1, std::min<size_t>(groups, FIELD_SCRATCH / rec_group));
     // up to 64 targets: one wavefront per workgroup; from 1,024 targets on 4 per lane
     // (2 with more than 4 densities), if that leaves three workgroups a CU
     // (18,860 nodes: 1,024 targets 83 us with 4, 69 with 1; 3,000 targets the same)
@@ -253,13 +255,17 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
             if (f > fill + 0.03) fill = f, want = n;
         }
     }
+    // a pass's partial sums stay within FIELD_SCRATCH too (8 rhs on 65,535 targets, the most
+    // of one group, have room for 32 chunks)
+    const size_t part_chunk = (size_t)std::min(nrhs, gb * nr) * nt * sizeof(double2);
+    want = std::max<int64_t>(1, std::min<int64_t>(want, FIELD_SCRATCH / part_chunk));
     const int64_t chunk = ceil_div(c.N, want);
     const int nchunk = (int)ceil_div(c.N, chunk);
     double *rec = (double *)c.scratch(WS_TMP, rec_group * gb);
-    const int64_t items = (int64_t)nrhs * nt;
-    double2 *part = nchunk > 1 ? (double2 *)c.scratch(WS_TMP2, (size_t)nchunk * items * sizeof(double2)) : (double2 *)u;
+    double2 *sums = nchunk > 1 ? (double2 *)c.scratch(WS_TMP2, nchunk * part_chunk) : nullptr;
     for (int g0 = 0; g0 < groups; g0 += gb) {
-        const int ng = std::min(gb, groups - g0), c0 = g0 * nr;
+        const int ng = std::min(gb, groups - g0), c0 = g0 * nr, nc = std::min(nrhs - c0, ng * nr);
+        double2 *out = (double2 *)u + (int64_t)c0 * nt, *part = nchunk > 1 ? sums : out;
         hipLaunchKernelGGL(field_records_kernel, dim3((unsigned)ceil_div(c.N, 256), ng), dim3(256), 0, c.stream, c.g64,
                            c.N, (const double2 *)sigma, c0, nrhs, nr, sx, sn, rec);
         AXS_HIP(hipGetLastError());
@@ -267,7 +273,7 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
         switch (nr) {
 #define AXS_FIELD_NR(NR_)                                                                                      \
     case NR_:                                                                                                  \
-        launch_field<KIND, NR_>(c, grid, bs, many, rec, chunk, tgt, nt, eta, wide, c0, nrhs, part);            \
+        launch_field<KIND, NR_>(c, grid, bs, many, rec, chunk, tgt, nt, eta, wide, nc, part);                  \
         break;
             AXS_FIELD_NR(1)
             AXS_FIELD_NR(2)
@@ -279,11 +285,12 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
             AXS_FIELD_NR(8)
 #undef AXS_FIELD_NR
         }
-    }
-    if (nchunk > 1) {
-        hipLaunchKernelGGL(field_reduce_kernel, dim3((unsigned)ceil_div(items, 16)), dim3(256), 0, c.stream, part, nchunk,
-                           items, (double2 *)u);
-        AXS_HIP(hipGetLastError());
+        if (nchunk > 1) {
+            const int64_t items = (int64_t)nc * nt;
+            hipLaunchKernelGGL(field_reduce_kernel, dim3((unsigned)ceil_div(items, 16)), dim3(256), 0, c.stream, part,
+                               nchunk, items, out);
+            AXS_HIP(hipGetLastError());
+        }
     }
 }
 

@@ -127,3 +127,47 @@ def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset):
         err = float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
         assert err < 64 * np.finfo(np.float64).eps, (h, err)
     ctx.close()
+
+
+@pytest.mark.parametrize("kappa", [0.0, 2.0])
+def test_many_right_hand_sides_within_bounded_scratch(kappa):
+    """4,096 densities: more than one pass over groups of right-hand sides (47 of the 512 groups'
+    records of 32,400 nodes fit 256 MiB), every one of them against the reference; and the device memory the
+    evaluation keeps stays within twice 256 MiB, records and partial sums."""
+    import torch
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    ctx = Context(0)
+    c = geo.sphere(1.0, 20, 10)
+    for k in range(2):
+        ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, 40, np.array([3.0 * k, 0.0, 0.0]), np.eye(3))
+    ctx.precompute_scattering()
+    g = ctx.node_geometry()
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    dev = torch.randn((4096, ctx.N), dtype=torch.complex128, device="cuda:0", generator=gen)
+    rng = np.random.default_rng(1)
+    for nt in (64, 1500):
+        t = rng.uniform(-4, 12, (nt, 3))
+        t[:, 2] = 3.0 + 2 * rng.random(nt)
+        before = torch.cuda.memory_allocated()
+        got = ctx.eval_field(dev, t)
+        kept = torch.cuda.memory_allocated() - before - got.numel() * 16
+        assert kept <= (2 << 28) + (1 << 20), (nt, kept)
+        d = t[:, None, :] - g[None, :, :3]
+        R = np.linalg.norm(d, axis=2)
+        nd = np.einsum("tjk,jk->tj", d, g[:, 3:6])
+        K = (nd / R ** 2 + 1.5) / R if kappa == 0 else \
+            np.exp(1j * kappa * R) / R * (nd / R ** 2 * (1 - 1j * kappa * R) + 1.5j)
+        K = torch.from_numpy((K * (g[:, 6] / (4 * math.pi))).astype(np.complex128).T.copy()).to("cuda:0")
+        ref = dev @ K
+        # as TOL, with 32,400 terms for 1,500
+        assert float((got - ref).abs().max() / ref.abs().max()) < 22 * TOL
+        if kappa > 0:
+            x = rng.standard_normal((nt, 3))
+            x /= np.linalg.norm(x, axis=1, keepdims=True)
+            K = np.exp(-1j * kappa * (x @ g[:, :3].T)) * (1j * (1.5 - kappa * (x @ g[:, 3:6].T)))
+            K = torch.from_numpy((K * (g[:, 6] / (4 * math.pi))).T.copy()).to("cuda:0")
+            ref = dev @ K
+            got = ctx.far_field(dev, x)
+            assert float((got - ref).abs().max() / ref.abs().max()) < 22 * TOL
+    ctx.close()
