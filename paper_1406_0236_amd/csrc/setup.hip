@@ -44,8 +44,8 @@ namespace axs {
 // Gauss points per level: the interpolation l_j(s) times the curve's own
 // polynomial has degree 2p and more, which 10 points do not integrate for p > 10
 // (with 10 the largest error of an entry is 2e-12 at p = 11, 1e-11 at 12 and
-// 1e-8 at 16; with p points the kernel values' noise, 1e-12).  kl: the longest panel in
-// units of 1/kappa; the kernel's own oscillation takes one more for every two
+// 1e-8 at 16; with p points the kernel values' noise, 1e-12).  kl: the shape's longest panel
+// in units of 1/kappa; the kernel's own oscillation takes one more for every two
 // beyond 5 (with 10 the error is 1e-10 at kl = 9).
 static int level_points(int p, double kl) {
     return std::max(p, 10 + (int)std::ceil(std::min(std::max(0.0, 0.5 * (kl - 5.0)), 54.0)));
@@ -93,11 +93,15 @@ struct FarDesc {
 };
 
 // where a shape's matrices go; nodes and panels are numbered through all shapes
-// that are set up together
+// that are set up together.  Its rules, in the table of constants: `ngl` Gauss points a
+// level from gl on and their weights behind, own_pts(ngl) of the own panel from own on
+// and their weights behind.
 struct ShapeRef {
     double2 *A;
     int32_t NG, node0;
+    int32_t ngl, gl, own, pad;
 };
+__host__ __device__ inline int own_pts(int ngl) { return OWN_LEV * ngl + OWN_NQ; }
 
 // ---------------------------------------------------------------------------
 // evaluation points
@@ -127,12 +131,14 @@ __global__ void gen_far_kernel(const FarDesc *__restrict__ pairs, int n, int p, 
 __global__ __launch_bounds__(128) void gen_near_kernel(const NearDesc *__restrict__ desc, int p,
                                                        const double *__restrict__ snode,
                                                        const double *__restrict__ lden,
-                                                       const double *__restrict__ glu, const double *__restrict__ glw,
-                                                       int ngl, const double *__restrict__ ownx,
-                                                       const double *__restrict__ ownw, const double *__restrict__ r,
+                                                       const ShapeRef *__restrict__ shapes,
+                                                       const double *__restrict__ tab, const double *__restrict__ r,
                                                        const double *__restrict__ z, const double *__restrict__ rd,
                                                        const double *__restrict__ zd, Pts pts, int64_t base) {
     const NearDesc d = desc[blockIdx.x];
+    const ShapeRef sh = shapes[d.shape];
+    const int ngl = sh.ngl;
+    const double *glu = tab + sh.gl, *glw = glu + ngl, *ownx = tab + sh.own, *ownw = ownx + own_pts(ngl);
     const int own = (d.i / p) == d.P;
     const int iloc = own ? d.i - d.P * p : -1;
     const double *rP = r + d.P * p, *zP = z + d.P * p, *rdP = rd + d.P * p, *zdP = zd + d.P * p;
@@ -1045,10 +1051,8 @@ static int modal_nt(const Shape &s) {
 // the offsets of the tables in the upload
 struct ShapePlan {
     Shape all;        // contour nodes of all of them (p, M, Nt, kappa and eta are common)
-    int ngl = 0;
-    size_t tab = 0, refs = 0;   // the doubles below, in one array; the ShapeRefs
-    size_t o_sn = 0, o_lden = 0, o_gu = 0, o_gw = 0, o_ox = 0, o_ow = 0, o_r = 0, o_z = 0, o_nr = 0, o_nz = 0, o_aw = 0,
-           o_rd = 0, o_zd = 0;
+    size_t tab = 0, refs = 0;   // the doubles below and the shapes' rules, in one array; the ShapeRefs
+    size_t o_sn = 0, o_lden = 0, o_r = 0, o_z = 0, o_nr = 0, o_nz = 0, o_aw = 0, o_rd = 0, o_zd = 0;
     struct Batch {   // target rows
         size_t far = 0, near = 0;
         int nfar = 0, nd = 0;
@@ -1066,7 +1070,7 @@ static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
     s.NG = s.n_panels = 0;
     for (auto *v : {&s.r, &s.z, &s.dr, &s.dz, &s.gw}) v->clear();
     for (auto *q : shapes) {
-        refs.push_back(ShapeRef{(double2 *)q->A64, q->NG, s.NG});
+        refs.push_back(ShapeRef{(double2 *)q->A64, q->NG, s.NG, 0, 0, 0, 0});
         first_panel.push_back(s.n_panels);
         shape_of.resize(s.n_panels + q->n_panels, (int)refs.size() - 1);
         s.NG += q->NG;
@@ -1078,7 +1082,6 @@ static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
         s.gw.insert(s.gw.end(), q->gw.begin(), q->gw.end());
     }
     first_panel.push_back(s.n_panels);
-    plan.refs = up.put(refs);
     const int NG = s.NG, p = s.p, np_ = s.n_panels;
 
     std::vector<double> sn, sw;
@@ -1100,24 +1103,43 @@ static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
         plen[i / p] += sp * s.gw[i];
         smax[i / p] = std::max(smax[i / p], sp);
     }
-    std::vector<double> gu, gwq, qu, qw;
-    const int ngl = plan.ngl = level_points(p, s.kappa * *std::max_element(plen.begin(), plen.end()));
-    const int own_pts = OWN_LEV * ngl + OWN_NQ;
-    gauss_legendre(ngl, gu, gwq);
+    std::vector<double> hc;   // the table of constants
+    auto put = [&](const std::vector<double> &v) {
+        const size_t o = hc.size();
+        hc.insert(hc.end(), v.begin(), v.end());
+        return o;
+    };
+    // every shape's rules by its own panels, so that its matrices are the same beside any
+    // other shape; shapes of one rule share it
+    std::vector<double> qu, qw;
     gauss_legendre(OWN_NQ, qu, qw);
-    // the own-panel rule on [0, 1], singular at 0
-    std::vector<double> ownx, ownw;
-    for (int lev = 0; lev < OWN_LEV; ++lev)
-        for (int k = 0; k < ngl; ++k) {
-            const double half = std::ldexp(0.25, -lev);   // half of [2^-(lev + 1), 2^-lev]
-            ownx.push_back(2.0 * half + half * (gu[k] + 1.0));
-            ownw.push_back(half * gwq[k]);
+    for (size_t k = 0; k < refs.size(); ++k) {
+        const double longest = *std::max_element(plen.begin() + first_panel[k], plen.begin() + first_panel[k + 1]);
+        const int ngl = level_points(p, s.kappa * longest);
+        for (size_t o = 0; o < k; ++o)
+            if (refs[o].ngl == ngl) refs[k].gl = refs[o].gl, refs[k].own = refs[o].own;
+        refs[k].ngl = ngl;
+        if (refs[k].own > 0) continue;
+        std::vector<double> gu, gw, ownx, ownw;
+        gauss_legendre(ngl, gu, gw);
+        // the own-panel rule on [0, 1], singular at 0
+        for (int lev = 0; lev < OWN_LEV; ++lev)
+            for (int q = 0; q < ngl; ++q) {
+                const double half = std::ldexp(0.25, -lev);   // half of [2^-(lev + 1), 2^-lev]
+                ownx.push_back(2.0 * half + half * (gu[q] + 1.0));
+                ownw.push_back(half * gw[q]);
+            }
+        for (int q = 0; q < OWN_NQ; ++q) {
+            const double u = 0.5 * (qu[q] + 1.0), h = std::ldexp(1.0, -OWN_LEV);
+            ownx.push_back(h * std::pow(u, OWN_Q));
+            ownw.push_back(h * OWN_Q * std::pow(u, OWN_Q - 1) * 0.5 * qw[q]);
         }
-    for (int k = 0; k < OWN_NQ; ++k) {
-        const double u = 0.5 * (qu[k] + 1.0), h = std::ldexp(1.0, -OWN_LEV);
-        ownx.push_back(h * std::pow(u, OWN_Q));
-        ownw.push_back(h * OWN_Q * std::pow(u, OWN_Q - 1) * 0.5 * qw[k]);
+        refs[k].gl = (int32_t)put(gu);
+        put(gw);
+        refs[k].own = (int32_t)put(ownx);
+        put(ownw);
     }
+    plan.refs = up.put(refs);
     // derivative of every panel's interpolant at its nodes
     std::vector<double> rd(NG, 0.0), zd(NG, 0.0);
     for (int i = 0; i < NG; ++i) {
@@ -1151,7 +1173,7 @@ static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
     }
     // points on one side (length Ls in s) of a panel at distance d: halve until
     // the innermost interval is shorter than d / 8
-    auto side_points = [&](double Ls, double d, double speed) {
+    auto side_points = [&](double Ls, double d, double speed, int ngl) {
         if (!(Ls > 1e-14)) return 0;
         int n = 1;
         while (n < MAX_LEV && std::ldexp(Ls, 1 - n) * speed > 0.125 * d) ++n;
@@ -1182,24 +1204,17 @@ static ShapePlan plan_shapes(const std::vector<Shape *> &shapes, Upload &up) {
             d.shape = sh;
             if (P == own) {
                 d.sstar = sn[i - own * p];
-                d.n0 = d.n1 = own_pts;
+                d.n0 = d.n1 = own_pts(refs[sh].ngl);
             } else {
                 d.sstar = bs;
-                d.n0 = side_points(bs + 1.0, best, smax[P]);
-                d.n1 = side_points(1.0 - bs, best, smax[P]);
+                d.n0 = side_points(bs + 1.0, best, smax[P], refs[sh].ngl);
+                d.n1 = side_points(1.0 - bs, best, smax[P], refs[sh].ngl);
             }
             near[i].push_back(d);
         }
     }
-    std::vector<double> hc;
-    auto put = [&](const std::vector<double> &v) {
-        const size_t o = hc.size();
-        hc.insert(hc.end(), v.begin(), v.end());
-        return o;
-    };
-    plan.o_sn = put(sn), plan.o_lden = put(lden), plan.o_gu = put(gu), plan.o_gw = put(gwq), plan.o_ox = put(ownx),
-    plan.o_ow = put(ownw), plan.o_r = put(s.r), plan.o_z = put(s.z), plan.o_nr = put(nr), plan.o_nz = put(nz),
-    plan.o_aw = put(aw), plan.o_rd = put(rd), plan.o_zd = put(zd);
+    plan.o_sn = put(sn), plan.o_lden = put(lden), plan.o_r = put(s.r), plan.o_z = put(s.z), plan.o_nr = put(nr),
+    plan.o_nz = put(nz), plan.o_aw = put(aw), plan.o_rd = put(rd), plan.o_zd = put(zd);
     plan.tab = up.put(hc);
     // batches of target rows, bounded number of evaluation points
     const int64_t max_pts = 1 << 19;
@@ -1263,8 +1278,7 @@ static void run_shapes(Ctx &c, const ShapePlan &plan, const Upload &up) {
         }
         // a target's own panel is always near, so no batch is without near points
         hipLaunchKernelGGL(gen_near_kernel, dim3(bt.nd), dim3(128), 0, c.stream, d_nd, p, dc + plan.o_sn,
-                           dc + plan.o_lden, dc + plan.o_gu, dc + plan.o_gw, plan.ngl, dc + plan.o_ox, dc + plan.o_ow,
-                           dc + plan.o_r, dc + plan.o_z, dc + plan.o_rd, dc + plan.o_zd, pts, nfar);
+                           dc + plan.o_lden, refs, dc, dc + plan.o_r, dc + plan.o_z, dc + plan.o_rd, dc + plan.o_zd, pts, nfar);
         AXS_HIP(hipGetLastError());
         modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, s.kappa, s.kappa > 0 ? 0.0 : s.eta,
                      s.kappa > 0 ? s.eta : 0.0, kv);

@@ -211,3 +211,19 @@ def test_refused_wavenumber_leaves_nothing_behind():
     ok = _context([geo.sphere(1.0, 2, 8)], 1.0, 2)
     _check_inverse(ok, 0, 2, 16)
     ok.close()
+
+
+def test_shapes_of_long_and_short_panels_together_as_alone():
+    """Panels of more than 5 / kappa take more points a level; the shapes beside them do not."""
+    from workloads import geometry as geo
+    M, kappa = 6, 4.0     # kappa times the longest panel: 6.3, 3.1 and 12.6
+    shapes = [geo.sphere(1.0, 2, 10), geo.sphere(1.0, 4, 10), geo.sphere(0.99, 1, 10)]
+    ctx = _context(shapes, kappa, M)
+    for b, c in enumerate(shapes):
+        one = _context([c], kappa, M)
+        for which in (0, 1):
+            got = ctx.modal_matrices(b, which, M=M, NG=c.NG).cpu().numpy()
+            diff = float(np.max(np.abs(got - one.modal_matrices(0, which, M=M, NG=c.NG).cpu().numpy())))
+            assert diff == 0.0, (b, which, diff)
+        one.close()
+    ctx.close()
