@@ -503,6 +503,19 @@ static void mlp_backward(Mlp &n, const float *T, const int32_t *rows, int B, flo
         n.cap_part = nparts;
     }
     if (!n.loss_dev) n.loss_dev = (double *)c.dalloc(sizeof(double));
+    // dH has few output tiles and, for the output layer, a long k range: split K.  The
+    // workspace is there before the first launch: a call that fails for want of memory
+    // has not written to `grad`
+    int64_t need = 0;
+    for (int k = 1; k < L; ++k) need = std::max(need, gemm_ws(B, n.sizes[k], n.sizes[k + 1]));
+    if (need > n.cap_ws) {
+        AXS_HIP(hipStreamSynchronize(c.stream));
+        c.dfree(n.ws);
+        n.ws = nullptr;
+        n.cap_ws = 0;
+        n.ws = (float *)c.dalloc((size_t)need * sizeof(float));
+        n.cap_ws = need;
+    }
     mlp_hidden(n, B);
     GemmArgs f = layer_args(n, L - 1, B);
     f.mode = GM_LOSS;
@@ -531,16 +544,6 @@ static void mlp_backward(Mlp &n, const float *T, const int32_t *rows, int B, flo
         w.colsum = grad + n.boff[k];
         gemm<true, false>(c, w);
         if (k == 0) break;
-        // dH has few output tiles and, for the output layer, a long k range: split K
-        const int64_t need = gemm_ws(B, a, b);
-        if (need > n.cap_ws) {
-            AXS_HIP(hipStreamSynchronize(c.stream));
-            c.dfree(n.ws);
-            n.ws = nullptr;
-            n.cap_ws = 0;
-            n.ws = (float *)c.dalloc((size_t)need * sizeof(float));
-            n.cap_ws = need;
-        }
         GemmArgs h;
         h.M = B;
         h.N = a;
@@ -552,7 +555,7 @@ static void mlp_backward(Mlp &n, const float *T, const int32_t *rows, int B, flo
         h.mode = GM_DGELU;
         h.aux = n.Z[k - 1];
         h.out = Gn;
-        gemm<false, true>(c, h, need > 0 ? n.ws : nullptr);
+        gemm<false, true>(c, h, gemm_ws(B, a, b) > 0 ? n.ws : nullptr);
         std::swap(G, Gn);
     }
 }

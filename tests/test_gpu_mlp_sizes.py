@@ -54,3 +54,30 @@ def test_products_at_edges(width, depth, n_out, B):
     assert abs(l2 - lr) <= tol * lr
     net.close()
     ctx.close()
+
+
+def test_gradient_that_fails_leaves_the_callers_array_alone():
+    """No device memory for the workspace of a split product: the call fails before it writes."""
+    import ctypes
+    from paper_1406_0236_amd import Context, Mlp
+    ctx = Context(0)
+    net = Mlp(ctx, 4, 512, 1, 70001)
+    B = 20
+    X, T = torch.randn(B, 4, device="cuda:0"), torch.randn(B, 70001, device="cuda:0")
+    net.forward(X)                  # the activations are there
+    grad = torch.full((net.nparams,), 7.0, device="cuda:0")
+    real = torch.cuda.caching_allocator_alloc
+    try:
+        # everything but large blocks: the partial sums of the loss, not the split product's workspace
+        torch.cuda.caching_allocator_alloc = lambda n, *a: real(n, *a) if n < (1 << 20) else 1 // 0
+        st = net.lib.axs_mlp_gradient(net.h, ctypes.c_void_p(X.data_ptr()), ctypes.c_void_p(T.data_ptr()), B, None,
+                                      ctypes.c_void_p(grad.data_ptr()))
+    finally:
+        torch.cuda.caching_allocator_alloc = real
+    torch.cuda.synchronize()
+    assert st == -3, st
+    assert bool((grad == 7.0).all())
+    loss, g = net.gradient(X, T)    # and succeeds once there is memory
+    assert np.isfinite(loss) and bool(torch.isfinite(g).all())
+    net.close()
+    ctx.close()
