@@ -54,6 +54,7 @@ void *Ctx::scratch(int slot, size_t bytes) {
         if (b.ptr) {
             AXS_HIP(hipStreamSynchronize(stream));   // the old buffer may still be in use
             dfree(b.ptr);
+            b = Buffer{};   // nothing left to use if the allocation fails
         }
         b.ptr = dalloc(bytes);
         b.bytes = bytes;

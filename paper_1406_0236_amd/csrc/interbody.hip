@@ -1664,6 +1664,7 @@ static const IBWork *get_work(Ctx &c, int pi, int wi, const IBShape &s, Units un
         if (c.ib_work[pi][wi]) {
             AXS_HIP(hipStreamSynchronize(c.stream));
             c.dfree(c.ib_work[pi][wi]);
+            c.ib_work[pi][wi] = nullptr;   // nothing left to use if the allocation fails
         }
         c.ib_work[pi][wi] = (IBWork *)c.dalloc(work.size() * sizeof(IBWork));
         AXS_HIP(hipMemcpy(c.ib_work[pi][wi], work.data(), work.size() * sizeof(IBWork), hipMemcpyHostToDevice));

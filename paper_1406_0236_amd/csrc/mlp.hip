@@ -568,6 +568,7 @@ static void load_order(Mlp &n, const int32_t *order, int64_t total) {
         AXS_HIP(hipStreamSynchronize(c.stream));
         c.dfree(n.order);
         n.order = nullptr;
+        n.cap_order = 0;
         n.order = (int32_t *)c.dalloc((size_t)total * sizeof(int32_t));
         n.cap_order = total;
     }
