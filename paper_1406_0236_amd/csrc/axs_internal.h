@@ -297,6 +297,14 @@ struct Skeleton {
 // launches (defined in the .hip files)
 // ---------------------------------------------------------------------------
 // setup.hip
+// Host array to device memory of the context, complete on return and after everything
+// queued on its stream before (hipMemcpy takes its turn on the null stream, which
+// a non-blocking stream does not wait for, nor it for that).
+inline void copy_in(Ctx &c, void *dst, const void *src, size_t bytes) {
+    AXS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c.stream));
+    AXS_HIP(hipStreamSynchronize(c.stream));
+}
+
 // Host arrays gathered into one block and copied to the device at once (a copy
 // from pageable memory holds the host up for some 10 us whatever its size).  The
 // host copy is read until the stream has come that far: an owner that has

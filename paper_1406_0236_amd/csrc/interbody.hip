@@ -1667,7 +1667,7 @@ static const IBWork *get_work(Ctx &c, int pi, int wi, const IBShape &s, Units un
             c.ib_work[pi][wi] = nullptr;   // nothing left to use if the allocation fails
         }
         c.ib_work[pi][wi] = (IBWork *)c.dalloc(work.size() * sizeof(IBWork));
-        AXS_HIP(hipMemcpy(c.ib_work[pi][wi], work.data(), work.size() * sizeof(IBWork), hipMemcpyHostToDevice));
+        copy_in(c, c.ib_work[pi][wi], work.data(), work.size() * sizeof(IBWork));
         c.ib_nwork[pi][wi] = (int)work.size();
         key[0] = s.tpt;
         key[1] = s.bs;

@@ -681,9 +681,9 @@ axs_status axs_mlp_set_params(axs_mlp *h, const float *host) {
     return mlp_guarded(h, [&](Mlp &n, Ctx &c) -> axs_status {
         AXS_REQUIRE(host, AXS_EINVAL, "null parameters");
         for (int64_t i = 0; i < n.nparams; ++i) AXS_REQUIRE(std::isfinite(host[i]), AXS_ENONFINITE, "non-finite parameter");
-        AXS_HIP(hipMemcpy(n.p, host, n.nparams * sizeof(float), hipMemcpyHostToDevice));
-        AXS_HIP(hipMemset(n.m, 0, n.nparams * sizeof(float)));
-        AXS_HIP(hipMemset(n.v, 0, n.nparams * sizeof(float)));
+        copy_in(c, n.p, host, n.nparams * sizeof(float));
+        AXS_HIP(hipMemsetAsync(n.m, 0, n.nparams * sizeof(float), c.stream));
+        AXS_HIP(hipMemsetAsync(n.v, 0, n.nparams * sizeof(float), c.stream));
         n.step = 0;
         return AXS_OK;
     });
@@ -945,8 +945,8 @@ struct WsTables {
         toff = (int64_t *)c.dalloc(off.size() * sizeof(int64_t));
         dirs = (double *)c.dalloc((size_t)3 * nrhs * sizeof(double));
         ph = (double2 *)c.dalloc((size_t)nrhs * nb * (nb - 1) * sizeof(double2));
-        AXS_HIP(hipMemcpy(toff, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-        AXS_HIP(hipMemcpy(dirs, dirs_host, (size_t)3 * nrhs * sizeof(double), hipMemcpyHostToDevice));
+        copy_in(c, toff, off.data(), off.size() * sizeof(int64_t));
+        copy_in(c, dirs, dirs_host, (size_t)3 * nrhs * sizeof(double));
         const int64_t n = (int64_t)nrhs * nb * (nb - 1);
         hipLaunchKernelGGL(ws_phase_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, c.stream, c.frame64, dirs,
                            nb, nrhs, c.kappa, ph);
@@ -1296,7 +1296,7 @@ axs_status axs_mlp_predict(axs_mlp *h, axs_ctx *ctx, const double *dirs, const d
             xf[(size_t)4 * i + 3] = (float)ks;
         }
         float *xd = (float *)n.ctx->dalloc(xf.size() * sizeof(float));
-        AXS_HIP(hipMemcpy(xd, xf.data(), xf.size() * sizeof(float), hipMemcpyHostToDevice));
+        copy_in(*n.ctx, xd, xf.data(), xf.size() * sizeof(float));
         axs::mlp_forward(n, xd, nrhs, nullptr);
         AXS_HIP(hipStreamSynchronize(n.ctx->stream));
         n.ctx->dfree(xd);

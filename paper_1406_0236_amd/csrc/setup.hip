@@ -1425,7 +1425,7 @@ void modal_values(Ctx &c, double kappa, double gam_re, double gam_im, int M, int
                   const std::vector<double> &h, int64_t P, double2 *kout) {
     const int nq = M + Nt / 2;
     double *pbuf = (double *)c.scratch(WS_MISC, (size_t)P * 9 * sizeof(double));
-    AXS_HIP(hipMemcpy(pbuf, h.data(), (size_t)P * 7 * sizeof(double), hipMemcpyHostToDevice));
+    copy_in(c, pbuf, h.data(), (size_t)P * 7 * sizeof(double));
     Pts pts{pbuf, pbuf + P, pbuf + 2 * P, pbuf + 3 * P, pbuf + 4 * P, pbuf + 5 * P, pbuf + 6 * P, nullptr};
     double *qv = (double *)c.scratch(WS_TMP, (size_t)P * nq * sizeof(double));
     modal_launch(c, pts, P, Nt, M, qv, pbuf + 7 * P, pbuf + 8 * P, kappa, gam_re, gam_im, kout);

@@ -404,7 +404,7 @@ static void ring_id(Ctx &c, const Shape &s, double R_p, double eps, std::vector<
     // projections per step; stop when the pivot norm falls below eps x the first
     int *active = (int *)c.dalloc(NG * sizeof(int));
     std::vector<int> one(NG, 1);
-    AXS_HIP(hipMemcpy(active, one.data(), NG * sizeof(int), hipMemcpyHostToDevice));
+    copy_in(c, active, one.data(), NG * sizeof(int));
     double *nrm = (double *)c.dalloc(NG * sizeof(double));
     double2 *coef = (double2 *)c.dalloc(NG * sizeof(double2));
     double2 *R = (double2 *)c.dalloc((size_t)NG * NG * sizeof(double2));
@@ -447,9 +447,9 @@ static void ring_id(Ctx &c, const Shape &s, double R_p, double eps, std::vector<
     const int nJ = (int)J.size();
     int *d_piv = (int *)c.dalloc((k + nJ + k + 1) * sizeof(int));
     int *d_J = d_piv + k, *d_col = d_J + nJ;
-    AXS_HIP(hipMemcpy(d_piv, piv.data(), k * sizeof(int), hipMemcpyHostToDevice));
-    if (nJ) AXS_HIP(hipMemcpy(d_J, J.data(), nJ * sizeof(int), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_col, colof.data(), k * sizeof(int), hipMemcpyHostToDevice));
+    copy_in(c, d_piv, piv.data(), k * sizeof(int));
+    if (nJ) copy_in(c, d_J, J.data(), nJ * sizeof(int));
+    copy_in(c, d_col, colof.data(), k * sizeof(int));
     double2 *T = (double2 *)c.dalloc((size_t)std::max(1, k * nJ) * sizeof(double2));
     if (nJ) {
         hipLaunchKernelGGL(ttrsm_kernel, dim3(ceil_div(nJ, 64)), dim3(64), 0, c.stream, R, NG, k, d_piv, d_J, nJ, T);
@@ -504,7 +504,7 @@ void skeletonize(Ctx &c, double eps, double factor) {
             std::vector<double2> id((size_t)s.NG * s.NG, make_double2(0.0, 0.0));
             for (int i = 0; i < s.NG; ++i) id[(size_t)i * s.NG + i] = make_double2(1.0, 0.0);
             Xs[k] = (double2 *)c.dalloc(id.size() * sizeof(double2));
-            AXS_HIP(hipMemcpy(Xs[k], id.data(), id.size() * sizeof(double2), hipMemcpyHostToDevice));
+            copy_in(c, Xs[k], id.data(), id.size() * sizeof(double2));
         }
         const int kk = (int)rings[k].size(), NG = s.NG, M = s.M;
         double2 *Y = (double2 *)c.dalloc((size_t)(M + 1) * NG * kk * sizeof(double2));
@@ -592,7 +592,7 @@ void skeletonize(Ctx &c, double eps, double factor) {
     }
     finish_precompute(ch);
     sk->desc = (SkelBody *)c.dalloc(desc.size() * sizeof(SkelBody));
-    AXS_HIP(hipMemcpy(sk->desc, desc.data(), desc.size() * sizeof(SkelBody), hipMemcpyHostToDevice));
+    copy_in(c, sk->desc, desc.data(), desc.size() * sizeof(SkelBody));
     sk->Ns = ch.N;
     sk->eps = eps;
     release_skeleton(c);
@@ -822,7 +822,7 @@ static std::vector<double2> dft_matrix(int M, int NF, double sign, double scale,
 
 static double2 *upload(Ctx &c, const std::vector<double2> &h) {
     double2 *d = (double2 *)c.dalloc(h.size() * sizeof(double2));
-    AXS_HIP(hipMemcpy(d, h.data(), h.size() * sizeof(double2), hipMemcpyHostToDevice));
+    copy_in(c, d, h.data(), h.size() * sizeof(double2));
     return d;
 }
 
@@ -1364,8 +1364,8 @@ static void point_id(Ctx &c, const Shape &s, double R_p, double eps, int npx, ui
     for (int t = 0; t < k; ++t)
         colof[t] = (int)(std::lower_bound(nodes.begin(), nodes.end(), perm[t]) - nodes.begin());
     int *d_perm = (int *)c.dalloc((n + k) * sizeof(int));
-    AXS_HIP(hipMemcpy(d_perm, perm.data(), n * sizeof(int), hipMemcpyHostToDevice));
-    AXS_HIP(hipMemcpy(d_perm + n, colof.data(), k * sizeof(int), hipMemcpyHostToDevice));
+    copy_in(c, d_perm, perm.data(), n * sizeof(int));
+    copy_in(c, d_perm + n, colof.data(), k * sizeof(int));
     XT = (double2 *)c.dalloc((size_t)k * n * sizeof(double2));
     hipLaunchKernelGGL(assemble_xt_kernel, dim3(ceil_div((int64_t)k * n, 256)), dim3(256), 0, c.stream, Rm,
                        (int64_t)ell, d_perm, d_perm + n, k, n, XT);
@@ -1503,7 +1503,7 @@ void skeletonize_points(Ctx &c, double eps, double factor, int n_proxy, uint64_t
         ch.bodies.push_back(B);
     }
     int64_t *d_idx = (int64_t *)ch.dalloc(Ns * sizeof(int64_t));
-    AXS_HIP(hipMemcpy(d_idx, gidx.data(), Ns * sizeof(int64_t), hipMemcpyHostToDevice));
+    copy_in(c, d_idx, gidx.data(), Ns * sizeof(int64_t));
     ch.g64 = (double *)ch.dalloc(7 * Ns * sizeof(double));
     ch.g32 = (float *)ch.dalloc(6 * Ns * sizeof(float));
     hipLaunchKernelGGL(gather_geo_kernel, dim3(ceil_div(7 * Ns, 256)), dim3(256), 0, c.stream, c.g64, c.N, d_idx, Ns,
@@ -1532,13 +1532,13 @@ void skeletonize_points(Ctx &c, double eps, double factor, int n_proxy, uint64_t
         bo.push_back(Ns);
         ch.nblk = bk.back();
         ch.body_off = (int64_t *)ch.dalloc(bo.size() * sizeof(int64_t));
-        AXS_HIP(hipMemcpy(ch.body_off, bo.data(), bo.size() * sizeof(int64_t), hipMemcpyHostToDevice));
+        copy_in(c, ch.body_off, bo.data(), bo.size() * sizeof(int64_t));
         ch.blk_off = (int32_t *)ch.dalloc(bk.size() * sizeof(int32_t));
-        AXS_HIP(hipMemcpy(ch.blk_off, bk.data(), bk.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        copy_in(c, ch.blk_off, bk.data(), bk.size() * sizeof(int32_t));
     }
     if (c.mf_src64) {
         int64_t *d_gi = (int64_t *)ch.dalloc(Ns * sizeof(int64_t));
-        AXS_HIP(hipMemcpy(d_gi, gidx.data(), Ns * sizeof(int64_t), hipMemcpyHostToDevice));
+        copy_in(c, d_gi, gidx.data(), Ns * sizeof(int64_t));
         ch.mf_src64 = (double *)ch.dalloc(8 * Ns * sizeof(double));
         ch.mf_src = (float *)ch.dalloc(8 * Ns * sizeof(float));
         hipLaunchKernelGGL(gather_mf_kernel, dim3(ceil_div(8 * Ns, 256)), dim3(256), 0, c.stream, c.mf_src64, c.N,
@@ -1731,7 +1731,7 @@ static BodyMats upload_mats(Ctx &c, const std::vector<BodyMat> &blocks, const st
     t.nitems = (int)items.size();
     auto up = [&](const void *h, size_t bytes) {
         void *d = c.dalloc(bytes);
-        AXS_HIP(hipMemcpy(d, h, bytes, hipMemcpyHostToDevice));
+        copy_in(c, d, h, bytes);
         return d;
     };
     t.mats = (BodyMat *)up(blocks.data(), blocks.size() * sizeof(BodyMat));

@@ -81,3 +81,29 @@ def test_gradient_that_fails_leaves_the_callers_array_alone():
     assert np.isfinite(loss) and bool(torch.isfinite(g).all())
     net.close()
     ctx.close()
+
+
+def test_parameters_set_while_the_stream_is_busy():
+    """On a stream of its own that has not come to an earlier forward pass yet, new parameters take
+    their turn: the pass before them uses the old ones, the pass after them the new ones."""
+    from paper_1406_0236_amd import Context, Mlp
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = Context(0)
+        net = Mlp(ctx, 4, 24, 2, 33)
+        X = torch.randn(7, 4, device="cuda:0")
+        p = [np.random.default_rng(k).standard_normal(net.nparams).astype(np.float32) for k in range(2)]
+        want = []
+        for q in p:
+            net.set_params(q)
+            want.append(net.forward(X).clone())
+        net.set_params(p[0])
+        torch.cuda.synchronize()
+        torch.cuda._sleep(50_000_000)
+        got0 = net.forward(X)
+        net.set_params(p[1])
+        got1 = net.forward(X)
+        torch.cuda.synchronize()
+        assert torch.equal(got0, want[0]) and torch.equal(got1, want[1])
+        net.close()
+        ctx.close()
