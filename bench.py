@@ -48,7 +48,7 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6
 # (profiles/interbody_sphere_lattice_27_k4pi_pmc.md); valid only for the kernel
 # source they were taken on (source_fingerprint: code, not comments).
 TRAFFIC_BYTES = 115.17e6
-TRAFFIC_SOURCE_SHA = "fb4bf746cfa3045c"
+TRAFFIC_SOURCE_SHA = "8f0854f7aba2f82b"
 
 
 def source_fingerprint(path):
