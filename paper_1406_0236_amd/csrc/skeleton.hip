@@ -1595,7 +1595,7 @@ template <typename R, int NR, int KW, bool TRANS>
 __global__ __launch_bounds__(64 * KW) void body_matvec_kernel(
     const int2 *__restrict__ items, const BodyMat *__restrict__ mats, const int64_t *__restrict__ in0,
     const int64_t *__restrict__ out0, const double2 *__restrict__ in, int64_t inN, int nrhs,
-    const double2 *__restrict__ add, double2 *__restrict__ out, int64_t outN, double alpha) {
+    const double2 *add, double2 *out, int64_t outN, double alpha) {   // add may be out: a thread reads what it writes
     using C = typename CplxOf<R>::T;
     constexpr int STAGE = KW * BM_KC * NR, RED = KW / 2 * NR * 64;
     __shared__ C sw[STAGE > RED ? STAGE : RED];
@@ -1694,7 +1694,6 @@ static void launch_body_matvec(Ctx &c, const BodyMats &t, const double2 *in, int
     const int64_t cols = (int64_t)t.max_bodies * nrhs;
     const int64_t groups = std::max(ceil_div(cols, 16), std::min(cols, ceil_div((int64_t)256, (int64_t)t.nitems)));
     const int width = (int)ceil_div(cols, groups);
-    const dim3 grid(t.nitems, (unsigned)groups);
     const bool few = (int64_t)t.nitems * groups < 1024;
 #define AXS_BM(NR_)                                                                                              \
     if (width <= NR_) {                                                                                          \
