@@ -680,9 +680,10 @@ axs_status axs_incident_plane_waves(axs_ctx *ctx, const double *dirs, int nrhs, 
         AXS_REQUIRE(dirs && v && nrhs >= 1, AXS_EINVAL, "bad arguments");
         for (int i = 0; i < 3 * nrhs; ++i) AXS_REQUIRE(std::isfinite(dirs[i]), AXS_ENONFINITE, "non-finite direction");
         double *d = (double *)c.scratch(axs::WS_EVAL, 3 * nrhs * sizeof(double));
-        copy_in(c, d, dirs, 3 * nrhs * sizeof(double));
+        axs::CopyIn in(c);
+        in(d, dirs, 3 * nrhs * sizeof(double));
         axs::incident_plane_launch(c, d, nrhs, v);
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        in.finish();
         return AXS_OK;
     });
 }
@@ -695,9 +696,10 @@ axs_status axs_incident_point_sources(axs_ctx *ctx, const double *src, const dou
         buf.insert(buf.end(), amp, amp + 2 * ns);
         for (double x : buf) AXS_REQUIRE(std::isfinite(x), AXS_ENONFINITE, "non-finite source data");
         double *d = (double *)c.scratch(axs::WS_EVAL, buf.size() * sizeof(double));
-        copy_in(c, d, buf.data(), buf.size() * sizeof(double));
+        axs::CopyIn in(c);
+        in(d, buf.data(), buf.size() * sizeof(double));
         axs::incident_point_launch(c, d, d + 3 * ns, ns, v);
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        in.finish();
         return AXS_OK;
     });
 }
@@ -719,9 +721,10 @@ axs_status axs_eval_field(axs_ctx *ctx, const void *sigma, int nrhs, const doubl
         AXS_REQUIRE(sigma && tgt && u && nt >= 1 && nrhs >= 1 && nt <= 65535 && nrhs <= 4096, AXS_EINVAL,
                     "bad arguments");
         double *d = (double *)c.scratch(axs::WS_EVAL, 3 * nt * sizeof(double));
-        copy_in(c, d, tgt, 3 * nt * sizeof(double));
+        axs::CopyIn in(c);
+        in(d, tgt, 3 * nt * sizeof(double));
         axs::eval_field_launch(c, sigma, nrhs, d, nt, largest_norm(tgt, nt), u);
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        in.finish();
         return AXS_OK;
     });
 }
@@ -733,9 +736,10 @@ axs_status axs_far_field(axs_ctx *ctx, const void *sigma, int nrhs, const double
                     "bad arguments");
         AXS_REQUIRE(c.kappa > 0, AXS_EINVAL, "no far field at kappa = 0");
         double *d = (double *)c.scratch(axs::WS_EVAL, 3 * nd * sizeof(double));
-        copy_in(c, d, xhat, 3 * nd * sizeof(double));
+        axs::CopyIn in(c);
+        in(d, xhat, 3 * nd * sizeof(double));
         axs::far_field_launch(c, sigma, nrhs, d, nd, largest_norm(xhat, nd), out);
-        AXS_HIP(hipStreamSynchronize(c.stream));
+        in.finish();
         return AXS_OK;
     });
 }

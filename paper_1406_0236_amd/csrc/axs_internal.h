@@ -305,6 +305,27 @@ inline void copy_in(Ctx &c, void *dst, const void *src, size_t bytes) {
     AXS_HIP(hipStreamSynchronize(c.stream));
 }
 
+// The same for a call that waits for its stream at its end: queues the copies, and
+// finish() waits, as does an error on the way (the host array is the caller's).
+struct CopyIn {
+    Ctx &c;
+    bool pending = false;
+    explicit CopyIn(Ctx &c_) : c(c_) {}
+    CopyIn(const CopyIn &) = delete;
+    CopyIn &operator=(const CopyIn &) = delete;
+    ~CopyIn() {
+        if (pending) (void)hipStreamSynchronize(c.stream);
+    }
+    void operator()(void *dst, const void *src, size_t bytes) {
+        pending = true;
+        AXS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c.stream));
+    }
+    void finish() {
+        pending = false;
+        AXS_HIP(hipStreamSynchronize(c.stream));
+    }
+};
+
 // Host arrays gathered into one block and copied to the device at once (a copy
 // from pageable memory holds the host up for some 10 us whatever its size).  The
 // host copy is read until the stream has come that far: an owner that has
