@@ -301,8 +301,7 @@ struct Skeleton {
 // queued on its stream before (hipMemcpy takes its turn on the null stream, which
 // a non-blocking stream does not wait for, nor it for that).
 inline void copy_in(Ctx &c, void *dst, const void *src, size_t bytes) {
-    AXS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c.stream));
-    AXS_HIP(hipStreamSynchronize(c.stream));
+    AXS_HIP(hipMemcpyWithStream(dst, src, bytes, hipMemcpyHostToDevice, c.stream));
 }
 
 // The same for a call that waits for its stream at its end: queues the copies, and

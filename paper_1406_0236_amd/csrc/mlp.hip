@@ -937,22 +937,24 @@ static void ws_check_mmax(const Ctx &c, int mmax) {
 // device copies of the layout offsets and the phase table for nrhs directions
 struct WsTables {
     Ctx &c;
+    CopyIn in;
     int64_t *toff = nullptr;
     double *dirs = nullptr;
     double2 *ph = nullptr;
-    WsTables(Ctx &c_, const std::vector<int64_t> &off, const double *dirs_host, int nrhs) : c(c_) {
+    WsTables(Ctx &c_, const std::vector<int64_t> &off, const double *dirs_host, int nrhs) : c(c_), in(c_) {
         const int nb = (int)c.bodies.size();
         toff = (int64_t *)c.dalloc(off.size() * sizeof(int64_t));
         dirs = (double *)c.dalloc((size_t)3 * nrhs * sizeof(double));
         ph = (double2 *)c.dalloc((size_t)nrhs * nb * (nb - 1) * sizeof(double2));
-        copy_in(c, toff, off.data(), off.size() * sizeof(int64_t));
-        copy_in(c, dirs, dirs_host, (size_t)3 * nrhs * sizeof(double));
+        in(toff, off.data(), off.size() * sizeof(int64_t));   // both outlive this object
+        in(dirs, dirs_host, (size_t)3 * nrhs * sizeof(double));
         const int64_t n = (int64_t)nrhs * nb * (nb - 1);
         hipLaunchKernelGGL(ws_phase_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, c.stream, c.frame64, dirs,
                            nb, nrhs, c.kappa, ph);
         AXS_HIP(hipGetLastError());
     }
     ~WsTables() {
+        in.pending = false;
         (void)hipStreamSynchronize(c.stream);
         c.dfree(toff);
         c.dfree(dirs);
