@@ -183,6 +183,91 @@ __global__ __launch_bounds__(256) void field_reduce_kernel(const double2 *__rest
     u[i] = a;
 }
 
+// Small calls, and few targets with many densities: one workgroup per target and right-
+// hand side straight from the node arrays, one launch without records, table and
+// partial sums.  Bound by its own latency, a lane's pass over N / 256 nodes (30 us a
+// call, and 1.7 us per 1,000 nodes; far 2.2), until some 600 workgroups fill the chip
+// (then 6 ps a pair and density).
+template <int KIND>
+__global__ __launch_bounds__(256) void field_direct_kernel(const double *__restrict__ g, int64_t N,
+                                                           const double2 *__restrict__ sigma,
+                                                           const double *__restrict__ tgt, int nt, double kappa,
+                                                           double eta, double2 *__restrict__ u) {
+    __shared__ double2 s_sum[4];
+    const int t = blockIdx.x, c = blockIdx.y;
+    const double tx = tgt[3 * t], ty = tgt[3 * t + 1], tz = tgt[3 * t + 2];
+    const double2 *q = sigma + (int64_t)c * N;
+    double re = 0, im = 0;
+    for (int64_t j = threadIdx.x; j < N; j += 256) {
+        const double x = g[j], y = g[N + j], z = g[2 * N + j];
+        const double nx = g[3 * N + j], ny = g[4 * N + j], nz = g[5 * N + j];
+        double gr, gi;
+        if constexpr (KIND == FIELD_FAR) {
+            double sn, cs;
+            sincos(-kappa * (tx * x + ty * y + tz * z), &sn, &cs);
+            const double f = eta - kappa * (tx * nx + ty * ny + tz * nz);
+            gr = -f * sn;
+            gi = f * cs;
+        } else {
+            const double dx = tx - x, dy = ty - y, dz = tz - z;
+            const double r2 = dx * dx + dy * dy + dz * dz, R = sqrt(r2);
+            const double a = (nx * dx + ny * dy + nz * dz) / r2;
+            if constexpr (KIND == FIELD_LAPLACE) {
+                gr = (a + eta) / R;
+                gi = 0.0;
+            } else {
+                double sn, cs;
+                sincos(kappa * R, &sn, &cs);
+                // e^{ikR}/R [a (1 - i k R) + i eta], a = n.d / R^2
+                const double b = eta - a * kappa * R, er = cs / R, ei = sn / R;
+                gr = er * a - ei * b;
+                gi = er * b + ei * a;
+            }
+        }
+        const double w = g[6 * N + j] * (0.25 / M_PI);
+        const double qr = q[j].x * w, qi = q[j].y * w;
+        re += gr * qr - gi * qi;
+        im += gr * qi + gi * qr;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        re += __shfl_xor(re, o, 64);
+        im += __shfl_xor(im, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = make_double2(re, im);
+    __syncthreads();
+    if (threadIdx.x) return;
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        re += s_sum[k].x;
+        im += s_sum[k].y;
+    }
+    u[(int64_t)c * nt + t] = make_double2(re, im);
+}
+
+// The line between the two, from sweeps of 288 to 437,400 nodes, 1 to 1,024 targets and 1
+// to 256 densities (us a call, direct / through records).
+//  - Small calls.  The nodes set the direct kernel's latency: near, 1 and 8 densities,
+//    3,060 nodes 34 / 41 and 34 / 54, 8,200 nodes 43 / 43 and 44 / 56; far 35 / 37 and 36 / 46,
+//    48 / 40 and 48 / 48; zero frequency 34 / 34 and 34 / 53, 43 / 35 and 44 / 54; near, 64
+//    densities, 16,400 nodes 59 / 113.  The work, counted with 256 nodes' worth for a
+//    workgroup's start, sets the time beyond it: near, 840 nodes, 1 density, 1,024
+//    targets 36 / 44; 4: 512 targets 40 / 43, 1,024 50 / 48; 64: 64 targets 49 / 55, 128 70 / 50.
+//  - Few targets, many densities, any number of nodes: a lane of field_kernel is one
+//    target and idle without, and the records are written and read for nothing: 65,280
+//    nodes, 256 densities, 1 and 8 targets: near 236 / 1,410 and 819 / 1,411, far 338 /
+//    1,164 and 615 / 1,157, zero frequency 235 / 935 and 718 / 934; 437,400 nodes, 64 densities,
+//    8 targets: near 1,896 / 2,344, far 3,079 / 1,953, zero frequency 1,839 / 1,438.
+template <int KIND>
+static bool field_direct(int64_t N, int nt, int nrhs, int nr) {
+    const int64_t nodes = (KIND == FIELD_NEAR ? 6144 + 768 * nr : 2048 + 1024 * nr) + 128 * std::min(nrhs, 64);
+    const int64_t work = nr <= 4 ? 1 << (KIND == FIELD_LAPLACE ? 20 : 21) : KIND == FIELD_FAR ? 1 << 22 : 3 << 21;
+    if (N <= nodes && (int64_t)nt * nrhs * (N + 256) <= work) return true;
+    if (KIND == FIELD_NEAR) return nrhs >= 48 && nt <= (nrhs >= 128 ? 12 : nrhs >= 56 ? 8 : 4);
+    if (KIND == FIELD_FAR) return nrhs >= 96 && nt <= 12;
+    return nrhs >= 80 && nt <= (nrhs >= 128 ? 8 : 4);
+}
+
 // targets per lane where there are many: they share a node's LDS reads
 constexpr int field_tpt(int nr) { return nr > 4 ? 2 : 4; }
 
@@ -229,6 +314,12 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
                        double eta, int wide, void *u) {
     // groups of equal width, at most 8 rhs each
     const int groups = (int)ceil_div(nrhs, 8), nr = (int)ceil_div(nrhs, groups);
+    if (field_direct<KIND>(c.N, nt, nrhs, nr)) {
+        hipLaunchKernelGGL(field_direct_kernel<KIND>, dim3(nt, nrhs), dim3(256), 0, c.stream, c.g64, c.N,
+                           (const double2 *)sigma, tgt, nt, c.kappa, eta, (double2 *)u);
+        AXS_HIP(hipGetLastError());
+        return;
+    }
     const size_t rec_group = (size_t)c.N * (6 + 2 * nr) * sizeof(double);
     // groups of one pass: as many as have their records within FIELD_SCRATCH (at least one)
     const int gb = (int)std::max<size_t>(1, std::min<size_t>(groups, FIELD_SCRATCH / rec_group));

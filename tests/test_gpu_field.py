@@ -101,7 +101,8 @@ def _near_extended(g, q, t, kappa, eta):
 
 @pytest.mark.parametrize("kappa", [0.7, 3.0])
 @pytest.mark.parametrize("offset", [0.0, 1000.0])
-def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset):
+@pytest.mark.parametrize("panels,M", [(4, 8), (10, 20)])   # by the direct kernel, and through records
+def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset, panels, M):
     """Points 1e-3 and 1e-2 off the nodes of a scene at the origin and of one far from it: the
     distances come from the differences of the coordinates as given, so that neither the closeness nor the
     place costs digits."""
@@ -109,8 +110,8 @@ def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset):
     from paper_1406_0236_amd import Context
     from workloads import geometry as geo
     ctx = Context(0)
-    for k, c in enumerate((geo.sphere(1.0, 4, 10), geo.prolate(0.8, 1.3, 5, 9))):
-        ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, 8,
+    for k, c in enumerate((geo.sphere(1.0, panels, 10), geo.prolate(0.8, 1.3, panels + 1, 10))):
+        ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, M,
                        np.array([3.0 * k + offset, 0.5 * k + offset, -0.2]), geo.random_rotation(np.random.default_rng(k)))
     ctx.precompute_scattering()
     g = ctx.node_geometry()
@@ -123,7 +124,7 @@ def test_field_close_to_the_surface_wherever_the_scene_lies(kappa, offset):
         ref = _near_extended(g, q, t, kappa, 1.5)
         got = ctx.eval_field(torch.from_numpy(sig).to("cuda:0"), t).cpu().numpy()
         # differences, R and 1/R^3 to about 10 roundings, a phase of at most 20 radians to 3 more
-        # each, sums of chunks of 66 terms: 64 eps of the largest value
+        # each, sums of chunks of 70 terms: 64 eps of the largest value
         err = float(np.max(np.abs(got - ref)) / np.max(np.abs(ref)))
         assert err < 64 * np.finfo(np.float64).eps, (h, err)
     ctx.close()
@@ -171,3 +172,44 @@ def test_many_right_hand_sides_within_bounded_scratch(kappa):
             got = ctx.far_field(dev, x)
             assert float((got - ref).abs().max() / ref.abs().max()) < 22 * TOL
     ctx.close()
+
+
+@pytest.fixture(scope="module")
+def larger():
+    """8,610 nodes: beyond the direct kernel with one density, at its edges with several."""
+    import torch
+    from paper_1406_0236_amd import Context
+    from workloads import geometry as geo
+    out = {}
+    for kappa in (0.0, 2.0):
+        ctx = Context(0)
+        for k, c in enumerate((geo.sphere(1.0, 10, 10), geo.prolate(0.8, 1.3, 11, 10))):
+            ctx.build_body(c.rz, c.drz, c.gw, c.n_panels, c.p, kappa, 1.5, 20, np.array([3.0 * k, 0.4, 0.0]), np.eye(3))
+        ctx.precompute_scattering()
+        rng = np.random.default_rng(8)
+        sig = rng.standard_normal((130, ctx.N)) + 1j * rng.standard_normal((130, ctx.N))
+        out[kappa] = (ctx, ctx.node_geometry(), sig, torch.from_numpy(sig).to("cuda:0"))
+    yield out
+    for v in out.values():
+        v[0].close()
+
+
+@pytest.mark.parametrize("kappa", [0.0, 2.0])
+@pytest.mark.parametrize("nt,nrhs", [(1, 1), (1, 16), (63, 2), (64, 5), (65, 1), (59, 8), (60, 8), (257, 3), (700, 7),
+                                     (1, 130), (4, 80), (5, 80), (8, 56), (9, 56), (12, 130), (13, 130)])
+def test_few_targets_of_a_larger_scene(larger, kappa, nt, nrhs):
+    ctx, g, sig, dev = larger[kappa]
+    rng = np.random.default_rng(nt)
+    q = sig[:nrhs] * (g[:, 6] / (4 * math.pi))
+    t = rng.uniform(-4, 8, (nt, 3))
+    t[:, 2] = 3.0 + 2 * rng.random(nt)
+    ref = _near(g, q, t, kappa, 1.5)
+    got = ctx.eval_field(dev[:nrhs].contiguous(), t).cpu().numpy()
+    tol = TOL * 8610 / 1500     # as TOL
+    assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
+    if kappa > 0:
+        x = rng.standard_normal((nt, 3))
+        x /= np.linalg.norm(x, axis=1, keepdims=True)
+        ref = q @ (np.exp(-1j * kappa * (x @ g[:, :3].T)) * (1j * (1.5 - kappa * (x @ g[:, 3:6].T)))).T
+        got = ctx.far_field(dev[:nrhs].contiguous(), x).cpu().numpy()
+        assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
