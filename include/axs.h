@@ -396,9 +396,10 @@ axs_status axs_mlp_gradient(axs_mlp *mlp, const float *X, const float *T, int ba
 axs_status axs_mlp_adam_step(axs_mlp *mlp, const float *X, const float *T, int batch, double lr,
                              double beta1, double beta2, double eps, double *loss);
 /* `steps` Adam steps over sample rows held on the device: step s gathers rows
- * order[s batch .. (s+1) batch - 1] of X (device float [rows][n_in]) and of T
- * (device float [rows][n_out]) into the network's own batch buffers and takes
- * the step of axs_mlp_adam_step with learning rate lr[s].  order (host int32
+ * order[s batch .. (s+1) batch - 1] of X (device float [rows][n_in]) into the
+ * network's own batch buffer, reads the same rows of T (device float
+ * [rows][n_out]) where they lie, and takes the step of axs_mlp_adam_step with
+ * learning rate lr[s].  order (host int32
  * [steps x batch], each in [0, rows)) and lr (host double [steps], each > 0)
  * are checked and copied before the first step is queued, so the caller may
  * reuse them on return; a bad entry gives AXS_EINVAL with nothing queued.

@@ -5,8 +5,8 @@
 //   near:  K = e^{ikR}/R [ (n.d)(1 - i k R)/R^2 + gamma ],  d = x_t - x_j
 //   far:   K = i (eta - k xh.n_j) e^{-i k xh.x_j}
 //
-// Bound: FP64 VALU issue (about 45 instructions per target-node pair and 4 per
-// right-hand side), so a pair is evaluated once for all right-hand sides of a group of
+// Bound: FP64 VALU issue (counted per target-node pair: near 44 instructions with one
+// density, far 47 with four; 4 of them for each density), so a pair is evaluated once for all right-hand sides of a group of
 // up to 8, its sin/cos come from the inter-body sums' LDS table, and nothing else
 // is read per pair: targets sit in lanes (TPT per lane), and the nodes' records
 // (position and normal, for the far field scaled, and the group's densities, packed
@@ -15,9 +15,12 @@
 // instead the kernels took 8 % longer, prefetched or not).  The nodes are cut
 // into chunks so that even a few targets fill the chip; the chunks' partial sums
 // are added in a fixed order.
-// 20,000 directions x 18,860 nodes x 4 densities: 0.60 ms, 72 % of the FP64
-// issue rate (one workgroup per target and right-hand side with the library
-// sincos: 5.7 ms); 1,024 points x 437,400 nodes: 0.68 ms, 80 % (2.7 ms).
+// In a kernel trace, 20,000 directions x 18,860 nodes x 4 densities: 0.65 ms, 79 % of the
+// FP64 issue rate at the clock it ran at; 1,024 points x 437,400 nodes: 0.77 ms, 80 % (the
+// whole calls, untraced, 0.65 and 0.72 ms; with one workgroup per target and right-hand
+// side and the library sincos 5.7 to 6.1 and 2.7 to 3.0).
+// Small calls, and few targets with many densities, take field_direct_kernel: one
+// workgroup per target and right-hand side after all, in one launch.
 #include "axs_internal.h"
 #include "fp64_math.h"
 
@@ -334,7 +337,7 @@ static void field_sums(Ctx &c, const void *sigma, int nrhs, const double *tgt, i
     // workgroups of four wavefronts (4 per CU; more cost as much as they fill).  Many: as
     // fill whole rounds of the workgroups the CUs hold at a time, one or up to four
     // where the tiles do not divide a round well (20,000 directions, 4 densities: 38
-    // chunks, 760 workgroups of the 768 held, 0.68 ms; 52 chunks, a round and a third, 0.76)
+    // chunks, 760 workgroups of the 768 held, 0.65 ms; 52 chunks, a round and a third, 0.70)
     const int64_t all = (int64_t)tiles * gb;
     int64_t want = std::max<int64_t>(1, std::min(most, ceil_div((int64_t)1024 * 256, all * bs)));
     if (many) {

@@ -67,8 +67,8 @@ struct Mlp {
 // one m with a lane: 16-byte stores.  Loads and stores of 16 bytes need 4-byte
 // alignment only; rows and columns past the edges are read as zero.
 // Network 4 -> 512 x 4 -> 116,620 at a batch of 256, products with the output layer:
-// forward with loss 364 us (84 TFLOP/s), weights' gradient 298 (103), inputs'
-// 280 (109), the whole gradient 1.00 ms; 64 x 64 tiles without a prefetch ran at 35
+// forward with loss 362 us (84 TFLOP/s), weights' gradient 291 (105), inputs'
+// 276 (111), the whole gradient 1.00 ms; 64 x 64 tiles without a prefetch ran at 35
 // TFLOP/s with separate passes for loss, sums and GELU', and took 3.15.  The 128 x 128
 // tiles' depth: 16 where B is read along n, with three workgroups a CU (32, with
 // two: 392 and 331 us), 32 where both run along k (16: 295).
